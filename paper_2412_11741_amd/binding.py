@@ -1,16 +1,22 @@
-"""Thin ctypes binding of libcsr_hip.so (the C ABI of include/csr.h).
+"""Thin binding of libcsr_hip.so (the C ABI of include/csr.h).
 
 Argument marshalling only: every step of the hot path runs in the HIP kernels.  PyTorch is
 used for device memory and the current stream.  There is no CPU fallback: if the library is
 missing, or a tensor is not on the GPU, the call raises.
+
+csr_encode, csr_decode_attn and csr_reconstruct first hand their arguments to the compiled marshalling of
+csrc/torch_binding (1 - 2 us of host time a call; in ctypes it is about 25 us, as long as the small shapes take on the
+GPU).  It returns None for anything it does not take; the ctypes path below then runs, and says what is wrong.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch  # must precede loading the library: it brings the HIP runtime the library binds to
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libcsr_hip.so")
+NATIVE_PATH = os.path.join(_HERE, "_csr_torch.so")
 
 CSR_OK, CSR_ERR_INVALID_ARG, CSR_ERR_UNSUPPORTED, CSR_ERR_WORKSPACE, CSR_ERR_DEVICE = range(5)
 CSR_F32, CSR_F16 = 0, 1
@@ -100,6 +106,24 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def _load_native():
+    """The compiled marshalling, bound to the loaded library's entry points; raises if it has not been built."""
+    global _native
+    L = lib()
+    if not os.path.exists(NATIVE_PATH):
+        raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2412_11741_amd.build`")
+    spec = importlib.util.spec_from_file_location("_csr_torch", NATIVE_PATH)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                  (L.csr_encode_workspace_bytes, L.csr_encode, L.csr_decode_workspace_bytes, L.csr_decode_attn, L.csr_reconstruct)))
+    _native = module
+    return module
+
+
 def last_error():
     return lib().csr_last_error().decode()
 
@@ -181,6 +205,9 @@ def csr_encode(X, D, s, coef_dtype=None, idx_dtype=None, algo=CSR_ENCODE_AUTO, i
     final residual, i.e. its squared reconstruction error.  `gram` (csr_gram_build(D)) lets a few vectors per
     dictionary - one decoding step's - be encoded with one sweep of each dictionary instead of s.
     closed_loop: CSR_FLAG_CLOSED_LOOP - Eq.4 subtracts the coefficient as it is stored (rounded to coef_dtype)."""
+    done = (_native or _load_native()).encode(X, D, s, coef_dtype, idx_dtype, algo, idx, coef, workspace, res_norm2, gram, closed_loop)
+    if done is not None:
+        return done
     _dev(X, "X"); _dev(D, "D")
     if X.dim() != 3 or D.dim() not in (3, 4) or D.shape[0] < 1 or X.shape[0] % D.shape[0] != 0 or \
             D.shape[-1] * (D.shape[1] if D.dim() == 4 else 1) != X.shape[2]:
@@ -229,6 +256,9 @@ def csr_reconstruct(D, idx, coef, out=None, out_dtype=None):
     """Eq.12, X~ = D r.  D [H', N, d] with codes [H, T, s], or chunked D [H', s_n, N, d / s_n] with codes
     [H, T, s_n, s] (H' divides H: block h uses dictionary h % H') -> out [H, T, d].  `idx` / `coef` may be views
     into a larger cache (blocks further apart); `out` may be a strided view with contiguous vectors."""
+    done = (_native or _load_native()).reconstruct(D, idx, coef, out, out_dtype)
+    if done is not None:
+        return done
     for name, t in (("D", D), ("idx", idx), ("coef", coef)):
         _dev(t, name)
     chunked = D.dim() == 4
@@ -320,6 +350,11 @@ def csr_decode_attn(q, DK, idxK, coefK, DV, idxV, coefV, scale=0.0, seq_lens=Non
     rope_base > 1: the keys were coded before the rotary embedding; cache token t sits at position rope_pos0 + t.
     static_scratch: call csr_decode_attn_static (the library's own static device scratch, no workspace; `out` must
     then be given, so that nothing at all is allocated)."""
+    if not static_scratch:
+        done = (_native or _load_native()).decode(q, DK, idxK, coefK, DV, idxV, coefV, scale, seq_lens, out, out_dtype, workspace,
+                                                  rope_base, rope_layout, rope_pos0)
+        if done is not None:
+            return done
     for name, t in (("q", q), ("DK", DK), ("idxK", idxK), ("coefK", coefK), ("DV", DV), ("idxV", idxV),
                     ("coefV", coefV)):
         _dev(t, name)

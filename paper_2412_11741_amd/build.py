@@ -52,6 +52,28 @@ def build(verbose: bool = False, extra=()) -> str:
     return LIB
 
 
+NATIVE_SRC = os.path.join(CSRC, "torch_binding", "csr_torch.cpp")
+NATIVE = os.path.join(HERE, "_csr_torch.so")
+
+
+def build_native(verbose: bool = False) -> str:
+    """The compiled marshalling between PyTorch tensors and the C ABI: host code against PyTorch's own headers."""
+    import sysconfig
+    import torch
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    top = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-function", "-DUSE_ROCM=1",
+           "-D__HIP_PLATFORM_AMD__=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", INCLUDE,
+           "-I", sysconfig.get_paths()["include"], "-isystem", os.path.join(top, "include"),
+           "-isystem", os.path.join(top, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(rocm, "include"),
+           NATIVE_SRC, "-o", NATIVE + ".tmp", "-L", os.path.join(top, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(NATIVE + ".tmp", NATIVE)
+    return NATIVE
+
+
 C_SMOKE_SRC = os.path.join(os.path.dirname(HERE), "tests", "c_abi", "smoke.c")
 C_SMOKE_BIN = os.path.join(HERE, "csr_c_smoke.bin")
 
@@ -85,5 +107,6 @@ def build_probe(verbose: bool = False) -> str:
 
 if __name__ == "__main__":
     print(build(verbose=True, extra=sys.argv[1:]))
+    print(build_native(verbose=True))
     print(build_c_smoke(verbose=True))
     print(build_probe(verbose=True))
