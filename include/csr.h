@@ -53,7 +53,7 @@ typedef enum { CSR_I32 = 0, CSR_I16 = 1 } csr_itype; /* atom indices; I16 is uns
 
 /* Which encoder kernel runs.  AUTO picks SPLIT when a dictionary serves few vectors (the tokens of one
  * decoding step; GRAM instead when the descriptor brings the dictionaries' Gram matrices and there are at
- * most 128), RESIDENT when the dictionary fits the LDS, MFMA when the shape allows it, else VALU. */
+ * most 128), RESIDENT when the dictionary fits the LDS, MFMA or WIDE when the shape allows it (fp32: WIDE), else VALU. */
 typedef enum {
     CSR_ENCODE_AUTO = 0,
     CSR_ENCODE_VALU = 1, /* fp32 vector-ALU correlation, any supported shape               */
@@ -64,6 +64,9 @@ typedef enum {
     CSR_ENCODE_RESIDENT = 4, /* small dictionaries (N * d/s_n * 2 bytes <= 128 KB, e.g. the 256 - 512 atoms per
                             head of the paper's experiments): the dictionary stays in LDS, exact
                             fp32-accumulated correlations on the matrix cores; same input types     */
+    CSR_ENCODE_WIDE = 6, /* fp16 matrix-core screening + exact fp32 selection like MFMA, with the atoms split over the
+                            waves of a workgroup: fp32 or fp16 inputs, any N up to 65536; needs scratch of the size of
+                            the dictionaries in fp16                                                        */
     CSR_ENCODE_GRAM = 5  /* the correlations of all atoms are updated with the Gram matrix of the dictionary
                             (in fp16: atom norms must stay below 250) instead of being recomputed; same input
                             types.  Without csr_encode_desc.gram: at most 256 atoms, the matrix is built into LDS

@@ -34,6 +34,27 @@ bool valid_itype(int32_t v) { return v == CSR_I32 || v == CSR_I16; }
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 size_t round256(size_t v) { return (v + 255) & ~size_t(255); }
 
+// Whether CSR_ENCODE_AUTO runs the wide encoder in place of `algo`, the one the shape would get otherwise (whose codes it
+// reproduces bit for bit).  Measured on 8 to 64 dictionaries (us, s = 8):
+//   fp32, or an N that is no multiple of 32: the alternative is the vector ALU (2 x 4096 fp32 vectors, N = 1024: 775
+//     against 57); a handful of vectors stays there, which needs no scratch
+//   dictionaries that fit the LDS: the resident encoder needs 512 vectors per CU to fill the chip (N = 256, 8 x 1600
+//     vectors: 133 against 60, 64 x 400: 125 against 98, 64 x 800: 133 against 183)
+//   the prefill encoder needs as many (N = 4096, 8 x 1600 vectors: 734 against 211, 8 x 9000: 918 against 747, 64 x 1600:
+//     1076 against 1126)
+bool wide_pays(const csr::EncodeArgs &a, int algo)
+{
+    if (!csr::encode_wide_supported(a)) return false;
+    const int64_t M = (int64_t)(a.H / (a.dict_count ? a.dict_count : 1)) * a.T;   // vectors per dictionary
+    const int64_t all = M * a.dict_count * a.sn;
+    switch (algo) {
+        case CSR_ENCODE_VALU: return M >= 32;
+        case CSR_ENCODE_RESIDENT: return all < 36 * 1000;
+        case CSR_ENCODE_MFMA: return a.d != 32 && all < 100 * 1000;
+        default: return false;
+    }
+}
+
 // Checks everything about an encode descriptor that does not need the pointers; fills the shape part of the
 // kernels' arguments and names the kernel that will run (AUTO resolved to one of the others).
 csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, int *algo_out)
@@ -45,7 +66,7 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
     if (!valid_dtype(d->x_dtype) || !valid_dtype(d->dict_dtype) || !valid_dtype(d->coef_dtype) || !valid_itype(d->idx_dtype))
         return fail(CSR_ERR_INVALID_ARG, "csr_encode: unknown dtype / index type");
     if (d->algo != CSR_ENCODE_AUTO && d->algo != CSR_ENCODE_VALU && d->algo != CSR_ENCODE_MFMA && d->algo != CSR_ENCODE_SPLIT &&
-        d->algo != CSR_ENCODE_RESIDENT && d->algo != CSR_ENCODE_GRAM)
+        d->algo != CSR_ENCODE_RESIDENT && d->algo != CSR_ENCODE_GRAM && d->algo != CSR_ENCODE_WIDE)
         return fail(CSR_ERR_INVALID_ARG, "csr_encode: unknown algo %d", d->algo);
     if (d->s < 1 || d->s > 32) return fail(CSR_ERR_INVALID_ARG, "csr_encode: s=%d outside 1..32", d->s);
     if (d->N < 1) return fail(CSR_ERR_INVALID_ARG, "csr_encode: N=%d must be >= 1", d->N);
@@ -95,6 +116,8 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
         return fail(CSR_ERR_UNSUPPORTED, "csr_encode: the split encoder needs fp16 inputs, chunks of 64 or 128 dimensions, N a multiple of 32 "
                     "and at most 128 vectors per dictionary (got d/s_n=%d N=%d %s, %lld vectors per dictionary)",
                     dc, d->N, a.f16 ? "f16" : "f32", (long long)(a.dict_count ? (int64_t)(a.H / a.dict_count) * a.T : 0));
+    if (d->algo == CSR_ENCODE_WIDE && !csr::encode_wide_supported(a))
+        return fail(CSR_ERR_UNSUPPORTED, "csr_encode: the wide encoder takes at most 65536 atoms (got N=%d)", d->N);
     const bool resident_ok = csr::encode_resident_supported(a);
     if (d->algo == CSR_ENCODE_RESIDENT && !resident_ok)
         return fail(CSR_ERR_UNSUPPORTED, "csr_encode: the LDS-resident encoder needs fp16 inputs, chunks of 64 or 128 dimensions, N a multiple "
@@ -120,12 +143,19 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
     return CSR_OK;
 }
 
-size_t encode_workspace(const csr::EncodeArgs &a, int algo)
+// Scratch for `algo` and for the wide encoder where CSR_ENCODE_AUTO would run that one at this shape: a workspace sized
+// with an explicit algo serves AUTO, too.
+size_t encode_workspace(const csr::EncodeArgs &a, int algo, bool automatic)
 {
     if (a.H == 0 || a.T == 0) return 0;
-    if (algo == CSR_ENCODE_MFMA) return csr::encode_mfma_workspace_bytes(a.dict_count * a.sn, a.T, a.N, a.s);
-    if (algo == CSR_ENCODE_SPLIT) return csr::encode_split_workspace_bytes(a);
+    if (algo == CSR_ENCODE_MFMA || algo == CSR_ENCODE_SPLIT || (algo == CSR_ENCODE_VALU && automatic)) {
+        const size_t own = algo == CSR_ENCODE_MFMA    ? csr::encode_mfma_workspace_bytes(a.dict_count * a.sn, a.T, a.N, a.s)
+                           : algo == CSR_ENCODE_SPLIT ? csr::encode_split_workspace_bytes(a) : 0;
+        const size_t wide = wide_pays(a, algo) ? csr::encode_wide_workspace_bytes(a) : 0;
+        return own > wide ? own : wide;
+    }
     if (algo == kAlgoGramStep) return csr::encode_gramstep_workspace_bytes(a);
+    if (algo == CSR_ENCODE_WIDE) return csr::encode_wide_workspace_bytes(a);
     return 0;
 }
 
@@ -230,7 +260,7 @@ size_t csr_encode_workspace_bytes(const csr_encode_desc *desc)
     csr::EncodeArgs a{};
     int algo = 0;
     if (check_encode_desc(desc, &a, &algo) != CSR_OK) return (size_t)-1;
-    return encode_workspace(a, algo);
+    return encode_workspace(a, algo, desc->algo == CSR_ENCODE_AUTO);
 }
 
 csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D, void *idx,
@@ -245,7 +275,8 @@ csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D,
     if (!aligned(X, 16) || !aligned(D, 16)) return fail(CSR_ERR_INVALID_ARG, "csr_encode: X and D must be 16-byte aligned");
     if (!aligned(idx, a.idx16 ? 2 : 4) || !aligned(coef, a.coef16 ? 2 : 4))
         return fail(CSR_ERR_INVALID_ARG, "csr_encode: idx and coef must be aligned to their element size");
-    const size_t need = encode_workspace(a, algo);
+    const size_t need = encode_workspace(a, algo, desc->algo == CSR_ENCODE_AUTO);
+    if (desc->algo == CSR_ENCODE_AUTO && wide_pays(a, algo)) algo = CSR_ENCODE_WIDE;
     if (need) {
         if (!workspace || workspace_bytes < need || !aligned(workspace, 256))
             return fail(CSR_ERR_WORKSPACE, "csr_encode: workspace of %zu bytes (256-byte aligned) required, got %zu", need, workspace ? workspace_bytes : (size_t)0);
@@ -260,7 +291,8 @@ csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D,
                          : algo == CSR_ENCODE_SPLIT ? csr::launch_encode_split(a)
                          : algo == CSR_ENCODE_RESIDENT ? csr::launch_encode_resident(a)
                          : algo == CSR_ENCODE_GRAM ? csr::launch_encode_gram(a)
-                         : algo == kAlgoGramStep ? csr::launch_encode_gramstep(a) : csr::launch_encode_valu(a);
+                         : algo == kAlgoGramStep ? csr::launch_encode_gramstep(a)
+                         : algo == CSR_ENCODE_WIDE ? csr::launch_encode_wide(a) : csr::launch_encode_valu(a);
     if (e != hipSuccess) return fail(CSR_ERR_DEVICE, "csr_encode: %s", hipGetErrorString(e));
     return CSR_OK;
 }

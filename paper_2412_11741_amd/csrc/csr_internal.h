@@ -44,6 +44,11 @@ struct EncodeArgs {
 // fp32 vector-ALU encoder: any N, d in {32, 64, 128}.
 hipError_t launch_encode_valu(const EncodeArgs &a);
 
+// matrix-core encoder with the atoms split over a workgroup's waves: fp32 or fp16, small launches; N up to 65536.
+bool encode_wide_supported(const EncodeArgs &a);
+size_t encode_wide_workspace_bytes(const EncodeArgs &a);
+hipError_t launch_encode_wide(const EncodeArgs &a);
+
 // fp16 matrix-core encoder: chunks of 64 or 128 dimensions, fp16 inputs.
 bool encode_mfma_supported(const EncodeArgs &a);
 size_t encode_mfma_workspace_bytes(int32_t n_dicts, int64_t T, int32_t N, int32_t s);

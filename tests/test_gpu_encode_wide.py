@@ -1,0 +1,87 @@
+"""GPU parity: the encoder that splits the atoms over a workgroup's waves (encode_wide.hip), what CSR_ENCODE_AUTO runs for
+fp32 inputs and for fp16 launches that do not fill the chip otherwise."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2412_11741_amd as csr
+from paper_2412_11741_amd import synth
+from tests.test_gpu_encode import _assert_ok, _compare
+
+pytestmark = pytest.mark.gpu
+
+
+def _encode(X, D, s, **kw):
+    idx, coef = csr.csr_encode(torch.from_numpy(X).cuda(), torch.from_numpy(D).cuda(), s, algo=csr.CSR_ENCODE_WIDE, **kw)
+    torch.cuda.synchronize()
+    return idx.cpu().numpy(), coef.cpu().numpy()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("d,N,T,H,s", [
+    (128, 1024, 700, 2, 8),    # two passes of vectors would not fill the chip: one pass, ragged last workgroup
+    (128, 31, 33, 1, 4),       # fewer atoms than a tile, two workgroups
+    (128, 1, 1, 1, 2),         # one atom, one vector
+    (128, 257, 65, 3, 6),      # one atom in a tile of its own, waves without tiles
+    (128, 4099, 40, 1, 5),     # odd atom count over 16 or 17 tiles a wave
+    (64, 1000, 150, 2, 8),     # teams of eight lanes, two lists each
+    (32, 600, 300, 2, 8),      # teams of four lanes, four lists each
+    (128, 256, 9000, 2, 3),    # two passes of vectors per workgroup
+    (64, 160, 17000, 2, 3),
+])
+def test_shapes_against_the_oracle(dtype, d, N, T, H, s):
+    D = synth.dictionary(5, "dict_k", H, N, d, dtype)
+    X = synth.vectors(5, "keys", H, T, d, dtype, outliers=4)
+    X[0, 0] = 0.0                                  # a zero residual emits (0, 0)
+    if dtype == "f16":
+        X[-1, T // 2] = 3.0 * D[-1, N // 2]        # a residual that collapses after one step
+    idx, coef = _encode(X, D, s)
+    rows = None if T <= 1000 else np.r_[0:40, T // 2 - 20:T // 2 + 20, T - 40:T]
+    _assert_ok(_compare(X, D, s, idx, coef, rows=rows))
+    if T > 1:
+        assert not idx[0, 0].any() and not coef[0, 0].any()
+
+
+@pytest.mark.parametrize("dtype,scale", [("f32", 1e-20), ("f32", 1e15), ("f16", 1.0)])
+def test_equal_atoms_and_extreme_scales(dtype, scale):
+    # every atom three times: the best group, other groups and whole lists are undecided; the lowest atom has to win
+    base = synth.dictionary(6, "dict_k", 1, 96, 128, dtype)
+    D = np.concatenate([base] * 3, axis=1)
+    X = (synth.vectors(6, "values", 1, 50, 128, dtype).astype(np.float64) * scale).astype(base.dtype)
+    idx, coef = _encode(X, D, 4)
+    _assert_ok(_compare(X, D, 4, idx, coef))
+    assert idx.max() < 96
+
+
+def test_shared_dictionaries_in_place_chunks_and_errors():
+    B, Hkv, T, N, s, sn = 3, 2, 70, 160, 4, 2
+    D = np.stack([synth.dictionary(7 + c, "dict_v", Hkv, N, 64, "f16") for c in range(sn)], axis=1)
+    X = synth.vectors(7, "values", B * Hkv, T, 128, "f16")
+    Xg, Dg = torch.from_numpy(X).cuda(), torch.from_numpy(D).cuda()
+    icache = torch.zeros(B * Hkv, T + 9, sn, s, dtype=torch.int16, device="cuda")
+    ccache = torch.zeros(B * Hkv, T + 9, sn, s, dtype=torch.float16, device="cuda")
+    err = torch.empty(B * Hkv, T, sn, device="cuda")
+    csr.csr_encode(Xg, Dg, s, algo=csr.CSR_ENCODE_WIDE, idx=icache[:, 5:5 + T], coef=ccache[:, 5:5 + T], res_norm2=err)
+    for c in range(sn):
+        Xc, Dc = np.ascontiguousarray(X[:, :, 64 * c:64 * c + 64]), np.tile(D[:, c], (B, 1, 1))
+        _assert_ok(_compare(Xc, Dc, s, icache[:, 5:5 + T, c].cpu().numpy(), ccache[:, 5:5 + T, c].cpu().numpy()))
+    rebuilt = csr.csr_reconstruct(Dg, icache[:, 5:5 + T], ccache[:, 5:5 + T], out_dtype=torch.float32)
+    exact = ((Xg.float() - rebuilt).view(B * Hkv, T, sn, 64) ** 2).sum(-1)
+    assert torch.allclose(err, exact, rtol=5e-3, atol=1e-3)
+    assert not icache[:, :5].any() and not ccache[:, 5 + T:].any()
+
+
+@pytest.mark.parametrize("algo,dtype,d,N,T,H", [
+    ("valu", "f32", 128, 1024, 3000, 2), ("valu", "f32", 64, 500, 2000, 2), ("valu", "f32", 32, 1024, 2000, 2),
+    ("valu", "f16", 128, 1000, 2000, 2), ("mfma", "f16", 128, 2048, 9000, 2), ("mfma", "f16", 64, 2048, 9000, 2),
+    ("resident", "f16", 128, 256, 9000, 2), ("resident", "f16", 128, 512, 3000, 2), ("resident", "f16", 64, 1024, 9000, 2),
+])
+@pytest.mark.parametrize("closed", [False, True])
+def test_same_bits_as_the_encoder_of_the_larger_launches(algo, dtype, d, N, T, H, closed):
+    # CSR_ENCODE_AUTO chooses between the two by the launch's size: the codes must not depend on it, down to ties
+    algo = {"valu": csr.CSR_ENCODE_VALU, "mfma": csr.CSR_ENCODE_MFMA, "resident": csr.CSR_ENCODE_RESIDENT}[algo]
+    X = torch.from_numpy(synth.vectors(8, "keys", H, T, d, dtype, outliers=4)).cuda()
+    D = torch.from_numpy(synth.dictionary(8, "dict_k", H, N, d, dtype)).cuda()
+    iw, cw = csr.csr_encode(X, D, 8, algo=csr.CSR_ENCODE_WIDE, closed_loop=closed)
+    ie, ce = csr.csr_encode(X, D, 8, algo=algo, closed_loop=closed)
+    assert torch.equal(iw, ie) and torch.equal(cw, ce)
