@@ -1,213 +1,200 @@
 // Matching Pursuit encoder for FEW vectors per dictionary (gfx950): the tokens generated in one decoding step,
 // which Section "KV Decomposition and Sparse Storage" encodes like the prompt's (Eq.2-4, s iterations).
 //
-// With a handful of vectors per dictionary the work is a matrix-vector product per iteration: every iteration
-// must read the whole dictionary (1 MB at N = 4096) for a few dot products per atom, and one workgroup per
-// dictionary - the shape of the prefill encoder - leaves most of the chip idle while a single CU streams it
-// (0.7 ms for 64 dictionaries, whatever the vector count).  Here the ATOMS of every dictionary are split over
-// k workgroups, so that all CUs stream dictionary slices at once, and the iteration's arg-max over the slices
-// is taken by the next launch: one launch per iteration plus one that stores the last pair, s + 1 in all, no
-// spinning between workgroups.
+// With a handful of vectors per dictionary the work is a matrix-vector product per iteration: every iteration must look
+// at the whole dictionary (1 MB at N = 4096) for a few dot products per atom.  One workgroup per dictionary - the shape of
+// the prefill encoder - leaves most of the chip idle while a single CU streams it.  Here the ATOMS of every dictionary are
+// split over k workgroups, one per CU, and ONE launch runs all iterations: a workgroup reads its slice once, into registers
+// (the dictionaries of a layer's 32 heads, 33 MB, are 128 KB per CU, a quarter of its registers), and the k workgroups of a
+// dictionary exchange their slices' candidates through device memory after every iteration.
 //
-//   launch g, workgroup (slice sl, dictionary): for each block of 32 vectors of that dictionary
-//     g > 0   the slices' candidates of iteration g - 1 give its pick (largest |c|, lowest atom on ties),
-//             R_g = R_{g-1} - c d (Eq.4, fp32, residual kept in scratch); every slice's workgroup does this
-//             with identical arithmetic, slice 0 stores R_g and the pair (i, c) of iteration g - 1
-//     g = 0   R_0 = x, scaled by the power of two that brings its largest element into [2^11, 2^12)
-//     g < s   R_g is split into hi + lo (two fp16, 22 significant bits); c[n] = hi . d_n + lo . d_n on the
-//             matrix cores (v_mfma_f32_32x32x16_f16, atoms as rows straight from global memory, vectors as
-//             columns in registers; products of fp16 pairs are exact, accumulation is fp32), so the decision
-//             has the precision of the prefill encoder's exact resolve step; the slice's best (|c|, n, c) per
-//             vector goes to scratch.
-// Scratch per vector: two residuals (ping-pong: a launch reads one and writes the other), two scale exponents,
-// 2 k candidates.
+//   sweep    each wave: c[n] = hi . d_n + lo . d_n for its tiles on the matrix cores (v_mfma_f32_32x32x16_f16, atoms as
+//            rows, vectors as columns; R = hi + lo, two fp16, 22 significant bits; products of fp16 pairs are exact,
+//            accumulation is fp32), the wave's best (|c|, n, c) per vector
+//   publish  the slice's best per vector as ONE 64-bit word - |c|, atom, sign and the iteration's tag - in a slot of its own
+//            (iteration, vector, slice), with a relaxed device-scope store: the word says by itself whether it has arrived
+//   collect  the other slices' words, polled with relaxed device-scope loads
+//   update   every workgroup of the dictionary applies Eq.4 to its own copy of the residuals (fp32, in LDS) with identical
+//            arithmetic, so the copies never diverge; slice 0 stores the pair
+//
+// The workgroups need not run at the same time: one that starts late finds the others' words and catches up, and one that
+// waits in vain for kPatience (its partners hold no CU, because other work does) computes the missing slices' candidates
+// itself, from device memory, with the same arithmetic - every wait ends, and the result does not depend on it.  The slots
+// are cleared by a launch of their own before (a workspace's contents are undefined); a slot is written once per call.
+//
+// Bound: reading the dictionaries once, then a dependent chain per iteration - hi and lo from LDS, 16 dependent matrix
+// instructions per tile, the tournament over the waves, publish and poll (one trip each to where the chip's L2s meet, 0.5
+// us together), the row of the chosen atom, the update.  32 dictionaries of 4096 atoms, s = 8, one vector each: 37 us (11
+// us for one iteration, 3.5 us for every further one) against 98 us for the s + 1 launches this replaces, which read the
+// dictionaries again in every iteration; 64 vectors each 62 against 328; 32 x 256 atoms, where nothing is exchanged, 20
+// against 49.
+#include <atomic>
 #include <cmath>
 
 #include "csr_internal.h"
 #include "encode_common.h"
+#include "lane_ops.h"
 
 namespace csr {
 namespace {
 
 using namespace enc;
+using namespace lane;
 
-constexpr int kWaves = 4;
+constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kMaxVectors = 128;  // per dictionary; beyond that the prefill encoder's shape is the better one
+constexpr int kMaxVectors = 128;   // per dictionary; beyond that the prefill encoders' shapes are the better ones
 constexpr int kMaxSlices = 16;
-constexpr int kTargetGroups = 512;  // workgroups per launch aimed at (two per CU)
-
-
-
+constexpr int kTargetGroups = 256; // one workgroup per CU
+constexpr int kPatience = 10000;   // ticks of the 100 MHz counter a workgroup waits for its partners: 100 us
 
 struct SplitParams {
     const __half *X;
     const __half *Dict;
     void *idx_out;
     void *coef_out;
-    float *Rbuf;       // [2][V][DC]
-    int32_t *sexp;     // [2][V]
-    float4 *cand;      // [2][V][k]
-    int64_t V;         // vectors in all
+    unsigned long long *slots;   // [s][V][k]
+    int64_t V;                   // vectors in all
     int64_t T;
     int64_t x_stride_h, x_stride_t, code_stride_h;
-    int32_t N, s, sn, dict_count, M, k, g, idx16, coef16;   // coef16: kCoefF16 | kCoefClosed
-    float *res_norm2;  // optional [H][T][sn]
+    int32_t N, s, sn, dict_count, n_dicts, M, k, idx16, coef_mode;
+    float *res_norm2;            // optional [H][T][sn]
 };
 
-// Lane (col, hf): column col of the MFMA's B operand = vector m0 + col of the block; it holds dimensions
-// hf DC/2 .. hf DC/2 + DC/2 - 1 (the contraction index is permuted the same way in both operands), as
-// kFrags pieces of 8.
-template <int DC>
-__global__ __launch_bounds__(kThreads, 2) void encode_split_kernel(const SplitParams p)
+// A candidate as an integer whose maximum is the tie rule of Eq.3 (largest |c|, then the lowest atom):
+// |c| | 0xffffff - n | tag (7 bits) | sign of c
+__device__ __forceinline__ unsigned long long pack_candidate(float c, int n, int tag)
+{
+    const uint32_t b = __float_as_uint(c);
+    return ((unsigned long long)(b & 0x7fffffffu) << 32) | ((uint32_t)(0xffffff - n) << 8) | ((uint32_t)tag << 1) | (b >> 31);
+}
+__device__ __forceinline__ int candidate_atom(unsigned long long w) { return 0xffffff - (int)((uint32_t)w >> 8); }
+__device__ __forceinline__ int candidate_tag(unsigned long long w) { return (int)(((uint32_t)w >> 1) & 127u); }
+__device__ __forceinline__ float candidate_coef(unsigned long long w)
+{
+    return __uint_as_float((uint32_t)(w >> 32) | ((uint32_t)w << 31));
+}
+struct OpMaxU64 { __device__ __forceinline__ unsigned long long operator()(unsigned long long a, unsigned long long b) const { return a > b ? a : b; } };
+
+__global__ __launch_bounds__(256) void clear_slots_kernel(ulonglong2 *__restrict__ slots, int64_t n2)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n2) slots[i] = make_ulonglong2(0ull, 0ull);
+}
+
+// LDS byte offset of dimensions 4 pc .. 4 pc + 3 of vector v's residual: 32 vectors' rows are read at the same piece
+template <int DC> __device__ __forceinline__ int res_at(int v, int pc) { return v * (DC * 4) + ((pc ^ (v & 15)) << 4); }
+
+// ... of dimensions 8 p .. 8 p + 7 in its fp16 copies
+template <int DC> __device__ __forceinline__ int half_at(int v, int p) { return v * (DC * 2) + ((p ^ (DC == 128 ? (v & 15) : ((v >> 1) & 7))) << 4); }
+
+struct SplitState { int32_t sexp, pad; int64_t vid, code_at; };   // scale of a vector's residual, its number, its code's first pair
+
+// HELD: tiles of 32 atoms a wave keeps in registers
+template <int DC, int HELD>
+__global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParams p)
 {
     constexpr int kFrags = DC / 16;
-    __shared__ float4 red[kWaves][32];
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    constexpr int L = DC / 8;                  // lanes of a vector's team in the update, 8 dimensions each
+    constexpr int kTeams = kThreads / L;
+    constexpr int kSlots = kMaxSlices / L;     // slices a lane of a team waits for, at most: 1 or 2
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int m_pad = (p.M + 31) & ~31;        // vectors, whole blocks of 32
+    unsigned char *res = lds;                        // [m_pad][DC] fp32: the residuals
+    unsigned char *hi_s = res + m_pad * DC * 4;      // [m_pad][DC] fp16: hi, and behind it lo
+    unsigned char *lo_s = hi_s + m_pad * DC * 2;
+    unsigned long long *red = reinterpret_cast<unsigned long long *>(lo_s + m_pad * DC * 2);      // [kWaves][m_pad]
+    SplitState *state = reinterpret_cast<SplitState *>(red + kWaves * m_pad);                     // [M]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, hf = lane >> 5;
-    const int sl = blockIdx.x, dct = blockIdx.y;  // dct = dictionary * sn + chunk
+    const int sub = tid % L, team = tid / L;
+    // Workgroups are dealt to the 8 XCDs round-robin: the slices of a dictionary sit on one XCD, whose L2 then has the rows
+    // the update gathers.
+    int sl, dct;                               // dct = dictionary * sn + chunk
+    if (p.n_dicts % 8 == 0) {
+        const int i = blockIdx.x >> 3;
+        dct = (blockIdx.x & 7) * (p.n_dicts >> 3) + i / p.k;
+        sl = i % p.k;
+    } else {
+        dct = blockIdx.x / p.k;
+        sl = blockIdx.x % p.k;
+    }
     const int dict = dct / p.sn, ch = dct - dict * p.sn;
     const __half *Dh = p.Dict + (int64_t)dct * p.N * DC;
     const int tiles = p.N >> 5;
     const int per_slice = (tiles + p.k - 1) / p.k;
     const int t_begin = sl * per_slice, t_end = min(tiles, t_begin + per_slice);
-    const int g = p.g;
 
-    // This wave's first tiles of the slice are requested before anything else and stay in registers for all
-    // blocks of vectors: their fetch overlaps the dependent chain below (candidates -> atom row -> residual),
-    // which does not need them.  (The last launch sweeps nothing.)
-    constexpr int kPrefetch = 256 / DC;  // tiles: 2 of 128 dimensions, 4 of 64 (64 registers either way)
     auto load_tile = [&](int tile, uint4 (&a)[kFrags]) {
         const __half *row = Dh + ((int64_t)tile * 32 + col) * DC + hf * (DC / 2);
 #pragma unroll
         for (int j = 0; j < kFrags; ++j) a[j] = *reinterpret_cast<const uint4 *>(row + 8 * j);
     };
-    uint4 pre[kPrefetch][kFrags];
-    if (g < p.s) {
+    uint4 held[HELD][kFrags];
 #pragma unroll
-        for (int q = 0; q < kPrefetch; ++q)
-            if (t_begin + wave + q * kWaves < t_end) load_tile(t_begin + wave + q * kWaves, pre[q]);
-    }
+    for (int q = 0; q < HELD; ++q)
+        if (t_begin + wave + q * kWaves < t_end) load_tile(t_begin + wave + q * kWaves, held[q]);
 
-    for (int m0 = 0; m0 < p.M; m0 += 32) {
+    // this lane's 8 dimensions of a residual: fp32 and the split into hi + lo
+    auto put = [&](int v, const float (&R)[8]) {
+        half8 h, l;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const _Float16 hh = (_Float16)R[e];
+            h[e] = hh;
+            l[e] = (_Float16)(R[e] - (float)hh);
+        }
+        *reinterpret_cast<float4 *>(res + res_at<DC>(v, 2 * sub)) = make_float4(R[0], R[1], R[2], R[3]);
+        *reinterpret_cast<float4 *>(res + res_at<DC>(v, 2 * sub + 1)) = make_float4(R[4], R[5], R[6], R[7]);
+        *reinterpret_cast<half8 *>(hi_s + half_at<DC>(v, sub)) = h;
+        *reinterpret_cast<half8 *>(lo_s + half_at<DC>(v, sub)) = l;
+    };
+
+    // ---- the vectors, scaled by a power of two that brings max |x_k| into [2^11, 2^12): hi and lo stay normal ----------
+    for (int v = team; v < m_pad; v += kTeams) {
         // vector m of this dictionary: block h = (m / T) dict_count + dict, its token m % T
-        const bool valid = m0 + col < p.M;
-        const int m = valid ? m0 + col : p.M - 1;
+        const int m = min(v, p.M - 1);         // the last block's missing columns recompute the last vector
         const int rep = (int)(m / p.T);
-        const int64_t t = m - rep * p.T;
-        const int64_t h = (int64_t)rep * p.dict_count + dict;
-        const int64_t vid = (h * p.T + t) * p.sn + ch;
+        const int64_t t = m - rep * p.T, h = (int64_t)rep * p.dict_count + dict;
+        float R[8];
+        unpack8(*reinterpret_cast<const uint4 *>(p.X + h * p.x_stride_h + t * p.x_stride_t + ch * DC + sub * 8), R);
+        float amax = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(R[e]));
+        amax = row_reduce<L>(amax, OpMax());
+        int ex = 0;
+        if (amax > 0.0f && amax < INFINITY) {
+            (void)frexpf(amax, &ex);           // amax = f 2^ex, f in [0.5, 1)
+            ex = 12 - ex;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) R[e] = ldexpf(R[e], ex);
+        put(v, R);
+        if (sub == 0 && v < p.M) {
+            SplitState st;
+            st.sexp = ex; st.pad = 0;
+            st.vid = (h * p.T + t) * p.sn + ch;
+            st.code_at = h * p.code_stride_h + (t * p.sn + ch) * p.s;
+            state[v] = st;
+        }
+    }
+    __syncthreads();
 
-        float R[kFrags][8];
-        int sexp_cur = 0;
-        if (g == 0) {
-            const __half *xr = p.X + h * p.x_stride_h + t * p.x_stride_t + ch * DC + hf * (DC / 2);
-            float amax = 0.0f;
-#pragma unroll
-            for (int j = 0; j < kFrags; ++j) {
-                const uint4 raw = *reinterpret_cast<const uint4 *>(xr + 8 * j);
-                unpack8(raw, R[j]);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(R[j][e]));
-            }
-            amax = fmaxf(amax, xchg32f(amax, hf));
-            if (amax > 0.0f && amax < INFINITY) {
-                int ex;
-                (void)frexpf(amax, &ex);  // amax = f 2^ex, f in [0.5, 1)
-                sexp_cur = 12 - ex;       // brings amax into [2^11, 2^12): hi and lo stay normal fp16 numbers
-            }
-#pragma unroll
-            for (int j = 0; j < kFrags; ++j)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) R[j][e] = ldexpf(R[j][e], sexp_cur);
-        } else {
-            const int prev = (g - 1) & 1;
-            // the pick of iteration g - 1: slices ascend, so a strict comparison keeps the lowest atom on ties
-            const float4 *cd = p.cand + ((int64_t)prev * p.V + vid) * p.k;
-            float ba = -1.0f, bc = 0.0f;
-            int bi = 0;
-            for (int j = 0; j < p.k; ++j) {
-                const float4 c4 = cd[j];
-                if (c4.x > ba) { ba = c4.x; bi = __float_as_int(c4.y); bc = c4.z; }
-            }
-            const float *Rp = p.Rbuf + ((int64_t)prev * p.V + vid) * DC + hf * (DC / 2);
-            const __half *row = Dh + (int64_t)bi * DC + hf * (DC / 2);
-            const int sexp_prev = p.sexp[(int64_t)prev * p.V + vid];
-            // closed loop: what Eq.4 subtracts is the coefficient as it will be stored (rounded in the input's scale)
-            if (coef_rounds_in_loop(p.coef16)) bc = ldexpf(__half2float(__float2half_rn(ldexpf(bc, -sexp_prev))), sexp_prev);
-#pragma unroll
-            for (int j = 0; j < kFrags; ++j) {
-                const float4 r0 = *reinterpret_cast<const float4 *>(Rp + 8 * j);
-                const float4 r1 = *reinterpret_cast<const float4 *>(Rp + 8 * j + 4);
-                const uint4 raw = *reinterpret_cast<const uint4 *>(row + 8 * j);
-                float d[8];
-                unpack8(raw, d);
-                const float r[8] = {r0.x, r0.y, r0.z, r0.w, r1.x, r1.y, r1.z, r1.w};
-#pragma unroll
-                for (int e = 0; e < 8; ++e) R[j][e] = fmaf(-bc, d[e], r[e]);  // Eq.4 with the unrounded coefficient
-            }
-            if (sl == 0 && valid) {
-                const int64_t o = h * p.code_stride_h + (t * p.sn + ch) * p.s + (g - 1);
-                if (hf == 0) {
-                    if (p.idx16) reinterpret_cast<uint16_t *>(p.idx_out)[o] = (uint16_t)bi;
-                    else reinterpret_cast<int32_t *>(p.idx_out)[o] = bi;
-                } else {
-                    const float c_out = ldexpf(bc, -sexp_prev);
-                    if (coef_is_f16(p.coef16)) reinterpret_cast<__half *>(p.coef_out)[o] = __float2half_rn(c_out);
-                    else reinterpret_cast<float *>(p.coef_out)[o] = c_out;
-                }
-            }
-            sexp_cur = sexp_prev;
-        }
-        float r2 = 0.0f;
-#pragma unroll
-        for (int j = 0; j < kFrags; ++j)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) r2 = fmaf(R[j][e], R[j][e], r2);
-        r2 += xchg32f(r2, hf);
-        if (g == p.s) {  // the last launch only stores the last pair and what is left (uniform over the grid)
-            if (p.res_norm2 && sl == 0 && valid && hf == 0) p.res_norm2[vid] = ldexpf(r2, -2 * sexp_cur);
-            continue;
-        }
-        // A residual that has shrunk a lot (a vector that is nearly a multiple of an atom) is scaled up again
-        // before the split, or lo would sink into the fp16 subnormals; one that has grown (atoms of norm above
-        // sqrt(2) make Eq.4 expand it) is scaled down before hi could leave the fp16 range.
-        if (g > 0 && ((r2 < 65536.0f && r2 > 0.0f) || (r2 >= 1073741824.0f && r2 < INFINITY))) {
-            int e2 = 0;
-            (void)frexpf(r2, &e2);                // |R| in [2^((e2-1)/2), 2^(e2/2))
-            const int k2 = 14 - (e2 + 1) / 2;     // brings |R| into [2^12.5, 2^14.5)
-            const float sc = ldexpf(1.0f, k2);
-#pragma unroll
-            for (int j = 0; j < kFrags; ++j)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) R[j][e] *= sc;
-            sexp_cur += k2;
-        }
-        if (sl == 0 && valid) {
-            float *Rw = p.Rbuf + ((int64_t)(g & 1) * p.V + vid) * DC + hf * (DC / 2);
-#pragma unroll
-            for (int j = 0; j < kFrags; ++j) {
-                *reinterpret_cast<float4 *>(Rw + 8 * j) = make_float4(R[j][0], R[j][1], R[j][2], R[j][3]);
-                *reinterpret_cast<float4 *>(Rw + 8 * j + 4) = make_float4(R[j][4], R[j][5], R[j][6], R[j][7]);
-            }
-            if (hf == 0) p.sexp[(int64_t)(g & 1) * p.V + vid] = sexp_cur;
-        }
+    // The best candidate of vectors m0 .. m0 + 31 over the tiles first, first + step .. below last, as a packed word with
+    // `tag` (lanes col of either half); `own`: this wave's tiles of the workgroup's slice, the first ones in registers.
+    auto sweep = [&](int m0, int first, int last, int step, bool own, int tag) {
         half8 hi[kFrags], lo[kFrags];
+        const int mine = min(m0 + col, p.M - 1);   // columns past the last vector repeat it: one LDS address for them all
 #pragma unroll
         for (int j = 0; j < kFrags; ++j) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const _Float16 hh = (_Float16)R[j][e];
-                hi[j][e] = hh;
-                lo[j][e] = (_Float16)(R[j][e] - (float)hh);
-            }
+            hi[j] = *reinterpret_cast<const half8 *>(hi_s + half_at<DC>(mine, hf * kFrags + j));
+            lo[j] = *reinterpret_cast<const half8 *>(lo_s + half_at<DC>(mine, hf * kFrags + j));
         }
-
-        // ---- this wave's tiles of the slice: c[n] = hi . d_n + lo . d_n ---------------------------
         float ba = -1.0f, bc = 0.0f;
         int bi = 0;
-        auto sweep_tile = [&](int tile, const uint4 (&a)[kFrags]) {
+        auto tile_best = [&](int tile, const uint4 (&a)[kFrags]) {
             floatx16 acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
@@ -217,44 +204,179 @@ __global__ __launch_bounds__(kThreads, 2) void encode_split_kernel(const SplitPa
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, hi[j], acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, lo[j], acc, 0, 0, 0);
             }
-            // accumulator r of lane half hf is atom 8 (r / 4) + (r % 4) + 4 hf of the tile: ascending in r
+            // accumulator r of lane half hf is atom 8 (r / 4) + (r % 4) + 4 hf of the tile, ascending in r: a tournament in
+            // which the left side wins ties
+            float c[8];
+            int at[8];
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float ab = fabsf(acc[r]);
-                if (ab > ba) { ba = ab; bi = tile * 32 + 8 * (r >> 2) + (r & 3) + 4 * hf; bc = acc[r]; }
+            for (int r = 0; r < 8; ++r) {
+                const bool right = fabsf(acc[2 * r + 1]) > fabsf(acc[2 * r]);
+                c[r] = right ? acc[2 * r + 1] : acc[2 * r];
+                at[r] = right ? 2 * r + 1 : 2 * r;
+            }
+#pragma unroll
+            for (int m = 4; m >= 1; m >>= 1) {
+#pragma unroll
+                for (int r = 0; r < m; ++r) {
+                    const bool right = fabsf(c[2 * r + 1]) > fabsf(c[2 * r]);
+                    c[r] = right ? c[2 * r + 1] : c[2 * r];
+                    at[r] = right ? at[2 * r + 1] : at[2 * r];
+                }
+            }
+            if (fabsf(c[0]) > ba) {
+                ba = fabsf(c[0]);
+                bi = tile * 32 + 8 * (at[0] >> 2) + (at[0] & 3) + 4 * hf;
+                bc = c[0];
             }
         };
+        if (own) {
 #pragma unroll
-        for (int q = 0; q < kPrefetch; ++q)
-            if (t_begin + wave + q * kWaves < t_end) sweep_tile(t_begin + wave + q * kWaves, pre[q]);
-        // tiles beyond the prefetched ones
-        for (int tile = t_begin + wave + kPrefetch * kWaves; tile < t_end; tile += kWaves) {
-            uint4 a_cur[kFrags];
-            load_tile(tile, a_cur);
-            sweep_tile(tile, a_cur);
+            for (int q = 0; q < HELD; ++q)
+                if (first + q * kWaves < last) tile_best(first + q * kWaves, held[q]);
         }
-        // the two lanes of a vector, then the waves
+        for (int tile = first + (own ? HELD * kWaves : 0); tile < last; tile += step) {
+            uint4 a[kFrags];
+            load_tile(tile, a);
+            tile_best(tile, a);
+        }
         take_better(ba, bi, bc, xchg32f(ba, hf), (int)xchg32((uint32_t)bi, hf), xchg32f(bc, hf));
-        if (hf == 0) red[wave][col] = make_float4(ba, __int_as_float(bi), bc, 0.0f);
-        __syncthreads();
-        if (wave == 0 && hf == 0) {
-#pragma unroll
-            for (int w = 1; w < kWaves; ++w) {
-                const float4 o = red[w][col];
-                take_better(ba, bi, bc, o.x, __float_as_int(o.y), o.z);
-            }
-            if (valid) p.cand[((int64_t)(g & 1) * p.V + vid) * p.k + sl] = make_float4(ba, __int_as_float(bi), bc, 0.0f);
+        // a wave without tiles: below every candidate
+        return ba >= 0.0f ? pack_candidate(bc, bi, tag) : (unsigned long long)((uint32_t)tag << 1);
+    };
+#pragma unroll 1
+    for (int g = 0; g < p.s; ++g) {
+        const int tag = g + 1;
+        for (int m0 = 0; m0 < p.M; m0 += 32) {
+            const unsigned long long w = sweep(m0, t_begin + wave, t_end, kWaves, true, tag);
+            if (hf == 0) red[wave * m_pad + m0 + col] = w;
         }
-        __syncthreads();  // `red` is reused by the next block of vectors
+        __syncthreads();
+        // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published:
+        unsigned long long *slot = p.slots + (int64_t)g * p.V * p.k;
+        for (int v = team; v < p.M; v += kTeams) {
+            unsigned long long w = red[(sub & (kWaves - 1)) * m_pad + v];
+            w = row_reduce<kWaves>(w, OpMaxU64());
+            if (sub == 0) {
+                red[v] = w;
+                if (p.k > 1) __hip_atomic_store(slot + state[v].vid * p.k + sl, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+        wave_lds_fence();
+        // ---- the other slices' candidates, the pick, Eq.4 -----------------------------------------------------------------
+        for (int v0 = wave * (64 / L); v0 < p.M; v0 += kTeams) {   // (uniform over the wave)
+            const int v = v0 + lane / L;
+            const int vc = min(v, p.M - 1);   // a team past the last vector idles along: it waits for nobody
+            const int slices = v < p.M ? p.k : 0;
+            unsigned long long w = vc == v ? red[v] : 0ull;
+            if (p.k > 1) {
+                unsigned long long *mine = slot + state[vc].vid * p.k;
+                unsigned long long got[kSlots];
+                bool ok = true;
+#pragma unroll
+                for (int i = 0; i < kSlots; ++i) {
+                    const int j = sub + i * L;
+                    got[i] = 0ull;
+                    if (j < slices && j != sl) {
+                        got[i] = __hip_atomic_load(mine + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        ok = ok && candidate_tag(got[i]) == tag;
+                    }
+                }
+                if (__ballot(!ok)) {
+                    const uint64_t began = wall_clock64();
+                    do {
+                        __builtin_amdgcn_s_sleep(1);
+                        ok = true;
+#pragma unroll
+                        for (int i = 0; i < kSlots; ++i) {
+                            const int j = sub + i * L;
+                            if (j < slices && j != sl && candidate_tag(got[i]) != tag) {
+                                got[i] = __hip_atomic_load(mine + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                ok = ok && candidate_tag(got[i]) == tag;
+                            }
+                        }
+                    } while (__ballot(!ok) && wall_clock64() - began <= (uint64_t)kPatience);
+                    if (__ballot(!ok)) {
+                        // partners that hold no CU: the missing slices' candidates computed here, by this wave alone
+                        for (int t = 0; t < 64 / L; ++t) {
+                            for (int j = 0; j < p.k; ++j) {
+                                const int from = t * L + j % L;        // the lane that waits for slice j
+                                bool miss = false;
+#pragma unroll
+                                for (int i = 0; i < kSlots; ++i) miss = miss || (j / L == i && j < slices && j != sl && candidate_tag(got[i]) != tag);
+                                if (!((__ballot(miss) >> from) & 1ull)) continue;
+                                const int vt = min(v0 + t, p.M - 1);
+                                const int first = j * per_slice;
+                                const unsigned long long o = sweep(vt & ~31, first, min(tiles, first + per_slice), 1, false, tag);
+                                const unsigned long long theirs = __shfl(o, vt & 31, 64);
+#pragma unroll
+                                for (int i = 0; i < kSlots; ++i)
+                                    if (lane == from && j / L == i) got[i] = theirs;
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < kSlots; ++i) w = got[i] > w ? got[i] : w;
+                w = row_reduce<L>(w, OpMaxU64());
+            }
+            // (no candidate at all - correlations that are not numbers - counts as atom 0 with coefficient 0)
+            const int n = candidate_atom(w) < p.N ? candidate_atom(w) : 0;
+            float c = candidate_coef(w);
+            float d[8];
+            unpack8(*reinterpret_cast<const uint4 *>(Dh + (int64_t)n * DC + sub * 8), d);
+            const int sexp = state[vc].sexp;
+            // closed loop: what Eq.4 subtracts is the coefficient as it will be stored (rounded in the input's scale)
+            if (coef_rounds_in_loop(p.coef_mode)) c = ldexpf(__half2float(__float2half_rn(ldexpf(c, -sexp))), sexp);
+            if (sl == 0 && v < p.M) {
+                const int64_t o = state[vc].code_at + g;
+                if (sub == 0) {
+                    if (p.idx16) reinterpret_cast<uint16_t *>(p.idx_out)[o] = (uint16_t)n;
+                    else reinterpret_cast<int32_t *>(p.idx_out)[o] = n;
+                } else if (sub == 1) {
+                    const float c_out = ldexpf(c, -sexp);
+                    if (coef_is_f16(p.coef_mode)) reinterpret_cast<__half *>(p.coef_out)[o] = __float2half_rn(c_out);
+                    else reinterpret_cast<float *>(p.coef_out)[o] = c_out;
+                }
+            }
+            const float4 x = *reinterpret_cast<const float4 *>(res + res_at<DC>(v, 2 * sub));
+            const float4 y = *reinterpret_cast<const float4 *>(res + res_at<DC>(v, 2 * sub + 1));
+            float R[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+            float r2 = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                R[e] = fmaf(-c, d[e], R[e]);   // Eq.4 with the unrounded coefficient
+                r2 = fmaf(R[e], R[e], r2);
+            }
+            r2 = row_reduce<L>(r2, OpAdd());
+            if (g + 1 == p.s) {
+                if (p.res_norm2 && sl == 0 && sub == 0 && v < p.M) p.res_norm2[state[vc].vid] = ldexpf(r2, -2 * sexp);
+                continue;
+            }
+            // A residual that has shrunk a lot (a vector that is nearly a multiple of an atom) is scaled up again
+            // before the split, or lo would sink into the fp16 subnormals; one that has grown (atoms of norm above
+            // sqrt(2) make Eq.4 expand it) is scaled down before hi could leave the fp16 range.
+            if ((r2 < 65536.0f && r2 > 0.0f) || (r2 >= 1073741824.0f && r2 < INFINITY)) {
+                int e2 = 0;
+                (void)frexpf(r2, &e2);                // |R| in [2^((e2-1)/2), 2^(e2/2))
+                const int k2 = 14 - (e2 + 1) / 2;     // brings |R| into [2^12.5, 2^14.5)
+                const float sc = ldexpf(1.0f, k2);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) R[e] *= sc;
+                wave_lds_fence();                     // the team has read the old exponent
+                if (sub == 0 && v < p.M) state[v].sexp = sexp + k2;
+            }
+            if (v < p.M) put(v, R);
+        }
+        __syncthreads();
     }
 }
 
 size_t r256(size_t v) { return (v + 255) & ~size_t(255); }
 
 struct SplitPlan {
-    int32_t k, M;
+    int32_t k, M, held;
     int64_t V;
-    size_t off_R, off_sexp, off_cand, total;
+    size_t lds, total;
 };
 
 SplitPlan plan_split(const EncodeArgs &a)
@@ -269,12 +391,30 @@ SplitPlan plan_split(const EncodeArgs &a)
     if (k > kMaxSlices) k = kMaxSlices;
     if (k < 1) k = 1;
     pl.k = k;
-    size_t off = 0;
-    pl.off_R = off;    off += r256((size_t)2 * pl.V * a.d * sizeof(float));
-    pl.off_sexp = off; off += r256((size_t)2 * pl.V * sizeof(int32_t));
-    pl.off_cand = off; off += r256((size_t)2 * pl.V * k * sizeof(float4));
-    pl.total = off;
+    const int per_wave = ((tiles + k - 1) / k + kWaves - 1) / kWaves;
+    pl.held = per_wave <= 1 ? 1 : per_wave <= 2 ? 2 : 4;   // of 128 dimensions: 32, 64 or 128 registers
+    const int m_pad = (pl.M + 31) & ~31;
+    pl.lds = (size_t)m_pad * a.d * 8 + (size_t)kWaves * m_pad * 8 + (size_t)pl.M * sizeof(SplitState);
+    pl.total = r256((size_t)a.s * pl.V * k * sizeof(unsigned long long));
     return pl;
+}
+
+template <int DC, int HELD>
+hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitParams &p)
+{
+    static std::atomic<bool> attr_set[64];   // per device, once: many vectors need more LDS than the default limit
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (!attr_set[dev].load(std::memory_order_acquire)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_split_kernel<DC, HELD>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                159 * 1024);   // (the barrier that votes has a little LDS of its own)
+        if (e != hipSuccess) return e;
+        attr_set[dev].store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL((encode_split_kernel<DC, HELD>), dim3((unsigned)(pl.k * p.n_dicts)), dim3(kThreads), pl.lds, a.stream, p);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -283,7 +423,7 @@ bool encode_split_supported(const EncodeArgs &a)
 {
     if (!(a.f16 && (a.d == 128 || a.d == 64) && a.N >= 32 && a.N % 32 == 0 && a.N <= (1 << 24))) return false;
     if (a.dict_count < 1 || a.H % a.dict_count != 0) return false;
-    if ((int64_t)a.dict_count * a.sn > 65535) return false;  // grid.y
+    if ((int64_t)a.dict_count * a.sn > 65535) return false;
     return (int64_t)(a.H / a.dict_count) * a.T <= kMaxVectors;
 }
 
@@ -292,24 +432,21 @@ size_t encode_split_workspace_bytes(const EncodeArgs &a) { return plan_split(a).
 hipError_t launch_encode_split(const EncodeArgs &a)
 {
     const SplitPlan pl = plan_split(a);
-    char *ws = static_cast<char *>(a.workspace);
     SplitParams p{};
     p.X = (const __half *)a.X; p.Dict = (const __half *)a.D; p.idx_out = a.idx; p.coef_out = a.coef;
-    p.Rbuf = reinterpret_cast<float *>(ws + pl.off_R);
-    p.sexp = reinterpret_cast<int32_t *>(ws + pl.off_sexp);
-    p.cand = reinterpret_cast<float4 *>(ws + pl.off_cand);
+    p.slots = reinterpret_cast<unsigned long long *>(a.workspace);
     p.V = pl.V; p.T = a.T; p.x_stride_h = a.x_stride_h; p.x_stride_t = a.x_stride_t; p.code_stride_h = a.code_stride_h;
-    p.N = a.N; p.s = a.s; p.sn = a.sn; p.dict_count = a.dict_count; p.M = pl.M; p.k = pl.k;
-    p.idx16 = a.idx16; p.coef16 = (a.coef16 ? kCoefF16 : 0) | (a.closed_loop ? kCoefClosed : 0); p.res_norm2 = a.res_norm2;
-    const dim3 grid((unsigned)pl.k, (unsigned)(a.dict_count * a.sn));
-    for (int g = 0; g <= a.s; ++g) {
-        p.g = g;
-        if (a.d == 64) hipLaunchKernelGGL(encode_split_kernel<64>, grid, dim3(kThreads), 0, a.stream, p);
-        else hipLaunchKernelGGL(encode_split_kernel<128>, grid, dim3(kThreads), 0, a.stream, p);
+    p.N = a.N; p.s = a.s; p.sn = a.sn; p.dict_count = a.dict_count; p.n_dicts = a.dict_count * a.sn; p.M = pl.M; p.k = pl.k;
+    p.idx16 = a.idx16; p.coef_mode = (a.coef16 ? kCoefF16 : 0) | (a.closed_loop ? kCoefClosed : 0); p.res_norm2 = a.res_norm2;
+    if (pl.k > 1) {
+        const int64_t n2 = (int64_t)(pl.total / 16);
+        hipLaunchKernelGGL(clear_slots_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, a.stream,
+                           reinterpret_cast<ulonglong2 *>(a.workspace), n2);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    if (a.d == 64) return pl.held == 1 ? launch_split_t<64, 1>(a, pl, p) : pl.held == 2 ? launch_split_t<64, 2>(a, pl, p) : launch_split_t<64, 4>(a, pl, p);
+    return pl.held == 1 ? launch_split_t<128, 1>(a, pl, p) : pl.held == 2 ? launch_split_t<128, 2>(a, pl, p) : launch_split_t<128, 4>(a, pl, p);
 }
 
 }  // namespace csr

@@ -1,0 +1,33 @@
+"""GPU parity: the few-vectors encoder's slices - several workgroups share a dictionary and exchange their candidates - at
+the edges of its split (tests of its options and storage types are with the other encoders')."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2412_11741_amd as csr
+from paper_2412_11741_amd import synth
+from tests.test_gpu_encode import _assert_ok, _compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dicts,M,N,d,s", [
+    (8, 1, 4160, 128, 6),      # 130 tiles on 16 slices of 9: the last slice is empty
+    (3, 31, 544, 128, 4),      # 17 tiles on 2 slices, a block of vectors with one column missing
+    (2, 33, 800, 128, 4),      # 25 tiles on 3 slices, a second block with one vector
+    (16, 128, 1024, 64, 4),    # the most vectors; two slots per lane
+    (5, 64, 64, 128, 3),       # fewer tiles than waves, no exchange
+    (40, 2, 2048, 128, 4),     # dictionaries dealt to the XCDs: 5 each, 6 slices
+    (1, 7, 65536, 128, 3),     # tiles beyond the registers are read again in every iteration
+    (300, 1, 256, 128, 3),     # more dictionaries than CUs
+])
+def test_slices_of_a_dictionary_agree(dicts, M, N, d, s):
+    D = synth.dictionary(91, "dict_k", dicts, N, d, "f16")
+    X = synth.vectors(91, "keys", dicts, M, d, "f16", outliers=4)
+    X[-1, -1] = 0.0
+    idx, coef = csr.csr_encode(torch.from_numpy(X).cuda(), torch.from_numpy(D).cuda(), s, algo=csr.CSR_ENCODE_SPLIT)
+    again = csr.csr_encode(torch.from_numpy(X).cuda(), torch.from_numpy(D).cuda(), s, algo=csr.CSR_ENCODE_SPLIT)
+    assert torch.equal(idx, again[0]) and torch.equal(coef, again[1])
+    heads = sorted({0, dicts // 2, dicts - 1})
+    _assert_ok(_compare(X, D, s, idx.cpu().numpy().view(np.uint16).astype(np.int32), coef.cpu().numpy(), heads=heads))
+    assert not idx[-1, -1].any() and not coef[-1, -1].any()
