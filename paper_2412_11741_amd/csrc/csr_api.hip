@@ -237,6 +237,7 @@ csr_status check_decode_desc(const csr_decode_desc *d, csr::DecodePlan *plan)
     if (!csr::plan_decode(d->B, d->Hq, d->Hkv, d->T, d->d, d->N, snK, snV, rope, code_vecs, plan))
         return fail(CSR_ERR_UNSUPPORTED, "csr_decode_attn: N=%d atoms do not fit the LDS-resident score and histogram tables, or T=%lld "
                                          "exceeds what 128 token chunks hold", d->N, (long long)d->T);
+    csr::plan_decode_direct(*d, plan);
     return CSR_OK;
 }
 
@@ -420,7 +421,7 @@ static csr_status decode_run(const csr_decode_desc *desc, const csr::DecodePlan 
     a.out16 = desc->out_dtype == CSR_F16;
     a.workspace = workspace;
     a.stream = static_cast<hipStream_t>(hip_stream);
-    const hipError_t e = csr::launch_decode(a, p);
+    const hipError_t e = p.direct ? csr::launch_decode_direct(a, p) : csr::launch_decode(a, p);
     if (e != hipSuccess) return fail(CSR_ERR_DEVICE, "csr_decode_attn: %s", hipGetErrorString(e));
     return CSR_OK;
 }

@@ -104,6 +104,9 @@ struct DecodePlan {
     int64_t chunk_tokens; // tokens per chunk (multiple of the block's token step)
     size_t off_qd, off_hist, off_ml, off_acc, total_bytes;
     size_t lds_bytes;     // dynamic LDS of the streaming kernel
+    bool direct;          // a short context: decode_direct.hip runs instead, with chunks of its own
+    int32_t direct_tokens, direct_chunks;
+    size_t off_direct_ml;
 };
 
 struct DecodeArgs {
@@ -130,6 +133,10 @@ struct DecodeArgs {
 bool plan_decode(int32_t B, int32_t Hq, int32_t Hkv, int64_t T, int32_t d, int32_t N, int32_t snK, int32_t snV,
                  bool rope, int code_vecs, DecodePlan *p);
 hipError_t launch_decode(const DecodeArgs &a, const DecodePlan &p);
+
+// Short contexts (decode_direct.hip): decides whether the shape is one, fills the plan's direct part (behind plan_decode).
+bool plan_decode_direct(const csr_decode_desc &d, DecodePlan *p);
+hipError_t launch_decode_direct(const DecodeArgs &a, const DecodePlan &p);
 
 // Streaming kernel for keys coded before the rotary embedding (decode_rope.hip); fills the same chunk histograms,
 // maxima and sums as the position-free one.

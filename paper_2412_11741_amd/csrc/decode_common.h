@@ -90,6 +90,12 @@ template <> struct IdxLoad<uint16_t, 4> {
         o[0] = r.x & 0xffff; o[1] = r.x >> 16; o[2] = r.y & 0xffff; o[3] = r.y >> 16;
     }
 };
+template <> struct IdxLoad<uint16_t, 2> {
+    static __device__ __forceinline__ void ld(const uint16_t *p, int (&o)[2]) {
+        const uint32_t r = *reinterpret_cast<const uint32_t *>(p);
+        o[0] = r & 0xffff; o[1] = r >> 16;
+    }
+};
 template <> struct IdxLoad<uint16_t, 1> {
     static __device__ __forceinline__ void ld(const uint16_t *p, int (&o)[1]) { o[0] = p[0]; }
 };
@@ -104,6 +110,12 @@ template <> struct IdxLoad<int32_t, 4> {
     static __device__ __forceinline__ void ld(const int32_t *p, int (&o)[4]) {
         const int4 a = *reinterpret_cast<const int4 *>(p);
         o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+    }
+};
+template <> struct IdxLoad<int32_t, 2> {
+    static __device__ __forceinline__ void ld(const int32_t *p, int (&o)[2]) {
+        const int2 a = *reinterpret_cast<const int2 *>(p);
+        o[0] = a.x; o[1] = a.y;
     }
 };
 template <> struct IdxLoad<int32_t, 1> {
@@ -122,6 +134,12 @@ template <> struct CoefLoad<__half, 4> {
         o[0] = f0.x; o[1] = f0.y; o[2] = f1.x; o[3] = f1.y;
     }
 };
+template <> struct CoefLoad<__half, 2> {
+    static __device__ __forceinline__ void ld(const __half *p, float (&o)[2]) {
+        const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(p));
+        o[0] = f.x; o[1] = f.y;
+    }
+};
 template <> struct CoefLoad<__half, 1> {
     static __device__ __forceinline__ void ld(const __half *p, float (&o)[1]) { o[0] = h2f(p[0]); }
 };
@@ -132,6 +150,12 @@ template <> struct CoefLoad<float, 4> {
     static __device__ __forceinline__ void ld(const float *p, float (&o)[4]) {
         const float4 a = *reinterpret_cast<const float4 *>(p);
         o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w;
+    }
+};
+template <> struct CoefLoad<float, 2> {
+    static __device__ __forceinline__ void ld(const float *p, float (&o)[2]) {
+        const float2 a = *reinterpret_cast<const float2 *>(p);
+        o[0] = a.x; o[1] = a.y;
     }
 };
 template <> struct CoefLoad<float, 1> {

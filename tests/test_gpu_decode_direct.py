@@ -1,0 +1,71 @@
+"""GPU parity: attention over short contexts, where the cached tokens are rebuilt on the fly (decode_direct.hip), at the edges
+of its teams and chunks; and the score-table path's own checks at contexts above that form's limit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2412_11741_amd import synth
+from tests.test_gpu_decode import TOL_F16_OUT, TOL_F32_OUT, _case, _check, _chunked_case, _run, _u16
+from tests import test_gpu_decode_rope as rope
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,T,N,sK,sV,dtype", [
+    (1, 1, 1, 1, 32, 1, 1, "f16"),        # one token, one pair
+    (2, 6, 2, 15, 100, 3, 5, "f16"),      # fewer tokens than teams, odd codes, three query heads
+    (1, 5, 1, 17, 300, 6, 2, "f16"),      # one token past a round, five query heads, codes read in words
+    (3, 16, 2, 333, 512, 8, 16, "f16"),   # eight query heads, a second block of value pairs
+    (2, 4, 2, 700, 1024, 32, 12, "f16"),  # the longest codes
+    (40, 2, 2, 16, 256, 8, 8, "f16"),     # one chunk per sequence: no second launch
+    (1, 2, 1, 6000, 512, 4, 4, "f32"),    # fp32 throughout, many chunks
+    (2, 7, 1, 90, 96, 7, 9, "f32"),
+])
+def test_short_contexts(B, Hq, Hkv, T, N, sK, sV, dtype):
+    args = _case(61, B, Hq, Hkv, T, N, sK, sV, dtype=dtype, itype="i16" if dtype == "f16" else "i32")
+    lens = np.full(B, T, dtype=np.int32)
+    if B > 1:
+        lens[0], lens[-1] = 0, max(1, T // 2)
+    out = _run(*args, seq_lens=lens)
+    ref = oracle.decode_attn(*args[:2], *(a if i % 3 else _u16(a) if dtype == "f16" else a for i, a in enumerate(args[2:])), seq_lens=lens)
+    assert B == 1 or np.all(out[0] == 0)
+    _check(out[lens > 0], ref[lens > 0], TOL_F16_OUT if dtype == "f16" else TOL_F32_OUT, f"direct {B} {Hq} {Hkv} {T}")
+
+
+@pytest.mark.parametrize("snK,sK,snV,sV", [(1, 8, 2, 4), (2, 4, 4, 2), (8, 2, 8, 3)])
+def test_short_contexts_in_chunks(snK, sK, snV, sV):
+    q, DK, iK, cK, DV, iV, cV = _chunked_case(62, 2, 4, 2, 150, 256, snK, sK, snV, sV)
+    whole = (DK, iK, cK) if snK > 1 else (DK[:, 0], np.ascontiguousarray(iK[:, :, :, 0]), np.ascontiguousarray(cK[:, :, :, 0]))
+    out = _run(q, *whole, DV, iV, cV)
+    _check(out, oracle.decode_attn_chunked(q, DK, _u16(iK), cK, DV, _u16(iV), cV), TOL_F16_OUT, f"direct chunks {snK} {snV}")
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("Hq,T,pos0", [(2, 33, 0), (8, 500, 100000)])
+def test_short_contexts_with_rotary_keys(layout, Hq, T, pos0):
+    args = rope._case(63, 2, Hq, 2, T, 256, 8, 4, snV=2)
+    rope._check(rope._run(args, 10000.0, layout, pos0), oracle.decode_attn_rope(*args, 10000.0, layout, pos0), f"direct rope {layout} {Hq}")
+
+
+@pytest.mark.parametrize("what", ["hot", "growing", "tiny", "f32", "odd", "rope"])
+def test_the_score_table_path_above_the_limit(what):
+    # the scatter's unit, its checks and the wide form (see test_gpu_decode.py), and code widths of the streaming kernel
+    B, Hq, Hkv, T, N, s = 2, 4, 1, 36000, 512, 8
+    if what == "odd":
+        args = list(_case(64, B, Hq, Hkv, T, 1000, 6, 10))
+    elif what == "rope":
+        args = rope._case(64, B, Hq, Hkv, T, 256, 8, 6)
+        return rope._check(rope._run(args, 10000.0, 0, 5), oracle.decode_attn_rope(*args, 10000.0, 0, 5), "rope above the limit")
+    else:
+        f32 = what == "f32"
+        args = list(_case(64, B, Hq, Hkv, T, N, s, s, dtype="f32" if f32 else "f16", itype="i32" if f32 else "i16"))
+    if what == "hot":
+        args[3][...], args[5][...], args[6][...] = 0, 3, np.float16(60000.0)
+    elif what == "growing":
+        args[6][:, :, :1024] = 0
+        args[6][:, :, 1024:] *= np.float16(512.0)
+    elif what == "tiny":
+        args[6][...] = (args[6].astype(np.float32) * 2.0 ** -20).astype(np.float16)
+    out = _run(*args, out_dtype=torch.float32)
+    _check(out, oracle.decode_attn(*args), TOL_F32_OUT, f"table path, {what}")
