@@ -8,9 +8,8 @@
 // so with G prepared once per dictionary (csr_gram_build: N x N fp16 in device memory, 32 MB at N = 4096) only the
 // first iteration sweeps the dictionary; each later one reads ONE row of G (2 N bytes) per vector.
 //
-//   launch 1, sweep_kernel, workgroup (dictionary, 256-atom slice): C_1[n] = x . d_n for the dictionary's vectors
-//       (exact fp16 products, fp32 sums) into scratch, and the slice's largest squared atom norm.  Up to 8 vectors
-//       per dictionary on the vector ALU (the launch is bound by reading the dictionaries), more on the matrix cores.
+//   launch 1, sweep_kernel, workgroup (dictionary, 128-atom slice): C_1[n] = x . d_n for the dictionary's vectors
+//       (exact fp16 products, fp32 sums, on the matrix cores) into scratch, and the slice's largest squared atom norm.
 //   launch 2, iterate_kernel, one workgroup per vector (8 waves when few vectors wait and the length of the chain
 //       counts, 2 or 4 from 12 vectors per dictionary on, when instruction issue does): the correlations live in
 //       registers (8 consecutive atoms per thread and round), the fp32 residual R in every wave.  Per iteration: block arg-max of |C|; the row of G and
@@ -26,6 +25,7 @@
 //       coefficient, and the recursion on C.
 #include "csr_internal.h"
 #include "encode_common.h"
+#include "lane_ops.h"
 
 namespace csr {
 namespace {
@@ -33,7 +33,7 @@ namespace {
 using namespace enc;
 
 constexpr int kSweepThreads = 256;
-constexpr int kSliceAtoms = 256;        // atoms per sweep workgroup
+constexpr int kSliceAtoms = 128;        // atoms per sweep workgroup, 32 per wave
 constexpr int kIterThreadsMax = 512;     // threads of an iterate workgroup: 512 when few vectors wait (the chain of an
                                         // iteration is shortest), 128 or 256 from kThroughputVectors per dictionary on
                                         // (what every wave repeats - merge, coefficient, residual - is done by fewer)
@@ -41,9 +41,7 @@ constexpr int kThroughputVectors = 12;
 constexpr int kMaxRounds = 4;           // rounds of 8 atoms per thread: N <= 512 * 8 * 4
 constexpr int kMaxAtoms = kIterThreadsMax * 8 * kMaxRounds;  // 16384
 constexpr int kMaxVectors = 128;        // per dictionary: a decoding step of up to 128 sequences
-constexpr int kValuSweepVectors = 8;    // up to here the sweep is a matrix-vector product on the vector ALU
-constexpr int kSweepTiles = 2;          // 32-atom tiles per wave of the matrix-core sweep (4 waves: 256 atoms)
-static_assert(kSliceAtoms == (kSweepThreads / 64) * 32 * kSweepTiles, "a sweep workgroup covers one slice");
+static_assert(kSliceAtoms == kSweepThreads / 64 * 32, "a sweep workgroup covers one slice");
 constexpr int kCand = 256;              // candidate list; beyond it every atom is evaluated
 
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
@@ -141,65 +139,18 @@ __global__ __launch_bounds__(256) void gram_build_kernel(const __half *__restric
 }
 
 // ---- launch 1: C_1 and the atom norms ----------------------------------------------------------------------------------
-// LPR = DC / 8 lanes read one atom row (16 bytes each), 64 / LPR rows per wave and load.
+// On the matrix cores, v_mfma_f32_32x32x16_f16 with 32 vectors as the rows of A and 32 atoms as the columns of B.
+// Lane (col = lane % 32, hf = lane / 32) supplies dimensions 16 j + 8 hf .. + 7 of step j for vector col (A) and atom
+// col (B) - 16 contiguous bytes of a row per step - and receives, in accumulator 4 r4 + e, the product of vector
+// 8 r4 + 4 hf + e with atom col.  A wave keeps the rows of its tile in registers and walks the vectors 32 at a time.
+// What counts is the chain of one wave (read the atoms, multiply, store), not the products: a matrix-vector product on
+// the vector ALU, which spends nothing on vectors that are not there but reads its atoms row after row, took 17 us for 8
+// vectors on each of 8 dictionaries of 4096 atoms where this takes 5.
 template <int DC>
 __global__ __launch_bounds__(kSweepThreads) void sweep_kernel(const __half *__restrict__ X, const __half *__restrict__ Dict,
                                                               float *__restrict__ Cbuf, float *__restrict__ dmax2_part, int64_t T,
                                                               int32_t M, int32_t N, int32_t s, int32_t sn, int64_t x_stride_h,
                                                               int64_t x_stride_t, int32_t dict_count, int32_t nslices)
-{
-    constexpr int LPR = DC / 8, RPW = 64 / LPR;
-    __shared__ float red[kSweepThreads / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int piece = lane % LPR, rg = lane / LPR;
-    const int dct = blockIdx.x / nslices, sl = blockIdx.x - dct * nslices;
-    const __half *Dh = Dict + (int64_t)dct * N * DC;
-    float nmax = 0.0f;
-    for (int m0 = 0; m0 < M; m0 += 8) {
-        uint4 xp[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            xp[j] = make_uint4(0u, 0u, 0u, 0u);
-            if (m0 + j < M) {
-                const VecAt v = locate(dct, m0 + j, T, sn, s, DC, dict_count, x_stride_h, x_stride_t, 0);
-                xp[j] = *reinterpret_cast<const uint4 *>(X + v.x_off + 8 * piece);
-            }
-        }
-        for (int r0 = sl * kSliceAtoms + wave * RPW; r0 < (sl + 1) * kSliceAtoms; r0 += (kSweepThreads / 64) * RPW) {
-            const int r = r0 + rg;
-            const int rc = r < N ? r : N - 1;  // the last slice may be ragged: those lanes recompute the last atom
-            const uint4 dr = *reinterpret_cast<const uint4 *>(Dh + (int64_t)rc * DC + 8 * piece);
-            if (m0 == 0) nmax = fmaxf(nmax, row_sum<LPR>(dot8(dr, dr)));
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                if (m0 + j < M) {  // (uniform)
-                    const float c = row_sum<LPR>(dot8(xp[j], dr));
-                    if (piece == 0 && r < N) Cbuf[((int64_t)dct * M + m0 + j) * N + r] = c;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) nmax = fmaxf(nmax, __shfl_xor(nmax, m, 64));
-    if (lane == 0) red[wave] = nmax;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float v = red[0];
-        for (int w = 1; w < kSweepThreads / 64; ++w) v = fmaxf(v, red[w]);
-        dmax2_part[(int64_t)dct * nslices + sl] = v;
-    }
-}
-
-// The same launch for more than a handful of vectors per dictionary, on the matrix cores: v_mfma_f32_32x32x16_f16 with
-// 32 vectors as the rows of A and 32 atoms as the columns of B.  Lane (col = lane % 32, hf = lane / 32) supplies
-// dimensions 16 j + 8 hf .. + 7 of step j for vector col (A) and atom col (B) - 16 contiguous bytes of a row per step -
-// and receives, in accumulator 4 r4 + e, the product of vector 8 r4 + 4 hf + e with atom col.  A wave keeps the rows
-// of its kSweepTiles tiles in registers and walks the vectors 32 at a time.
-template <int DC>
-__global__ __launch_bounds__(kSweepThreads) void sweep_mfma_kernel(const __half *__restrict__ X, const __half *__restrict__ Dict,
-                                                                   float *__restrict__ Cbuf, float *__restrict__ dmax2_part, int64_t T,
-                                                                   int32_t M, int32_t N, int32_t s, int32_t sn, int64_t x_stride_h,
-                                                                   int64_t x_stride_t, int32_t dict_count, int32_t nslices)
 {
     constexpr int NF = DC / 16;  // matrix-core steps per product
     __shared__ float red[kSweepThreads / 64];
@@ -207,54 +158,43 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_mfma_kernel(const __half 
     const int col = lane & 31, hf = lane >> 5;
     const int dct = blockIdx.x / nslices, sl = blockIdx.x - dct * nslices;
     const __half *Dh = Dict + (int64_t)dct * N * DC;
-    const int n_first = sl * kSliceAtoms + wave * 32 * kSweepTiles;
-    float nmax = 0.0f;
-    half8 bfrag[kSweepTiles][NF];
+    const int n = sl * kSliceAtoms + wave * 32 + col;
+    const int nc = n < N ? n : N - 1;  // the last slice may be ragged: those lanes hold the last atom again
+    uint4 braw[NF], araw[NF];
 #pragma unroll
-    for (int t = 0; t < kSweepTiles; ++t) {
-        const int n = n_first + 32 * t + col;
-        const int nc = n < N ? n : N - 1;  // the last slice may be ragged: those lanes hold the last atom again
-        float nn = 0.0f;
+    for (int j = 0; j < NF; ++j) braw[j] = *reinterpret_cast<const uint4 *>(Dh + (int64_t)nc * DC + 16 * j + 8 * hf);
+    auto load_vectors = [&](int v0) {
+        const int m = v0 + col;
+        const VecAt at = locate(dct, m < M ? m : M - 1, T, sn, s, DC, dict_count, x_stride_h, x_stride_t, 0);
 #pragma unroll
         for (int j = 0; j < NF; ++j) {
-            const uint4 raw = *reinterpret_cast<const uint4 *>(Dh + (int64_t)nc * DC + 16 * j + 8 * hf);
-            bfrag[t][j] = *reinterpret_cast<const half8 *>(&raw);
-            nn += dot8(raw, raw);
+            araw[j] = make_uint4(0u, 0u, 0u, 0u);
+            if (m < M) araw[j] = *reinterpret_cast<const uint4 *>(X + at.x_off + 16 * j + 8 * hf);
         }
-        nn += __shfl_xor(nn, 32, 64);  // the other half of the atom's dimensions
-        nmax = fmaxf(nmax, nn);
-    }
+    };
+    load_vectors(0);
     for (int v0 = 0; v0 < M; v0 += 32) {
-        const int m = v0 + col;
-        half8 afrag[NF];
-        {
-            const VecAt at = locate(dct, m < M ? m : M - 1, T, sn, s, DC, dict_count, x_stride_h, x_stride_t, 0);
+        floatx16 acc;
 #pragma unroll
-            for (int j = 0; j < NF; ++j) {
-                uint4 raw = make_uint4(0u, 0u, 0u, 0u);
-                if (m < M) raw = *reinterpret_cast<const uint4 *>(X + at.x_off + 16 * j + 8 * hf);
-                afrag[j] = *reinterpret_cast<const half8 *>(&raw);
-            }
-        }
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-        for (int t = 0; t < kSweepTiles; ++t) {
-            floatx16 acc;
+        for (int j = 0; j < NF; ++j)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8 *>(&araw[j]), *reinterpret_cast<const half8 *>(&braw[j]), acc, 0, 0, 0);
+        if (v0 + 32 < M) load_vectors(v0 + 32);
+        if (n < N) {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-            for (int j = 0; j < NF; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(afrag[j], bfrag[t][j], acc, 0, 0, 0);
-            const int n = n_first + 32 * t + col;
-            if (n < N) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int mv = v0 + 8 * (r >> 2) + 4 * hf + (r & 3);
-                    if (mv < M) Cbuf[((int64_t)dct * M + mv) * N + n] = acc[r];
-                }
+            for (int r = 0; r < 16; ++r) {
+                const int mv = v0 + 8 * (r >> 2) + 4 * hf + (r & 3);
+                if (mv < M) Cbuf[((int64_t)dct * M + mv) * N + n] = acc[r];
             }
         }
     }
+    float nmax = 0.0f;
 #pragma unroll
-    for (int mm = 32; mm >= 1; mm >>= 1) nmax = fmaxf(nmax, __shfl_xor(nmax, mm, 64));
+    for (int j = 0; j < NF; ++j) nmax += dot8(braw[j], braw[j]);
+    nmax += __shfl_xor(nmax, 32, 64);  // the other half of the atom's dimensions
+#pragma unroll
+    for (int mm = 16; mm >= 1; mm >>= 1) nmax = fmaxf(nmax, __shfl_xor(nmax, mm, 64));
     if (lane == 0) red[wave] = nmax;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -293,7 +233,8 @@ __global__ __launch_bounds__(THREADS) void iterate_kernel(const __half *__restri
     const float *Cv = Cbuf + ((int64_t)dct * M + m) * N;
 
     float dmax2 = 0.0f;
-    for (int sl = 0; sl < nslices; ++sl) dmax2 = fmaxf(dmax2, dmax2_part[(int64_t)dct * nslices + sl]);
+    for (int sl = lane; sl < nslices; sl += 64) dmax2 = fmaxf(dmax2, dmax2_part[(int64_t)dct * nslices + sl]);
+    dmax2 = lane::wave_max(dmax2);
     const float dmax = sqrtf(dmax2);
     const float g_eps = dmax2 * (2.44140625e-4f + kGammaAcc) + 2.98023224e-8f;  // |G16 - G| <= g_eps
 
@@ -518,14 +459,9 @@ hipError_t launch_step_t(const EncodeArgs &a)
     char *ws = static_cast<char *>(a.workspace);
     float *Cbuf = reinterpret_cast<float *>(ws);
     float *dpart = reinterpret_cast<float *>(ws + p.c_bytes);
-    if (p.M <= kValuSweepVectors)
-        hipLaunchKernelGGL(sweep_kernel<DC>, dim3((unsigned)(p.dicts * p.nslices)), dim3(kSweepThreads), 0, a.stream, (const __half *)a.X,
-                           (const __half *)a.D, Cbuf, dpart, a.T, (int32_t)p.M, a.N, a.s, a.sn, a.x_stride_h, a.x_stride_t, a.dict_count,
-                           p.nslices);
-    else
-        hipLaunchKernelGGL(sweep_mfma_kernel<DC>, dim3((unsigned)(p.dicts * p.nslices)), dim3(kSweepThreads), 0, a.stream,
-                           (const __half *)a.X, (const __half *)a.D, Cbuf, dpart, a.T, (int32_t)p.M, a.N, a.s, a.sn, a.x_stride_h,
-                           a.x_stride_t, a.dict_count, p.nslices);
+    hipLaunchKernelGGL(sweep_kernel<DC>, dim3((unsigned)(p.dicts * p.nslices)), dim3(kSweepThreads), 0, a.stream, (const __half *)a.X,
+                       (const __half *)a.D, Cbuf, dpart, a.T, (int32_t)p.M, a.N, a.s, a.sn, a.x_stride_h, a.x_stride_t, a.dict_count,
+                       p.nslices);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p.M >= kThroughputVectors && a.N <= 128 * 8 * kMaxRounds) launch_iterate<DC, 4, 128>(a, p, Cbuf, dpart);
