@@ -100,6 +100,7 @@ struct DecodePlan {
     int32_t GB;           // query heads of one KV head handled together by a block (1, 2 or 4)
     int32_t ngs;          // group slices per KV head = G / GB
     int32_t nchunks;      // split of the token axis
+    int32_t code_pairs;   // see plan_decode
     int32_t threads;      // threads of a workgroup of the streaming kernel = tokens per round
     int64_t chunk_tokens; // tokens per chunk (multiple of the block's token step)
     size_t off_qd, off_hist, off_ml, off_acc, total_bytes;
@@ -128,10 +129,11 @@ struct DecodeArgs {
 
 // Fills the plan; returns false if no kernel configuration fits (e.g. N too large for LDS).
 // rope: the plan is for the kernel that keeps the key dictionary in LDS (keys coded before the rotary embedding).
-// code_vecs: 1 or 2 if key and value codes are whole-vector codes of 8 or 16 pairs in the paper's storage types
-// (one or two 16-byte vectors per token and stream: the streaming kernel's fast variants), else 0.
+// code_pairs: the pairs of a token's key code and of its value code, chunks together, if both have as many and the
+// streaming kernel is built for that number (stream_code_pairs), else 0.
 bool plan_decode(int32_t B, int32_t Hq, int32_t Hkv, int64_t T, int32_t d, int32_t N, int32_t snK, int32_t snV,
-                 bool rope, int code_vecs, DecodePlan *p);
+                 bool rope, int code_pairs, DecodePlan *p);
+int stream_code_pairs(const csr_decode_desc &d, int32_t snK, int32_t snV);
 hipError_t launch_decode(const DecodeArgs &a, const DecodePlan &p);
 
 // Short contexts (decode_direct.hip): decides whether the shape is one, fills the plan's direct part (behind plan_decode).

@@ -259,10 +259,10 @@ __global__ __launch_bounds__(256) void qd_rows_kernel(const __half *__restrict__
 // LDS: the table of scores q.d, fp32 [N][GB] (pass 1), then the fixed-point histogram (pass 2, see finish_chunk) |
 // reduction scratch.
 // TPT: rounds of stream_threads(GB) tokens a chunk may have; a thread keeps the scores of its tokens (one per round) in registers.
-// VL > 0: a token's key code and its value code are VL 16-byte vectors of indices and of coefficients each (16-bit
-// indices, fp16 coefficients, whole-vector codes, s = 8 VL): the vectors are requested ahead of their use - the
-// first rounds' before the score table is loaded - so that several round trips to memory overlap.
-template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int VL, int THREADS = kStreamThreads>
+// NP > 0: a token's key code and its value code have NP pairs each, in all chunks together: the whole codes are
+// requested ahead of their use - the first rounds' before the score table is loaded - so that several round trips to
+// memory overlap.  NP = 0: any number of pairs, PV of a chunk at a time, loaded where they are used.
+template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int NP, int THREADS = kStreamThreads>
 __global__ __launch_bounds__(THREADS) void stream_kernel(
     const float *__restrict__ qd, const TI *__restrict__ idxK, const TC *__restrict__ coefK,
     const TI *__restrict__ idxV, const TC *__restrict__ coefV, const int32_t *__restrict__ seq_lens,
@@ -305,18 +305,20 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
     const int64_t code_row = ((int64_t)b * Hkv + h) * T;
     const int n_mine = (int)((t_end - t0 + THREADS - 1) / THREADS);  // rounds of THREADS tokens
 
-    static_assert(VL == 0 || (sizeof(TI) == 2 && sizeof(TC) == 2 && PV == 8 && !CH), "16-byte code vectors");
+    static_assert(NP == 0 || PV == pair_block<NP>(), "pairs worked on at a time");
     const int64_t tok0 = t0 + tid;  // this thread's token of round 0
-    constexpr int PF = prefetch_rounds<GB, TPT, VL>();
-    CodeVec<VL> ring[PF + 1];  // round i reads slot i % (PF + 1) while round i + PF is requested into the slot round i - 1 left
-    CodeWalk<VL, THREADS> walk(idxK, coefK, code_row + t0, tid);  // walks PF rounds ahead of the current one
-    if constexpr (VL > 0) {
+    constexpr int PIECE = pair_piece<GB, NP>(), STEPS = NP > 0 ? NP / PIECE : 1;   // steps per round
+    constexpr int PF = prefetch_steps<GB, TPT, CodeVec<TI, TC, PIECE>::W>();
+    CodeVec<TI, TC, PIECE> ring[PF + 1];  // step i reads slot i % (PF + 1) while step i + PF is requested into the slot step i - 1 left
+    CodeWalk<TI, TC, NP, PIECE, THREADS> walk(idxK, coefK, code_row + t0, tid);  // walks PF steps ahead of the current one
+    if constexpr (NP > 0) {
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
-            fetch_codes<VL, THREADS>(ring[k], walk, k < n_mine && tok0 + (int64_t)k * THREADS < t_end);
-            walk.next();
+            fetch_codes(ring[k], walk, k / STEPS < n_mine && tok0 + (int64_t)(k / STEPS) * THREADS < t_end);
+            walk.next(k);
         }
     }
+    const ChunkBase<CH, NP> chunk_base(sK, N);
     const int table = NK * GB;
     {
         const float *src = qd + (((int64_t)b * Hkv + h) * ngs + gs) * (int64_t)table;
@@ -373,46 +375,53 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
         if (i < n_mine) {
             round_fence();
             const int64_t t = tok0 + (int64_t)i * THREADS;
-            CodeVec<VL> &cur = ring[i % (PF + 1)];
-            if constexpr (VL > 0) {
-                await_codes<VL>(cur);
-                if (i + PF < TPT) {
-                    fetch_codes<VL, THREADS>(ring[(i + PF) % (PF + 1)], walk, i + PF < n_mine && t + (int64_t)PF * THREADS < t_end);
-                    walk.next();
-                }
-            }
-            if (t < t_end) {
-                float acc[GB];
+            float acc[GB];
 #pragma unroll
-                for (int g = 0; g < GB; ++g) acc[g] = 0.0f;
-                if constexpr (VL > 0) {
-#pragma unroll
-                    for (int v = 0; v < VL; ++v) {
-                        int id[8];
-                        float cf[8];
-                        unpack8(cur.i[v], cur.c[v], id, cf);
-                        pairs(qd_s, id, cf, acc);
-                    }
-                } else {
-                    const TI *ip = idxK + (code_row + t) * sKt;
-                    const TC *cp = coefK + (code_row + t) * sKt;
-                    const float *tab = qd_s;
-                    for (int ch = 0; ch < snK; ++ch, tab += N * GB, ip += sK, cp += sK) {
-                        for (int j0 = 0; j0 < sK; j0 += PV) {  // PV divides sK: a vector load stays in its chunk
-                            int id[PV];
-                            float cf[PV];
-                            IdxLoad<TI, PV>::ld(ip + j0, id);
-                            CoefLoad<TC, PV>::ld(cp + j0, cf);
-                            pairs(tab, id, cf, acc);
-                        }
-                    }
-                }
+            for (int g = 0; g < GB; ++g) acc[g] = 0.0f;
+            auto keep = [&]() {
 #pragma unroll
                 for (int g = 0; g < GB; ++g) { sc[i][g] = acc[g]; mx[g] = fmaxf(mx[g], acc[g]); }
+            };
+            if constexpr (NP > 0) {
+#pragma unroll
+                for (int st = i * STEPS; st < (i + 1) * STEPS; ++st) {
+                    CodeVec<TI, TC, PIECE> &cur = ring[st % (PF + 1)];
+                    await_codes(cur);
+                    const int nx = st + PF;
+                    if (nx < TPT * STEPS) {
+                        fetch_codes(ring[nx % (PF + 1)], walk, nx / STEPS < n_mine && tok0 + (int64_t)(nx / STEPS) * THREADS < t_end);
+                        walk.next(nx);
+                    }
+                    if (t < t_end) {
+#pragma unroll
+                        for (int j0 = 0; j0 < PIECE; j0 += PV) {
+                            int id[PV];
+                            float cf[PV];
+                            unpack_codes(cur, j0, id, cf);
+                            chunk_base.shift((st % STEPS) * PIECE + j0, id);
+                            pairs(qd_s, id, cf, acc);
+                        }
+                        if (st == (i + 1) * STEPS - 1) keep();
+                    }
+                }
+            } else if (t < t_end) {
+                const TI *ip = idxK + (code_row + t) * sKt;
+                const TC *cp = coefK + (code_row + t) * sKt;
+                const float *tab = qd_s;
+                for (int ch = 0; ch < snK; ++ch, tab += N * GB, ip += sK, cp += sK) {
+                    for (int j0 = 0; j0 < sK; j0 += PV) {  // PV divides sK: a vector load stays in its chunk
+                        int id[PV];
+                        float cf[PV];
+                        IdxLoad<TI, PV>::ld(ip + j0, id);
+                        CoefLoad<TC, PV>::ld(cp + j0, cf);
+                        pairs(tab, id, cf, acc);
+                    }
+                }
+                keep();
             }
         }
     }
-    finish_chunk<GB, TI, TC, PV, CH, TPT, THREADS, VL>(smem_raw, red, sc, mx, n_mine, t0, t_end, code_row, tid, idxV,
+    finish_chunk<GB, TI, TC, PV, CH, TPT, THREADS, NP>(smem_raw, red, sc, mx, n_mine, t0, t_end, code_row, tid, idxV,
                                                              coefV, N, sV, snV_arg, ml, part_hist, slot);
 }
 
@@ -903,10 +912,10 @@ __global__ __launch_bounds__(256) void finalize_kernel(const float *__restrict__
     }
 }
 
-template <int GB, typename TI, typename TC, int PV, bool CH, int TPT = max_rounds(GB), int VL = 0, int THREADS = kStreamThreads>
+template <int GB, typename TI, typename TC, int PV, bool CH, int TPT = max_rounds(GB), int NP = 0, int THREADS = kStreamThreads>
 hipError_t launch_stream_t(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
 {
-    auto kern = stream_kernel<GB, TI, TC, PV, CH, TPT, VL, THREADS>;
+    auto kern = stream_kernel<GB, TI, TC, PV, CH, TPT, NP, THREADS>;
     // raising the dynamic-LDS limit is needed once per kernel and device
     static std::atomic<bool> attr_set[kMaxDevices];
     int dev = 0;
@@ -927,51 +936,68 @@ hipError_t launch_stream_t(const DecodeArgs &a, const DecodePlan &p, float *qd, 
     return hipGetLastError();
 }
 
-template <int GB, typename TI, typename TC>
+// NP pairs per key and value code: chunks of few rounds keep few scores per thread
+template <int GB, typename TI, typename TC, bool CH, int NP>
+hipError_t launch_stream_np(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
+{
+    constexpr int PV = pair_block<NP>();
+    if constexpr (GB == 4) {
+        if (p.threads == kLongThreads4)
+            return launch_stream_t<GB, TI, TC, PV, CH, kLongRounds4, NP, kLongThreads4>(a, p, qd, hist, ml);
+    }
+    const int rounds = (int)(p.chunk_tokens / kStreamThreads);
+    if (rounds == 1) return launch_stream_t<GB, TI, TC, PV, CH, 1, NP>(a, p, qd, hist, ml);
+    if constexpr (max_rounds(GB) > 8) {
+        if (rounds <= 8) return launch_stream_t<GB, TI, TC, PV, CH, 8, NP>(a, p, qd, hist, ml);
+    }
+    return launch_stream_t<GB, TI, TC, PV, CH, max_rounds(GB), NP>(a, p, qd, hist, ml);
+}
+
+template <int GB, typename TI, typename TC, bool CH>
 hipError_t launch_stream_pv(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
 {
-    if (a.snK > 1 || a.snV > 1) {
-        if (a.sK % 8 == 0 && a.sV % 8 == 0) return launch_stream_t<GB, TI, TC, 8, true>(a, p, qd, hist, ml);
-        if (a.sK % 4 == 0 && a.sV % 4 == 0) return launch_stream_t<GB, TI, TC, 4, true>(a, p, qd, hist, ml);
-        return launch_stream_t<GB, TI, TC, 1, true>(a, p, qd, hist, ml);
-    }
     if constexpr (sizeof(TI) == 2 && sizeof(TC) == 2) {
-        // the paper's storage (16-bit indices, fp16 coefficients) with 8 or 16 pairs per code: 16-byte code vectors
-        // requested ahead; chunks of at most 1024 tokens (short contexts) keep one score per thread
-        if constexpr (GB == 4) {
-            if (p.threads == kLongThreads4)
-                return launch_stream_t<GB, TI, TC, 8, false, kLongRounds4, 1, kLongThreads4>(a, p, qd, hist, ml);
+        switch (p.code_pairs) {
+            case 4: return launch_stream_np<GB, TI, TC, CH, 4>(a, p, qd, hist, ml);
+            case 6: return launch_stream_np<GB, TI, TC, CH, 6>(a, p, qd, hist, ml);
+            case 8: return launch_stream_np<GB, TI, TC, CH, 8>(a, p, qd, hist, ml);
+            case 16: return launch_stream_np<GB, TI, TC, CH, 16>(a, p, qd, hist, ml);
         }
-        const int rounds = (int)(p.chunk_tokens / kStreamThreads);
-        if (a.sK == 8 && a.sV == 8)
-            return rounds == 1 ? launch_stream_t<GB, TI, TC, 8, false, 1, 1>(a, p, qd, hist, ml)
-                 : rounds <= 8 ? launch_stream_t<GB, TI, TC, 8, false, 8, 1>(a, p, qd, hist, ml)
-                               : launch_stream_t<GB, TI, TC, 8, false, max_rounds(GB), 1>(a, p, qd, hist, ml);
-        if (a.sK == 16 && a.sV == 16)
-            return rounds == 1 ? launch_stream_t<GB, TI, TC, 8, false, 1, 2>(a, p, qd, hist, ml)
-                 : rounds <= 8 ? launch_stream_t<GB, TI, TC, 8, false, 8, 2>(a, p, qd, hist, ml)
-                               : launch_stream_t<GB, TI, TC, 8, false, max_rounds(GB), 2>(a, p, qd, hist, ml);
     }
-    if (a.sK % 8 == 0 && a.sV % 8 == 0) return launch_stream_t<GB, TI, TC, 8, false>(a, p, qd, hist, ml);
-    if (a.sK % 4 == 0 && a.sV % 4 == 0) return launch_stream_t<GB, TI, TC, 4, false>(a, p, qd, hist, ml);
-    return launch_stream_t<GB, TI, TC, 1, false>(a, p, qd, hist, ml);
+    if (a.sK % 8 == 0 && a.sV % 8 == 0) return launch_stream_t<GB, TI, TC, 8, CH>(a, p, qd, hist, ml);
+    if (a.sK % 4 == 0 && a.sV % 4 == 0) return launch_stream_t<GB, TI, TC, 4, CH>(a, p, qd, hist, ml);
+    return launch_stream_t<GB, TI, TC, 1, CH>(a, p, qd, hist, ml);
+}
+
+template <int GB, typename TI, typename TC>
+hipError_t launch_stream_ch(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
+{
+    return a.snK > 1 || a.snV > 1 ? launch_stream_pv<GB, TI, TC, true>(a, p, qd, hist, ml)
+                                  : launch_stream_pv<GB, TI, TC, false>(a, p, qd, hist, ml);
 }
 
 template <int GB>
 hipError_t launch_stream_gb(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
 {
     if (a.idx16) {
-        if (a.coef16) return launch_stream_pv<GB, uint16_t, __half>(a, p, qd, hist, ml);
-        return launch_stream_pv<GB, uint16_t, float>(a, p, qd, hist, ml);
+        if (a.coef16) return launch_stream_ch<GB, uint16_t, __half>(a, p, qd, hist, ml);
+        return launch_stream_ch<GB, uint16_t, float>(a, p, qd, hist, ml);
     }
-    if (a.coef16) return launch_stream_pv<GB, int32_t, __half>(a, p, qd, hist, ml);
-    return launch_stream_pv<GB, int32_t, float>(a, p, qd, hist, ml);
+    if (a.coef16) return launch_stream_ch<GB, int32_t, __half>(a, p, qd, hist, ml);
+    return launch_stream_ch<GB, int32_t, float>(a, p, qd, hist, ml);
 }
 
 }  // namespace
 
+int stream_code_pairs(const csr_decode_desc &d, int32_t snK, int32_t snV)
+{
+    if (d.idx_dtype != CSR_I16 || d.coef_dtype != CSR_F16 || snK * d.sK != snV * d.sV) return 0;
+    const int n = snK * d.sK;
+    return n == 4 || n == 6 || n == 8 || n == 16 ? n : 0;
+}
+
 bool plan_decode(int32_t B, int32_t Hq, int32_t Hkv, int64_t T, int32_t d, int32_t N, int32_t snK, int32_t snV,
-                 bool rope, int code_vecs, DecodePlan *p)
+                 bool rope, int code_pairs, DecodePlan *p)
 {
     const size_t NK = (size_t)snK * N, NV = (size_t)snV * N;  // entries of the score table / of a histogram
     const int G = Hq / Hkv;
@@ -987,6 +1013,7 @@ bool plan_decode(int32_t B, int32_t Hq, int32_t Hkv, int64_t T, int32_t d, int32
     }
     if (!GB) return false;
     p->GB = GB;
+    p->code_pairs = code_pairs;
     p->ngs = G / GB;
     // Split the token axis until every CU has a workgroup (two per CU was measured slower); every extra chunk costs one histogram
     // round trip through scratch, so no more than that, except that a chunk holds at most
@@ -995,9 +1022,9 @@ bool plan_decode(int32_t B, int32_t Hq, int32_t Hkv, int64_t T, int32_t d, int32
     int64_t want = (256 + groups - 1) / groups;
     int64_t threads = rope ? rope_threads(GB) : kStreamThreads;  // tokens per round of the streaming kernel
     int64_t tpt = rope ? rope_rounds(GB) : max_rounds(GB);       // rounds per chunk
-    // four query heads, 8 pairs per code in the paper's storage types, a context too long for `want` chunks of the
+    // four query heads, codes requested as a whole, a context too long for `want` chunks of the
     // 16-wave shape: the 8-wave shape with four times the rounds
-    if (!rope && GB == 4 && code_vecs == 1 && T > want * tpt * threads) { threads = kLongThreads4; tpt = kLongRounds4; }
+    if (!rope && GB == 4 && code_pairs > 0 && T > want * tpt * threads) { threads = kLongThreads4; tpt = kLongRounds4; }
     p->threads = (int32_t)threads;
     const int64_t most = T > 0 ? (T + threads - 1) / threads : 1;
     const int64_t least = T > 0 ? (T + tpt * threads - 1) / (tpt * threads) : 1;

@@ -20,7 +20,7 @@ constexpr int max_rounds(int GB) { return GB == 4 ? 8 : 16; }
 // ... which makes long contexts many short chunks, and every chunk costs a fixed 10 us (dispatch, table load, histogram
 // clear and read-out, checks).  For those the four-head kernel has a second shape: 8 waves of 256 registers keep 32
 // rounds - chunks of 16384 tokens, like the other variants' (measured at 8 sequences x 8 KV heads x 131072 tokens:
-// 185 against 211 us per call).  Built for the paper's storage types with 8 pairs per code.
+// 185 against 211 us per call).  Built for codes that are requested as a whole (NP > 0 below).
 constexpr int kLongThreads4 = 512;
 constexpr int kLongRounds4 = 32;
 constexpr int kMaxChunks = 128;
@@ -207,68 +207,128 @@ __device__ __forceinline__ float from_fixed(unsigned long long v)
 // order, so it is the same on every run, and so are the output bits.
 //
 // sc[i][g]: score of the token this thread owns in round i (token t0 + i * THREADS + owner_off), -inf if none.
-// VL > 0: the value code of a token is VL 16-byte vectors of indices and of coefficients (16-bit indices, fp16
-// coefficients, whole-vector codes): they are then requested PF rounds ahead of their use.
-template <int VL> struct CodeVec { uint4 i[VL > 0 ? VL : 1], c[VL > 0 ? VL : 1]; };
-// Rounds whose code vectors are requested ahead: two where the registers allow it without spilling (one query head
-// per workgroup, one vector per code: what bounds that kernel is the number of bytes in flight per CU), else one.
-template <int GB, int TPT, int VL> constexpr int prefetch_rounds() { return GB == 1 && VL == 1 && TPT >= 4 ? 2 : 1; }
+// NP > 0: a token's value code has NP pairs in all its chunks together; its NP indices and NP coefficients are then
+// requested as a whole, PF steps ahead of their use.  What bounds the scatter and the scores is how many bytes of codes are
+// under way: loaded where they are used, 268 MB of codes took (8 sequences x 8 KV heads x 4 query heads, 4096 atoms)
+// 151 us with 4 pairs, 177 with 6, 299 with 2 x 2 and 96 with 16; requested ahead 120, 121, 164 and 83.
+template <typename TI, typename TC, int NP> struct CodeVec {
+    static_assert(NP == 0 || (sizeof(TI) == sizeof(TC) && NP * sizeof(TI) % 4 == 0), "whole 32-bit words, as many of each");
+    static constexpr int W = NP > 0 ? NP * (int)sizeof(TI) / 4 : 1;   // 32-bit words of the indices and of the coefficients
+    uint32_t i[W], c[W];
+};
+// Steps whose codes are requested ahead, as far as the registers go without spilling: 8 words with one query head per
+// workgroup (what bounds that kernel is the number of bytes in flight per CU), else 4, at least one step.
+template <int GB, int TPT, int W> constexpr int prefetch_steps()
+{
+    constexpr int words = GB == 1 && TPT >= 4 ? 8 : 4;
+    return words >= W ? words / W : 1;
+}
+// pairs worked on at a time
+template <int NP> constexpr int pair_block() { return NP % 8 == 0 ? 8 : NP; }
+// Pairs requested at a time: the whole code, or with several query heads per workgroup half of a code of 16 (the scores
+// leave no registers for two whole ones: 26 spilled).  A "step" is one such piece of one token.
+template <int GB, int NP> constexpr int pair_piece() { return GB > 1 && NP > 8 ? 8 : NP; }
 
-// The code streams of a thread's tokens, walked round by round: two workgroup-uniform base addresses (the code
-// vectors of the chunk's first token) and one 32-bit offset per thread, in 16-byte vectors.  The offset passes
+// The code streams of a thread's tokens, walked round by round: two workgroup-uniform base addresses (the codes of the
+// chunk's first token) and one 32-bit offset per thread, in bytes.  The offset passes
 // through an empty asm statement at every step, so that the compiler cannot work out all rounds' addresses ahead of
 // time (they would occupy registers from the start of the loop).
-template <int VL, int THREADS> struct CodeWalk {
-    const uint4 *ib, *cb;   // uniform
-    uint32_t off;           // this thread's token of the round the walk stands at, times VL
-    __device__ __forceinline__ CodeWalk(const void *idx, const void *coef, int64_t first_token, int owner_off)
-        : ib(reinterpret_cast<const uint4 *>(idx) + first_token * (VL > 0 ? VL : 1)),
-          cb(reinterpret_cast<const uint4 *>(coef) + first_token * (VL > 0 ? VL : 1)),
-          off((uint32_t)owner_off * (VL > 0 ? VL : 1)) {}
-    __device__ __forceinline__ void next()
+template <typename TI, typename TC, int NP, int PIECE, int THREADS> struct CodeWalk {
+    const unsigned char *ib, *cb;   // uniform
+    uint32_t off;                   // the piece of this thread's token at which the walk stands
+    __device__ __forceinline__ CodeWalk(const TI *idx, const TC *coef, int64_t first_token, int owner_off)
+        : ib(reinterpret_cast<const unsigned char *>(idx + first_token * NP)),
+          cb(reinterpret_cast<const unsigned char *>(coef + first_token * NP)), off((uint32_t)owner_off * (NP * sizeof(TI))) {}
+    // `step`: the step at which the walk stands
+    __device__ __forceinline__ void next(int step)
     {
-        off += THREADS * (VL > 0 ? VL : 1);
+        constexpr int P = PIECE > 0 ? NP / PIECE : 1;
+        off += (step % P == P - 1 ? THREADS * NP - (P - 1) * PIECE : PIECE) * (uint32_t)sizeof(TI);
         asm volatile("" : "+v"(off));
     }
 };
-// Requests the 16-byte code vectors of the token the walk stands at.  Without such a token (`have` false: past the
+typedef uint32_t word3 __attribute__((ext_vector_type(3), aligned(4)));   // 12 bytes at any word
+template <int W> __device__ __forceinline__ void load_words(const unsigned char *p, uint32_t (&o)[W])
+{
+    if constexpr (W == 3) {
+        const word3 r = *reinterpret_cast<const word3 *>(p);
+        o[0] = r.x; o[1] = r.y; o[2] = r.z;
+    } else if constexpr (W % 4 == 0) {
+#pragma unroll
+        for (int k = 0; k < W; k += 4) {
+            const uint4 r = *reinterpret_cast<const uint4 *>(p + 4 * k);
+            o[k] = r.x; o[k + 1] = r.y; o[k + 2] = r.z; o[k + 3] = r.w;
+        }
+    } else if constexpr (W % 2 == 0) {
+#pragma unroll
+        for (int k = 0; k < W; k += 2) {
+            const uint2 r = *reinterpret_cast<const uint2 *>(p + 4 * k);
+            o[k] = r.x; o[k + 1] = r.y;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < W; ++k) o[k] = reinterpret_cast<const uint32_t *>(p)[k];
+    }
+}
+// Requests the piece of a code at which the walk stands.  Without such a token (`have` false: past the
 // end of the chunk) the chunk's first token is requested instead and the caller ignores what arrives: a request
 // under a branch would make the destination registers the meeting point of two paths, and the compiler then copies
 // them - and waits for the request - right behind it.
-template <int VL, int THREADS>
-__device__ __forceinline__ void fetch_codes(CodeVec<VL> &r, const CodeWalk<VL, THREADS> &w, bool have)
+template <typename TI, typename TC, int NP, int PIECE, int THREADS>
+__device__ __forceinline__ void fetch_codes(CodeVec<TI, TC, PIECE> &r, const CodeWalk<TI, TC, NP, PIECE, THREADS> &w, bool have)
 {
     const uint32_t o = have ? w.off : 0u;
-#pragma unroll
-    for (int v = 0; v < (VL > 0 ? VL : 1); ++v) {
-        if constexpr (VL > 0) { r.i[v] = w.ib[o + v]; r.c[v] = w.cb[o + v]; }
-        else r.i[v] = r.c[v] = make_uint4(0u, 0u, 0u, 0u);
-    }
+    load_words(w.ib + o, r.i);
+    load_words(w.cb + o, r.c);
 }
-// The code vectors of the current round must have arrived BEFORE a later round's request is issued: the empty asm
+// The codes of the current step must have arrived BEFORE a later round's request is issued: the empty asm
 // statements make the compiler place the wait for them here, where only older requests are outstanding, instead of
 // behind the new request, where it would wait for both.
-template <int VL>
-__device__ __forceinline__ void await_codes(CodeVec<VL> &cur)
+template <typename TI, typename TC, int NP>
+__device__ __forceinline__ void await_codes(CodeVec<TI, TC, NP> &cur)
 {
 #pragma unroll
-    for (int v = 0; v < (VL > 0 ? VL : 1); ++v) {
-        asm volatile("" : "+v"(cur.i[v].x), "+v"(cur.i[v].y), "+v"(cur.i[v].z), "+v"(cur.i[v].w));
-        asm volatile("" : "+v"(cur.c[v].x), "+v"(cur.c[v].y), "+v"(cur.c[v].z), "+v"(cur.c[v].w));
-    }
+    for (int k = 0; k < CodeVec<TI, TC, NP>::W; ++k) asm volatile("" : "+v"(cur.i[k]), "+v"(cur.c[k]));
 }
-__device__ __forceinline__ void unpack8(const uint4 &ri, const uint4 &rc, int (&id)[8], float (&cf)[8])
+// pairs B * j0 .. of a code, B = pair_block
+template <typename TI, typename TC, int NP, int B>
+__device__ __forceinline__ void unpack_codes(const CodeVec<TI, TC, NP> &r, int j0, int (&id)[B], float (&cf)[B])
 {
-    id[0] = ri.x & 0xffff; id[1] = ri.x >> 16; id[2] = ri.y & 0xffff; id[3] = ri.y >> 16;
-    id[4] = ri.z & 0xffff; id[5] = ri.z >> 16; id[6] = ri.w & 0xffff; id[7] = ri.w >> 16;
-    const __half2 *h2 = reinterpret_cast<const __half2 *>(&rc);
+    if constexpr (sizeof(TI) == 2) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float2 f = __half22float2(h2[j]);
-        cf[2 * j] = f.x;
-        cf[2 * j + 1] = f.y;
+        for (int j = 0; j < B; j += 2) {
+            const uint32_t wi = r.i[(j0 + j) / 2], wc = r.c[(j0 + j) / 2];
+            id[j] = wi & 0xffff; id[j + 1] = wi >> 16;
+            const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&wc));
+            cf[j] = f.x; cf[j + 1] = f.y;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < B; ++j) { id[j] = (int)r.i[j0 + j]; cf[j] = __uint_as_float(r.c[j0 + j]); }
     }
 }
+// The table (or histogram) entry at which the chunk of pair j of a token starts, s pairs and n entries per chunk.  Scalars.
+template <bool CH, int NP> struct ChunkBase {
+    int at[CH && NP > 0 ? NP : 1];
+    __device__ __forceinline__ ChunkBase(int s, int n)
+    {
+        if constexpr (CH && NP > 0) {
+            int base = 0, left = s;
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                at[j] = base;
+                if (--left == 0) { base += n; left = s; }
+            }
+        }
+    }
+    template <int B> __device__ __forceinline__ void shift(int j0, int (&id)[B]) const
+    {
+        if constexpr (CH && NP > 0) {
+#pragma unroll
+            for (int j = 0; j < B; ++j) id[j] += at[j0 + j];
+        }
+    }
+};
 
 // A thread keeps one value per round and query head in registers, sc[round][head]: the loops over the rounds are
 // fully unrolled (registers cannot be indexed by a loop counter).  Left alone, the compiler then pulls the loads and
@@ -276,7 +336,7 @@ __device__ __forceinline__ void unpack8(const uint4 &ri, const uint4 &rc, int (&
 // their side of it, so that only the explicitly requested vectors (fetch_codes) are in flight.
 __device__ __forceinline__ void round_fence() { asm volatile("" ::: "memory"); }
 
-template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int THREADS, int VL>
+template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int THREADS, int NP>
 __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red, float (&sc)[TPT][GB], const float (&mx)[GB],
                                              int n_mine, int64_t t0, int64_t t_end, int64_t code_row, int owner_off,
                                              const TI *__restrict__ idxV, const TC *__restrict__ coefV, int32_t N,
@@ -284,7 +344,7 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
 {
     constexpr int WAVES = THREADS / 64;
     static_assert(WAVES <= 16 && GB <= 4, "layout of the reduction scratch");
-    static_assert(VL == 0 || (sizeof(TI) == 2 && sizeof(TC) == 2 && PV == 8 && !CH), "16-byte code vectors");
+    static_assert(NP == 0 || PV == pair_block<NP>(), "pairs worked on at a time");
     const int snV = CH ? snV_arg : 1;
     // 32-bit form: |sum| of c > 0 and of c < 0 per (query head, atom).  [g][n][sign]; for an even number of heads
     // [g / 2][n][sign][g % 2]: the bins of two heads side by side, so that ONE 64-bit add serves both (a loop of 16
@@ -302,17 +362,18 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
 
     // ---- the chunk's maximum; a sample of the value coefficients (the first round's tokens) ---------------
     float cm = 0.0f;
-    constexpr int PF = prefetch_rounds<GB, TPT, VL>();
-    CodeVec<VL> ring[PF + 1];  // round i reads slot i % (PF + 1) while round i + PF is requested into the slot round i - 1 left
-    auto prime = [&](CodeWalk<VL, THREADS> &w) {   // requests rounds 0 .. PF-1, leaves w at round PF
+    constexpr int PIECE = pair_piece<GB, NP>(), STEPS = NP > 0 ? NP / PIECE : 1;   // steps per round
+    constexpr int PF = prefetch_steps<GB, TPT, CodeVec<TI, TC, PIECE>::W>();
+    CodeVec<TI, TC, PIECE> ring[PF + 1];  // step i reads slot i % (PF + 1) while step i + PF is requested into the slot step i - 1 left
+    auto prime = [&](CodeWalk<TI, TC, NP, PIECE, THREADS> &w) {   // requests steps 0 .. PF-1, leaves w at step PF
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
-            fetch_codes<VL, THREADS>(ring[k], w, k < n_mine && tok0 + (int64_t)k * THREADS < t_end);
-            w.next();
+            fetch_codes(ring[k], w, k / STEPS < n_mine && tok0 + (int64_t)(k / STEPS) * THREADS < t_end);
+            w.next(k);
         }
     };
-    if constexpr (VL > 0) {
-        CodeWalk<VL, THREADS> w0(idxV, coefV, code_row + t0, owner_off);
+    if constexpr (NP > 0) {
+        CodeWalk<TI, TC, NP, PIECE, THREADS> w0(idxV, coefV, code_row + t0, owner_off);
         prime(w0);
     }
 #pragma unroll
@@ -320,15 +381,15 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
         const float wm = wave_max(mx[g]);
         if (lane == 0) red[kRedMax + wave * GB + g] = wm;
     }
-    if constexpr (VL > 0) {
+    if constexpr (NP > 0) {
 #pragma unroll
-        for (int v = 0; v < VL; ++v) {
-            int id[8];
-            float cf[8];
-            unpack8(ring[0].i[v], ring[0].c[v], id, cf);
+        for (int j0 = 0; j0 < PIECE; j0 += PV) {
+            int id[PV];
+            float cf[PV];
+            unpack_codes(ring[0], j0, id, cf);
             if (n_mine > 0 && tok0 < t_end) {   // else the vectors are not this thread's
 #pragma unroll
-                for (int j = 0; j < 8; ++j) cm = fmaxf(cm, fabsf(cf[j]));
+                for (int j = 0; j < PV; ++j) cm = fmaxf(cm, fabsf(cf[j]));
             }
         }
     } else {
@@ -392,6 +453,7 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
 
     // ---- scatter ----------------------------------------------------------------------------------------
     float *dst = part_hist + slot * (int64_t)bins;
+    const ChunkBase<CH, NP> chunk_base(sV, N);
     const float n_adds = (float)(t_end - t0) * (float)sVt;
     bool wide = false;
 #pragma unroll 1
@@ -400,12 +462,12 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
 #pragma unroll
         for (int g = 0; g < GB; ++g) scale[g] = ldexpf(1.0f, k_exp[g]);
         float s_thr = 0.0f, m_thr = 0.0f;  // sum and maximum of p' * sum_j |c_j| over this thread's tokens and heads
-        CodeWalk<VL, THREADS> walk(idxV, coefV, code_row + t0, owner_off);  // walks PF rounds ahead of the current one
-        if constexpr (VL > 0) {
+        CodeWalk<TI, TC, NP, PIECE, THREADS> walk(idxV, coefV, code_row + t0, owner_off);  // walks PF steps ahead of the current one
+        if constexpr (NP > 0) {
             if (attempt > 0) prime(walk);
             else {
 #pragma unroll
-                for (int k = 0; k < PF; ++k) walk.next();
+                for (int k = 0; k < PF; ++k) walk.next(k);
             }
         }
         auto rounds = [&](auto wide_c) {
@@ -415,76 +477,84 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
                 if (i < n_mine) {
                     round_fence();
                     const int64_t t = tok0 + (int64_t)i * THREADS;
-                    CodeVec<VL> &cur = ring[i % (PF + 1)];
-                    if constexpr (VL > 0) {
-                        await_codes<VL>(cur);
-                        if (i + PF < TPT) {
-                            fetch_codes<VL, THREADS>(ring[(i + PF) % (PF + 1)], walk, i + PF < n_mine && t + (int64_t)PF * THREADS < t_end);
-                            walk.next();
-                        }
-                    }
-                    if (t < t_end) {
-                        float pp[GB];
+                    float pp[GB];
 #pragma unroll
-                        for (int g = 0; g < GB; ++g) pp[g] = sc[i][g] * scale[g];
-                        float a_t = 0.0f;
-                        auto pairs = [&](int base, const int (&id)[PV], const float (&cf)[PV]) {
+                    for (int g = 0; g < GB; ++g) pp[g] = sc[i][g] * scale[g];
+                    float a_t = 0.0f;
+                    auto pairs = [&](int base, const int (&id)[PV], const float (&cf)[PV]) {
 #pragma unroll
-                            for (int j = 0; j < PV; ++j) {
-                                const float ac = fabsf(cf[j]);
-                                a_t += ac;
-                                if constexpr (WIDE) {
+                        for (int j = 0; j < PV; ++j) {
+                            const float ac = fabsf(cf[j]);
+                            a_t += ac;
+                            if constexpr (WIDE) {
 #pragma unroll
-                                    for (int g = 0; g < GB; ++g) atomicAdd(&h64[g * NV + base + id[j]], to_fixed(pp[g] * cf[j]));
-                                } else {
-                                    const int cell = 2 * (base + id[j]) + (int)(__float_as_uint(cf[j]) >> 31);
-                                    if constexpr (PAIRED) {
+                                for (int g = 0; g < GB; ++g) atomicAdd(&h64[g * NV + base + id[j]], to_fixed(pp[g] * cf[j]));
+                            } else {
+                                const int cell = 2 * (base + id[j]) + (int)(__float_as_uint(cf[j]) >> 31);
+                                if constexpr (PAIRED) {
 #pragma unroll
-                                        for (int g = 0; g < GB; g += 2) {
-                                            const uint32_t a0 = __float2uint_rz(fmaf(pp[g], ac, 0.5f));
-                                            const uint32_t a1 = __float2uint_rz(fmaf(pp[g + 1], ac, 0.5f));
-                                            atomicAdd(h64 + cell + g * NV, ((unsigned long long)a1 << 32) | a0);
-                                        }
-                                    } else {
-#pragma unroll
-                                        for (int g = 0; g < GB; ++g)
-                                            atomicAdd(h32 + cell + 2 * g * NV, __float2uint_rz(fmaf(pp[g], ac, 0.5f)));
+                                    for (int g = 0; g < GB; g += 2) {
+                                        const uint32_t a0 = __float2uint_rz(fmaf(pp[g], ac, 0.5f));
+                                        const uint32_t a1 = __float2uint_rz(fmaf(pp[g + 1], ac, 0.5f));
+                                        atomicAdd(h64 + cell + g * NV, ((unsigned long long)a1 << 32) | a0);
                                     }
-                                }
-                                // one pair after the other (the next pair's products depend on this statement), so
-                                // that the values of all 8 x GB adds are not computed ahead and held in registers
+                                } else {
 #pragma unroll
-                                for (int g = 0; g < GB; ++g) asm volatile("" : "+v"(pp[g]));
-                            }
-                        };
-                        if constexpr (VL > 0) {
-#pragma unroll
-                            for (int v = 0; v < VL; ++v) {
-                                int id[8];
-                                float cf[8];
-                                unpack8(cur.i[v], cur.c[v], id, cf);
-                                pairs(0, id, cf);
-                            }
-                        } else {
-                            const TI *ip = idxV + (code_row + t) * sVt;
-                            const TC *cp = coefV + (code_row + t) * sVt;
-                            int base = 0;
-                            for (int ch = 0; ch < snV; ++ch, base += N, ip += sV, cp += sV) {
-                                for (int j0 = 0; j0 < sV; j0 += PV) {  // PV divides sV: a vector load stays in its chunk
-                                    int id[PV];
-                                    float cf[PV];
-                                    IdxLoad<TI, PV>::ld(ip + j0, id);
-                                    CoefLoad<TC, PV>::ld(cp + j0, cf);
-                                    pairs(base, id, cf);
+                                    for (int g = 0; g < GB; ++g)
+                                        atomicAdd(h32 + cell + 2 * g * NV, __float2uint_rz(fmaf(pp[g], ac, 0.5f)));
                                 }
                             }
+                            // one pair after the other (the next pair's products depend on this statement), so
+                            // that the values of all 8 x GB adds are not computed ahead and held in registers
+#pragma unroll
+                            for (int g = 0; g < GB; ++g) asm volatile("" : "+v"(pp[g]));
                         }
+                    };
+                    auto totals = [&]() {
 #pragma unroll
                         for (int g = 0; g < GB; ++g) {
                             const float pa = pp[g] * a_t;
                             s_thr += pa;
                             m_thr = fmaxf(m_thr, pa);
                         }
+                    };
+                    if constexpr (NP > 0) {
+#pragma unroll
+                        for (int st = i * STEPS; st < (i + 1) * STEPS; ++st) {
+                            // the codes of this step are awaited; behind them step st + PF is requested
+                            CodeVec<TI, TC, PIECE> &cur = ring[st % (PF + 1)];
+                            await_codes(cur);
+                            const int nx = st + PF;
+                            if (nx < TPT * STEPS) {
+                                fetch_codes(ring[nx % (PF + 1)], walk, nx / STEPS < n_mine && tok0 + (int64_t)(nx / STEPS) * THREADS < t_end);
+                                walk.next(nx);
+                            }
+                            if (t < t_end) {
+#pragma unroll
+                                for (int j0 = 0; j0 < PIECE; j0 += PV) {
+                                    int id[PV];
+                                    float cf[PV];
+                                    unpack_codes(cur, j0, id, cf);
+                                    chunk_base.shift((st % STEPS) * PIECE + j0, id);
+                                    pairs(0, id, cf);
+                                }
+                                if (st == (i + 1) * STEPS - 1) totals();
+                            }
+                        }
+                    } else if (t < t_end) {
+                        const TI *ip = idxV + (code_row + t) * sVt;
+                        const TC *cp = coefV + (code_row + t) * sVt;
+                        int base = 0;
+                        for (int ch = 0; ch < snV; ++ch, base += N, ip += sV, cp += sV) {
+                            for (int j0 = 0; j0 < sV; j0 += PV) {  // PV divides sV: a vector load stays in its chunk
+                                int id[PV];
+                                float cf[PV];
+                                IdxLoad<TI, PV>::ld(ip + j0, id);
+                                CoefLoad<TC, PV>::ld(cp + j0, cf);
+                                pairs(base, id, cf);
+                            }
+                        }
+                        totals();
                     }
                 }
             }

@@ -77,11 +77,12 @@ __device__ __forceinline__ float sum8(float v)
 // fixed-point histogram (pass 2, finish_chunk) | reduction scratch | rotation constants [8 lane classes][32] |
 // the group's query pairs, packed fp16 [8 lane classes][4][8] (ROTK only) | theta_k as doubles [64]
 // TPT: rounds of rope_threads(GB) tokens a chunk may have (a lane keeps one score per round and query head).
+// NP, PV: pairs of a value code, see finish_chunk.
 // ONEB: a key code is exactly one block of PVK pairs.
 // GLOBAL: the key dictionary does not fit the LDS (more than 512 atoms): every gathered row piece then comes from
 // device memory - the L2 for dictionaries of a few MB - instead, brought into the same pair-adjacent form in
 // registers.  The arithmetic is the same; the call is then bound by those gathers (256 bytes per code pair).
-template <int GB, bool ROTK, int PVK, bool ONEB, int PV, int TPT, bool GLOBAL>
+template <int GB, bool ROTK, int PVK, bool ONEB, int PV, int NP, int TPT, bool GLOBAL>
 __global__ __launch_bounds__(rope_threads(GB)) void stream_rope_kernel(
     const __half *__restrict__ q, const __half *__restrict__ DK, const uint16_t *__restrict__ idxK,
     const __half *__restrict__ coefK, const uint16_t *__restrict__ idxV, const __half *__restrict__ coefV,
@@ -385,15 +386,15 @@ __global__ __launch_bounds__(rope_threads(GB)) void stream_rope_kernel(
             }
         }
     }
-    finish_chunk<GB, uint16_t, __half, PV, true, TPT, THREADS, 0>(smem_raw, red, sc, mx, n_mine, t0, t_end, code_row,
+    finish_chunk<GB, uint16_t, __half, PV, true, TPT, THREADS, NP>(smem_raw, red, sc, mx, n_mine, t0, t_end, code_row,
                                                                   wave * 64 + 8 * sub + eighth, idxV, coefV, N, sV, snV, ml,
                                                                   part_hist, slot);
 }
 
-template <int GB, bool ROTK, int PVK, bool ONEB, int PV, bool GLOBAL>
+template <int GB, bool ROTK, int PVK, bool ONEB, int PV, int NP, bool GLOBAL>
 hipError_t launch_rope_t(const DecodeArgs &a, const DecodePlan &p, float *hist, float *ml)
 {
-    auto kern = stream_rope_kernel<GB, ROTK, PVK, ONEB, PV, rope_rounds(GB), GLOBAL>;
+    auto kern = stream_rope_kernel<GB, ROTK, PVK, ONEB, PV, NP, rope_rounds(GB), GLOBAL>;
     static std::atomic<bool> attr_set[kMaxDevices];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -419,9 +420,13 @@ hipError_t launch_rope_t(const DecodeArgs &a, const DecodePlan &p, float *hist, 
 template <int GB, bool ROTK, int PVK, bool ONEB, bool GLOBAL>
 hipError_t launch_rope_pv(const DecodeArgs &a, const DecodePlan &p, float *hist, float *ml)
 {
-    if (a.sV % 8 == 0) return launch_rope_t<GB, ROTK, PVK, ONEB, 8, GLOBAL>(a, p, hist, ml);
-    if (a.sV % 4 == 0) return launch_rope_t<GB, ROTK, PVK, ONEB, 4, GLOBAL>(a, p, hist, ml);
-    return launch_rope_t<GB, ROTK, PVK, ONEB, 1, GLOBAL>(a, p, hist, ml);
+    switch (a.snV * a.sV) {   // value codes read as a whole, requested ahead
+        case 4: return launch_rope_t<GB, ROTK, PVK, ONEB, 4, 4, GLOBAL>(a, p, hist, ml);
+        case 8: return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 8, GLOBAL>(a, p, hist, ml);
+        case 16: return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 16, GLOBAL>(a, p, hist, ml);
+    }
+    if (a.sV % 4 == 0) return launch_rope_t<GB, ROTK, PVK, ONEB, 4, 0, GLOBAL>(a, p, hist, ml);
+    return launch_rope_t<GB, ROTK, PVK, ONEB, 1, 0, GLOBAL>(a, p, hist, ml);
 }
 
 template <int GB, bool ROTK>

@@ -8,7 +8,7 @@
 // so with G prepared once per dictionary (csr_gram_build: N x N fp16 in device memory, 32 MB at N = 4096) only the
 // first iteration sweeps the dictionary; each later one reads ONE row of G (2 N bytes) per vector.
 //
-//   launch 1, sweep_kernel, workgroup (dictionary, 128-atom slice): C_1[n] = x . d_n for the dictionary's vectors
+//   launch 1, sweep_kernel, workgroup (dictionary, 256-atom slice): C_1[n] = x . d_n for the dictionary's vectors
 //       (exact fp16 products, fp32 sums, on the matrix cores) into scratch, and the slice's largest squared atom norm.
 //   launch 2, iterate_kernel, one workgroup per vector (8 waves when few vectors wait and the length of the chain
 //       counts, 2 or 4 from 12 vectors per dictionary on, when instruction issue does): the correlations live in
@@ -32,8 +32,8 @@ namespace {
 
 using namespace enc;
 
-constexpr int kSweepThreads = 256;
-constexpr int kSliceAtoms = 128;        // atoms per sweep workgroup, 32 per wave
+constexpr int kSweepThreads = 512;
+constexpr int kSliceAtoms = 256;        // atoms per sweep workgroup, 32 per wave
 constexpr int kIterThreadsMax = 512;     // threads of an iterate workgroup: 512 when few vectors wait (the chain of an
                                         // iteration is shortest), 128 or 256 from kThroughputVectors per dictionary on
                                         // (what every wave repeats - merge, coefficient, residual - is done by fewer)
