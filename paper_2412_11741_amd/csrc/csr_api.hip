@@ -143,20 +143,26 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
     return CSR_OK;
 }
 
+size_t own_workspace(const csr::EncodeArgs &a, int algo)
+{
+    switch (algo) {
+        case CSR_ENCODE_MFMA: return csr::encode_mfma_workspace_bytes(a.dict_count * a.sn, a.T, a.N, a.s);
+        case CSR_ENCODE_SPLIT: return csr::encode_split_workspace_bytes(a);
+        case CSR_ENCODE_WIDE: return csr::encode_wide_workspace_bytes(a);
+        case kAlgoGramStep: return csr::encode_gramstep_workspace_bytes(a);
+        default: return 0;
+    }
+}
+
 // Scratch for `algo` and for the wide encoder where CSR_ENCODE_AUTO would run that one at this shape: a workspace sized
 // with an explicit algo serves AUTO, too.
 size_t encode_workspace(const csr::EncodeArgs &a, int algo, bool automatic)
 {
     if (a.H == 0 || a.T == 0) return 0;
-    if (algo == CSR_ENCODE_MFMA || algo == CSR_ENCODE_SPLIT || (algo == CSR_ENCODE_VALU && automatic)) {
-        const size_t own = algo == CSR_ENCODE_MFMA    ? csr::encode_mfma_workspace_bytes(a.dict_count * a.sn, a.T, a.N, a.s)
-                           : algo == CSR_ENCODE_SPLIT ? csr::encode_split_workspace_bytes(a) : 0;
-        const size_t wide = wide_pays(a, algo) ? csr::encode_wide_workspace_bytes(a) : 0;
-        return own > wide ? own : wide;
-    }
-    if (algo == kAlgoGramStep) return csr::encode_gramstep_workspace_bytes(a);
-    if (algo == CSR_ENCODE_WIDE) return csr::encode_wide_workspace_bytes(a);
-    return 0;
+    const size_t own = own_workspace(a, algo);
+    if (!(automatic || algo == CSR_ENCODE_MFMA || algo == CSR_ENCODE_SPLIT) || !wide_pays(a, algo)) return own;
+    const size_t wide = csr::encode_wide_workspace_bytes(a);
+    return own > wide ? own : wide;
 }
 
 // Device address of `scratch` on the current device (looked up on the first call per device, then cached).
@@ -234,8 +240,18 @@ csr_status check_decode_desc(const csr_decode_desc *d, csr::DecodePlan *plan)
     if (!csr::plan_decode(d->B, d->Hq, d->Hkv, d->T, d->d, d->N, snK, snV, rope, csr::stream_code_pairs(*d, snK, snV), plan))
         return fail(CSR_ERR_UNSUPPORTED, "csr_decode_attn: N=%d atoms do not fit the LDS-resident score and histogram tables, or T=%lld "
                                          "exceeds what 128 token chunks hold", d->N, (long long)d->T);
+    plan->table_bytes = plan->total_bytes;
     csr::plan_decode_direct(*d, plan);
     return CSR_OK;
+}
+
+// A workspace that holds the score-table form's scratch but not that of the short contexts' form - one sized for a longer
+// context on a small dictionary - runs the former: what it held before the context was a short one it still holds.
+void fit_decode_plan(size_t bytes, csr::DecodePlan *p)
+{
+    if (!p->direct || bytes >= p->total_bytes || bytes < p->table_bytes) return;
+    p->direct = false;
+    p->total_bytes = p->table_bytes;
 }
 
 }  // namespace
@@ -273,12 +289,13 @@ csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D,
     if (!aligned(X, 16) || !aligned(D, 16)) return fail(CSR_ERR_INVALID_ARG, "csr_encode: X and D must be 16-byte aligned");
     if (!aligned(idx, a.idx16 ? 2 : 4) || !aligned(coef, a.coef16 ? 2 : 4))
         return fail(CSR_ERR_INVALID_ARG, "csr_encode: idx and coef must be aligned to their element size");
-    const size_t need = encode_workspace(a, algo, desc->algo == CSR_ENCODE_AUTO);
-    if (desc->algo == CSR_ENCODE_AUTO && wide_pays(a, algo)) algo = CSR_ENCODE_WIDE;
-    if (need) {
-        if (!workspace || workspace_bytes < need || !aligned(workspace, 256))
-            return fail(CSR_ERR_WORKSPACE, "csr_encode: workspace of %zu bytes (256-byte aligned) required, got %zu", need, workspace ? workspace_bytes : (size_t)0);
-    }
+    // The wide encoder gives the codes of the one it stands in for: a workspace that is too small for it (one sized for
+    // more vectors, where the rule above takes the other encoder) is no reason to refuse the call.
+    const size_t given = workspace && aligned(workspace, 256) ? workspace_bytes : 0;
+    if (desc->algo == CSR_ENCODE_AUTO && wide_pays(a, algo) && given >= csr::encode_wide_workspace_bytes(a)) algo = CSR_ENCODE_WIDE;
+    const size_t need = own_workspace(a, algo);
+    if (given < need)
+        return fail(CSR_ERR_WORKSPACE, "csr_encode: workspace of %zu bytes (256-byte aligned) required, got %zu", need, workspace ? workspace_bytes : (size_t)0);
     if (desc->res_norm2 && !aligned(desc->res_norm2, 4)) return fail(CSR_ERR_INVALID_ARG, "csr_encode: res_norm2 must be 4-byte aligned");
     if (algo == kAlgoGramStep && !aligned(desc->gram, 16)) return fail(CSR_ERR_INVALID_ARG, "csr_encode: gram must be 16-byte aligned");
     a.X = X; a.D = D; a.idx = idx; a.coef = coef;
@@ -432,6 +449,7 @@ csr_status csr_decode_attn(const csr_decode_desc *desc, const void *q, const voi
     csr_status st = check_decode_desc(desc, &p);
     if (st != CSR_OK) return st;
     if (desc->B == 0) return CSR_OK;
+    fit_decode_plan(workspace_bytes, &p);
     if (!workspace || workspace_bytes < p.total_bytes || !aligned(workspace, 256))
         return fail(CSR_ERR_WORKSPACE, "csr_decode_attn: workspace of %zu bytes (256-byte aligned) required, got %zu",
                     p.total_bytes, workspace ? workspace_bytes : (size_t)0);
@@ -446,6 +464,7 @@ csr_status csr_decode_attn_static(const csr_decode_desc *desc, const void *q, co
     csr_status st = check_decode_desc(desc, &p);
     if (st != CSR_OK) return st;
     if (desc->B == 0) return CSR_OK;
+    fit_decode_plan(kStaticScratchBytes, &p);
     if (p.total_bytes > kStaticScratchBytes)
         return fail(CSR_ERR_WORKSPACE, "csr_decode_attn_static: this shape needs %zu bytes of scratch, the library's static "
                     "scratch holds %zu; use csr_decode_attn with a workspace", p.total_bytes, kStaticScratchBytes);

@@ -108,6 +108,7 @@ struct DecodePlan {
     bool direct;          // a short context: decode_direct.hip runs instead, with chunks of its own
     int32_t direct_tokens, direct_chunks;
     size_t off_direct_ml;
+    size_t table_bytes;   // scratch of the score-table form alone (total_bytes: of both)
 };
 
 struct DecodeArgs {

@@ -5,7 +5,8 @@ import pytest
 import torch
 
 import oracle
-from paper_2412_11741_amd import synth
+import paper_2412_11741_amd as csr
+from paper_2412_11741_amd import binding, synth
 from tests.test_gpu_decode import TOL_F16_OUT, TOL_F32_OUT, _case, _check, _chunked_case, _run, _u16
 from tests import test_gpu_decode_rope as rope
 
@@ -69,3 +70,18 @@ def test_the_score_table_path_above_the_limit(what):
         args[6][...] = (args[6].astype(np.float32) * 2.0 ** -20).astype(np.float16)
     out = _run(*args, out_dtype=torch.float32)
     _check(out, oracle.decode_attn(*args), TOL_F32_OUT, f"table path, {what}")
+
+
+def test_a_workspace_of_the_score_table_form_is_enough():
+    # one sized for a longer context on a small dictionary holds the table and the histograms, not the short form's partial sums
+    B, Hq, Hkv, T, N, s = 1, 4, 1, 2000, 64, 4
+    args = _case(65, B, Hq, Hkv, T, N, s, s)
+
+    def scratch(tokens):
+        return binding.csr_decode_workspace_bytes(binding.DecodeDesc(
+            B=B, Hq=Hq, Hkv=Hkv, T=tokens, d=128, N=N, sK=s, sV=s, q_dtype=1, dict_dtype=1, coef_dtype=1, idx_dtype=1, out_dtype=1))
+    longer = 70000   # 560000 gathered rows
+    assert scratch(longer) < scratch(T)
+    out = csr.csr_decode_attn(*(torch.from_numpy(a).cuda() for a in args), workspace=torch.empty(scratch(longer), dtype=torch.uint8, device="cuda"))
+    ref = oracle.decode_attn(*args[:2], *(a if i % 3 else _u16(a) for i, a in enumerate(args[2:])))
+    _check(out.cpu().numpy(), ref, TOL_F16_OUT, "table form for lack of scratch")

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import paper_2412_11741_amd as csr
-from paper_2412_11741_amd import synth
+from paper_2412_11741_amd import binding, synth
 from tests.test_gpu_encode import _assert_ok, _compare
 
 pytestmark = pytest.mark.gpu
@@ -85,3 +85,21 @@ def test_same_bits_as_the_encoder_of_the_larger_launches(algo, dtype, d, N, T, H
     iw, cw = csr.csr_encode(X, D, 8, algo=csr.CSR_ENCODE_WIDE, closed_loop=closed)
     ie, ce = csr.csr_encode(X, D, 8, algo=algo, closed_loop=closed)
     assert torch.equal(iw, ie) and torch.equal(cw, ce)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_a_workspace_too_small_for_this_encoder_keeps_the_other_one(dtype):
+    # sized for more vectors (fp16), or none, where the vector ALU needs none: accepted, with the same codes
+    T, N, s, f16 = 300, 1024, 4, int(dtype == "f16")
+    D = torch.from_numpy(synth.dictionary(9, "dict_k", 1, N, 128, dtype)).cuda()
+    X = torch.from_numpy(synth.vectors(9, "keys", 1, T, 128, dtype, outliers=4)).cuda()
+
+    def scratch(algo, tokens):
+        return binding.csr_encode_workspace_bytes(binding.EncodeDesc(
+            H=1, T=tokens, d=128, N=N, s=s, x_dtype=f16, dict_dtype=f16, coef_dtype=f16, idx_dtype=f16, x_stride_h=tokens * 128,
+            x_stride_t=128, algo=algo))
+    small = scratch(csr.CSR_ENCODE_MFMA, 120000) if f16 else scratch(csr.CSR_ENCODE_VALU, T)
+    assert small < scratch(csr.CSR_ENCODE_AUTO, T)
+    one = csr.csr_encode(X, D, s, workspace=torch.empty(small, dtype=torch.uint8, device="cuda"))
+    two = csr.csr_encode(X, D, s)
+    assert torch.equal(one[0], two[0]) and torch.equal(one[1], two[1])
