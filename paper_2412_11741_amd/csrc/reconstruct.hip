@@ -73,7 +73,7 @@ __device__ __forceinline__ Where locate(int64_t e, int pieces, int ppc, int64_t 
     return w;
 }
 
-// Any types, any s: one pair at a time.
+// Any types, any s, any alignment: one pair at a time.
 template <typename TD, typename TI, typename TC, typename TO>
 __global__ __launch_bounds__(256) void reconstruct_kernel(const TD *__restrict__ Dict, const TI *__restrict__ idx,
                                                           const TC *__restrict__ coef, TO *__restrict__ out, int64_t T,
@@ -146,6 +146,60 @@ __global__ __launch_bounds__(256) void reconstruct_vec_kernel(const TD *__restri
     store8f(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
 }
 
+// The paper's storage with 1 to 7 pairs: the code is requested as a whole (in 32-bit words, or for odd NP pair by pair),
+// then all its rows; same sum order.  One pair at a time every row waits for its own index: 32 x 4096 vectors, 4096 atoms
+// (us) 4 pairs 20.3 -> 15.2, 6 pairs 22.7 -> 17.9, 2 x 2 15.9 -> 12.9, 2 x 3 16.7 -> 13.8, 2 x 4 18.5 -> 14.2.
+template <typename TD, typename TO, int NP>
+__global__ __launch_bounds__(256) void reconstruct_few_kernel(const TD *__restrict__ Dict, const uint16_t *__restrict__ idx,
+                                                              const __half *__restrict__ coef, TO *__restrict__ out,
+                                                              int64_t T, int32_t d, int32_t N, int32_t sn,
+                                                              int32_t dict_count, int64_t code_stride_h,
+                                                              int64_t out_stride_h, int64_t out_stride_t, int64_t total)
+{
+    const int pieces = d >> 3;
+    const int dc = d / sn, ppc = dc >> 3;
+    const int64_t e = xcd_contiguous_block() * 256 + threadIdx.x;
+    if (e >= total) return;
+    const Where w = locate(e, pieces, ppc, T, sn, NP, code_stride_h);
+    int n[NP];
+    float c[NP];
+    if constexpr (NP % 2 == 0) {
+        uint32_t wi[NP / 2], wc[NP / 2];
+#pragma unroll
+        for (int j = 0; j < NP / 2; ++j) {
+            wi[j] = reinterpret_cast<const uint32_t *>(idx + w.code)[j];
+            wc[j] = reinterpret_cast<const uint32_t *>(coef + w.code)[j];
+        }
+#pragma unroll
+        for (int j = 0; j < NP / 2; ++j) {
+            n[2 * j] = (int)(wi[j] & 0xffffu);
+            n[2 * j + 1] = (int)(wi[j] >> 16);
+            const float2 cf = __half22float2(*reinterpret_cast<const __half2 *>(&wc[j]));
+            c[2 * j] = cf.x;
+            c[2 * j + 1] = cf.y;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            n[j] = load_idx(idx + w.code + j);
+            c[j] = load_coef(coef + w.code + j);
+        }
+    }
+    const TD *Dh = Dict + ((int64_t)(w.h % dict_count) * sn + w.ch) * N * dc + w.pc * 8;
+    float row[NP][8];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) load8f<TD>(Dh + (int64_t)n[j] * dc, row[j]);
+    float acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc[k] = fmaf(c[j], row[j][k], acc[k]);
+    }
+    store8f(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
+}
+
 template <typename TD, typename TI, typename TC, typename TO>
 hipError_t launch_t(const ReconstructArgs &a)
 {
@@ -168,6 +222,26 @@ hipError_t launch_t(const ReconstructArgs &a)
                 default: CSR_REC_VEC(4); break;
             }
 #undef CSR_REC_VEC
+            return hipGetLastError();
+        }
+        // even s: every code starts at a 32-bit word
+        const bool words = a.code_stride_h % 2 == 0 && (reinterpret_cast<uintptr_t>(a.idx) % 4) == 0 &&
+                           (reinterpret_cast<uintptr_t>(a.coef) % 4) == 0;
+        if (a.s < 8 && (a.s % 2 == 1 || words)) {
+#define CSR_REC_FEW(NP)                                                                                             \
+    hipLaunchKernelGGL((reconstruct_few_kernel<TD, TO, NP>), grid, dim3(256), 0, a.stream, (const TD *)a.D,         \
+                       (const uint16_t *)a.idx, (const __half *)a.coef, (TO *)a.out, a.T, a.d, a.N, a.sn,           \
+                       a.dict_count, a.code_stride_h, a.out_stride_h, a.out_stride_t, total)
+            switch (a.s) {
+                case 1: CSR_REC_FEW(1); break;
+                case 2: CSR_REC_FEW(2); break;
+                case 3: CSR_REC_FEW(3); break;
+                case 4: CSR_REC_FEW(4); break;
+                case 5: CSR_REC_FEW(5); break;
+                case 6: CSR_REC_FEW(6); break;
+                default: CSR_REC_FEW(7); break;
+            }
+#undef CSR_REC_FEW
             return hipGetLastError();
         }
     }

@@ -69,3 +69,33 @@ def test_reconstruct_of_the_encoders_codes_shrinks_the_error_and_reads_codes_in_
     _check(rec, ref, D, cc[:, 10:10 + T].cpu().numpy(), "f16")
     x = X.astype(np.float64)
     assert np.all(((x - ref) ** 2).sum(-1) < (x ** 2).sum(-1))      # Eq.4 removes energy at every step
+
+
+@pytest.mark.parametrize("out_dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 6, 7])
+def test_short_codes_at_any_alignment(s, out_dtype):
+    # a short code is read as a whole where it is aligned; the same pairs off a word, one at a time, and padded to eight with
+    # zero coefficients, as two 16-byte vectors: the sums have one order, so the bits are equal
+    H, T, N, d, sn = 2, 131, 320, 128, 2
+    gen = torch.Generator().manual_seed(70 + s)
+    D = torch.randn(H, sn, N, d // sn, generator=gen).half().cuda()
+    idx = torch.randint(0, N, (H, T, sn, s), generator=gen).short()
+    idx[0, 0], idx[-1, -1] = 0, N - 1
+    coef = torch.randn(H, T, sn, s, generator=gen).half()
+
+    def off_a_word(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+        return buf[1:].view(t.shape).copy_(t)
+
+    def padded(t):
+        return torch.nn.functional.pad(t, (0, 8 - s)).cuda()
+    one = csr.csr_reconstruct(D, idx.cuda(), coef.cuda(), out_dtype=out_dtype)
+    assert torch.equal(one, csr.csr_reconstruct(D, off_a_word(idx), off_a_word(coef), out_dtype=out_dtype))
+    assert torch.equal(one, csr.csr_reconstruct(D, padded(idx), padded(coef), out_dtype=out_dtype))
+    rows = torch.gather(D.cpu().double().unsqueeze(1).expand(H, T, sn, N, d // sn), 3,
+                        idx.long().unsqueeze(-1).expand(H, T, sn, s, d // sn))
+    terms = rows * coef.double().unsqueeze(-1)
+    ref, size = terms.sum(3).view(H, T, d), terms.abs().sum(3).view(H, T, d)
+    # s fp32 multiply-adds, then one rounding to the output type
+    bound = size * s * 2.0 ** -23 + (ref.abs() * 2.0 ** -11 + 2.0 ** -25 if out_dtype == torch.float16 else 0.0)
+    assert ((one.cpu().double() - ref).abs() <= bound).all()
