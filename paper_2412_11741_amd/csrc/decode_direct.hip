@@ -18,6 +18,7 @@
 // Bound: L2 gathers (about 15 TB/s) once a few hundred workgroups are in flight, before that the chain of one token - codes,
 // rows, reduction, combine.  All sums run in a fixed order: the same inputs give the same bits.  When it is taken: see
 // kMostGathers.
+#include <cfloat>
 #include <cmath>
 
 #include "csr_internal.h"
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
     float m[GM], l[GM], acc[GM][8];
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
-        m[g] = -INFINITY;
+        m[g] = -FLT_MAX;   // below every finite score, and a difference with a score of minus infinity is no NaN
         l[g] = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[g][e] = 0.0f;
@@ -208,6 +209,28 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
     auto codes = [&](int64_t t) {   // the first 8 pairs of token t's codes
         load_pairs<TI, TC, PV>(iK + t * p.snK * p.sK, cK + t * p.snK * p.sK, p.sK, ik, ck);
         load_pairs<TI, TC, PV>(iV + t * p.snV * p.sV, cV + t * p.snV * p.sV, p.sV, iv, cv);
+    };
+    // The score as the code-domain form has it, sum_j c_j (q . d_j): an infinite coefficient is an infinite score there, while
+    // the rebuilt key mixes infinities of both signs.  One pair at a time: codes of finite numbers never come here.
+    auto score_by_pairs = [&](int64_t t, const float (&qg)[8]) {
+        const int width = 16 / p.snK;   // lanes of a chunk
+        float s = 0.0f;
+#pragma unroll 1
+        for (int j = 0; j < p.sK; ++j) {
+            int id[1];
+            float cf[1], f[8], dot = 0.0f;
+            IdxLoad<TI, 1>::ld(iK + t * p.snK * p.sK + j, id);
+            CoefLoad<TC, 1>::ld(cK + t * p.snK * p.sK + j, cf);
+            Piece<TD> row;
+            fetch<ROPE == 1>(row, DKh + (int64_t)id[0] * dcK);
+            row.get(f);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dot = fmaf(qg[e], f[e], dot);
+            for (int x = 1; x < width; x <<= 1) dot += __shfl_xor(dot, x, 16);
+            s = fmaf(cf[0], dot, s);
+        }
+        for (int x = width; x < 16; x <<= 1) s += __shfl_xor(s, x, 16);
+        return s;
     };
     for (int64_t t = t0 + team; t < t_end; t += kTeams) {   // (the lanes of a team leave together)
         codes(t);
@@ -260,15 +283,29 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
                 y = bb;
             }
         }
-        float pw[GM];
+        float sc[GM], pw[GM];
+        bool odd = false;
 #pragma unroll
         for (int g = 0; g < GM; ++g) {
             float s = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) s = fmaf(q[g][e], k[e], s);
-            s = row_reduce<16>(s, OpAdd());
-            const float mn = fmaxf(m[g], s), old = __expf(m[g] - mn);
-            pw[g] = __expf(s - mn);
+            // as in the streaming kernels a score that is no number counts like minus infinity: weight zero
+            sc[g] = row_reduce<16>(s, OpAdd());
+            if constexpr (ROPE == 0) odd = odd || !(fabsf(sc[g]) < INFINITY);
+            else sc[g] = sc[g] > -INFINITY ? sc[g] : -INFINITY;
+        }
+        if (odd) {
+#pragma unroll
+            for (int g = 0; g < GM; ++g) {
+                const float s = score_by_pairs(t, q[g]);
+                sc[g] = s > -INFINITY ? s : -INFINITY;
+            }
+        }
+#pragma unroll
+        for (int g = 0; g < GM; ++g) {
+            const float mn = fmaxf(m[g], sc[g]), old = __expf(m[g] - mn);   // (mn is finite or +infinity, see m)
+            pw[g] = __expf(sc[g] - mn);
             m[g] = mn;
             l[g] = l[g] * old + pw[g];
 #pragma unroll
@@ -296,7 +333,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
         const float M = fmaxf(fmaxf(lane_read(m[g], 0), lane_read(m[g], 16)), fmaxf(lane_read(m[g], 32), lane_read(m[g], 48)));
-        const float w = m[g] > -INFINITY ? __expf(m[g] - M) : 0.0f;
+        const float w = __expf(m[g] - M);
         float ls = l[g] * w;
         ls = fold32(ls, ls);
         ls = fold16(ls, ls);
@@ -316,7 +353,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
         for (int i = 0; i < 4; ++i) M = fmaxf(M, ml_s[i][g].x);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            w[i] = ml_s[i][g].x > -INFINITY ? __expf(ml_s[i][g].x - M) : 0.0f;
+            w[i] = __expf(ml_s[i][g].x - M);
             L = fmaf(w[i], ml_s[i][g].y, L);
         }
 #pragma unroll
@@ -332,7 +369,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
             if (sub == 0) p.ml[(oq + g) * p.nchunks + c] = make_float2(M, L);
         } else {
 #pragma unroll
-            for (int x = 0; x < 8; ++x) o[x] = o[x] / L;
+            for (int x = 0; x < 8; ++x) o[x] = L > 0.0f ? o[x] / L : 0.0f;   // (no token with a weight)
             store8(p, (oq + g) * 128 + 8 * sub, o);
         }
     }

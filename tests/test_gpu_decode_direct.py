@@ -85,3 +85,40 @@ def test_a_workspace_of_the_score_table_form_is_enough():
     out = csr.csr_decode_attn(*(torch.from_numpy(a).cuda() for a in args), workspace=torch.empty(scratch(longer), dtype=torch.uint8, device="cuda"))
     ref = oracle.decode_attn(*args[:2], *(a if i % 3 else _u16(a) for i, a in enumerate(args[2:])))
     _check(out.cpu().numpy(), ref, TOL_F16_OUT, "table form for lack of scratch")
+
+
+@pytest.mark.parametrize("B,G,Hkv,T,snK", [
+    (1, 1, 2, 40, 1),      # several chunks
+    (1, 3, 1, 40, 2),      # keys in chunks, a query group
+    (40, 1, 32, 16, 1),    # one chunk: no second launch
+])
+def test_a_score_of_minus_infinity_has_weight_zero(B, G, Hkv, T, snK):
+    # an overflowed key coefficient against the query's sign: the token drops out, as with a coefficient of -6e4
+    # (whose weight, exp(-6e4 * 0.1), is zero in any precision); a sequence of such tokens only gives zero
+    N, s = 256, 4
+    q, DK, iK, cK, DV, iV, cV = _chunked_case(66, B, Hkv * G, Hkv, T, N, snK, s, 1, 4)
+    groups = q.reshape(B, Hkv, G, -1)
+    groups[:] = groups[:, :, :1] * np.arange(1, G + 1, dtype=np.float16)[:, None]
+    far = cK.copy()
+    dc = 128 // snK
+    for b in range(B):
+        for h in range(Hkv):
+            dots = DK[h, 0].astype(np.float64) @ q[b, h * G, :dc].astype(np.float64)
+            n = int(np.abs(dots).argmax())
+            assert abs(dots[n]) / np.sqrt(128) > 0.1
+            for t in (range(T) if b == B - 1 and B > 1 else (0, T // 2, T - 1)):
+                iK[b, h, t, 0, 1] = n
+                cK[b, h, t, 0, 1] = -np.inf * np.sign(dots[n])
+                far[b, h, t, 0, 1] = -6e4 * np.sign(dots[n])
+
+    def plain(*codes):
+        return [a if snK > 1 else np.ascontiguousarray(a[:, :, :, 0]) for a in codes]
+    DKx, DVx, vals = (DK if snK > 1 else DK[:, 0]), DV[:, 0], [np.ascontiguousarray(a[:, :, :, 0]) for a in (iV, cV)]
+    out = _run(q, DKx, *plain(iK, cK), DVx, *vals)
+    some = slice(0, B - 1 if B > 1 else 1)
+    if snK > 1:
+        ref = oracle.decode_attn_chunked(q, DK, _u16(iK), far, DV, _u16(iV), cV)
+    else:
+        ref = oracle.decode_attn(q, DKx, *(_u16(a) if i == 0 else a for i, a in enumerate(plain(iK, far))), DVx, _u16(vals[0]), vals[1])
+    _check(out[some], ref[some], TOL_F16_OUT, f"minus infinity {B} {G} {Hkv} {snK}")
+    assert B == 1 or np.all(out[-1] == 0)
