@@ -209,8 +209,9 @@ size_t csr_decode_workspace_bytes(const csr_decode_desc *desc);
  *   out      [B][Hq][d]        out
  *   workspace: device memory, 256-byte aligned, >= csr_decode_workspace_bytes().
  *   q, DK, DV, the four code streams and out must be 16-byte aligned.
- * Indices are not range-checked on the device: an index >= N reads outside the score table (csr_check_codes counts
- * such indices, off the hot path).
+ * Indices must lie in 0 .. N-1 (csr_check_codes counts those that do not, off the hot path).  What an index >= N adds is
+ * undefined: it reads outside the score table, in a short context it counts as atom N-1, and rotary key codes on dictionaries
+ * beyond the LDS read outside the dictionary.
  */
 csr_status csr_decode_attn(const csr_decode_desc *desc, const void *q, const void *DK,
                            const void *idxK, const void *coefK, const void *DV, const void *idxV,

@@ -69,9 +69,13 @@ template <bool SPLIT> __device__ __forceinline__ void fetch(Piece<float> &p, con
     p.b = *reinterpret_cast<const float4 *>(row + (SPLIT ? 64 : 4));
 }
 
-// up to 8 pairs of a code: indices and coefficients, zero past the end
+// An index as it is used: one outside the dictionary counts as the last atom.  The rows are read from device memory, where an
+// index that a program left stale would otherwise read outside the allocation (the score-table form's stays in the LDS).
+__device__ __forceinline__ int inside(int id, uint32_t last) { return (int)min((uint32_t)id, last); }
+
+// up to 8 pairs of a code: indices (at most `last`) and coefficients, zero past the end
 template <typename TI, typename TC, int PV>
-__device__ __forceinline__ void load_pairs(const TI *ip, const TC *cp, int n, int (&id)[8], float (&cf)[8])
+__device__ __forceinline__ void load_pairs(const TI *ip, const TC *cp, int n, uint32_t last, int (&id)[8], float (&cf)[8])
 {
 #pragma unroll
     for (int j0 = 0; j0 < 8; j0 += PV) {
@@ -84,7 +88,7 @@ __device__ __forceinline__ void load_pairs(const TI *ip, const TC *cp, int n, in
             CoefLoad<TC, PV>::ld(cp + j0, c);
         }
 #pragma unroll
-        for (int j = 0; j < PV; ++j) { id[j0 + j] = i[j]; cf[j0 + j] = c[j]; }
+        for (int j = 0; j < PV; ++j) { id[j0 + j] = inside(i[j], last); cf[j0 + j] = c[j]; }
     }
 }
 
@@ -196,6 +200,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
             turns[e] = exp2(-(2.0 * (4 * sub + e) / 128.0) * log2((double)p.rope_base)) * 0.15915494309189533577;
     }
 
+    const uint32_t last = (uint32_t)p.N - 1u;
     float m[GM], l[GM], acc[GM][8];
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
@@ -207,8 +212,8 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
     int ik[8], iv[8];
     float ck[8], cv[8];
     auto codes = [&](int64_t t) {   // the first 8 pairs of token t's codes
-        load_pairs<TI, TC, PV>(iK + t * p.snK * p.sK, cK + t * p.snK * p.sK, p.sK, ik, ck);
-        load_pairs<TI, TC, PV>(iV + t * p.snV * p.sV, cV + t * p.snV * p.sV, p.sV, iv, cv);
+        load_pairs<TI, TC, PV>(iK + t * p.snK * p.sK, cK + t * p.snK * p.sK, p.sK, last, ik, ck);
+        load_pairs<TI, TC, PV>(iV + t * p.snV * p.sV, cV + t * p.snV * p.sV, p.sV, last, iv, cv);
     };
     // The score as the code-domain form has it, sum_j c_j (q . d_j): an infinite coefficient is an infinite score there, while
     // the rebuilt key mixes infinities of both signs.  One pair at a time: codes of finite numbers never come here.
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
             IdxLoad<TI, 1>::ld(iK + t * p.snK * p.sK + j, id);
             CoefLoad<TC, 1>::ld(cK + t * p.snK * p.sK + j, cf);
             Piece<TD> row;
-            fetch<ROPE == 1>(row, DKh + (int64_t)id[0] * dcK);
+            fetch<ROPE == 1>(row, DKh + (int64_t)inside(id[0], last) * dcK);
             row.get(f);
 #pragma unroll
             for (int e = 0; e < 8; ++e) dot = fmaf(qg[e], f[e], dot);
@@ -262,7 +267,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
         for (int j0 = 8; j0 < p.sK; j0 += 8) {       // longer codes: the rest, 8 pairs at a time
             int id[8];
             float cf[8];
-            load_pairs<TI, TC, PV>(iK + t * p.snK * p.sK + j0, cK + t * p.snK * p.sK + j0, p.sK - j0, id, cf);
+            load_pairs<TI, TC, PV>(iK + t * p.snK * p.sK + j0, cK + t * p.snK * p.sK + j0, p.sK - j0, last, id, cf);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 rk[j].zero();
@@ -315,7 +320,7 @@ __global__ __launch_bounds__(kThreads, (waves_per_simd<GM, TD>())) void direct_k
         for (int j0 = 8; j0 < p.sV; j0 += 8) {
             int id[8];
             float cf[8];
-            load_pairs<TI, TC, PV>(iV + t * p.snV * p.sV + j0, cV + t * p.snV * p.sV + j0, p.sV - j0, id, cf);
+            load_pairs<TI, TC, PV>(iV + t * p.snV * p.sV + j0, cV + t * p.snV * p.sV + j0, p.sV - j0, last, id, cf);
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 rv[j].zero();

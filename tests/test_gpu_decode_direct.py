@@ -122,3 +122,25 @@ def test_a_score_of_minus_infinity_has_weight_zero(B, G, Hkv, T, snK):
         ref = oracle.decode_attn(q, DKx, *(_u16(a) if i == 0 else a for i, a in enumerate(plain(iK, far))), DVx, _u16(vals[0]), vals[1])
     _check(out[some], ref[some], TOL_F16_OUT, f"minus infinity {B} {G} {Hkv} {snK}")
     assert B == 1 or np.all(out[-1] == 0)
+
+
+@pytest.mark.parametrize("what", ["f16", "f32", "rope"])
+def test_an_index_outside_the_dictionary_reads_inside_it(what):
+    # one sequence's codes hold stale indices: the call ends, they count as the last atom, the other sequences do not notice
+    B, Hq, Hkv, T, N = 3, 4, 2, 77, 256
+    if what == "rope":
+        args, bad = list(rope._case(67, B, Hq, Hkv, T, N, 12, 4)), np.array([256, 40000, 65535], dtype=np.uint16).view(np.int16)
+    else:
+        args = list(_case(67, B, Hq, Hkv, T, N, 8, 12, dtype=what, itype="i16" if what == "f16" else "i32"))
+        bad = np.array([256, 40000, 65535], dtype=np.uint16).view(np.int16) if what == "f16" else np.array([256, -1, 2 ** 30], dtype=np.int32)
+
+    def run(a):
+        return rope._run(a, 10000.0, 0, 5) if what == "rope" else _run(*a)
+    clean = run(args)
+    stale, last = [a.copy() for a in args], [a.copy() for a in args]
+    for side in (2, 5):
+        stale[side][1, :, ::7, -1] = np.resize(bad, stale[side][1, :, ::7, -1].shape)
+        last[side][1, :, ::7, -1] = N - 1
+    out = run(stale)
+    assert np.array_equal(out[[0, 2]], clean[[0, 2]]) and not np.array_equal(out[1], clean[1])
+    assert np.array_equal(out, run(last))
