@@ -32,8 +32,8 @@ namespace {
 
 using namespace enc;
 
-constexpr int kSweepThreads = 512;
-constexpr int kSliceAtoms = 256;        // atoms per sweep workgroup, 32 per wave
+constexpr int kSweepThreads = 256;
+constexpr int kSliceAtoms = 256;        // atoms per sweep workgroup
 constexpr int kIterThreadsMax = 512;     // threads of an iterate workgroup: 512 when few vectors wait (the chain of an
                                         // iteration is shortest), 128 or 256 from kThroughputVectors per dictionary on
                                         // (what every wave repeats - merge, coefficient, residual - is done by fewer)
@@ -41,7 +41,8 @@ constexpr int kThroughputVectors = 12;
 constexpr int kMaxRounds = 4;           // rounds of 8 atoms per thread: N <= 512 * 8 * 4
 constexpr int kMaxAtoms = kIterThreadsMax * 8 * kMaxRounds;  // 16384
 constexpr int kMaxVectors = 128;        // per dictionary: a decoding step of up to 128 sequences
-static_assert(kSliceAtoms == kSweepThreads / 64 * 32, "a sweep workgroup covers one slice");
+constexpr int kSweepTiles = 2;          // 32-atom tiles per wave of the sweep
+static_assert(kSliceAtoms == kSweepThreads / 64 * 32 * kSweepTiles, "a sweep workgroup covers one slice");
 constexpr int kCand = 256;              // candidate list; beyond it every atom is evaluated
 
 __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
@@ -142,27 +143,38 @@ __global__ __launch_bounds__(256) void gram_build_kernel(const __half *__restric
 // On the matrix cores, v_mfma_f32_32x32x16_f16 with 32 vectors as the rows of A and 32 atoms as the columns of B.
 // Lane (col = lane % 32, hf = lane / 32) supplies dimensions 16 j + 8 hf .. + 7 of step j for vector col (A) and atom
 // col (B) - 16 contiguous bytes of a row per step - and receives, in accumulator 4 r4 + e, the product of vector
-// 8 r4 + 4 hf + e with atom col.  A wave keeps the rows of its tile in registers and walks the vectors 32 at a time.
-// What counts is the chain of one wave (read the atoms, multiply, store), not the products: a matrix-vector product on
-// the vector ALU, which spends nothing on vectors that are not there but reads its atoms row after row, took 17 us for 8
-// vectors on each of 8 dictionaries of 4096 atoms where this takes 5.
+// 8 r4 + 4 hf + e with atom col.  A wave keeps the rows of its kSweepTiles tiles in registers and walks the vectors 32 at a time.
+// The rows are requested the way they lie in memory - 1 KB of whole rows per load - and change places through LDS of the
+// wave's own: gathered fragment by fragment a load touches 32 rows, and what a workgroup requests does not stay in a 32 KB L1
+// until the rows' other pieces are asked for.  Workgroups of 4 waves, three on a CU: while one multiplies and stores, the
+// others' requests are under way (8 waves of one tile each, which leave room for two: 2 us more at 64 dictionaries).
+// Bound by reading the dictionaries, with many vectors by writing C_1.  Whole encode call, 4096 atoms, s = 8 (us), against the
+// vector ALU row by row (up to 8 vectors per dictionary) or gathered fragments: 64 dictionaries x 1 vector 30.7 / 30.6 / 36.2,
+// x 8 38.4 / 49.3 / 44.3, x 64 103.4 / - / 111.5; 8 dictionaries x 1 20.9 / 23.0 / 20.9, x 8 20.9 / 30.0 / 21.4.
 template <int DC>
-__global__ __launch_bounds__(kSweepThreads) void sweep_kernel(const __half *__restrict__ X, const __half *__restrict__ Dict,
+__global__ __launch_bounds__(kSweepThreads, 2) void sweep_kernel(const __half *__restrict__ X, const __half *__restrict__ Dict,
                                                               float *__restrict__ Cbuf, float *__restrict__ dmax2_part, int64_t T,
                                                               int32_t M, int32_t N, int32_t s, int32_t sn, int64_t x_stride_h,
                                                               int64_t x_stride_t, int32_t dict_count, int32_t nslices)
 {
-    constexpr int NF = DC / 16;  // matrix-core steps per product
-    __shared__ float red[kSweepThreads / 64];
+    constexpr int TILES = kSweepTiles, WAVES = kSweepThreads / 64;
+    constexpr int NF = DC / 16;  // matrix-core steps per product = loads of a tile
+    constexpr int P = DC / 8;    // 16-byte pieces of a row
+    __shared__ uint4 tile_s[WAVES][32 * P];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = lane & 31, hf = lane >> 5;
     const int dct = blockIdx.x / nslices, sl = blockIdx.x - dct * nslices;
     const __half *Dh = Dict + (int64_t)dct * N * DC;
-    const int n = sl * kSliceAtoms + wave * 32 + col;
-    const int nc = n < N ? n : N - 1;  // the last slice may be ragged: those lanes hold the last atom again
-    uint4 braw[NF], araw[NF];
+    const int n0 = sl * kSliceAtoms + wave * 32 * TILES;
+    uint4 braw[TILES][NF], araw[NF];
 #pragma unroll
-    for (int j = 0; j < NF; ++j) braw[j] = *reinterpret_cast<const uint4 *>(Dh + (int64_t)nc * DC + 16 * j + 8 * hf);
+    for (int t = 0; t < TILES; ++t) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) {
+            const int r = n0 + 32 * t + j * (64 / P) + lane / P;   // the last slice may be ragged: the last atom again
+            braw[t][j] = *reinterpret_cast<const uint4 *>(Dh + (int64_t)(r < N ? r : N - 1) * DC + 8 * (lane % P));
+        }
+    }
     auto load_vectors = [&](int v0) {
         const int m = v0 + col;
         const VecAt at = locate(dct, m < M ? m : M - 1, T, sn, s, DC, dict_count, x_stride_h, x_stride_t, 0);
@@ -173,33 +185,56 @@ __global__ __launch_bounds__(kSweepThreads) void sweep_kernel(const __half *__re
         }
     };
     load_vectors(0);
+    // piece p of row r: 32 rows are read at the same piece, so that the pieces are XORed with the row
+    auto at = [](int r, int p) { return r * P + (p ^ (P == 16 ? (r & 15) : ((r >> 1) & 7))); };
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) tile_s[wave][at(j * (64 / P) + lane / P, lane % P)] = braw[t][j];
+        wave_lds_fence();
+#pragma unroll
+        for (int j = 0; j < NF; ++j) braw[t][j] = tile_s[wave][at(col, 2 * j + hf)];
+        wave_lds_fence();
+    }
     for (int v0 = 0; v0 < M; v0 += 32) {
-        floatx16 acc;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+        for (int t = 0; t < TILES; ++t) {
+            floatx16 acc;
 #pragma unroll
-        for (int j = 0; j < NF; ++j)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8 *>(&araw[j]), *reinterpret_cast<const half8 *>(&braw[j]), acc, 0, 0, 0);
-        if (v0 + 32 < M) load_vectors(v0 + 32);
-        if (n < N) {
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int mv = v0 + 8 * (r >> 2) + 4 * hf + (r & 3);
-                if (mv < M) Cbuf[((int64_t)dct * M + mv) * N + n] = acc[r];
+            for (int j = 0; j < NF; ++j)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8 *>(&araw[j]),
+                                                             *reinterpret_cast<const half8 *>(&braw[t][j]), acc, 0, 0, 0);
+            if (t == TILES - 1 && v0 + 32 < M) load_vectors(v0 + 32);
+            const int n = n0 + 32 * t + col;
+            if (n < N) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int mv = v0 + 8 * (r >> 2) + 4 * hf + (r & 3);
+                    if (mv < M) Cbuf[((int64_t)dct * M + mv) * N + n] = acc[r];
+                }
             }
         }
     }
     float nmax = 0.0f;
 #pragma unroll
-    for (int j = 0; j < NF; ++j) nmax += dot8(braw[j], braw[j]);
-    nmax += __shfl_xor(nmax, 32, 64);  // the other half of the atom's dimensions
+    for (int t = 0; t < TILES; ++t) {
+        float nn = 0.0f;
+#pragma unroll
+        for (int j = 0; j < NF; ++j) nn += dot8(braw[t][j], braw[t][j]);
+        nn += __shfl_xor(nn, 32, 64);  // the other half of the atom's dimensions
+        nmax = fmaxf(nmax, nn);
+    }
 #pragma unroll
     for (int mm = 16; mm >= 1; mm >>= 1) nmax = fmaxf(nmax, __shfl_xor(nmax, mm, 64));
+    __syncthreads();   // every tile has been read: its LDS is free
+    float *red = reinterpret_cast<float *>(tile_s);
     if (lane == 0) red[wave] = nmax;
     __syncthreads();
     if (threadIdx.x == 0) {
         float v = red[0];
-        for (int w = 1; w < kSweepThreads / 64; ++w) v = fmaxf(v, red[w]);
+        for (int w = 1; w < WAVES; ++w) v = fmaxf(v, red[w]);
         dmax2_part[(int64_t)dct * nslices + sl] = v;
     }
 }
