@@ -59,7 +59,7 @@ typedef enum {
     CSR_ENCODE_VALU = 1, /* fp32 vector-ALU correlation, any supported shape               */
     CSR_ENCODE_MFMA = 2, /* fp16 matrix-core screening pass + exact fp32 selection          */
     CSR_ENCODE_SPLIT = 3, /* few vectors per dictionary (at most 128): every dictionary's atoms are
-                            split over several workgroups, one launch per iteration; fp16 inputs,
+                            split over several workgroups, one launch for all iterations; fp16 inputs,
                             chunks of 64 or 128 dimensions, N a multiple of 32                   */
     CSR_ENCODE_RESIDENT = 4, /* small dictionaries (N * d/s_n * 2 bytes <= 128 KB, e.g. the 256 - 512 atoms per
                             head of the paper's experiments): the dictionary stays in LDS, exact
@@ -82,6 +82,10 @@ typedef enum {
  * unrounded c_g and rounds on store only; with fp32 coefficients the two coincide.  Taken by the VALU, MFMA, SPLIT
  * and RESIDENT encoders (the Gram forms return CSR_ERR_UNSUPPORTED, and AUTO does not choose them with the flag). */
 #define CSR_FLAG_CLOSED_LOOP 1u
+/* NO_WAIT: the workgroups of the SPLIT encoder that share a dictionary do not wait for one another's candidates but compute
+ * them all, each for itself: the same codes, slower on an idle chip, and independent of when the GPU has room for the other
+ * workgroups (without the flag a workgroup does so once it has waited 40 us in vain).  The other encoders ignore it. */
+#define CSR_FLAG_NO_WAIT 0x100u
 
 /*
  * Matching Pursuit encode (Eq.2-4), H independent dictionaries with T vectors each.
@@ -115,7 +119,7 @@ typedef struct {
                            (Section "KV Decomposition and Sparse Storage": a generated token is
                            encoded like the prompt's)                                       */
     int32_t algo;       /* csr_encode_algo                                                  */
-    uint32_t flags;     /* 0 or CSR_FLAG_CLOSED_LOOP                                        */
+    uint32_t flags;     /* CSR_FLAG_CLOSED_LOOP, CSR_FLAG_NO_WAIT or both; or 0             */
     float *res_norm2;   /* optional device pointer, [H][T][s_n] fp32, or NULL: receives |R_{s+1}|^2, the
                            squared norm of what the s pairs leave of each vector (chunk) - by Eq.4 the
                            squared reconstruction error |x - D r|^2 with unrounded coefficients, i.e. the

@@ -61,7 +61,7 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
 {
     if (!d) return fail(CSR_ERR_INVALID_ARG, "csr_encode: descriptor is NULL");
     if (d->H < 0 || d->T < 0) return fail(CSR_ERR_INVALID_ARG, "csr_encode: H=%d T=%lld must be >= 0", d->H, (long long)d->T);
-    if ((d->flags & ~CSR_FLAG_CLOSED_LOOP) != 0) return fail(CSR_ERR_INVALID_ARG, "csr_encode: unknown flags 0x%x", d->flags);
+    if ((d->flags & ~(CSR_FLAG_CLOSED_LOOP | CSR_FLAG_NO_WAIT)) != 0) return fail(CSR_ERR_INVALID_ARG, "csr_encode: unknown flags 0x%x", d->flags);
     const bool closed = (d->flags & CSR_FLAG_CLOSED_LOOP) != 0;
     if (!valid_dtype(d->x_dtype) || !valid_dtype(d->dict_dtype) || !valid_dtype(d->coef_dtype) || !valid_itype(d->idx_dtype))
         return fail(CSR_ERR_INVALID_ARG, "csr_encode: unknown dtype / index type");
@@ -124,6 +124,7 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
                     "of 32 and a dictionary of at most 128 KB (got d/s_n=%d N=%d %s)", dc, d->N, a.f16 ? "f16" : "f32");
     a.gram = d->gram;
     a.closed_loop = closed;
+    a.no_wait = (d->flags & CSR_FLAG_NO_WAIT) != 0;
     if (closed && d->algo == CSR_ENCODE_GRAM)
         return fail(CSR_ERR_UNSUPPORTED, "csr_encode: the Gram encoders do not take CSR_FLAG_CLOSED_LOOP");
     const bool step_ok = !closed && d->gram != nullptr && csr::encode_gramstep_supported(a);

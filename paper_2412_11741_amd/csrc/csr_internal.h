@@ -35,6 +35,7 @@ struct EncodeArgs {
     bool f16;                        // X and D are fp16 (else fp32)
     bool coef16, idx16;
     bool closed_loop;                // Eq.4 subtracts the coefficient as it is stored (CSR_FLAG_CLOSED_LOOP)
+    bool no_wait;                    // CSR_FLAG_NO_WAIT
     float *res_norm2;                // optional [H][T][sn] output, or nullptr
     const void *gram;                // optional Gram matrices [dict_count * sn][N][N] fp16 (csr_gram_build), or nullptr
     void *workspace;
@@ -55,7 +56,7 @@ size_t encode_mfma_workspace_bytes(int32_t n_dicts, int64_t T, int32_t N, int32_
 hipError_t launch_encode_mfma(const EncodeArgs &a);
 
 // fp16 matrix-core encoder for few vectors per dictionary (a decoding step): atoms split over workgroups,
-// one launch per iteration.
+// one launch for all iterations.
 bool encode_split_supported(const EncodeArgs &a);
 size_t encode_split_workspace_bytes(const EncodeArgs &a);
 hipError_t launch_encode_split(const EncodeArgs &a);

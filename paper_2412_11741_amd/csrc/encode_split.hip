@@ -18,8 +18,10 @@
 //            arithmetic, so the copies never diverge; slice 0 stores the pair
 //
 // The workgroups need not run at the same time: one that starts late finds the others' words and catches up, and one that
-// waits in vain for kPatience (its partners hold no CU, because other work does) computes the missing slices' candidates
-// itself, from device memory, with the same arithmetic - every wait ends, and the result does not depend on it.  The slots
+// waits in vain for kPatience (its partners hold no CU, because other work does) goes on alone: the wave that waited computes
+// the other slices' candidates of its vectors itself, and from the next iteration on all waves of the workgroup sweep the
+// other slices, too, from device memory.  The arithmetic is the same, so every wait ends and the result does not depend on
+// it; a call waits in vain once, not in every iteration.  CSR_FLAG_NO_WAIT goes that way from the start.  The slots
 // are cleared by a launch of their own before (a workspace's contents are undefined); a slot is written once per call.
 //
 // Bound: reading the dictionaries once, then a dependent chain per iteration - hi and lo from LDS, 16 dependent matrix
@@ -46,7 +48,7 @@ constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxVectors = 128;   // per dictionary; beyond that the prefill encoders' shapes are the better ones
 constexpr int kMaxSlices = 16;
 constexpr int kTargetGroups = 256; // one workgroup per CU
-constexpr int kPatience = 10000;   // ticks of the 100 MHz counter a workgroup waits for its partners: 100 us
+constexpr int kPatience = 4000;    // ticks of the 100 MHz counter a wave waits for the partners, 40 us: a whole call's time
 
 struct SplitParams {
     const __half *X;
@@ -57,7 +59,7 @@ struct SplitParams {
     int64_t V;                   // vectors in all
     int64_t T;
     int64_t x_stride_h, x_stride_t, code_stride_h;
-    int32_t N, s, sn, dict_count, n_dicts, M, k, idx16, coef_mode;
+    int32_t N, s, sn, dict_count, n_dicts, M, k, idx16, coef_mode, patience;   // patience: kPatience, or -1: not even look
     float *res_norm2;            // optional [H][T][sn]
 };
 
@@ -104,7 +106,9 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
     unsigned char *hi_s = res + m_pad * DC * 4;      // [m_pad][DC] fp16: hi, and behind it lo
     unsigned char *lo_s = hi_s + m_pad * DC * 2;
     unsigned long long *red = reinterpret_cast<unsigned long long *>(lo_s + m_pad * DC * 2);      // [kWaves][m_pad]
-    SplitState *state = reinterpret_cast<SplitState *>(red + kWaves * m_pad);                     // [M]
+    unsigned long long *red_other = red + kWaves * m_pad;   // the same of the other slices' tiles, once the workgroup is alone
+    SplitState *state = reinterpret_cast<SplitState *>(red_other + kWaves * m_pad);               // [M]
+    __shared__ int alone_s;                    // the partners have been waited for in vain
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -152,6 +156,7 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
         *reinterpret_cast<half8 *>(lo_s + half_at<DC>(v, sub)) = l;
     };
 
+    if (tid == 0) alone_s = 0;
     // ---- the vectors, scaled by a power of two that brings max |x_k| into [2^11, 2^12): hi and lo stay normal ----------
     for (int v = team; v < m_pad; v += kTeams) {
         // vector m of this dictionary: block h = (m / T) dict_count + dict, its token m % T
@@ -182,9 +187,10 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
     }
     __syncthreads();
 
-    // The best candidate of vectors m0 .. m0 + 31 over the tiles first, first + step .. below last, as a packed word with
-    // `tag` (lanes col of either half); `own`: this wave's tiles of the workgroup's slice, the first ones in registers.
-    auto sweep = [&](int m0, int first, int last, int step, bool own, int tag) {
+    // The best candidate of vectors m0 .. m0 + 31 as a packed word with `tag` (lanes col of either half): `own`, over this
+    // wave's tiles of the workgroup's slice, the first ones in registers; else over the tiles first, first + step .. of the
+    // other slices.
+    auto sweep = [&](int m0, int first, int step, bool own, int tag) {
         half8 hi[kFrags], lo[kFrags];
         const int mine = min(m0 + col, p.M - 1);   // columns past the last vector repeat it: one LDS address for them all
 #pragma unroll
@@ -232,9 +238,10 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
         if (own) {
 #pragma unroll
             for (int q = 0; q < HELD; ++q)
-                if (first + q * kWaves < last) tile_best(first + q * kWaves, held[q]);
+                if (first + q * kWaves < t_end) tile_best(first + q * kWaves, held[q]);
         }
-        for (int tile = first + (own ? HELD * kWaves : 0); tile < last; tile += step) {
+        for (int tile = first + (own ? HELD * kWaves : 0); tile < (own ? t_end : tiles); tile += step) {
+            if (!own && tile >= t_begin && tile < t_end) continue;
             uint4 a[kFrags];
             load_tile(tile, a);
             tile_best(tile, a);
@@ -246,9 +253,16 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
 #pragma unroll 1
     for (int g = 0; g < p.s; ++g) {
         const int tag = g + 1;
+        const bool alone = p.k > 1 && __builtin_amdgcn_readfirstlane(alone_s) != 0;   // (set behind this iteration's barrier at the earliest)
         for (int m0 = 0; m0 < p.M; m0 += 32) {
-            const unsigned long long w = sweep(m0, t_begin + wave, t_end, kWaves, true, tag);
+            const unsigned long long w = sweep(m0, t_begin + wave, kWaves, true, tag);
             if (hf == 0) red[wave * m_pad + m0 + col] = w;
+        }
+        if (alone) {
+            for (int m0 = 0; m0 < p.M; m0 += 32) {
+                const unsigned long long w = sweep(m0, wave, kWaves, false, tag);
+                if (hf == 0) red_other[wave * m_pad + m0 + col] = w;
+            }
         }
         __syncthreads();
         // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published:
@@ -260,15 +274,21 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
                 red[v] = w;
                 if (p.k > 1) __hip_atomic_store(slot + state[v].vid * p.k + sl, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            if (alone) {
+                unsigned long long o = red_other[(sub & (kWaves - 1)) * m_pad + v];
+                o = row_reduce<kWaves>(o, OpMaxU64());
+                if (sub == 0) red[v] = o > w ? o : w;
+            }
         }
         wave_lds_fence();
+        bool vain = false;   // this wave has waited for nothing in this iteration
         // ---- the other slices' candidates, the pick, Eq.4 -----------------------------------------------------------------
         for (int v0 = wave * (64 / L); v0 < p.M; v0 += kTeams) {   // (uniform over the wave)
             const int v = v0 + lane / L;
             const int vc = min(v, p.M - 1);   // a team past the last vector idles along: it waits for nobody
             const int slices = v < p.M ? p.k : 0;
             unsigned long long w = vc == v ? red[v] : 0ull;
-            if (p.k > 1) {
+            if (p.k > 1 && !alone) {
                 unsigned long long *mine = slot + state[vc].vid * p.k;
                 unsigned long long got[kSlots];
                 bool ok = true;
@@ -277,13 +297,13 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
                     const int j = sub + i * L;
                     got[i] = 0ull;
                     if (j < slices && j != sl) {
-                        got[i] = __hip_atomic_load(mine + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (p.patience >= 0) got[i] = __hip_atomic_load(mine + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         ok = ok && candidate_tag(got[i]) == tag;
                     }
                 }
                 if (__ballot(!ok)) {
                     const uint64_t began = wall_clock64();
-                    do {
+                    while (p.patience >= 0) {
                         __builtin_amdgcn_s_sleep(1);
                         ok = true;
 #pragma unroll
@@ -294,29 +314,20 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
                                 ok = ok && candidate_tag(got[i]) == tag;
                             }
                         }
-                    } while (__ballot(!ok) && wall_clock64() - began <= (uint64_t)kPatience);
+                        if (!__ballot(!ok) || vain || wall_clock64() - began > (uint64_t)p.patience) break;
+                    }
                     if (__ballot(!ok)) {
-                        // partners that hold no CU: the missing slices' candidates computed here, by this wave alone
-                        for (int t = 0; t < 64 / L; ++t) {
-                            for (int j = 0; j < p.k; ++j) {
-                                const int from = t * L + j % L;        // the lane that waits for slice j
-                                bool miss = false;
-#pragma unroll
-                                for (int i = 0; i < kSlots; ++i) miss = miss || (j / L == i && j < slices && j != sl && candidate_tag(got[i]) != tag);
-                                if (!((__ballot(miss) >> from) & 1ull)) continue;
-                                const int vt = min(v0 + t, p.M - 1);
-                                const int first = j * per_slice;
-                                const unsigned long long o = sweep(vt & ~31, first, min(tiles, first + per_slice), 1, false, tag);
-                                const unsigned long long theirs = __shfl(o, vt & 31, 64);
-#pragma unroll
-                                for (int i = 0; i < kSlots; ++i)
-                                    if (lane == from && j / L == i) got[i] = theirs;
-                            }
-                        }
+                        // partners that hold no CU: the other slices' candidates of this wave's vectors - they are of one
+                        // block of 32 - computed here; from the next iteration on the whole workgroup does
+                        vain = true;
+                        if (lane == 0) alone_s = 1;
+                        const unsigned long long o = sweep(v0 & ~31, 0, 1, false, tag);
+                        const unsigned long long theirs = __shfl(o, v & 31, 64);
+                        w = theirs > w ? theirs : w;
                     }
                 }
 #pragma unroll
-                for (int i = 0; i < kSlots; ++i) w = got[i] > w ? got[i] : w;
+                for (int i = 0; i < kSlots; ++i) w = candidate_tag(got[i]) == tag && got[i] > w ? got[i] : w;
                 w = row_reduce<L>(w, OpMaxU64());
             }
             // (no candidate at all - correlations that are not numbers - counts as atom 0 with coefficient 0)
@@ -394,7 +405,7 @@ SplitPlan plan_split(const EncodeArgs &a)
     const int per_wave = ((tiles + k - 1) / k + kWaves - 1) / kWaves;
     pl.held = per_wave <= 1 ? 1 : per_wave <= 2 ? 2 : 4;   // of 128 dimensions: 32, 64 or 128 registers
     const int m_pad = (pl.M + 31) & ~31;
-    pl.lds = (size_t)m_pad * a.d * 8 + (size_t)kWaves * m_pad * 8 + (size_t)pl.M * sizeof(SplitState);
+    pl.lds = (size_t)m_pad * a.d * 8 + 2 * (size_t)kWaves * m_pad * 8 + (size_t)pl.M * sizeof(SplitState);
     pl.total = r256((size_t)a.s * pl.V * k * sizeof(unsigned long long));
     return pl;
 }
@@ -409,7 +420,7 @@ hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitP
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_split_kernel<DC, HELD>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                159 * 1024);   // (the barrier that votes has a little LDS of its own)
+                                159 * 1024);   // (plan_split: at most 147 KB; a word of static LDS besides)
         if (e != hipSuccess) return e;
         attr_set[dev].store(true, std::memory_order_release);
     }
@@ -438,6 +449,7 @@ hipError_t launch_encode_split(const EncodeArgs &a)
     p.V = pl.V; p.T = a.T; p.x_stride_h = a.x_stride_h; p.x_stride_t = a.x_stride_t; p.code_stride_h = a.code_stride_h;
     p.N = a.N; p.s = a.s; p.sn = a.sn; p.dict_count = a.dict_count; p.n_dicts = a.dict_count * a.sn; p.M = pl.M; p.k = pl.k;
     p.idx16 = a.idx16; p.coef_mode = (a.coef16 ? kCoefF16 : 0) | (a.closed_loop ? kCoefClosed : 0); p.res_norm2 = a.res_norm2;
+    p.patience = a.no_wait ? -1 : kPatience;
     if (pl.k > 1) {
         const int64_t n2 = (int64_t)(pl.total / 16);
         hipLaunchKernelGGL(clear_slots_kernel, dim3((unsigned)((n2 + 255) / 256)), dim3(256), 0, a.stream,

@@ -1,11 +1,13 @@
 """GPU parity: the few-vectors encoder's slices - several workgroups share a dictionary and exchange their candidates - at
 the edges of its split (tests of its options and storage types are with the other encoders')."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2412_11741_amd as csr
-from paper_2412_11741_amd import synth
+from paper_2412_11741_amd import binding, synth
 from tests.test_gpu_encode import _assert_ok, _compare
 
 pytestmark = pytest.mark.gpu
@@ -31,3 +33,32 @@ def test_slices_of_a_dictionary_agree(dicts, M, N, d, s):
     heads = sorted({0, dicts // 2, dicts - 1})
     _assert_ok(_compare(X, D, s, idx.cpu().numpy().view(np.uint16).astype(np.int32), coef.cpu().numpy(), heads=heads))
     assert not idx[-1, -1].any() and not coef[-1, -1].any()
+
+
+@pytest.mark.parametrize("dicts,M,N,d,s,sn", [
+    (8, 1, 4160, 128, 6, 1),    # 16 slices, the last one empty
+    (2, 33, 800, 128, 4, 1),    # 3 slices, a second block of vectors
+    (3, 128, 1024, 64, 5, 2),   # the most vectors in chunks: two slots per lane, several groups of vectors per wave
+    (4, 31, 2048, 64, 32, 1),   # 8 slices, the longest code
+])
+@pytest.mark.parametrize("closed", [0, csr.CSR_FLAG_CLOSED_LOOP])
+def test_codes_do_not_depend_on_who_computed_them(dicts, M, N, d, s, sn, closed):
+    # with CSR_FLAG_NO_WAIT every workgroup takes every other one for absent: the first iteration's missing candidates are
+    # computed by the wave that wants them, the later iterations' by the whole workgroup.  The sums are the same, so are the bits
+    D = torch.from_numpy(synth.dictionary(92, "dict_k", dicts * sn, N, d, "f16")).cuda()
+    D = D.view(dicts, sn, N, d) if sn > 1 else D
+    X = torch.from_numpy(synth.vectors(92, "keys", dicts, M, d * sn, "f16", outliers=4)).cuda()
+    X[-1, -1] = 0.0
+    got = []
+    for flags in (closed, closed | csr.CSR_FLAG_NO_WAIT):
+        desc = binding.encode_desc(X, D, s, torch.float16, torch.int16, csr.CSR_ENCODE_SPLIT, flags=flags)
+        idx = torch.empty(dicts, M, sn, s, dtype=torch.int16, device="cuda")
+        coef, err = torch.empty(idx.shape, dtype=torch.float16, device="cuda"), torch.empty(dicts, M, sn, device="cuda")
+        desc.res_norm2 = err.data_ptr()
+        ws = torch.empty(binding.csr_encode_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+        assert ws.numel() > 0                    # several workgroups share a dictionary
+        binding._check(binding.lib().csr_encode(ctypes.byref(desc), *(ctypes.c_void_p(t.data_ptr()) for t in (X, D, idx, coef, ws)),
+                                                ws.numel(), binding._stream()))
+        torch.cuda.synchronize()
+        got.append((idx, coef, err))
+    assert all(torch.equal(a, b) for a, b in zip(*got))
