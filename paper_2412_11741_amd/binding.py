@@ -22,7 +22,7 @@ CSR_OK, CSR_ERR_INVALID_ARG, CSR_ERR_UNSUPPORTED, CSR_ERR_WORKSPACE, CSR_ERR_DEV
 CSR_F32, CSR_F16 = 0, 1
 CSR_I32, CSR_I16 = 0, 1
 CSR_ENCODE_AUTO, CSR_ENCODE_VALU, CSR_ENCODE_MFMA, CSR_ENCODE_SPLIT, CSR_ENCODE_RESIDENT, CSR_ENCODE_GRAM, CSR_ENCODE_WIDE = range(7)
-CSR_FLAG_CLOSED_LOOP = 1
+CSR_FLAG_CLOSED_LOOP, CSR_FLAG_NO_WAIT = 1, 0x100
 
 EXPORTS = ("csr_version", "csr_last_error", "csr_code_bytes", "csr_encode_workspace_bytes",
            "csr_encode", "csr_decode_workspace_bytes", "csr_decode_attn", "csr_reconstruct", "csr_atom_norms2",
