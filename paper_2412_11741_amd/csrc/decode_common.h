@@ -470,7 +470,9 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
                 for (int k = 0; k < PF; ++k) walk.next(k);
             }
         }
-        auto rounds = [&](auto wide_c) {
+        // (inlined by order: unrolled as a function of its own, its body would be too large for the compiler to inline, and the
+        // scores it is handed would live in scratch memory)
+        auto rounds = [&](auto wide_c) __attribute__((always_inline)) {
             constexpr bool WIDE = decltype(wide_c)::value;
 #pragma unroll
             for (int i = 0; i < TPT; ++i) {

@@ -1,0 +1,41 @@
+"""What the compiler made of the kernels that stand or fall with it, from the metadata of the built library: needs no GPU."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2412_11741_amd import binding
+
+READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: metadata} of every kernel in libcsr_hip.so: its code objects are ELF images inside the host's one."""
+    if not os.path.exists(READELF):
+        pytest.skip("no llvm-readelf")
+    binding.lib()
+    image, found = open(binding.LIB_PATH, "rb").read(), {}
+    path = tmp_path_factory.mktemp("code") / "object"
+    for at in (m.start() for m in re.finditer(rb"\x7fELF\x02\x01\x01\x40", image)):   # 0x40: AMD GPU HSA
+        path.write_bytes(image[at:])
+        notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True).stdout
+        for block in re.split(r"\n  - \.", notes):
+            name, fields = re.search(r"\.name: +(\S+)", block), dict(re.findall(r"\.?(\w+): +(\d+)", block))
+            if name and "private_segment_fixed_size" in fields:
+                found[name.group(1)] = {k: int(v) for k, v in fields.items()}
+    return found
+
+
+def test_the_streaming_kernels_keep_their_scores_in_registers(kernels):
+    # a thread's scores, one per round and query head, are an array that is only in registers if every loop over it is
+    # unrolled and everything that takes it is inlined; else every score goes through scratch memory
+    stream = {n: k["private_segment_fixed_size"] for n, k in kernels.items() if "13stream_kernel" in n}
+    assert len(stream) > 50
+
+    def scores(name):   # bytes of the array: query heads x rounds
+        heads, rounds = re.search(r"stream_kernelILi(\d+)E.*?Lb[01]ELi(\d+)E", name).groups()
+        return 4 * int(heads) * int(rounds)
+    # (up to 25 spilled registers in the variants for two query heads)
+    assert not {n: v for n, v in stream.items() if v >= max(scores(n), 128)}
