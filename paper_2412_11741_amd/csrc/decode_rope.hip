@@ -420,11 +420,17 @@ hipError_t launch_rope_t(const DecodeArgs &a, const DecodePlan &p, float *hist, 
 template <int GB, bool ROTK, int PVK, bool ONEB, bool GLOBAL>
 hipError_t launch_rope_pv(const DecodeArgs &a, const DecodePlan &p, float *hist, float *ml)
 {
-    switch (a.snV * a.sV) {   // value codes read as a whole, requested ahead
-        case 4: return launch_rope_t<GB, ROTK, PVK, ONEB, 4, 4, GLOBAL>(a, p, hist, ml);
-        case 8: return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 8, GLOBAL>(a, p, hist, ml);
-        case 16: return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 16, GLOBAL>(a, p, hist, ml);
+    // Value codes read as a whole, requested ahead - except in the variant that has no registers for it (one query head, 8
+    // key rows at a time from device memory: 240 spilled registers become 279, 32 heads x 4096 tokens on 4096 atoms take
+    // 101.9 us instead of 92.9; with groups of 2 and 4 the requests are worth 1 - 2 %).
+    if constexpr (!(GLOBAL && GB == 1 && PVK == 8)) {
+        switch (a.snV * a.sV) {
+            case 4: return launch_rope_t<GB, ROTK, PVK, ONEB, 4, 4, GLOBAL>(a, p, hist, ml);
+            case 8: return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 8, GLOBAL>(a, p, hist, ml);
+            case 16: return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 16, GLOBAL>(a, p, hist, ml);
+        }
     }
+    if (a.sV % 8 == 0) return launch_rope_t<GB, ROTK, PVK, ONEB, 8, 0, GLOBAL>(a, p, hist, ml);
     if (a.sV % 4 == 0) return launch_rope_t<GB, ROTK, PVK, ONEB, 4, 0, GLOBAL>(a, p, hist, ml);
     return launch_rope_t<GB, ROTK, PVK, ONEB, 1, 0, GLOBAL>(a, p, hist, ml);
 }

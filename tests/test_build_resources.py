@@ -39,3 +39,16 @@ def test_the_streaming_kernels_keep_their_scores_in_registers(kernels):
         return 4 * int(heads) * int(rounds)
     # (up to 25 spilled registers in the variants for two query heads)
     assert not {n: v for n, v in stream.items() if v >= max(scores(n), 128)}
+
+
+def test_rotary_kernels_spill_no_more_for_value_codes_requested_ahead(kernels):
+    # variants of the same kernel by NP, the pairs of a value code that is requested as a whole; 0: loaded where it is used
+    by_shape = {}
+    for n, k in kernels.items():
+        m = re.search(r"stream_rope_kernelILi(\d+)ELb(\d)ELi(\d+)ELb(\d)ELi\d+ELi(\d+)ELi\d+ELb(\d)E", n)
+        if m:
+            heads, rotk, pvk, oneb, pairs, rows_gathered = m.groups()
+            by_shape.setdefault((heads, rotk, pvk, oneb, rows_gathered), {}).setdefault(int(pairs), []).append(k["private_segment_fixed_size"])
+    assert len(by_shape) > 8
+    for shape, sizes in by_shape.items():
+        assert max(map(max, sizes.values())) <= max(sizes[0]), shape
