@@ -372,9 +372,12 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
             w.next(k);
         }
     };
+    static_assert(STEPS <= 2 && (STEPS == 1 || PF == 1), "the sample below takes the coefficients of the steps that prime left out");
+    uint32_t other[STEPS > 1 ? CodeVec<TI, TC, PIECE>::W : 1];   // the second half's coefficients of the first round's token
     if constexpr (NP > 0) {
         CodeWalk<TI, TC, NP, PIECE, THREADS> w0(idxV, coefV, code_row + t0, owner_off);
         prime(w0);
+        if constexpr (STEPS > 1) load_words(w0.cb + (n_mine > 0 && tok0 < t_end ? w0.off : 0u), other);
     }
 #pragma unroll
     for (int g = 0; g < GB; ++g) {
@@ -390,6 +393,13 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
             if (n_mine > 0 && tok0 < t_end) {   // else the vectors are not this thread's
 #pragma unroll
                 for (int j = 0; j < PV; ++j) cm = fmaxf(cm, fabsf(cf[j]));
+                if constexpr (STEPS > 1) {
+#pragma unroll
+                    for (int j = 0; j < PV; j += 2) {
+                        const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&other[(j0 + j) / 2]));
+                        cm = fmaxf(cm, fmaxf(fabsf(f.x), fabsf(f.y)));
+                    }
+                }
             }
         }
     } else {

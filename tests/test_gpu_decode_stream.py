@@ -3,6 +3,7 @@ requests as a whole - 4, 6, 8 and 16 pairs, whole-vector and chunked - by query 
 chunk, with lengths that end inside a round, and for codes whose sizes differ (loaded where they are used)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from tests.test_gpu_decode import TOL_F16_OUT, _case, _check, _chunked_case, _run, _u16
@@ -52,3 +53,16 @@ def test_chunked_codes(Hq, snK, sK, snV, sV, T):
 def test_values_of_rotary_keys(Hq, N, sK, snV, sV, T):
     args = rope._case(73, 1, Hq, 1, T, N, sK, sV, snV=snV)
     rope._check(rope._run(args, 10000.0, 0, 3), oracle.decode_attn_rope(*args, 10000.0, 0, 3), f"stream rope {Hq} {sK} {snV} {sV}")
+
+
+def test_both_halves_of_a_code_are_sampled():
+    # values in two chunks of 8 pairs, one with coefficients 1024 times the other's: the scatter's unit, chosen from a sample of
+    # the coefficients, must not depend on which half of the code the large ones are in.  The two calls are each other's
+    # mirror image, so the bits are equal - unless one of them has had to repeat its scatter in 64 bits
+    Hq, T, N, s = 4, 20000, 256, 8
+    q, DK, iK, cK, DV, iV, cV = _chunked_case(74, 1, Hq, 1, T, N, 1, 16, 2, s)
+    cV[:, :, :, 1] = (cV[:, :, :, 1].astype(np.float32) / 1024).astype(np.float16)
+    keys = (DK[:, 0], np.ascontiguousarray(iK[:, :, :, 0]), np.ascontiguousarray(cK[:, :, :, 0]))
+    one = _run(q, *keys, DV, iV, cV, out_dtype=torch.float32)
+    two = _run(q, *keys, *(np.ascontiguousarray(np.flip(a, ax)) for a, ax in ((DV, 1), (iV, 3), (cV, 3))), out_dtype=torch.float32)
+    assert np.array_equal(one, np.concatenate([two[..., 64:], two[..., :64]], axis=-1))
