@@ -225,9 +225,10 @@ template <int GB, int TPT, int W> constexpr int prefetch_steps()
 }
 // pairs worked on at a time
 template <int NP> constexpr int pair_block() { return NP % 8 == 0 ? 8 : NP; }
-// Pairs requested at a time: the whole code, or with several query heads per workgroup half of a code of 16 (the scores
-// leave no registers for two whole ones: 26 spilled).  A "step" is one such piece of one token.
-template <int GB, int NP> constexpr int pair_piece() { return GB > 1 && NP > 8 ? 8 : NP; }
+// Pairs requested at a time: the whole code, or with four query heads per workgroup half of a code of 16 (the scores
+// leave no registers for two whole ones).  With two heads whole ones cost 3 spilled registers and are worth it: 4 sequences x
+// 16 KV heads x 2 query heads, 32768 tokens, 4096 atoms 72.5 us against 75.9 in halves.  A "step" is one such piece of one token.
+template <int GB, int NP> constexpr int pair_piece() { return GB > 2 && NP > 8 ? 8 : NP; }
 
 // The code streams of a thread's tokens, walked round by round: two workgroup-uniform base addresses (the codes of the
 // chunk's first token) and one 32-bit offset per thread, in bytes.  The offset passes
@@ -287,8 +288,17 @@ __device__ __forceinline__ void fetch_codes(CodeVec<TI, TC, PIECE> &r, const Cod
 template <typename TI, typename TC, int NP>
 __device__ __forceinline__ void await_codes(CodeVec<TI, TC, NP> &cur)
 {
+    constexpr int W = CodeVec<TI, TC, NP>::W;
+    if constexpr (W % 4 == 0) {   // a request at a time: the wait for the coefficients then stands behind the use of the indices
 #pragma unroll
-    for (int k = 0; k < CodeVec<TI, TC, NP>::W; ++k) asm volatile("" : "+v"(cur.i[k]), "+v"(cur.c[k]));
+        for (int k = 0; k < W; k += 4) {
+            asm volatile("" : "+v"(cur.i[k]), "+v"(cur.i[k + 1]), "+v"(cur.i[k + 2]), "+v"(cur.i[k + 3]));
+            asm volatile("" : "+v"(cur.c[k]), "+v"(cur.c[k + 1]), "+v"(cur.c[k + 2]), "+v"(cur.c[k + 3]));
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < W; ++k) asm volatile("" : "+v"(cur.i[k]), "+v"(cur.c[k]));
+    }
 }
 // pairs B * j0 .. of a code, B = pair_block
 template <typename TI, typename TC, int NP, int B>
