@@ -88,19 +88,16 @@ struct Workspace {
     c10::DataPtr own;
     void *ptr = nullptr;
     size_t bytes = 0;
-    bool take(PyObject *given, size_t need)
+    Workspace(const Tensor *given, size_t need)
     {
-        if (given != Py_None) {
-            const Tensor *w = gpu_tensor(given);
-            if (!w) return false;
-            ptr = w->data_ptr();
-            bytes = (size_t)w->numel() * w->element_size();
+        if (given) {
+            ptr = given->data_ptr();
+            bytes = (size_t)given->numel() * given->element_size();
         } else if (need) {
             own = c10::hip::HIPCachingAllocator::get()->allocate(need);
             ptr = own.get();
             bytes = need;
         }
-        return true;
     }
 };
 
@@ -109,6 +106,20 @@ void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
 Tensor fresh(at::IntArrayRef shape, ScalarType t, const Tensor &like)
 {
     return at::empty(shape, at::TensorOptions().dtype(t).device(like.device()));
+}
+
+// The interpreter's lock given up while memory is taken and kernels are launched: other threads' Python runs meanwhile.
+struct Unlocked {
+    PyThreadState *state = PyEval_SaveThread();
+    ~Unlocked() { PyEval_RestoreThread(state); }
+};
+
+// The caller's output, or the one that was made for the call; nullptr (with Python's error set) if it cannot be wrapped
+PyObject *output(PyObject *given, Tensor &made)
+{
+    if (given == Py_None) return THPVariable_Wrap(std::move(made));
+    Py_INCREF(given);
+    return given;
 }
 
 #define CSR_PUNT() Py_RETURN_NONE
@@ -169,31 +180,29 @@ PyObject *encode(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (si != sc) CSR_PUNT();
         e.code_stride_h = si;
     }
-    const size_t need = api.encode_workspace(&e);
-    Workspace ws;
-    if (need == kInvalid || !ws.take(a[8], need)) CSR_PUNT();
-    PyObject *res[2] = {nullptr, nullptr};
-    void *out[2];
-    for (int k = 0; k < 2; ++k) {
-        if (given[k]) {
-            Py_INCREF(a[6 + k]);
-            res[k] = a[6 + k];
-            out[k] = given[k]->data_ptr();
-        } else {
-            Tensor t = fresh(shape, k == 0 ? it : ct, *X);
-            out[k] = t.data_ptr();
-            res[k] = THPVariable_Wrap(std::move(t));
+    const Tensor *workspace = nullptr;
+    if (a[8] != Py_None && !(workspace = gpu_tensor(a[8]))) CSR_PUNT();
+    Tensor made[2];   // owned here until the call has been made: an allocation that throws takes the other one along
+    csr_status st;
+    {
+        Unlocked unlocked;
+        const size_t need = api.encode_workspace(&e);
+        void *out[2];
+        st = need == kInvalid ? CSR_ERR_WORKSPACE : CSR_OK;
+        const Workspace ws(workspace, st == CSR_OK ? need : 0);
+        for (int k = 0; k < 2 && st == CSR_OK; ++k) {
+            if (!given[k]) made[k] = fresh(shape, k == 0 ? it : ct, *X);
+            out[k] = given[k] ? given[k]->data_ptr() : made[k].data_ptr();
         }
+        if (st == CSR_OK) st = api.encode(&e, X->data_ptr(), D->data_ptr(), out[0], out[1], ws.ptr, ws.bytes, stream());
     }
-    const csr_status st = api.encode(&e, X->data_ptr(), D->data_ptr(), out[0], out[1], ws.ptr, ws.bytes, stream());
-    if (st != CSR_OK) {
-        Py_XDECREF(res[0]);
-        Py_XDECREF(res[1]);
-        CSR_PUNT();
-    }
+    if (st != CSR_OK) CSR_PUNT();
     PyObject *pair = PyTuple_New(2);
-    PyTuple_SET_ITEM(pair, 0, res[0]);
-    PyTuple_SET_ITEM(pair, 1, res[1]);
+    for (int k = 0; k < 2 && pair; ++k) {
+        PyObject *o = output(a[6 + k], made[k]);
+        if (o) PyTuple_SET_ITEM(pair, k, o);
+        else Py_CLEAR(pair);
+    }
     return pair;
 }
 
@@ -246,18 +255,22 @@ PyObject *decode(PyObject *, PyObject *const *a, Py_ssize_t n)
     }
     const Tensor *given = nullptr;
     if (a[9] != Py_None && !(given = gpu_tensor(a[9]))) CSR_PUNT();
-    const size_t need = api.decode_workspace(&e);
-    Workspace ws;
-    if (need == kInvalid || !ws.take(a[11], need)) CSR_PUNT();
+    const Tensor *workspace = nullptr;
+    if (a[11] != Py_None && !(workspace = gpu_tensor(a[11]))) CSR_PUNT();
     Tensor made;
-    if (!given) made = fresh(q.sizes(), ot, q);
-    void *out = given ? given->data_ptr() : made.data_ptr();
-    const csr_status st = api.decode(&e, q.data_ptr(), DK.data_ptr(), iK.data_ptr(), cK.data_ptr(), DV.data_ptr(), iV.data_ptr(),
-                                     cV.data_ptr(), lens, out, ws.ptr, ws.bytes, stream());
+    csr_status st = CSR_ERR_WORKSPACE;
+    {
+        Unlocked unlocked;
+        const size_t need = api.decode_workspace(&e);
+        if (need != kInvalid) {
+            const Workspace ws(workspace, need);
+            if (!given) made = fresh(q.sizes(), ot, q);
+            st = api.decode(&e, q.data_ptr(), DK.data_ptr(), iK.data_ptr(), cK.data_ptr(), DV.data_ptr(), iV.data_ptr(), cV.data_ptr(),
+                            lens, given ? given->data_ptr() : made.data_ptr(), ws.ptr, ws.bytes, stream());
+        }
+    }
     if (st != CSR_OK) CSR_PUNT();
-    if (!given) return THPVariable_Wrap(std::move(made));
-    Py_INCREF(a[9]);
-    return a[9];
+    return output(a[9], made);
 }
 
 // (D, idx, coef, out, out_dtype) -> out
@@ -283,7 +296,10 @@ PyObject *reconstruct(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!given || given->sizes() != shape || given->scalar_type() != ot || given->stride(2) != 1) CSR_PUNT();
     }
     Tensor made;
-    if (!given) made = fresh(shape, ot, *D);
+    if (!given) {
+        Unlocked unlocked;
+        made = fresh(shape, ot, *D);
+    }
     const Tensor &o = given ? *given : made;
     csr_reconstruct_desc e{};
     e.H = (int32_t)H; e.T = T; e.d = (int32_t)d; e.N = (int32_t)D->size(-2); e.s = (int32_t)idx->size(-1); e.s_n = (int32_t)sn;
@@ -293,10 +309,13 @@ PyObject *reconstruct(PyObject *, PyObject *const *a, Py_ssize_t n)
     e.code_stride_h = H > 1 && T > 0 ? idx->stride(0) : 0;
     e.out_stride_h = H > 1 && T > 0 ? o.stride(0) : 0;
     e.out_stride_t = T > 1 ? o.stride(1) : 0;
-    if (api.reconstruct(&e, D->data_ptr(), idx->data_ptr(), coef->data_ptr(), o.data_ptr(), stream()) != CSR_OK) CSR_PUNT();
-    if (!given) return THPVariable_Wrap(std::move(made));
-    Py_INCREF(a[3]);
-    return a[3];
+    csr_status st;
+    {
+        Unlocked unlocked;
+        st = api.reconstruct(&e, D->data_ptr(), idx->data_ptr(), coef->data_ptr(), o.data_ptr(), stream());
+    }
+    if (st != CSR_OK) CSR_PUNT();
+    return output(a[3], made);
 }
 
 // C++ exceptions of PyTorch (an allocation that fails) must not cross into the interpreter: the Python path meets the

@@ -103,3 +103,26 @@ def test_a_workspace_too_small_for_this_encoder_keeps_the_other_one(dtype):
     one = csr.csr_encode(X, D, s, workspace=torch.empty(small, dtype=torch.uint8, device="cuda"))
     two = csr.csr_encode(X, D, s)
     assert torch.equal(one[0], two[0]) and torch.equal(one[1], two[1])
+
+
+def test_an_output_that_does_not_fit_leaves_nothing_behind():
+    # the atom numbers fit the device memory that is left, the coefficients do not: the call fails and gives the first back
+    H, T, s = 1, 1 << 20, 32
+    X = torch.zeros(H, T, 128, dtype=torch.float16, device="cuda")
+    D = torch.ones(H, 32, 128, dtype=torch.float16, device="cuda")
+    ws = torch.empty(1 << 20, dtype=torch.uint8, device="cuda")
+    torch.cuda.empty_cache()
+    room = torch.cuda.memory_reserved() + (96 << 20)            # idx takes 64 MB, coef 128 MB
+    torch.cuda.set_per_process_memory_fraction(room / torch.cuda.mem_get_info()[1])
+    try:
+        before = torch.cuda.memory_allocated()
+        for _ in range(2):
+            try:
+                csr.csr_encode(X, D, s, coef_dtype=torch.float32, workspace=ws)
+                pytest.fail("the limit has no effect")
+            except torch.OutOfMemoryError:
+                pass
+        assert torch.cuda.memory_allocated() == before
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+        torch.cuda.empty_cache()
