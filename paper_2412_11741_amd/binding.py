@@ -6,11 +6,13 @@ missing, or a tensor is not on the GPU, the call raises.
 
 csr_encode, csr_decode_attn and csr_reconstruct first hand their arguments to the compiled marshalling of
 csrc/torch_binding (1 - 2 us of host time a call; in ctypes it is about 25 us, as long as the small shapes take on the
-GPU).  It returns None for anything it does not take; the ctypes path below then runs, and says what is wrong.
+GPU).  It returns None for anything it does not take; the ctypes path below then runs, and says what is wrong.  Where the
+compiled part is missing or does not fit the interpreter and its PyTorch, every call takes the ctypes path (with a warning).
 """
 import ctypes
 import importlib.util
 import os
+import warnings
 
 import torch  # must precede loading the library: it brings the HIP runtime the library binds to
 
@@ -106,20 +108,28 @@ def lib():
     return _lib
 
 
+class _CtypesOnly:
+    """Stands in for the compiled marshalling where it cannot be loaded: takes no call."""
+    encode = decode = reconstruct = staticmethod(lambda *_: None)
+
+
 _native = None
 
 
 def _load_native():
-    """The compiled marshalling, bound to the loaded library's entry points; raises if it has not been built."""
+    """The compiled marshalling, bound to the loaded library's entry points."""
     global _native
     L = lib()
-    if not os.path.exists(NATIVE_PATH):
-        raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2412_11741_amd.build`")
-    spec = importlib.util.spec_from_file_location("_csr_torch", NATIVE_PATH)
-    module = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(module)
-    module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
-                  (L.csr_encode_workspace_bytes, L.csr_encode, L.csr_decode_workspace_bytes, L.csr_decode_attn, L.csr_reconstruct)))
+    try:
+        spec = importlib.util.spec_from_file_location("_csr_torch", NATIVE_PATH)
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        module.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                      (L.csr_encode_workspace_bytes, L.csr_encode, L.csr_decode_workspace_bytes, L.csr_decode_attn, L.csr_reconstruct)))
+    except ImportError as e:
+        warnings.warn(f"{NATIVE_PATH} cannot be loaded ({e}): calls go through ctypes, about 25 us of host time each; build it "
+                      "with `python -m paper_2412_11741_amd.build`", RuntimeWarning, stacklevel=3)
+        module = _CtypesOnly
     _native = module
     return module
 

@@ -296,3 +296,17 @@ def test_the_header_is_plain_c99():
     r = subprocess.run(["gcc", "-std=c99", "-Wall", "-Wextra", "-pedantic", "-Werror", "-fsyntax-only", "-I",
                         os.path.join(root, "include"), "-x", "c", "-"], input=prog, text=True, capture_output=True)
     assert r.returncode == 0, r.stderr
+
+
+@pytest.mark.parametrize("what", ["missing", "of another interpreter"])
+def test_without_the_compiled_marshalling_calls_go_through_ctypes(what, tmp_path, monkeypatch):
+    torch = pytest.importorskip("torch")
+    from paper_2412_11741_amd import binding
+    path = tmp_path / "_csr_torch.so"
+    if what != "missing":
+        path.write_bytes(b"not a shared object of this interpreter")
+    monkeypatch.setattr(binding, "NATIVE_PATH", str(path))
+    monkeypatch.setattr(binding, "_native", None)
+    with pytest.warns(RuntimeWarning, match="ctypes"):
+        with pytest.raises(ValueError, match="GPU tensor"):   # the ctypes path's own check: there is no CPU path
+            binding.csr_encode(torch.zeros(1, 2, 128), torch.zeros(1, 32, 128), 2)
