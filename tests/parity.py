@@ -18,6 +18,8 @@ Encode (per vector, walking the iterations in order):
     must be that projection within coef_tol.
 Decode: relative L2 error per (sequence, query head).
 """
+import os
+import re
 from dataclasses import dataclass, field
 
 import numpy as np
@@ -151,3 +153,12 @@ def assert_decode_close(out_c, out_o, tol, what=""):
     assert rel.size == 0 or rel.max() <= tol, f"{what}: relative L2 error {rel.max():.3e} above {tol:.1e}"
     assert mx <= tol, f"{what}: largest element error {mx:.3e} of the vector's peak, above {tol:.1e}"
     return rel, mx
+
+
+def decode_form(B, Hkv, T, pairs, f32=False):
+    """Which form of csr_decode_attn a shape of the two plain type sets takes: "short" (decode_direct.hip, every token rebuilt)
+    up to the number of gathered rows its source names, else "table" (the streaming kernels).  A test that is about one of the
+    forms asserts it, so that a change of the limit does not take it to the other one unnoticed."""
+    src = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2412_11741_amd", "csrc", "decode_direct.hip")
+    a, b = re.search(r"constexpr int64_t kMostGathers = (\d+) \* (\d+);", open(src).read()).groups()
+    return "short" if B * Hkv * T * pairs * (2 if f32 else 1) <= int(a) * int(b) else "table"
