@@ -214,7 +214,10 @@ __device__ __forceinline__ float from_fixed(unsigned long long v)
 template <typename TI, typename TC, int NP> struct CodeVec {
     static_assert(NP == 0 || (sizeof(TI) == sizeof(TC) && NP * sizeof(TI) % 4 == 0), "whole 32-bit words, as many of each");
     static constexpr int W = NP > 0 ? NP * (int)sizeof(TI) / 4 : 1;   // 32-bit words of the indices and of the coefficients
-    uint32_t i[W], c[W];
+    // Held and requested as 16-byte vectors, indices and coefficients in turn (word by word, all indices first, the same
+    // requests take 0.5 % longer: 4 x 32 heads x 32768 tokens, 16 pairs on 8192 atoms 135.7 against 135.2 us)
+    static constexpr bool kQuads = W % 4 == 0 && sizeof(TI) == 2;
+    typename std::conditional<kQuads, uint4, uint32_t>::type i[kQuads ? W / 4 : W], c[kQuads ? W / 4 : W];
 };
 // Steps whose codes are requested ahead, as far as the registers go without spilling: 8 words with one query head per
 // workgroup (what bounds that kernel is the number of bytes in flight per CU), else 4, at least one step.
@@ -231,20 +234,21 @@ template <int NP> constexpr int pair_block() { return NP % 8 == 0 ? 8 : NP; }
 template <int GB, int NP> constexpr int pair_piece() { return GB > 2 && NP > 8 ? 8 : NP; }
 
 // The code streams of a thread's tokens, walked round by round: two workgroup-uniform base addresses (the codes of the
-// chunk's first token) and one 32-bit offset per thread, in bytes.  The offset passes
+// chunk's first token) and one 32-bit offset per thread, in bytes or 16-byte vectors.  The offset passes
 // through an empty asm statement at every step, so that the compiler cannot work out all rounds' addresses ahead of
 // time (they would occupy registers from the start of the loop).
 template <typename TI, typename TC, int NP, int PIECE, int THREADS> struct CodeWalk {
+    static constexpr uint32_t kUnit = CodeVec<TI, TC, PIECE>::kQuads ? 16 : 1;   // bytes the offset counts in
     const unsigned char *ib, *cb;   // uniform
     uint32_t off;                   // the piece of this thread's token at which the walk stands
     __device__ __forceinline__ CodeWalk(const TI *idx, const TC *coef, int64_t first_token, int owner_off)
         : ib(reinterpret_cast<const unsigned char *>(idx + first_token * NP)),
-          cb(reinterpret_cast<const unsigned char *>(coef + first_token * NP)), off((uint32_t)owner_off * (NP * sizeof(TI))) {}
+          cb(reinterpret_cast<const unsigned char *>(coef + first_token * NP)), off((uint32_t)owner_off * (NP * (uint32_t)sizeof(TI) / kUnit)) {}
     // `step`: the step at which the walk stands
     __device__ __forceinline__ void next(int step)
     {
         constexpr int P = PIECE > 0 ? NP / PIECE : 1;
-        off += (step % P == P - 1 ? THREADS * NP - (P - 1) * PIECE : PIECE) * (uint32_t)sizeof(TI);
+        off += (step % P == P - 1 ? THREADS * NP - (P - 1) * PIECE : PIECE) * (uint32_t)sizeof(TI) / kUnit;
         asm volatile("" : "+v"(off));
     }
 };
@@ -279,8 +283,16 @@ template <typename TI, typename TC, int NP, int PIECE, int THREADS>
 __device__ __forceinline__ void fetch_codes(CodeVec<TI, TC, PIECE> &r, const CodeWalk<TI, TC, NP, PIECE, THREADS> &w, bool have)
 {
     const uint32_t o = have ? w.off : 0u;
-    load_words(w.ib + o, r.i);
-    load_words(w.cb + o, r.c);
+    if constexpr (CodeVec<TI, TC, PIECE>::kQuads) {
+#pragma unroll
+        for (int v = 0; v < CodeVec<TI, TC, PIECE>::W / 4; ++v) {
+            r.i[v] = reinterpret_cast<const uint4 *>(w.ib)[o + v];
+            r.c[v] = reinterpret_cast<const uint4 *>(w.cb)[o + v];
+        }
+    } else {
+        load_words(w.ib + o, r.i);
+        load_words(w.cb + o, r.c);
+    }
 }
 // The codes of the current step must have arrived BEFORE a later round's request is issued: the empty asm
 // statements make the compiler place the wait for them here, where only older requests are outstanding, instead of
@@ -289,11 +301,11 @@ template <typename TI, typename TC, int NP>
 __device__ __forceinline__ void await_codes(CodeVec<TI, TC, NP> &cur)
 {
     constexpr int W = CodeVec<TI, TC, NP>::W;
-    if constexpr (W % 4 == 0) {   // a request at a time: the wait for the coefficients then stands behind the use of the indices
+    if constexpr (CodeVec<TI, TC, NP>::kQuads) {   // a request at a time
 #pragma unroll
-        for (int k = 0; k < W; k += 4) {
-            asm volatile("" : "+v"(cur.i[k]), "+v"(cur.i[k + 1]), "+v"(cur.i[k + 2]), "+v"(cur.i[k + 3]));
-            asm volatile("" : "+v"(cur.c[k]), "+v"(cur.c[k + 1]), "+v"(cur.c[k + 2]), "+v"(cur.c[k + 3]));
+        for (int v = 0; v < W / 4; ++v) {
+            asm volatile("" : "+v"(cur.i[v].x), "+v"(cur.i[v].y), "+v"(cur.i[v].z), "+v"(cur.i[v].w));
+            asm volatile("" : "+v"(cur.c[v].x), "+v"(cur.c[v].y), "+v"(cur.c[v].z), "+v"(cur.c[v].w));
         }
     } else {
 #pragma unroll
@@ -304,7 +316,12 @@ __device__ __forceinline__ void await_codes(CodeVec<TI, TC, NP> &cur)
 template <typename TI, typename TC, int NP, int B>
 __device__ __forceinline__ void unpack_codes(const CodeVec<TI, TC, NP> &r, int j0, int (&id)[B], float (&cf)[B])
 {
-    if constexpr (sizeof(TI) == 2) {
+    if constexpr (CodeVec<TI, TC, NP>::kQuads) {
+        const uint4 &ri = r.i[j0 / 8], &rc = r.c[j0 / 8];
+        id[0] = ri.x & 0xffff; id[1] = ri.x >> 16; id[2] = ri.y & 0xffff; id[3] = ri.y >> 16;
+        id[4] = ri.z & 0xffff; id[5] = ri.z >> 16; id[6] = ri.w & 0xffff; id[7] = ri.w >> 16;
+        load8_raw(rc, cf);
+    } else if constexpr (sizeof(TI) == 2) {
 #pragma unroll
         for (int j = 0; j < B; j += 2) {
             const uint32_t wi = r.i[(j0 + j) / 2], wc = r.c[(j0 + j) / 2];
@@ -387,7 +404,7 @@ __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red
     if constexpr (NP > 0) {
         CodeWalk<TI, TC, NP, PIECE, THREADS> w0(idxV, coefV, code_row + t0, owner_off);
         prime(w0);
-        if constexpr (STEPS > 1) load_words(w0.cb + (n_mine > 0 && tok0 < t_end ? w0.off : 0u), other);
+        if constexpr (STEPS > 1) load_words(w0.cb + (n_mine > 0 && tok0 < t_end ? w0.off * w0.kUnit : 0u), other);
     }
 #pragma unroll
     for (int g = 0; g < GB; ++g) {
