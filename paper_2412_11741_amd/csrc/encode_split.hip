@@ -18,10 +18,10 @@
 //            arithmetic, so the copies never diverge; slice 0 stores the pair
 //
 // The workgroups need not run at the same time: one that starts late finds the others' words and catches up, and one that
-// waits in vain for kPatience (its partners hold no CU, because other work does) goes on alone: the wave that waited computes
-// the other slices' candidates of its vectors itself, and from the next iteration on all waves of the workgroup sweep the
-// other slices, too, from device memory.  The arithmetic is the same, so every wait ends and the result does not depend on
-// it; a call waits in vain once, not in every iteration.  CSR_FLAG_NO_WAIT goes that way from the start.  The slots
+// waits in vain for kPatience (its partners hold no CU, because other work does) goes on alone: the wave that waited sweeps the
+// whole dictionary for its vectors, from device memory, and from the next iteration on all waves of the workgroup do.  The
+// arithmetic is the same, so every wait ends and the result does not depend on it; a call waits in vain once, not in every
+// iteration.  CSR_FLAG_NO_WAIT goes that way from the start.  The slots
 // are cleared by a launch of their own before (a workspace's contents are undefined); a slot is written once per call.
 //
 // Bound: reading the dictionaries once, then a dependent chain per iteration - hi and lo from LDS, 16 dependent matrix
@@ -106,8 +106,7 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
     unsigned char *hi_s = res + m_pad * DC * 4;      // [m_pad][DC] fp16: hi, and behind it lo
     unsigned char *lo_s = hi_s + m_pad * DC * 2;
     unsigned long long *red = reinterpret_cast<unsigned long long *>(lo_s + m_pad * DC * 2);      // [kWaves][m_pad]
-    unsigned long long *red_other = red + kWaves * m_pad;   // the same of the other slices' tiles, once the workgroup is alone
-    SplitState *state = reinterpret_cast<SplitState *>(red_other + kWaves * m_pad);               // [M]
+    SplitState *state = reinterpret_cast<SplitState *>(red + kWaves * m_pad);                     // [M]
     __shared__ int alone_s;                    // the partners have been waited for in vain
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -187,10 +186,9 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
     }
     __syncthreads();
 
-    // The best candidate of vectors m0 .. m0 + 31 as a packed word with `tag` (lanes col of either half): `own`, over this
-    // wave's tiles of the workgroup's slice, the first ones in registers; else over the tiles first, first + step .. of the
-    // other slices.
-    auto sweep = [&](int m0, int first, int step, bool own, int tag) {
+    // The best candidate of vectors m0 .. m0 + 31 over the tiles first, first + step .. below last, as a packed word with
+    // `tag` (lanes col of either half); `own`: this wave's tiles of the workgroup's slice, the first ones in registers.
+    auto sweep = [&](int m0, int first, int last, int step, bool own, int tag) {
         half8 hi[kFrags], lo[kFrags];
         const int mine = min(m0 + col, p.M - 1);   // columns past the last vector repeat it: one LDS address for them all
 #pragma unroll
@@ -238,10 +236,9 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
         if (own) {
 #pragma unroll
             for (int q = 0; q < HELD; ++q)
-                if (first + q * kWaves < t_end) tile_best(first + q * kWaves, held[q]);
+                if (first + q * kWaves < last) tile_best(first + q * kWaves, held[q]);
         }
-        for (int tile = first + (own ? HELD * kWaves : 0); tile < (own ? t_end : tiles); tile += step) {
-            if (!own && tile >= t_begin && tile < t_end) continue;
+        for (int tile = first + (own ? HELD * kWaves : 0); tile < last; tile += step) {
             uint4 a[kFrags];
             load_tile(tile, a);
             tile_best(tile, a);
@@ -253,19 +250,15 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
 #pragma unroll 1
     for (int g = 0; g < p.s; ++g) {
         const int tag = g + 1;
-        const bool alone = p.k > 1 && __builtin_amdgcn_readfirstlane(alone_s) != 0;   // (set behind this iteration's barrier at the earliest)
+        // alone: the whole dictionary (alone_s is set behind this iteration's barrier at the earliest)
+        const bool alone = __builtin_amdgcn_readfirstlane(alone_s) != 0;
         for (int m0 = 0; m0 < p.M; m0 += 32) {
-            const unsigned long long w = sweep(m0, t_begin + wave, kWaves, true, tag);
+            const unsigned long long w = sweep(m0, alone ? wave : t_begin + wave, alone ? tiles : t_end, kWaves, !alone, tag);
             if (hf == 0) red[wave * m_pad + m0 + col] = w;
         }
-        if (alone) {
-            for (int m0 = 0; m0 < p.M; m0 += 32) {
-                const unsigned long long w = sweep(m0, wave, kWaves, false, tag);
-                if (hf == 0) red_other[wave * m_pad + m0 + col] = w;
-            }
-        }
         __syncthreads();
-        // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published:
+        // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published (alone: the
+        // dictionary's, which leads the others to the same pick):
         unsigned long long *slot = p.slots + (int64_t)g * p.V * p.k;
         for (int v = team; v < p.M; v += kTeams) {
             unsigned long long w = red[(sub & (kWaves - 1)) * m_pad + v];
@@ -273,11 +266,6 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
             if (sub == 0) {
                 red[v] = w;
                 if (p.k > 1) __hip_atomic_store(slot + state[v].vid * p.k + sl, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            if (alone) {
-                unsigned long long o = red_other[(sub & (kWaves - 1)) * m_pad + v];
-                o = row_reduce<kWaves>(o, OpMaxU64());
-                if (sub == 0) red[v] = o > w ? o : w;
             }
         }
         wave_lds_fence();
@@ -317,11 +305,11 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
                         if (!__ballot(!ok) || vain || wall_clock64() - began > (uint64_t)p.patience) break;
                     }
                     if (__ballot(!ok)) {
-                        // partners that hold no CU: the other slices' candidates of this wave's vectors - they are of one
-                        // block of 32 - computed here; from the next iteration on the whole workgroup does
+                        // partners that hold no CU: the candidates of this wave's vectors - they are of one block of 32 -
+                        // over the whole dictionary, here; from the next iteration on the whole workgroup does that
                         vain = true;
                         if (lane == 0) alone_s = 1;
-                        const unsigned long long o = sweep(v0 & ~31, 0, 1, false, tag);
+                        const unsigned long long o = sweep(v0 & ~31, 0, tiles, 1, false, tag);
                         const unsigned long long theirs = __shfl(o, v & 31, 64);
                         w = theirs > w ? theirs : w;
                     }
@@ -405,7 +393,7 @@ SplitPlan plan_split(const EncodeArgs &a)
     const int per_wave = ((tiles + k - 1) / k + kWaves - 1) / kWaves;
     pl.held = per_wave <= 1 ? 1 : per_wave <= 2 ? 2 : 4;   // of 128 dimensions: 32, 64 or 128 registers
     const int m_pad = (pl.M + 31) & ~31;
-    pl.lds = (size_t)m_pad * a.d * 8 + 2 * (size_t)kWaves * m_pad * 8 + (size_t)pl.M * sizeof(SplitState);
+    pl.lds = (size_t)m_pad * a.d * 8 + (size_t)kWaves * m_pad * 8 + (size_t)pl.M * sizeof(SplitState);
     pl.total = r256((size_t)a.s * pl.V * k * sizeof(unsigned long long));
     return pl;
 }
@@ -420,7 +408,7 @@ hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitP
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_split_kernel<DC, HELD>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                159 * 1024);   // (plan_split: at most 147 KB; a word of static LDS besides)
+                                159 * 1024);   // (plan_split: at most 139 KB; a word of static LDS besides)
         if (e != hipSuccess) return e;
         attr_set[dev].store(true, std::memory_order_release);
     }
