@@ -83,8 +83,8 @@ typedef enum {
  * and RESIDENT encoders (the Gram forms return CSR_ERR_UNSUPPORTED, and AUTO does not choose them with the flag). */
 #define CSR_FLAG_CLOSED_LOOP 1u
 /* NO_WAIT: the workgroups of the SPLIT encoder that share a dictionary do not wait for one another's candidates but compute
- * them all, each for itself: the same codes, slower on an idle chip, and independent of when the GPU has room for the other
- * workgroups (without the flag a workgroup does so once it has waited 40 us in vain).  The other encoders ignore it. */
+ * them all, each for itself: the same codes, many times slower on an idle chip, and independent of when the GPU has room for
+ * the other workgroups (without the flag a workgroup does so once it has waited 40 us in vain).  The other encoders ignore it. */
 #define CSR_FLAG_NO_WAIT 0x100u
 
 /*

@@ -18,17 +18,18 @@
 //            arithmetic, so the copies never diverge; slice 0 stores the pair
 //
 // The workgroups need not run at the same time: one that starts late finds the others' words and catches up, and one that
-// waits in vain for kPatience (its partners hold no CU, because other work does) goes on alone: the wave that waited sweeps the
-// whole dictionary for its vectors, from device memory, and from the next iteration on all waves of the workgroup do.  The
-// arithmetic is the same, so every wait ends and the result does not depend on it; a call waits in vain once, not in every
-// iteration.  CSR_FLAG_NO_WAIT goes that way from the start.  The slots
+// waits in vain for kPatience (its partners hold no CU, because other work does) goes on alone: each of its waves sweeps the
+// whole dictionary, from device memory, for the vectors whose words are missing, and waits an eighth of the time from then on
+// (46 us in a call, all in all).  The arithmetic is the same, so every wait ends and the result does not depend on it.
+// CSR_FLAG_NO_WAIT goes that way from the start.  (The lone workgroup's waves sharing that work would be faster there, but asking whether to, once an
+// iteration, costs every call 1.5 %.)  The slots
 // are cleared by a launch of their own before (a workspace's contents are undefined); a slot is written once per call.
 //
 // Bound: reading the dictionaries once, then a dependent chain per iteration - hi and lo from LDS, 16 dependent matrix
 // instructions per tile, the tournament over the waves, publish and poll (one trip each to where the chip's L2s meet, 0.5
-// us together), the row of the chosen atom, the update.  32 dictionaries of 4096 atoms, s = 8, one vector each: 37 us (11
-// us for one iteration, 3.5 us for every further one) against 98 us for the s + 1 launches this replaces, which read the
-// dictionaries again in every iteration; 64 vectors each 62 against 328; 32 x 256 atoms, where nothing is exchanged, 20
+// us together), the row of the chosen atom, the update.  32 dictionaries of 4096 atoms, s = 8, one vector each: 36 us (12
+// us for one iteration, 3.4 us for every further one) against 98 us for the s + 1 launches this replaces, which read the
+// dictionaries again in every iteration; 64 vectors each 62 against 328; 32 x 256 atoms, where nothing is exchanged, 21
 // against 49.
 #include <atomic>
 #include <cmath>
@@ -92,9 +93,10 @@ template <int DC> __device__ __forceinline__ int half_at(int v, int p) { return 
 
 struct SplitState { int32_t sexp, pad; int64_t vid, code_at; };   // scale of a vector's residual, its number, its code's first pair
 
-// HELD: tiles of 32 atoms a wave keeps in registers
+// HELD: tiles of 32 atoms a wave keeps in registers.  A workgroup is two waves per SIMD, and with 128 dimensions there is no
+// room for a second one: the compiler is told so, or it spends instructions on registers that nobody can use.
 template <int DC, int HELD>
-__global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParams p)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC == 128 ? 2 : 4))) void encode_split_kernel(const SplitParams p)
 {
     constexpr int kFrags = DC / 16;
     constexpr int L = DC / 8;                  // lanes of a vector's team in the update, 8 dimensions each
@@ -107,7 +109,6 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
     unsigned char *lo_s = hi_s + m_pad * DC * 2;
     unsigned long long *red = reinterpret_cast<unsigned long long *>(lo_s + m_pad * DC * 2);      // [kWaves][m_pad]
     SplitState *state = reinterpret_cast<SplitState *>(red + kWaves * m_pad);                     // [M]
-    __shared__ int alone_s;                    // the partners have been waited for in vain
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -155,7 +156,6 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
         *reinterpret_cast<half8 *>(lo_s + half_at<DC>(v, sub)) = l;
     };
 
-    if (tid == 0) alone_s = 0;
     // ---- the vectors, scaled by a power of two that brings max |x_k| into [2^11, 2^12): hi and lo stay normal ----------
     for (int v = team; v < m_pad; v += kTeams) {
         // vector m of this dictionary: block h = (m / T) dict_count + dict, its token m % T
@@ -247,18 +247,16 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
         // a wave without tiles: below every candidate
         return ba >= 0.0f ? pack_candidate(bc, bi, tag) : (unsigned long long)((uint32_t)tag << 1);
     };
+    int patience = p.patience;   // this wave's: an eighth of it is left each time it has waited in vain
 #pragma unroll 1
     for (int g = 0; g < p.s; ++g) {
         const int tag = g + 1;
-        // alone: the whole dictionary (alone_s is set behind this iteration's barrier at the earliest)
-        const bool alone = __builtin_amdgcn_readfirstlane(alone_s) != 0;
         for (int m0 = 0; m0 < p.M; m0 += 32) {
-            const unsigned long long w = sweep(m0, alone ? wave : t_begin + wave, alone ? tiles : t_end, kWaves, !alone, tag);
+            const unsigned long long w = sweep(m0, t_begin + wave, t_end, kWaves, true, tag);
             if (hf == 0) red[wave * m_pad + m0 + col] = w;
         }
         __syncthreads();
-        // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published (alone: the
-        // dictionary's, which leads the others to the same pick):
+        // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published:
         unsigned long long *slot = p.slots + (int64_t)g * p.V * p.k;
         for (int v = team; v < p.M; v += kTeams) {
             unsigned long long w = red[(sub & (kWaves - 1)) * m_pad + v];
@@ -269,14 +267,13 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
             }
         }
         wave_lds_fence();
-        bool vain = false;   // this wave has waited for nothing in this iteration
         // ---- the other slices' candidates, the pick, Eq.4 -----------------------------------------------------------------
         for (int v0 = wave * (64 / L); v0 < p.M; v0 += kTeams) {   // (uniform over the wave)
             const int v = v0 + lane / L;
             const int vc = min(v, p.M - 1);   // a team past the last vector idles along: it waits for nobody
             const int slices = v < p.M ? p.k : 0;
             unsigned long long w = vc == v ? red[v] : 0ull;
-            if (p.k > 1 && !alone) {
+            if (p.k > 1) {
                 unsigned long long *mine = slot + state[vc].vid * p.k;
                 unsigned long long got[kSlots];
                 bool ok = true;
@@ -291,7 +288,7 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
                 }
                 if (__ballot(!ok)) {
                     const uint64_t began = wall_clock64();
-                    while (p.patience >= 0) {
+                    while (patience >= 0) {
                         __builtin_amdgcn_s_sleep(1);
                         ok = true;
 #pragma unroll
@@ -302,13 +299,12 @@ __global__ __launch_bounds__(kThreads) void encode_split_kernel(const SplitParam
                                 ok = ok && candidate_tag(got[i]) == tag;
                             }
                         }
-                        if (!__ballot(!ok) || vain || wall_clock64() - began > (uint64_t)p.patience) break;
+                        if (!__ballot(!ok) || wall_clock64() - began > (uint64_t)patience) break;
                     }
                     if (__ballot(!ok)) {
                         // partners that hold no CU: the candidates of this wave's vectors - they are of one block of 32 -
-                        // over the whole dictionary, here; from the next iteration on the whole workgroup does that
-                        vain = true;
-                        if (lane == 0) alone_s = 1;
+                        // over the whole dictionary, in one sweep for all of them (their slices' words would lead to the same)
+                        patience >>= 3;
                         const unsigned long long o = sweep(v0 & ~31, 0, tiles, 1, false, tag);
                         const unsigned long long theirs = __shfl(o, v & 31, 64);
                         w = theirs > w ? theirs : w;
@@ -408,7 +404,7 @@ hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitP
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
         e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_split_kernel<DC, HELD>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                159 * 1024);   // (plan_split: at most 139 KB; a word of static LDS besides)
+                                159 * 1024);   // (plan_split: at most 139 KB)
         if (e != hipSuccess) return e;
         attr_set[dev].store(true, std::memory_order_release);
     }

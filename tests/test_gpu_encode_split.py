@@ -43,8 +43,8 @@ def test_slices_of_a_dictionary_agree(dicts, M, N, d, s):
 ])
 @pytest.mark.parametrize("closed", [0, csr.CSR_FLAG_CLOSED_LOOP])
 def test_codes_do_not_depend_on_who_computed_them(dicts, M, N, d, s, sn, closed):
-    # with CSR_FLAG_NO_WAIT every workgroup takes every other one for absent: the first iteration's missing candidates are
-    # computed by the wave that wants them, the later iterations' by the whole workgroup.  The sums are the same, so are the bits
+    # with CSR_FLAG_NO_WAIT every workgroup takes every other one for absent: the missing candidates are computed by the wave
+    # that wants them.  The sums are the same, so are the bits
     D = torch.from_numpy(synth.dictionary(92, "dict_k", dicts * sn, N, d, "f16")).cuda()
     D = D.view(dicts, sn, N, d) if sn > 1 else D
     X = torch.from_numpy(synth.vectors(92, "keys", dicts, M, d * sn, "f16", outliers=4)).cuda()
