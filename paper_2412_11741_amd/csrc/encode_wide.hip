@@ -34,8 +34,9 @@
 //   kRes    encode_resident.hip: fp32 residual; comparisons as kMfma on its hi and lo, coefficients in four chains per half
 // The chains of a sum are spread over lanes (each chain keeps its order; the tree that joins them is the same).
 //
-// Bound by the L1's 64 bytes per cycle of dictionary per CU (every workgroup reads the dictionary once per iteration)
-// and by the select / update chain.  The rules in csr_api.hip say what it replaces, with figures.
+// Bound by the chain of an iteration - sweep, lists, select, update - which two waves per SIMD hide half of: three prompts of
+// 1571 tokens on 8 KV heads, 4096 atoms, keep the matrix cores of a CU that has work busy 44 % of the time and its L1, which
+// delivers the dictionary once per workgroup and iteration, at 0.58 of a 64-byte line per cycle.  The rules in csr_api.hip say what it replaces, with figures.
 #include "csr_internal.h"
 #include "encode_common.h"
 #include "lane_ops.h"

@@ -295,7 +295,8 @@ def test_value_coefficients_that_grow_far_beyond_the_sampled_ones(dtype):
 def test_an_outlier_coefficient_in_the_sample_and_a_diffuse_tail():
     # One sampled value coefficient is 2^14 times the typical one while nearly all of the attention mass sits on a
     # flat tail of tokens far below the maximum score: the adds of the tail are tiny against a unit fitted to the
-    # outlier, which the resolution check of the 32-bit scatter has to catch.
+    # outlier, which the resolution check of the 32-bit scatter has to catch.  (This context counts as a short one, which has
+    # no scatter; test_gpu_decode_forms.py asks the same of the streaming kernel.)
     B, Hq, Hkv, T, N, s = 1, 1, 1, 16384, 4096, 8
     q, DK, idxK, coefK, DV, idxV, coefV = _case(26, B, Hq, Hkv, T, N, s, s, dtype="f32", itype="i32")
     coefK[...] = 0
@@ -422,9 +423,10 @@ def test_chunked_values_full_layer_all_heads():
 
 @pytest.mark.parametrize("rope_base,gram", [(0.0, False), (10000.0, False), (0.0, True)])
 def test_a_decoding_step_can_be_captured_in_a_graph_and_replayed(rope_base, gram):
-    # (rope_base set: the keys count as coded before the rotary embedding and the other streaming kernel runs;
+    # (rope_base set: the keys count as coded before the rotary embedding;
     # gram: the append takes the dictionaries' Gram matrices - its two launches instead of the split encoder's)
-    # append (split encoder: s + 1 launches per call) + attention (4 launches) recorded once, replayed on new data;
+    # append (split encoder: one launch behind the one that clears its slots) + attention (a short context: two launches; the
+    # streaming kernels' capture is in test_gpu_decode_forms.py) recorded once, replayed on new data;
     # every replay must equal the eager result of the same inputs bit for bit (nothing allocates, nothing is cleared
     # by a memset node, every kernel argument is fixed at capture time)
     B, Hkv, G, T_max, N, d, s, pos = 2, 2, 2, 256, 512, 128, 8, 200
