@@ -31,8 +31,13 @@ constexpr int rope_threads(int GB) { return GB >= 2 ? 512 : 1024; }  // tokens p
 constexpr int rope_rounds(int GB) { return GB == 2 ? 16 : 8; }
 // the rotary-key kernel keeps the key dictionary of its KV head in LDS when it fits (at most 512 atoms of 128 halves)
 constexpr bool rope_dictionary_fits_lds(int N) { return (size_t)N * 256 <= 128 * 1024; }
-constexpr size_t kRopeTableBytes = 8 * 32 * 4 + 8 * 4 * 8 * 4 + 64 * 8;  // rotation constants, a group's query pairs, theta
+// 32-bit words of a lane class's rotation constants: 5 x 16, and 4 that spread the 8 classes' 16-byte reads over the banks
+constexpr int kRopeTurn = 84;
+constexpr size_t kRopeTableBytes = 8 * kRopeTurn * 4 + 8 * 4 * 8 * 4 + 64 * 8;  // rotation constants, a group's query pairs, theta
+// What of them counts against the LDS budget below: the largest dictionary that is taken does not depend on the tables' layout.
+constexpr size_t kRopeTableCounted = 2560;
 constexpr size_t kLdsBudget = 150 * 1024;
+static_assert(kRopeTableBytes >= kRopeTableCounted && kLdsBudget + kRopeTableBytes - kRopeTableCounted <= 160 * 1024, "within a CU's LDS");
 // Reduction scratch of the streaming kernels, in 4-byte words behind the table / histogram (WAVES <= 16, GB <= 4):
 constexpr int kRedMax = 0;     // [WAVES][GB]  wave maxima of the scores
 constexpr int kRedCm = 64;     // [WAVES]      wave maxima of the sampled |value coefficients|

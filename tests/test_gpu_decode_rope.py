@@ -82,6 +82,21 @@ def test_rotary_keys_shapes(B, Hq, Hkv, T, N, sK, sV, snV, layout, pos0):
     _check(out, ref, f"B{B} Hq{Hq} Hkv{Hkv} T{T} N{N} s{sK}/{sV} snV{snV} layout{layout} pos0 {pos0}")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,N,sK,sV,snV,layout,pos0,lens", [
+    (1, 4, 4, 8193, 256, 8, 8, 1, 0, 0, [8193]),         # one token past eight full rounds: steps of one token in a last chunk
+    (2, 4, 4, 9000, 256, 4, 4, 1, 0, 7, [9000, 65]),     # whole codes of 4 key pairs; a wave of one token
+    (1, 8, 2, 32800, 512, 4, 4, 1, 1, 0, [32767]),       # the same for a group of 4; a length below the buffer's
+    (1, 4, 2, 16500, 384, 16, 4, 1, 0, 0, [16421]),      # a group of 2, two blocks of 8 key pairs, last round ragged inside a step
+    (2, 8, 8, 2100, 256, 12, 8, 1, 1, 100, [2100, 1]),   # three blocks of 4 key pairs, a single token
+])
+def test_rotary_keys_streamed_at_the_edges_of_rounds_and_steps(B, Hq, Hkv, T, N, sK, sV, snV, layout, pos0, lens):
+    assert B * Hkv * T * (sK + snV * sV) > 512 * 1024   # beyond the contexts whose keys are rebuilt on the fly
+    args = _case(32, B, Hq, Hkv, T, N, sK, sV, snV)
+    out = _run(args, 10000.0, layout, pos0, seq_lens=lens)
+    ref = oracle.decode_attn_rope(*args, 10000.0, layout, pos0, seq_lens=np.asarray(lens, dtype=np.int32))
+    _check(out, ref, f"streamed: B{B} Hq{Hq} Hkv{Hkv} T{T} N{N} s{sK}/{sV} layout{layout} pos0 {pos0} lens {lens}")
+
+
 def test_rotary_keys_sequence_lengths_base_and_scale():
     B, T = 5, 2600
     args = _case(31, B, 4, 2, T, 256, 8, 8)
