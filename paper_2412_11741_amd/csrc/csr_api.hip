@@ -34,24 +34,35 @@ bool valid_itype(int32_t v) { return v == CSR_I32 || v == CSR_I16; }
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 size_t round256(size_t v) { return (v + 255) & ~size_t(255); }
 
-// Whether CSR_ENCODE_AUTO runs the wide encoder in place of `algo`, the one the shape would get otherwise (whose codes it
-// reproduces bit for bit).  Measured on 8 to 64 dictionaries (us, s = 8):
+// Of the vectors of every dictionary, how many CSR_ENCODE_AUTO gives to `algo`, the encoder that the shape would get
+// otherwise; the rest go to the wide encoder, which gives the same codes bit for bit.  Measured on 8 to 64 dictionaries (us, s = 8):
 //   fp32, or an N that is no multiple of 32: the alternative is the vector ALU (2 x 4096 fp32 vectors, N = 1024: 775
 //     against 57); a handful of vectors stays there, which needs no scratch
 //   dictionaries that fit the LDS: the resident encoder needs 512 vectors per CU to fill the chip (N = 256, 8 x 1600
 //     vectors: 133 against 60, 64 x 400: 125 against 98, 64 x 800: 133 against 183)
-//   the prefill encoder needs as many (N = 4096, 8 x 1600 vectors: 734 against 211, 8 x 9000: 918 against 747, 64 x 1600:
-//     1076 against 1126)
-bool wide_pays(const csr::EncodeArgs &a, int algo)
+//   the prefill encoder takes 512 vectors per CU and generation and a last generation costs nearly as much as a full one, however few
+//     workgroups it has (16 x 8192 vectors, N = 4096: 991, 16 x 10240: 1752; the generation alone with 16 x 2048 left to the
+//     wide encoder 1280): whole generations go to it and what remains to the wide encoder, or all to one of the two.
+int64_t auto_head(const csr::EncodeArgs &a, int algo)
 {
-    if (!csr::encode_wide_supported(a)) return false;
-    const int64_t M = (int64_t)(a.H / (a.dict_count ? a.dict_count : 1)) * a.T;   // vectors per dictionary
-    const int64_t all = M * a.dict_count * a.sn;
+    const int64_t M = a.m_end;   // vectors per dictionary
+    if (M == 0 || !csr::encode_wide_supported(a)) return M;
+    const int64_t dicts = (int64_t)a.dict_count * a.sn;
     switch (algo) {
-        case CSR_ENCODE_VALU: return M >= 32;
-        case CSR_ENCODE_RESIDENT: return all < 36 * 1000;
-        case CSR_ENCODE_MFMA: return a.d != 32 && all < 100 * 1000;
-        default: return false;
+        case CSR_ENCODE_VALU: return M >= 32 ? 0 : M;
+        case CSR_ENCODE_RESIDENT: return M * dicts < 36 * 1000 ? 0 : M;
+        case CSR_ENCODE_MFMA: {
+            if (a.d == 32) return M;
+            const float gen = csr::encode_mfma_generation_cost(a);
+            const int64_t per = csr::kMfmaWorkgroupVectors, groups = (M + per - 1) / per * dicts, full = groups / csr::kCus;
+            // a last, partial generation: 0.83 to 0.9 of a full one
+            const float own = gen * ((float)full + (groups % csr::kCus ? 0.87f : 0.0f)), wide = csr::encode_wide_cost(a, M);
+            const int64_t head = full * csr::kCus / dicts * per;   // what fills whole generations
+            const float both = head > 0 && head < M ? gen * (float)full + csr::encode_wide_cost(a, M - head) : own;
+            if (wide <= own && wide <= both) return 0;
+            return both < own ? head : M;
+        }
+        default: return M;
     }
 }
 
@@ -105,6 +116,7 @@ csr_status check_encode_desc(const csr_encode_desc *d, csr::EncodeArgs *args, in
     a.x_stride_t = st; a.x_stride_h = sh;
     a.dict_count = d->dict_count ? d->dict_count : d->H;
     a.code_stride_h = d->code_stride_h ? d->code_stride_h : code_block;
+    a.m_first = 0; a.m_end = a.dict_count ? (int64_t)(d->H / a.dict_count) * d->T : 0;
     a.f16 = d->x_dtype == CSR_F16;
     a.coef16 = d->coef_dtype == CSR_F16;
     a.idx16 = d->idx_dtype == CSR_I16;
@@ -161,7 +173,7 @@ size_t encode_workspace(const csr::EncodeArgs &a, int algo, bool automatic)
 {
     if (a.H == 0 || a.T == 0) return 0;
     const size_t own = own_workspace(a, algo);
-    if (!(automatic || algo == CSR_ENCODE_MFMA || algo == CSR_ENCODE_SPLIT) || !wide_pays(a, algo)) return own;
+    if (!(automatic || algo == CSR_ENCODE_MFMA || algo == CSR_ENCODE_SPLIT) || auto_head(a, algo) == a.m_end) return own;
     const size_t wide = csr::encode_wide_workspace_bytes(a);
     return own > wide ? own : wide;
 }
@@ -293,7 +305,10 @@ csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D,
     // The wide encoder gives the codes of the one it stands in for: a workspace that is too small for it (one sized for
     // more vectors, where the rule above takes the other encoder) is no reason to refuse the call.
     const size_t given = workspace && aligned(workspace, 256) ? workspace_bytes : 0;
-    if (desc->algo == CSR_ENCODE_AUTO && wide_pays(a, algo) && given >= csr::encode_wide_workspace_bytes(a)) algo = CSR_ENCODE_WIDE;
+    int64_t head = desc->algo == CSR_ENCODE_AUTO ? auto_head(a, algo) : a.m_end;
+    if (head < a.m_end && given < csr::encode_wide_workspace_bytes(a)) head = a.m_end;
+    if (head > 0 && head < a.m_end && given < own_workspace(a, algo)) head = 0;
+    if (head == 0 && a.m_end > 0) algo = CSR_ENCODE_WIDE;
     const size_t need = own_workspace(a, algo);
     if (given < need)
         return fail(CSR_ERR_WORKSPACE, "csr_encode: workspace of %zu bytes (256-byte aligned) required, got %zu", need, workspace ? workspace_bytes : (size_t)0);
@@ -303,6 +318,15 @@ csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D,
     a.res_norm2 = desc->res_norm2;
     a.workspace = workspace;
     a.stream = static_cast<hipStream_t>(hip_stream);
+    if (head > 0 && head < a.m_end) {   // one after the other on the stream: they share the scratch
+        csr::EncodeArgs rest = a;
+        rest.m_first = head;
+        a.m_end = head;
+        hipError_t e = csr::launch_encode_mfma(a);
+        if (e == hipSuccess) e = csr::launch_encode_wide(rest);
+        if (e != hipSuccess) return fail(CSR_ERR_DEVICE, "csr_encode: %s", hipGetErrorString(e));
+        return CSR_OK;
+    }
     const hipError_t e = algo == CSR_ENCODE_MFMA ? csr::launch_encode_mfma(a)
                          : algo == CSR_ENCODE_SPLIT ? csr::launch_encode_split(a)
                          : algo == CSR_ENCODE_RESIDENT ? csr::launch_encode_resident(a)

@@ -32,6 +32,7 @@ struct EncodeArgs {
     int64_t x_stride_h, x_stride_t;  // elements, already defaulted
     int32_t dict_count;              // block h uses dictionary h % dict_count (already defaulted to H)
     int64_t code_stride_h;           // elements between blocks' codes (already defaulted)
+    int64_t m_first, m_end;          // of the M = H / dict_count * T vectors of every dictionary, those this launch encodes
     bool f16;                        // X and D are fp16 (else fp32)
     bool coef16, idx16;
     bool closed_loop;                // Eq.4 subtracts the coefficient as it is stored (CSR_FLAG_CLOSED_LOOP)
@@ -48,10 +49,15 @@ hipError_t launch_encode_valu(const EncodeArgs &a);
 // matrix-core encoder with the atoms split over a workgroup's waves: fp32 or fp16, small launches; N up to 65536.
 bool encode_wide_supported(const EncodeArgs &a);
 size_t encode_wide_workspace_bytes(const EncodeArgs &a);
+// What `vectors` vectors of every dictionary cost, in units of one iteration-for-iteration pass of 4096 / d vectors per CU.
+float encode_wide_cost(const EncodeArgs &a, int64_t vectors);
 hipError_t launch_encode_wide(const EncodeArgs &a);
 
 // fp16 matrix-core encoder: chunks of 64 or 128 dimensions, fp16 inputs.
 bool encode_mfma_supported(const EncodeArgs &a);
+// What one full generation of its 512-vector workgroups (one per CU) costs, in the unit of encode_wide_cost.
+float encode_mfma_generation_cost(const EncodeArgs &a);
+constexpr int64_t kMfmaWorkgroupVectors = 512, kCus = 256;
 size_t encode_mfma_workspace_bytes(int32_t n_dicts, int64_t T, int32_t N, int32_t s);
 hipError_t launch_encode_mfma(const EncodeArgs &a);
 

@@ -34,9 +34,14 @@
 //   kRes    encode_resident.hip: fp32 residual; comparisons as kMfma on its hi and lo, coefficients in four chains per half
 // The chains of a sum are spread over lanes (each chain keeps its order; the tree that joins them is the same).
 //
-// Bound by the chain of an iteration - sweep, lists, select, update - which two waves per SIMD hide half of: three prompts of
-// 1571 tokens on 8 KV heads, 4096 atoms, keep the matrix cores of a CU that has work busy 44 % of the time and its L1, which
-// delivers the dictionary once per workgroup and iteration, at 0.58 of a 64-byte line per cycle.  The rules in csr_api.hip say what it replaces, with figures.
+// Bound by the sweep at the clock the chip allows the matrix cores under full load, and behind it by the select phase, in which
+// they stand still: three prompts of 1571 tokens on 8 KV heads, 4096 atoms, spend 250 of a call's 337 us in the sweeps (160
+// vectors a workgroup; 8 iterations of 31 us, 1.38 PFLOP/s) and 10 us an iteration in lists, select and update.  With 64
+// vectors a workgroup the same call made three generations and took 420 us.  Two vectors of a team selected together, so that
+// their chains overlap, is slower (356): the select phase is bound by its instructions.  The rules in csr_api.hip say what
+// this encoder replaces, with figures.
+#include <atomic>
+
 #include "csr_internal.h"
 #include "encode_common.h"
 #include "lane_ops.h"
@@ -114,7 +119,7 @@ struct WideParams {
     const float2 *bound;
     void *idx_out, *coef_out;
     float *res_norm2;
-    int64_t T, M, x_stride_h, x_stride_t, code_stride_h;
+    int64_t T, m_first, M, x_stride_h, x_stride_t, code_stride_h;
     int32_t N, s, sn, dict_count, tiles_per_h, n_groups, ntiles, slices, idx16, coef_mode;
     uint32_t code_mask;
 };
@@ -356,6 +361,18 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
     return __builtin_amdgcn_readfirstlane(bn);
 }
 
+// What a workgroup of P * 128 / DC blocks keeps in LDS: residuals | lists | state | HELD's bounds of the waves
+template <int DC, int W, int P> struct WideLds {
+    static constexpr int kTok = 32 * (P * 128 / DC);
+    static constexpr int kList = kTok * DC * 4, kState = kList + kTok * 2 * W * 16, kHeld = kState + kTok * (int)sizeof(VectorState);
+    static constexpr int kBytes = kHeld + W * 8;
+    static_assert(kBytes <= 160 * 1024, "a CU's LDS");
+};
+
+// Blocks whose fp16 operand a wave holds in registers for the whole sweep (the others are read from LDS for every tile): with
+// five or six of them 256 registers take three or two.
+template <int DC, int P> constexpr int blocks_held() { return P <= 4 ? P * 128 / DC : P == 5 ? 3 : 2; }
+
 // W waves; P * 128 / DC blocks of 32 vectors.  HELD: the dictionary's tiles - at most 16 / (DC / 16) a wave, 128 KB of
 // fp16 in all - are read once, from the dictionary itself, and stay in registers for all iterations: no prepared copy,
 // no scratch, no dictionary traffic in the sweeps.
@@ -372,12 +389,16 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
     constexpr int kLl = kLists > L ? kLists / L : 1;   // lists a lane of a team takes (with fewer lists than lanes some take none)
     static_assert(kTok % kTeams == 0, "whole passes");
     static_assert(MODE == kValu || DC >= 64, "the teams' exact dot products");
+    static_assert(P <= 4 || (MODE == kMfma && DC == 128), "operands from LDS: the residual's fp16 plane, whole vectors");
+    constexpr int kInRegs = blocks_held<DC, P>();
     using RES = Residuals<DC, MODE, kTok>;
-    __shared__ __attribute__((aligned(16))) unsigned char res_s[RES::kBytes];
-    __shared__ uint4 list_s[kTok][kLists];       // (tracked groups, best group: atom << 16 | place of the second << 2 | flags)
-    __shared__ VectorState state_s[kTok];
-    __shared__ float2 held_s[HELD ? W : 1];
-    const RES res{res_s};
+    using LDS = WideLds<DC, W, P>;
+    static_assert(RES::kBytes == LDS::kList, "layout");
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds_s[];
+    uint4(*list_s)[kLists] = reinterpret_cast<uint4(*)[kLists]>(lds_s + LDS::kList);   // (tracked groups, best group: atom << 16 | place of the second << 2 | flags)
+    VectorState *state_s = reinterpret_cast<VectorState *>(lds_s + LDS::kState);
+    float2 *held_s = reinterpret_cast<float2 *>(lds_s + LDS::kHeld);
+    const RES res{lds_s};
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -457,7 +478,7 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
 #pragma unroll 1
     for (int q = 0; q < kPass; ++q) {
         const int tok = q * kTeams + team;
-        const int64_t m = (int64_t)tile_wg * kTok + tok;
+        const int64_t m = p.m_first + (int64_t)tile_wg * kTok + tok;
         const bool valid = m < p.M;
         const int64_t mc = valid ? m : p.M - 1;   // past the end the last vector is recomputed, and never stored
         const int rep = (int)(mc / p.T);
@@ -494,27 +515,39 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
     for (int g = 0; g < p.s; ++g) {
         // ---- screen ------------------------------------------------------------------------------------------------
         {
-            half8 hi[kBlk][kFrags];
+            half8 hi[kInRegs][kFrags];
             uint32_t u[kBlk][kTrack], keep[kBlk][8];
 #pragma unroll
             for (int b = 0; b < kBlk; ++b) {
+                if (b < kInRegs) {
 #pragma unroll
-                for (int j = 0; j < kFrags; ++j) hi[b][j] = res.hi8(b * 32 + col, 2 * j + hf);
+                    for (int j = 0; j < kFrags; ++j) hi[b < kInRegs ? b : 0][j] = res.hi8(b * 32 + col, 2 * j + hf);
+                }
 #pragma unroll
                 for (int k = 0; k < kTrack; ++k) u[b][k] = 0u;
 #pragma unroll
                 for (int r = 0; r < 8; ++r) keep[b][r] = 0u;
             }
-            auto sweep = [&](int i, const uint4 (&a)[kFrags]) {
+            // `used(j)`: called once fragment j of the tile is multiplied for the last time
+            auto sweep = [&](int i, const uint4 (&a)[kFrags], auto used) {
                 const uint32_t code = (uint32_t)i;
+                // where the first fragment of this lane's column stands; not known from one tile to the next, or the compiler
+                // would read the blocks' operands once, ahead of all tiles, into registers that are not there
+                uint32_t hi_at = (uint32_t)RES::half_at(col, hf);
+                if constexpr (kInRegs < kBlk) asm volatile("" : "+v"(hi_at));
 #pragma unroll
                 for (int b = 0; b < kBlk; ++b) {
                     floatx16 acc;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-                    for (int j = 0; j < kFrags; ++j)
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8 *>(&a[j]), hi[b][j], acc, 0, 0, 0);
+                    for (int j = 0; j < kFrags; ++j) {
+                        half8 v;
+                        if (b < kInRegs) v = hi[b < kInRegs ? b : 0][j];
+                        else v = *reinterpret_cast<const half8 *>(lds_s + b * (32 * DC * 2) + (hi_at ^ (uint32_t)(j << 5)));
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(*reinterpret_cast<const half8 *>(&a[j]), v, acc, 0, 0, 0);
+                        if (b == kBlk - 1) used(j);
+                    }
                     float m = 0.0f;
 #pragma unroll
                     for (int r = 0; r < 16; r += 2) m = fmaxf(fmaxf(m, fabsf(acc[r])), fabsf(acc[r + 1]));
@@ -532,18 +565,26 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
                     u[b][2] = n2;
                 }
             };
+            auto none = [](int) {};
             if constexpr (HELD) {
 #pragma unroll
                 for (int i = 0; i < kHeld; ++i)
-                    if (i < my_tiles) sweep(i, a0[i]);
+                    if (i < my_tiles) sweep(i, a0[i], none);
+            } else if constexpr (P > 2) {
+                // a tile's fragments make room for the next tile's one by one (behind the last tile the next sweep's first):
+                // a wave waits for them a little, while the other one of its SIMD multiplies
+                for (int i = 0; i < my_tiles; ++i) {
+                    const uint4 *next = frag + (int64_t)(wave + W * (i + 1 < my_tiles ? i + 1 : 0)) * (kFrags * 64);
+                    sweep(i, a0[0], [&](int j) { a0[0][j] = next[j * 64]; });
+                }
             } else {
                 uint4 a1[kFrags];
                 for (int i = 0; i < my_tiles; i += 2) {
                     if (i + 1 < my_tiles) load_tile(i + 1, a1);
-                    sweep(i, a0[0]);
+                    sweep(i, a0[0], none);
                     if (i + 1 < my_tiles) {
                         if (i + 2 < my_tiles) load_tile(i + 2, a0[0]);
-                        sweep(i + 1, a1);
+                        sweep(i + 1, a1, none);
                     }
                 }
                 if (my_tiles > 0) load_tile(0, a0[0]);   // the next sweep's first tile, behind the select phase
@@ -711,7 +752,7 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
     if (p.res_norm2) {
 #pragma unroll 1
         for (int tok = tid; tok < kTok; tok += 64 * W) {
-            const int64_t m = (int64_t)tile_wg * kTok + tok;
+            const int64_t m = p.m_first + (int64_t)tile_wg * kTok + tok;
             if (m >= p.M) break;
             const int rep = (int)(m / p.T);
             p.res_norm2[(((int64_t)rep * p.dict_count + dict) * p.T + (m - rep * p.T)) * p.sn + ch] =
@@ -734,6 +775,28 @@ Mode wide_mode(const EncodeArgs &a)
     return encode_mfma_supported(a) && a.d >= 64 ? kMfma : kValu;
 }
 
+// How many passes P of 4096 / d vectors a workgroup takes.  A generation of workgroups (one per CU) costs about P + 0.4 passes
+// (16 dictionaries, s = 8, 4096 atoms, one full generation: 102, 159, 222, 299, 365, 433 us for P = 1 .. 6; 1024 atoms 37, 62,
+// 84, 115, 139, 164; fp32 on 1024 atoms 45, 77, 106, 141 for P = 1 .. 4), so what counts is how many generations a launch
+// makes: three prompts of 1571 tokens on 8 KV heads are 592 workgroups of 64 vectors, three generations, or 240 of 160, one.
+struct WidePasses {
+    int P;
+    float cost;
+};
+WidePasses wide_passes(const EncodeArgs &a, int64_t vectors)
+{
+    const Mode mode = wide_mode(a);
+    const int most = a.d == 32 ? 1 : mode == kRes ? 2 : a.d == 64 ? 3 : mode == kMfma ? 6 : 4;
+    const int64_t dicts = (int64_t)a.dict_count * a.sn;
+    WidePasses best{1, 0.0f};
+    for (int P = 1; P <= most; ++P) {
+        const int64_t tok = (int64_t)P * 4096 / a.d, groups = (vectors + tok - 1) / tok * dicts;
+        const float cost = (float)((groups + kCus - 1) / kCus) * ((float)P + 0.4f);
+        if (P == 1 || cost < best.cost) best = {P, cost};
+    }
+    return best;
+}
+
 WidePlan plan_wide(const EncodeArgs &a)
 {
     WidePlan pl{};
@@ -751,14 +814,28 @@ template <typename TE, int DC, int MODE, int P, bool HELD>
 hipError_t launch_p(const EncodeArgs &a, WideParams &p)
 {
     constexpr int W = 8, kTok = 32 * (P * 128 / DC);
-    const int64_t tiles = (p.M + kTok - 1) / kTok, groups = tiles * a.dict_count * a.sn;
+    const int64_t tiles = (p.M - p.m_first + kTok - 1) / kTok, groups = tiles * a.dict_count * a.sn;
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
     p.tiles_per_h = (int32_t)tiles;
     p.n_groups = (int32_t)groups;
     int bits = 0;
     while ((1 << bits) < (p.ntiles + W - 1) / W) ++bits;
     p.code_mask = (1u << bits) - 1u;
-    hipLaunchKernelGGL((encode_wide_kernel<TE, DC, MODE, W, P, HELD>), dim3((unsigned)groups), dim3(64 * W), 0, a.stream, p);
+    constexpr int kLds = WideLds<DC, W, P>::kBytes;
+    if constexpr (kLds > 64 * 1024) {   // above the default limit: per device, once
+        static std::atomic<bool> attr_set[64];
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+        if (!attr_set[dev].load(std::memory_order_acquire)) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_wide_kernel<TE, DC, MODE, W, P, HELD>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+            if (e != hipSuccess) return e;
+            attr_set[dev].store(true, std::memory_order_release);
+        }
+    }
+    hipLaunchKernelGGL((encode_wide_kernel<TE, DC, MODE, W, P, HELD>), dim3((unsigned)groups), dim3(64 * W), kLds, a.stream, p);
     return hipGetLastError();
 }
 
@@ -773,7 +850,7 @@ hipError_t launch_m(const EncodeArgs &a)
     const int dicts = a.dict_count * a.sn;
     WideParams p{};
     p.X = a.X; p.Dict = a.D; p.frag = frag; p.bound = bound; p.idx_out = a.idx; p.coef_out = a.coef; p.res_norm2 = a.res_norm2;
-    p.T = a.T; p.M = (int64_t)(a.H / a.dict_count) * a.T;
+    p.T = a.T; p.m_first = a.m_first; p.M = a.m_end;
     p.x_stride_h = a.x_stride_h; p.x_stride_t = a.x_stride_t; p.code_stride_h = a.code_stride_h;
     p.N = a.N; p.s = a.s; p.sn = a.sn; p.dict_count = a.dict_count; p.ntiles = pl.ntiles; p.slices = pl.slices;
     p.idx16 = a.idx16; p.coef_mode = (a.coef16 ? kCoefF16 : 0) | (a.closed_loop ? kCoefClosed : 0);
@@ -783,10 +860,19 @@ hipError_t launch_m(const EncodeArgs &a)
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // two passes of vectors per workgroup (half the dictionary traffic per vector) once that still gives every CU one
+    const int P = wide_passes(a, a.m_end - a.m_first).P;
+    if constexpr (MODE == kMfma && DC == 128) {
+        if (P == 6) return launch_p<TE, DC, MODE, 6, HELD>(a, p);
+        if (P == 5) return launch_p<TE, DC, MODE, 5, HELD>(a, p);
+    }
+    if constexpr (!HELD && DC == 128) {
+        if (P == 4) return launch_p<TE, DC, MODE, 4, HELD>(a, p);
+    }
+    if constexpr (!HELD && DC > 32) {
+        if (P == 3) return launch_p<TE, DC, MODE, 3, HELD>(a, p);
+    }
     if constexpr (DC > 32) {
-        constexpr int kTok2 = 64 * 128 / DC;
-        if ((p.M + kTok2 - 1) / kTok2 * dicts >= 256) return launch_p<TE, DC, MODE, 2, HELD>(a, p);
+        if (P == 2) return launch_p<TE, DC, MODE, 2, HELD>(a, p);
     }
     return launch_p<TE, DC, MODE, 1, HELD>(a, p);
 }
@@ -805,6 +891,9 @@ bool encode_wide_supported(const EncodeArgs &a)
 }
 
 size_t encode_wide_workspace_bytes(const EncodeArgs &a) { return wide_mode(a) == kRes ? 0 : plan_wide(a).total; }
+
+// 0.4: the preparation of the dictionary
+float encode_wide_cost(const EncodeArgs &a, int64_t vectors) { return 0.4f + wide_passes(a, vectors).cost; }
 
 hipError_t launch_encode_wide(const EncodeArgs &a)
 {

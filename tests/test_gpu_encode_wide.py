@@ -87,6 +87,42 @@ def test_same_bits_as_the_encoder_of_the_larger_launches(algo, dtype, d, N, T, H
     assert torch.equal(iw, ie) and torch.equal(cw, ce)
 
 
+@pytest.mark.parametrize("algo,dtype,d,N,T,H", [   # the passes per workgroup that the rule takes: 3, 4, 5, 6
+    ("valu", "f32", 128, 100, 9000, 2), ("valu", "f32", 128, 70, 16000, 2), ("valu", "f16", 64, 33, 20000, 2),
+    ("mfma", "f16", 128, 544, 16000, 2), ("mfma", "f16", 128, 544, 20001, 2), ("mfma", "f16", 128, 608, 24500, 2),
+    ("mfma", "f16", 128, 544, 2450, 16), ("mfma", "f16", 64, 1056, 20001, 2),
+])
+def test_same_bits_with_several_passes_per_workgroup(algo, dtype, d, N, T, H):
+    algo = {"valu": csr.CSR_ENCODE_VALU, "mfma": csr.CSR_ENCODE_MFMA}[algo]
+    X = torch.from_numpy(synth.vectors(9, "keys", H, T, d, dtype, outliers=4)).cuda()
+    D = torch.from_numpy(synth.dictionary(9, "dict_k", H, N, d, dtype)).cuda()
+    iw, cw = csr.csr_encode(X, D, 4, algo=csr.CSR_ENCODE_WIDE)
+    ie, ce = csr.csr_encode(X, D, 4, algo=algo)
+    assert torch.equal(iw, ie) and torch.equal(cw, ce)
+
+
+@pytest.mark.parametrize("B,Hkv,T,N,sn", [
+    (1, 2, 70000, 544, 1),     # one generation of the prefill encoder's workgroups, 4464 vectors of each dictionary left over
+    (5, 3, 9001, 544, 1),      # sequences that share three dictionaries: the line lies inside one of them
+    (1, 8, 10300, 1056, 2),    # chunks of 64 dimensions
+])
+def test_a_launch_shared_by_two_encoders_has_the_codes_of_one(B, Hkv, T, N, sn):
+    D = torch.from_numpy(synth.dictionary(10, "dict_k", Hkv * sn, N, 128 // sn, "f16")).cuda()
+    if sn > 1:
+        D = D.view(Hkv, sn, N, 128 // sn)
+    X = torch.from_numpy(synth.vectors(10, "keys", B * Hkv, T, 128, "f16", outliers=4)).cuda()
+    shape = (B * Hkv, T) + ((sn,) if sn > 1 else ())
+    ea, em = (torch.full(shape, -1.0, device="cuda") for _ in range(2))
+    ia, ca = csr.csr_encode(X, D, 4, res_norm2=ea)
+    im, cm = csr.csr_encode(X, D, 4, algo=csr.CSR_ENCODE_MFMA, res_norm2=em)
+    assert torch.equal(ia, im) and torch.equal(ca, cm)
+    assert torch.allclose(ea, em, rtol=1e-5, atol=1e-4)   # the squares are added in another order
+    # with scratch for the prefill encoder alone it takes all vectors
+    ws = torch.empty(256 * 64, dtype=torch.uint8, device="cuda")
+    iw, cw = csr.csr_encode(X, D, 4, workspace=ws)
+    assert torch.equal(iw, im) and torch.equal(cw, cm)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 def test_a_workspace_too_small_for_this_encoder_keeps_the_other_one(dtype):
     # sized for more vectors (fp16), or none, where the vector ALU needs none: accepted, with the same codes
