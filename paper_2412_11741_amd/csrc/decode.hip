@@ -283,17 +283,10 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
     const int tid = threadIdx.x;
     // (KV head, group slice) is the fastest grid dimension: workgroups are dealt to the 8 XCDs round-robin in that
     // order, so the chunks of one (sequence, KV head) - which load the same score table - tend to share an L2
-    const int c = blockIdx.y;
     const int h = blockIdx.x / ngs, gs = blockIdx.x % ngs;
-    const int b = blockIdx.z;
-
-    int64_t len = T;
-    if (seq_lens) {
-        const int32_t l = seq_lens[b];
-        len = l < 0 ? 0 : (l > T ? T : l);
-    }
-    const int64_t t0 = (int64_t)c * chunk_tokens;
-    const int64_t t_end = min(t0 + chunk_tokens, len);
+    const Chunk part = chunk_of<THREADS, 12288>(seq_lens, T, nchunks, chunk_tokens);
+    const int c = part.c, b = part.b;
+    const int64_t t0 = part.t0, t_end = part.t_end;
     const int64_t slot = (((int64_t)b * Hkv + h) * ngs + gs) * nchunks + c;
     float *ml = part_ml + slot * (2 * GB);
 

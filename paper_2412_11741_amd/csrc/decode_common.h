@@ -368,6 +368,70 @@ template <bool CH, int NP> struct ChunkBase {
 // their side of it, so that only the explicitly requested vectors (fetch_codes) are in flight.
 __device__ __forceinline__ void round_fence() { asm volatile("" ::: "memory"); }
 
+// A workgroup's part of the work: tokens [t0, t_end) of sequence b, its chunk c (of slots 0 .. nchunks - 1; one without tokens has
+// t_end <= t0).  The grid is (heads, nchunks, B): KV heads x group slices first.
+struct Chunk {
+    int b, c;
+    int64_t t0, t_end;
+};
+// The plan's chunks are cut for sequences that fill the buffer.  Where lengths are given, long chunks (CUT_FROM tokens or more,
+// several of them per sequence) are cut anew, every sequence by its own length and evenly, and the workgroups are numbered
+// so that those without tokens come last: one that ends at once in the middle of the numbers gives one shader engine a
+// workgroup more than it has CUs, and another one less.  A workgroup costs about kFixedRounds rounds besides its own, so a
+// sequence gets as few chunks as the plan's size allows, or more (at most the plan's number) where the whole launch then
+// makes cheaper generations of 256 workgroups, one per CU.  All of it follows from the lengths alone, and every wave works it out
+// for itself, in about 2 us: shorter chunks, one chunk per sequence and more than 64 sequences keep the plan's.  8 sequences of
+// 73728 to 131072 tokens, 8 KV heads x 4 query heads 147 us before, 136 now; 20 sequences of 15000 to 30000, 4 x 8 heads 134 and 113.
+template <int THREADS, int CUT_FROM>
+__device__ __forceinline__ Chunk chunk_of(const int32_t *__restrict__ seq_lens, int64_t T, int nchunks, int64_t chunk_tokens)
+{
+    constexpr float kFixedRounds = 7.0f;
+    const int B = gridDim.z, heads = gridDim.x, lane = threadIdx.x & 63;
+    if (!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM) {
+        int64_t len = T;
+        if (seq_lens) {
+            const int32_t l = seq_lens[blockIdx.z];
+            len = l < 0 ? 0 : (l > T ? T : l);
+        }
+        const int64_t t0 = (int64_t)blockIdx.y * chunk_tokens;
+        return {(int)blockIdx.z, (int)blockIdx.y, t0, min(t0 + chunk_tokens, len)};
+    }
+    const int most = (int)(chunk_tokens / THREADS);   // rounds per chunk of the plan
+    // lane i: sequence i (T is at most 2^20)
+    const int l = lane < B ? seq_lens[lane] : 0;
+    const int len = l < 0 ? 0 : (l > (int)T ? (int)T : l), R = (len + THREADS - 1) / THREADS;
+    // chunks of R rounds at r rounds a chunk: ceil(R / r); the quotient is at least 1 / (2 r) away from a whole number
+    auto chunks = [&](float r) { return min(nchunks, (int)(((float)R + r - 0.5f) * (1.0f / r))); };
+    const float sum = wave_sum((float)R) * (float)heads, g = ceilf(sum / (256.0f * (float)most));
+    float r = (float)most, best = INFINITY;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {   // the plan's size; what fills g and g + 1 generations, half a chunk lost per sequence
+        const float room = 256.0f * (g + (float)(k - 1)) - 0.5f * (float)(B * heads);
+        const float rk = k == 0 || !(room > 0.0f) ? (float)most : fminf((float)most, fmaxf(1.0f, ceilf(sum / room)));
+        const float groups = wave_sum((float)chunks(rk)) * (float)heads;
+        const float cost = ceilf(groups * (1.0f / 256.0f)) * (rk + kFixedRounds);
+        if (k == 0 || cost < 0.92f * best) { best = cost; r = rk; }
+    }
+    // workgroup j of a head: the j-th of all sequences' chunks, or, behind the last, the (j - all)-th empty slot
+    const int n = lane < B ? chunks(r) : 0;
+    int upto = n;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const int o = __shfl_up(upto, m, 64);
+        if (lane >= m) upto += o;
+    }
+    const int j = (int)(blockIdx.y + nchunks * blockIdx.z), all = __builtin_amdgcn_readlane(upto, 63);
+    const bool empty = j >= all;
+    // empty slots up to a lane's sequence: nchunks per sequence less its chunks
+    const int past_of = empty ? all + nchunks * (lane + 1) - upto : upto, mine = empty ? nchunks - n : n;
+    const unsigned long long past = __ballot(lane < B && j < past_of);
+    const int at = past ? __ffsll((long long)past) - 1 : 0;   // never none: chunks and empty slots are as many as the grid's workgroups
+    const int before = __builtin_amdgcn_readlane(past_of - mine, at), n_at = __builtin_amdgcn_readlane(n, at);
+    if (empty) return {at, n_at + j - before, 0, 0};
+    const int own = (__builtin_amdgcn_readlane(R, at) + n_at - 1) / n_at * THREADS, t0 = (j - before) * own;
+    return {at, j - before, t0, min(t0 + own, __builtin_amdgcn_readlane(len, at))};
+}
+
 template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int THREADS, int NP>
 __device__ __forceinline__ void finish_chunk(unsigned char *smem_raw, float *red, float (&sc)[TPT][GB], const float (&mx)[GB],
                                              int n_mine, int64_t t0, int64_t t_end, int64_t code_row, int owner_off,

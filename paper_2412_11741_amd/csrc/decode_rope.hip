@@ -128,17 +128,10 @@ __global__ __launch_bounds__(rope_threads(GB)) void stream_rope_kernel(
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int sub = lane & 7, eighth = lane >> 3;
-    const int c = blockIdx.x;
-    const int h = blockIdx.y / ngs, gs = blockIdx.y % ngs;
-    const int b = blockIdx.z;
-
-    int64_t len = T;
-    if (seq_lens) {
-        const int32_t l = seq_lens[b];
-        len = l < 0 ? 0 : (l > T ? T : l);
-    }
-    const int64_t t0 = (int64_t)c * chunk_tokens;
-    const int64_t t_end = min(t0 + chunk_tokens, len);
+    const int h = blockIdx.x / ngs, gs = blockIdx.x % ngs;
+    const Chunk part = chunk_of<THREADS, 4096>(seq_lens, T, nchunks, chunk_tokens);
+    const int c = part.c, b = part.b;
+    const int64_t t0 = part.t0, t_end = part.t_end;
     const int64_t slot = (((int64_t)b * Hkv + h) * ngs + gs) * nchunks + c;
     float *ml = part_ml + slot * (2 * GB);
     if (t_end <= t0) {  // nothing cached in this chunk: weight zero, histogram never read
@@ -532,7 +525,7 @@ hipError_t launch_rope_t(const DecodeArgs &a, const DecodePlan &p, float *hist, 
     }
     // the plan's LDS size = dictionary / histogram | reductions | constant tables (see plan_decode)
     const uint32_t tab_bytes = (uint32_t)(p.lds_bytes - kRedBytes - kRopeTableBytes);
-    const dim3 grid((unsigned)p.nchunks, (unsigned)(a.Hkv * p.ngs), (unsigned)a.B);
+    const dim3 grid((unsigned)(a.Hkv * p.ngs), (unsigned)p.nchunks, (unsigned)a.B);
     hipLaunchKernelGGL(kern, grid, dim3(rope_threads(GB)), p.lds_bytes, a.stream, (const __half *)a.q,
                        (const __half *)a.DK, (const uint16_t *)a.idxK, (const __half *)a.coefK,
                        (const uint16_t *)a.idxV, (const __half *)a.coefV, a.seq_lens, hist, ml, a.Hq, a.Hkv, a.G, p.ngs,

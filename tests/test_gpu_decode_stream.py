@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import oracle
+import paper_2412_11741_amd as csr
 from tests.test_gpu_decode import TOL_F16_OUT, _case, _check, _chunked_case, _run, _u16
 from tests import test_gpu_decode_rope as rope
 
@@ -66,3 +67,43 @@ def test_both_halves_of_a_code_are_sampled():
     one = _run(q, *keys, DV, iV, cV, out_dtype=torch.float32)
     two = _run(q, *keys, *(np.ascontiguousarray(np.flip(a, ax)) for a, ax in ((DV, 1), (iV, 3), (cV, 3))), out_dtype=torch.float32)
     assert np.array_equal(one, np.concatenate([two[..., 64:], two[..., :64]], axis=-1))
+
+
+@pytest.mark.parametrize("B,Hkv,G,T,N,rope_base", [
+    (13, 8, 4, 60000, 256, 0.0),       # 8-wave shape, four chunks of the plan
+    (6, 32, 1, 40000, 128, 0.0),       # 16-wave shape, one query head
+    (64, 1, 4, 50000, 128, 0.0),       # as many sequences as a wave has lanes
+    (9, 8, 4, 16000, 128, 10000.0),    # rotary keys, a group
+    (5, 32, 1, 12000, 64, 10000.0),    # rotary keys, one query head
+])
+def test_long_sequences_are_cut_by_their_own_lengths(B, Hkv, G, T, N, rope_base):
+    # lengths of 0, 1, the edges of the plan's chunks and rounds, out of range on both sides; sampled pairs against the oracle
+    s, d = 4, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(75)
+    unit = lambda *sh: (lambda a: (a / a.norm(dim=-1, keepdim=True)).half())(torch.randn(*sh, device="cuda", generator=gen))
+    idx = lambda: torch.randint(0, N, (B, Hkv, T, s), device="cuda", generator=gen, dtype=torch.int32).to(torch.int16)
+    coef = lambda: (torch.randn(B, Hkv, T, s, device="cuda", generator=gen) * 3).half()
+    q, DK, DV = torch.randn(B, Hkv * G, d, device="cuda", generator=gen).half(), unit(Hkv, N, d), unit(Hkv, N, d)
+    ik, ck, iv, cv = idx(), coef(), idx(), coef()
+    edges = [T, 0, 1, T // 4, T // 4 + 1, T // 2, -5, T + 70000, T - 1, 512, 1025, 4097, 3 * T // 4]
+    lens = np.array([edges[(7 * b) % len(edges)] for b in range(B)], dtype=np.int32)
+    out = csr.csr_decode_attn(q, DK, ik, ck, DV, iv, cv, seq_lens=torch.from_numpy(lens).cuda(), out_dtype=torch.float16,
+                              rope_base=rope_base)
+    torch.cuda.synchronize()
+    valid = np.clip(lens, 0, T)
+    n = lambda t: t.cpu().numpy()
+    for b in range(min(B, 13)):
+        if valid[b] == 0:
+            assert not n(out[b]).any()
+            continue
+        h = (3 * b) % Hkv
+        one = [n(a) for a in (q[b:b + 1, h * G:(h + 1) * G], DK[h:h + 1], ik[b:b + 1, h:h + 1], ck[b:b + 1, h:h + 1], DV[h:h + 1],
+                              iv[b:b + 1, h:h + 1], cv[b:b + 1, h:h + 1])]
+        ref = oracle.decode_attn_rope(*one, rope_base, 0, 0, seq_lens=valid[b:b + 1]) if rope_base else \
+            oracle.decode_attn(*one, seq_lens=valid[b:b + 1])
+        _check(n(out[b:b + 1, h * G:(h + 1) * G]), ref, TOL_F16_OUT, f"cut by length {B} {Hkv} {G} {T}: sequence {b}, {lens[b]} tokens")
+    # and the lengths of every sequence full: the same as no lengths at all
+    full = csr.csr_decode_attn(q, DK, ik, ck, DV, iv, cv, seq_lens=torch.full((B,), T, dtype=torch.int32, device="cuda"), rope_base=rope_base)
+    none = csr.csr_decode_attn(q, DK, ik, ck, DV, iv, cv, rope_base=rope_base)
+    assert torch.allclose(full.float(), none.float(), rtol=2e-3, atol=2e-3)
