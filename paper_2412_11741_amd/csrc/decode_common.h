@@ -387,7 +387,7 @@ __device__ __forceinline__ Chunk chunk_of(const int32_t *__restrict__ seq_lens, 
 {
     constexpr float kFixedRounds = 7.0f;
     const int B = gridDim.z, heads = gridDim.x, lane = threadIdx.x & 63;
-    if (!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM) {
+    if (__builtin_expect(!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM, 1)) {
         int64_t len = T;
         if (seq_lens) {
             const int32_t l = seq_lens[blockIdx.z];
