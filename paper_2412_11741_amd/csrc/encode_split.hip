@@ -26,11 +26,9 @@
 // are cleared by a launch of their own before (a workspace's contents are undefined); a slot is written once per call.
 //
 // Bound: reading the dictionaries once, then a dependent chain per iteration - hi and lo from LDS, 16 dependent matrix
-// instructions per tile, the tournament over the waves, publish and poll (one trip each to where the chip's L2s meet, 0.5
-// us together), the row of the chosen atom, the update.  32 dictionaries of 4096 atoms, s = 8, one vector each: 36 us (12
-// us for one iteration, 3.4 us for every further one) against 98 us for the s + 1 launches this replaces, which read the
-// dictionaries again in every iteration; 64 vectors each 62 against 328; 32 x 256 atoms, where nothing is exchanged, 21
-// against 49.
+// instructions per tile (8 with at most 16 vectors), the tournament over the waves, publish and poll (one trip each to where
+// the chip's L2s meet, 0.5 us together), the row of the chosen atom, the update.  32 dictionaries of 4096 atoms, s = 8, one vector
+// each: 34 us a call (36 with 16 instructions per tile; with 8192 atoms 48 and 53), 64 vectors each 62.
 #include <atomic>
 #include <cmath>
 
@@ -85,6 +83,13 @@ __global__ __launch_bounds__(256) void clear_slots_kernel(ulonglong2 *__restrict
     if (i < n2) slots[i] = make_ulonglong2(0ull, 0ull);
 }
 
+// the value of the lane whose number differs in bit 4 (`up`: this lane's bit 4)
+__device__ __forceinline__ uint32_t xchg16(uint32_t v, bool up)
+{
+    const auto x = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // rows (0, 0, 2, 2) and (1, 1, 3, 3)
+    return up ? x[0] : x[1];
+}
+
 // LDS byte offset of dimensions 4 pc .. 4 pc + 3 of vector v's residual: 32 vectors' rows are read at the same piece
 template <int DC> __device__ __forceinline__ int res_at(int v, int pc) { return v * (DC * 4) + ((pc ^ (v & 15)) << 4); }
 
@@ -95,7 +100,7 @@ struct SplitState { int32_t sexp, pad; int64_t vid, code_at; };   // scale of a 
 
 // HELD: tiles of 32 atoms a wave keeps in registers.  A workgroup is two waves per SIMD, and with 128 dimensions there is no
 // room for a second one: the compiler is told so, or it spends instructions on registers that nobody can use.
-template <int DC, int HELD>
+template <int DC, int HELD, bool kNarrow>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC == 128 ? 2 : 4))) void encode_split_kernel(const SplitParams p)
 {
     constexpr int kFrags = DC / 16;
@@ -188,13 +193,20 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
 
     // The best candidate of vectors m0 .. m0 + 31 over the tiles first, first + step .. below last, as a packed word with
     // `tag` (lanes col of either half); `own`: this wave's tiles of the workgroup's slice, the first ones in registers.
+    // kNarrow (at most 16 vectors): hi takes columns 0 - 15 and lo columns 16 - 31: one pass of matrix instructions instead of two, and
+    // half the values per lane behind it.
     auto sweep = [&](int m0, int first, int last, int step, bool own, int tag) {
-        half8 hi[kFrags], lo[kFrags];
-        const int mine = min(m0 + col, p.M - 1);   // columns past the last vector repeat it: one LDS address for them all
+        half8 hi[kFrags], lo[kNarrow ? 1 : kFrags];
+        // columns past the last vector repeat it: one LDS address for them all
+        const int mine = min(kNarrow ? (col & 15) : m0 + col, p.M - 1);
 #pragma unroll
         for (int j = 0; j < kFrags; ++j) {
-            hi[j] = *reinterpret_cast<const half8 *>(hi_s + half_at<DC>(mine, hf * kFrags + j));
-            lo[j] = *reinterpret_cast<const half8 *>(lo_s + half_at<DC>(mine, hf * kFrags + j));
+            if constexpr (kNarrow) {
+                hi[j] = *reinterpret_cast<const half8 *>((col < 16 ? hi_s : lo_s) + half_at<DC>(mine, hf * kFrags + j));
+            } else {
+                hi[j] = *reinterpret_cast<const half8 *>(hi_s + half_at<DC>(mine, hf * kFrags + j));
+                lo[j] = *reinterpret_cast<const half8 *>(lo_s + half_at<DC>(mine, hf * kFrags + j));
+            }
         }
         float ba = -1.0f, bc = 0.0f;
         int bi = 0;
@@ -206,7 +218,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             for (int j = 0; j < kFrags; ++j) {
                 const half8 av = *reinterpret_cast<const half8 *>(&a[j]);
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, hi[j], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, lo[j], acc, 0, 0, 0);
+                if constexpr (!kNarrow) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, lo[j], acc, 0, 0, 0);
             }
             // accumulator r of lane half hf is atom 8 (r / 4) + (r % 4) + 4 hf of the tile, ascending in r: a tournament in
             // which the left side wins ties
@@ -214,9 +226,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             int at[8];
 #pragma unroll
             for (int r = 0; r < 8; ++r) {
-                const bool right = fabsf(acc[2 * r + 1]) > fabsf(acc[2 * r]);
-                c[r] = right ? acc[2 * r + 1] : acc[2 * r];
-                at[r] = right ? 2 * r + 1 : 2 * r;
+                if constexpr (kNarrow) {   // lanes 0 - 15 of a half get the sum of accumulator 2 r, lanes 16 - 31 of 2 r + 1
+                    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[2 * r]), __float_as_uint(acc[2 * r + 1]), false, false);
+                    c[r] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
+                    at[r] = 2 * r;
+                } else {
+                    const bool right = fabsf(acc[2 * r + 1]) > fabsf(acc[2 * r]);
+                    c[r] = right ? acc[2 * r + 1] : acc[2 * r];
+                    at[r] = right ? 2 * r + 1 : 2 * r;
+                }
             }
 #pragma unroll
             for (int m = 4; m >= 1; m >>= 1) {
@@ -227,6 +245,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
                     at[r] = right ? at[2 * r + 1] : at[2 * r];
                 }
             }
+            if constexpr (kNarrow) at[0] += col >> 4;
             if (fabsf(c[0]) > ba) {
                 ba = fabsf(c[0]);
                 bi = tile * 32 + 8 * (at[0] >> 2) + (at[0] & 3) + 4 * hf;
@@ -244,6 +263,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             tile_best(tile, a);
         }
         take_better(ba, bi, bc, xchg32f(ba, hf), (int)xchg32((uint32_t)bi, hf), xchg32f(bc, hf));
+        if constexpr (kNarrow) {
+            const bool up = col >= 16;
+            take_better(ba, bi, bc, __uint_as_float(xchg16(__float_as_uint(ba), up)), (int)xchg16((uint32_t)bi, up),
+                        __uint_as_float(xchg16(__float_as_uint(bc), up)));
+        }
         // a wave without tiles: below every candidate
         return ba >= 0.0f ? pack_candidate(bc, bi, tag) : (unsigned long long)((uint32_t)tag << 1);
     };
@@ -394,7 +418,7 @@ SplitPlan plan_split(const EncodeArgs &a)
     return pl;
 }
 
-template <int DC, int HELD>
+template <int DC, int HELD, bool kNarrow>
 hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitParams &p)
 {
     static std::atomic<bool> attr_set[64];   // per device, once: many vectors need more LDS than the default limit
@@ -403,13 +427,21 @@ hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitP
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (!attr_set[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_split_kernel<DC, HELD>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_split_kernel<DC, HELD, kNarrow>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 159 * 1024);   // (plan_split: at most 139 KB)
         if (e != hipSuccess) return e;
         attr_set[dev].store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((encode_split_kernel<DC, HELD>), dim3((unsigned)(pl.k * p.n_dicts)), dim3(kThreads), pl.lds, a.stream, p);
+    hipLaunchKernelGGL((encode_split_kernel<DC, HELD, kNarrow>), dim3((unsigned)(pl.k * p.n_dicts)), dim3(kThreads), pl.lds, a.stream, p);
     return hipGetLastError();
+}
+
+template <int DC>
+hipError_t launch_split_held(const EncodeArgs &a, const SplitPlan &pl, const SplitParams &p)
+{
+    if (pl.M <= 16)
+        return pl.held == 1 ? launch_split_t<DC, 1, true>(a, pl, p) : pl.held == 2 ? launch_split_t<DC, 2, true>(a, pl, p) : launch_split_t<DC, 4, true>(a, pl, p);
+    return pl.held == 1 ? launch_split_t<DC, 1, false>(a, pl, p) : pl.held == 2 ? launch_split_t<DC, 2, false>(a, pl, p) : launch_split_t<DC, 4, false>(a, pl, p);
 }
 
 }  // namespace
@@ -441,8 +473,7 @@ hipError_t launch_encode_split(const EncodeArgs &a)
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (a.d == 64) return pl.held == 1 ? launch_split_t<64, 1>(a, pl, p) : pl.held == 2 ? launch_split_t<64, 2>(a, pl, p) : launch_split_t<64, 4>(a, pl, p);
-    return pl.held == 1 ? launch_split_t<128, 1>(a, pl, p) : pl.held == 2 ? launch_split_t<128, 2>(a, pl, p) : launch_split_t<128, 4>(a, pl, p);
+    return a.d == 64 ? launch_split_held<64>(a, pl, p) : launch_split_held<128>(a, pl, p);
 }
 
 }  // namespace csr

@@ -22,6 +22,10 @@ pytestmark = pytest.mark.gpu
     (40, 2, 2048, 128, 4),     # dictionaries dealt to the XCDs: 5 each, 6 slices
     (1, 7, 65536, 128, 3),     # tiles beyond the registers are read again in every iteration
     (300, 1, 256, 128, 3),     # more dictionaries than CUs
+    (4, 16, 1056, 128, 4),     # the most vectors whose hi and lo share a pass, 33 tiles on 4 slices
+    (4, 17, 1056, 128, 4),     # one more
+    (32, 15, 8192, 128, 3),    # four tiles a wave in registers
+    (6, 16, 320, 64, 4),       # chunks
 ])
 def test_slices_of_a_dictionary_agree(dicts, M, N, d, s):
     D = synth.dictionary(91, "dict_k", dicts, N, d, "f16")
