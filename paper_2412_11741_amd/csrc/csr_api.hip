@@ -38,8 +38,8 @@ size_t round256(size_t v) { return (v + 255) & ~size_t(255); }
 // otherwise; the rest go to the wide encoder, which gives the same codes bit for bit.  Measured on 8 to 64 dictionaries (us, s = 8):
 //   fp32, or an N that is no multiple of 32: the alternative is the vector ALU (2 x 4096 fp32 vectors, N = 1024: 775
 //     against 57); a handful of vectors stays there, which needs no scratch
-//   dictionaries that fit the LDS: the resident encoder needs 512 vectors per CU to fill the chip (N = 256, 8 x 1600
-//     vectors: 133 against 60, 64 x 400: 125 against 98, 64 x 800: 133 against 183)
+//   dictionaries that fit the LDS: the resident encoder needs 256 vectors per CU to fill the chip (N = 256, 16 x 1024
+//     vectors: 74 against 49, 16 x 2048: 74 against 94)
 //   the prefill encoder takes 512 vectors per CU and generation and a last generation costs nearly as much as a full one, however few
 //     workgroups it has (16 x 8192 vectors, N = 4096: 991, 16 x 10240: 1752; the generation alone with 16 x 2048 left to the
 //     wide encoder 1280): whole generations go to it and what remains to the wide encoder, or all to one of the two.
@@ -50,7 +50,7 @@ int64_t auto_head(const csr::EncodeArgs &a, int algo)
     const int64_t dicts = (int64_t)a.dict_count * a.sn;
     switch (algo) {
         case CSR_ENCODE_VALU: return M >= 32 ? 0 : M;
-        case CSR_ENCODE_RESIDENT: return M * dicts < 36 * 1000 ? 0 : M;
+        case CSR_ENCODE_RESIDENT: return csr::encode_wide_cost(a, M) < csr::encode_resident_cost(a) ? 0 : M;
         case CSR_ENCODE_MFMA: {
             if (a.d == 32) return M;
             const float gen = csr::encode_mfma_generation_cost(a);

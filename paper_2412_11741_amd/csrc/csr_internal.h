@@ -69,6 +69,7 @@ hipError_t launch_encode_split(const EncodeArgs &a);
 
 // fp16 matrix-core encoder for dictionaries that fit the LDS (at most 128 KB).
 bool encode_resident_supported(const EncodeArgs &a);
+float encode_resident_cost(const EncodeArgs &a);   // of a whole launch, in the unit of encode_wide_cost
 hipError_t launch_encode_resident(const EncodeArgs &a);
 
 // fp16 encoder for dictionaries of at most 256 atoms: Gram-matrix update of the correlations.

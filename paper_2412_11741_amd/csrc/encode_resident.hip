@@ -23,6 +23,7 @@
 // (Matching Pursuit commutes with it; lo stays clear of the fp16 subnormals).  The largest atom norm, which scales
 // delta, is computed while the dictionary is loaded.
 #include <atomic>
+#include <cmath>
 
 #include "csr_internal.h"
 #include "encode_common.h"
@@ -34,8 +35,9 @@ using namespace enc;
 
 constexpr int kWaves = 8;                    // two per SIMD; one workgroup per CU (the dictionary fills the LDS)
 constexpr int kThreads = 64 * kWaves;
-constexpr int kBlocksPerWave = 2;            // 32-vector blocks a wave works through, one after the other
-constexpr int kTokPerWG = kWaves * kBlocksPerWave * 32;  // 512
+constexpr int kBlockVectors = kWaves * 32;   // a workgroup takes whole multiples of this: its waves work through as many
+                                             // 32-vector blocks each, one after the other
+constexpr int kMostBlocks = 4;
 constexpr int kMaxDictBytes = 128 * 1024;
 constexpr int kScratchPerWave = 1024;        // LDS a wave uses to share one vector's state
 constexpr int kTrack = 4;                    // group maxima tracked per lane and sweep
@@ -119,24 +121,26 @@ __device__ __forceinline__ int resolve_vector(const unsigned char *dict, int32_t
 // OCC: waves per SIMD the register budget is set for.  64-dimensional vectors need few enough registers for 4, so
 // that two workgroups share a CU when their dictionaries both fit its LDS (measured 12 - 14 % faster; with one
 // workgroup per CU the tighter budget only costs spills).
-template <int DC, int OCC>
+// BLOCKS: blocks per wave where known at compile time (two: the loop over them unrolled is worth 2 - 6 %), else 0.
+template <int DC, int OCC, int BLOCKS>
 __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
     const __half *__restrict__ X, const __half *__restrict__ Dict, void *__restrict__ idx_out,
     void *__restrict__ coef_out, int64_t T, int64_t M, int32_t N, int32_t s, int32_t sn, int64_t x_stride_h, int64_t x_stride_t,
-    int32_t dict_count, int64_t code_stride_h, int32_t tiles_per_h, int32_t idx16, int32_t coef_mode, uint32_t code_mask,
+    int32_t dict_count, int64_t code_stride_h, int32_t tiles_per_h, int32_t blocks_arg, int32_t idx16, int32_t coef_mode, uint32_t code_mask,
     float *__restrict__ res_norm2)
 {
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
     constexpr int kFrags = DC / 16;       // 8-element operand fragments per lane
     constexpr int kRowBytes = DC * 2;
     constexpr int kPieces = kRowBytes / 16;
+    const int blocks = BLOCKS ? BLOCKS : blocks_arg;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, hf = lane >> 5;
     // work is dealt per dictionary: dct = dictionary * sn + chunk owns the vectors of all blocks that use it
-    // (block h uses dictionary h % dict_count), numbered m = (h / dict_count) * T + t, in tiles of 512
+    // (block h uses dictionary h % dict_count), numbered m = (h / dict_count) * T + t, in tiles of `blocks` x 256
     const int dct = blockIdx.x / tiles_per_h;
     const int tile_wg = blockIdx.x - dct * tiles_per_h;
     const int dict = dct / sn, ch = dct - dict * sn;
@@ -188,9 +192,9 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
     // relative slack of a packed value: its low mantissa bits were replaced by the tile code
     const float pack_q = (float)(code_mask + 1) * 1.1920929e-7f;
 
-    for (int bi = 0; bi < kBlocksPerWave; ++bi) {
-        const int64_t m = (int64_t)tile_wg * kTokPerWG + (wave * kBlocksPerWave + bi) * 32 + col;
-        if ((int64_t)tile_wg * kTokPerWG + (wave * kBlocksPerWave + bi) * 32 >= M) break;  // wave-uniform
+    for (int bi = 0; bi < blocks; ++bi) {
+        const int64_t m0 = ((int64_t)tile_wg * blocks + bi) * kBlockVectors + wave * 32, m = m0 + col;
+        if (m0 >= M) break;  // wave-uniform
         const bool valid = m < M;
         const int64_t mc = valid ? m : M - 1;  // tail lanes recompute the last vector, never store
         const int rep = (int)(mc / T);
@@ -423,11 +427,43 @@ bool encode_resident_supported(const EncodeArgs &a)
            (int64_t)a.N * a.d * 2 <= kMaxDictBytes;
 }
 
+// Workgroups that run at once: one per CU, or two where two 64-dimensional dictionaries (and the waves' scratch) fit its LDS
+static bool two_per_cu(const EncodeArgs &a)
+{
+    return a.d == 64 && 2 * ((size_t)a.N * 64 * 2 + kWaves * kScratchPerWave + 64) <= 160 * 1024;
+}
+
+// Blocks of 32 vectors per wave.  What counts is how many generations of workgroups the launch makes; a workgroup costs as
+// many block times, and the load of the dictionary besides, about a tenth of one.  Always two: 16 dictionaries of 256 atoms,
+// s = 8 (us) 4096 vectors each 134, 9000 247; as many as the rule takes 77 and 205.
+struct ResidentBlocks {
+    int blocks;
+    float cost;   // block times
+};
+static ResidentBlocks resident_blocks(const EncodeArgs &a)
+{
+    const int64_t M = (int64_t)(a.H / a.dict_count) * a.T, dicts = (int64_t)a.dict_count * a.sn, slots = two_per_cu(a) ? 2 * kCus : kCus;
+    ResidentBlocks best{2, INFINITY};
+    for (int b : {2, 1, 3, 4}) {
+        const int64_t groups = (M + b * kBlockVectors - 1) / (b * kBlockVectors) * dicts;
+        const float cost = (float)((groups + slots - 1) / slots) * ((float)b + 0.1f);
+        if (cost < best.cost) best = {b, cost};
+    }
+    return best;
+}
+
+// A block time is 66 us with 256 atoms and 87 with 512 (s = 8), where a pass of the wide encoder is 24 and 27.
+float encode_resident_cost(const EncodeArgs &a)
+{
+    return resident_blocks(a).cost * (2.35f + (float)(a.N * a.d) / (128.0f * 550.0f));
+}
+
 template <int DC, int OCC>
 static hipError_t launch_resident_t(const EncodeArgs &a)
 {
     const int64_t M = (int64_t)(a.H / a.dict_count) * a.T;  // vectors per dictionary
-    const int64_t tiles = (M + kTokPerWG - 1) / kTokPerWG;
+    const int blocks = resident_blocks(a).blocks;
+    const int64_t tiles = (M + blocks * kBlockVectors - 1) / (blocks * kBlockVectors);
     const int64_t groups = tiles * a.dict_count * a.sn;
     if (groups > 0x7fffffffLL) return hipErrorInvalidValue;
     const int lds_bytes = a.N * DC * 2 + kWaves * kScratchPerWave + 64;
@@ -435,21 +471,23 @@ static hipError_t launch_resident_t(const EncodeArgs &a)
     int bits = 0;
     while ((1 << bits) < ntiles) ++bits;
     const uint32_t code_mask = (1u << bits) - 1u;
+    auto kern = blocks == 2 ? &encode_resident_kernel<DC, OCC, 2> : &encode_resident_kernel<DC, OCC, 0>;
     // per device, once: the dictionary needs more LDS than the default limit
-    static std::atomic<bool> attr_set[64];
+    static std::atomic<bool> attr_set[2][64];
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    if (!attr_set[dev].load(std::memory_order_acquire)) {
-        e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_resident_kernel<DC, OCC>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kMaxDictBytes + kWaves * kScratchPerWave + 64);
+    std::atomic<bool> &set = attr_set[blocks == 2][dev];
+    if (!set.load(std::memory_order_acquire)) {
+        e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                kMaxDictBytes + kWaves * kScratchPerWave + 64);
         if (e != hipSuccess) return e;
-        attr_set[dev].store(true, std::memory_order_release);
+        set.store(true, std::memory_order_release);
     }
-    hipLaunchKernelGGL((encode_resident_kernel<DC, OCC>), dim3((unsigned)groups), dim3(kThreads), lds_bytes, a.stream,
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kThreads), lds_bytes, a.stream,
                        (const __half *)a.X, (const __half *)a.D, a.idx, a.coef, a.T, M, a.N, a.s, a.sn, a.x_stride_h,
-                       a.x_stride_t, a.dict_count, a.code_stride_h, (int32_t)tiles, (int32_t)a.idx16,
+                       a.x_stride_t, a.dict_count, a.code_stride_h, (int32_t)tiles, blocks, (int32_t)a.idx16,
                        (a.coef16 ? kCoefF16 : 0) | (a.closed_loop ? kCoefClosed : 0), code_mask, a.res_norm2);
     return hipGetLastError();
 }
@@ -457,9 +495,7 @@ static hipError_t launch_resident_t(const EncodeArgs &a)
 hipError_t launch_encode_resident(const EncodeArgs &a)
 {
     if (a.d == 128) return launch_resident_t<128, 2>(a);
-    // two workgroups per CU when two dictionaries (and the waves' scratch) fit the 160 KB of LDS
-    const size_t lds = (size_t)a.N * 64 * 2 + kWaves * kScratchPerWave + 64;
-    return 2 * lds <= 160 * 1024 ? launch_resident_t<64, 4>(a) : launch_resident_t<64, 3>(a);
+    return two_per_cu(a) ? launch_resident_t<64, 4>(a) : launch_resident_t<64, 3>(a);
 }
 
 }  // namespace csr

@@ -892,8 +892,8 @@ bool encode_wide_supported(const EncodeArgs &a)
 
 size_t encode_wide_workspace_bytes(const EncodeArgs &a) { return wide_mode(a) == kRes ? 0 : plan_wide(a).total; }
 
-// 0.4: the preparation of the dictionary
-float encode_wide_cost(const EncodeArgs &a, int64_t vectors) { return 0.4f + wide_passes(a, vectors).cost; }
+// 0.4: the preparation of the dictionary, where there is one
+float encode_wide_cost(const EncodeArgs &a, int64_t vectors) { return (wide_mode(a) == kRes ? 0.0f : 0.4f) + wide_passes(a, vectors).cost; }
 
 hipError_t launch_encode_wide(const EncodeArgs &a)
 {

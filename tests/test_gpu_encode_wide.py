@@ -101,6 +101,17 @@ def test_same_bits_with_several_passes_per_workgroup(algo, dtype, d, N, T, H):
     assert torch.equal(iw, ie) and torch.equal(cw, ce)
 
 
+@pytest.mark.parametrize("N,d,T,H", [   # blocks per wave that the resident encoder's rule takes: 1, 2, 3, 4
+    (64, 128, 30001, 2), (96, 128, 60007, 2), (64, 128, 90001, 2), (32, 128, 131000, 2), (96, 64, 130001, 2), (1024, 64, 40001, 2),
+])
+def test_resident_encoder_with_one_to_four_blocks_per_wave(N, d, T, H):
+    X = torch.from_numpy(synth.vectors(11, "keys", H, T, d, "f16", outliers=4)).cuda()
+    D = torch.from_numpy(synth.dictionary(11, "dict_k", H, N, d, "f16")).cuda()
+    ir, cr = csr.csr_encode(X, D, 2, algo=csr.CSR_ENCODE_RESIDENT)
+    iw, cw = csr.csr_encode(X, D, 2, algo=csr.CSR_ENCODE_WIDE)
+    assert torch.equal(ir, iw) and torch.equal(cr, cw)
+
+
 @pytest.mark.parametrize("B,Hkv,T,N,sn", [
     (1, 2, 70000, 544, 1),     # one generation of the prefill encoder's workgroups, 4464 vectors of each dictionary left over
     (5, 3, 9001, 544, 1),      # sequences that share three dictionaries: the line lies inside one of them
