@@ -6,6 +6,8 @@
 // Bound: HBM writes (2 d bytes per vector in fp16 against 4 s bytes of code read); the atom rows come from L2.
 // Lane (vector, chunk, 8-dimension piece): all lanes of a vector's chunk read the same s pairs (one broadcast
 // load each) and gather 16 bytes of each of the s atom rows, so a chunk's rows are fetched as whole lines.
+#include <utility>
+
 #include "csr_internal.h"
 
 namespace csr {
@@ -200,6 +202,63 @@ __global__ __launch_bounds__(256) void reconstruct_few_kernel(const TD *__restri
     store8f(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
 }
 
+// The paper's storage, whole vectors of 128 dimensions or a multiple: the 16 lanes of a row share one code.  A lane requests ONE
+// 32-bit word of it (S words in all, indices before coefficients; two words with more than 16 pairs) and the row hands them
+// round; with every lane requesting the whole code, pairs were a fifth of the bytes that the texture path delivered.
+// Divisions are in 32 bits.  Same sum order.  32 x 4096 vectors (us): 4096 atoms, 8
+// pairs 19.2 -> 18.4, 6 pairs 17.8 -> 17.1, 8192 atoms, 16 pairs 40.5 -> 39.2; 256 atoms, 8 pairs 16.1 -> 14.9, twice the vectors with 4 pairs
+// 22.5 -> 18.7; 4096 atoms, 4 pairs level (14.5).  Workgroups that stay and request the next tile's words ahead are slower (8 pairs 18.9).
+template <int S, int W, int... K>
+__device__ __forceinline__ void hand_round(uint32_t (&code)[S], const uint32_t (&w)[W], std::integer_sequence<int, K...>)
+{
+    ((code[K] = (uint32_t)__builtin_amdgcn_mov_dpp((int)w[K / 16], 0x150 + K % 16, 0xf, 0xf, true)), ...);   // row_newbcast
+}
+
+template <typename TD, typename TO, int S>
+__global__ __launch_bounds__(256) void reconstruct_row_kernel(const TD *__restrict__ Dict, const uint32_t *__restrict__ idx,
+                                                              const uint32_t *__restrict__ coef, TO *__restrict__ out,
+                                                              uint32_t T, int32_t d, int32_t N, uint32_t sn, uint32_t dict_count,
+                                                              int64_t code_stride_h, int64_t out_stride_h,
+                                                              int64_t out_stride_t, uint32_t rows)
+{
+    constexpr int kWords = (S + 15) / 16, kHalf = S / 2;
+    const uint32_t rows_per_vec = (uint32_t)d >> 7, sub = threadIdx.x & 15;
+    const uint32_t r = (uint32_t)xcd_contiguous_block() * 16 + (threadIdx.x >> 4);   // row of lanes: (vector, 128 dimensions)
+    if (r >= rows) return;   // whole rows: the words below come from lanes that are there
+    const uint32_t v = rows_per_vec == 1 ? r : r / rows_per_vec, col = (r - v * rows_per_vec) * 128 + sub * 8;   // first dimension
+    const uint32_t dc = (uint32_t)d / sn, ch = sn == 1 ? 0 : col / dc, h = v / T, t = v - h * T;
+    const int64_t code = ((int64_t)h * code_stride_h + ((int64_t)t * sn + ch) * S) >> 1;   // in words: S is even
+    uint32_t w[kWords];
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+        const int k = min((int)sub + 16 * i, S - 1);
+        w[i] = (k < kHalf ? idx + k : coef + (k - kHalf))[code];
+    }
+    uint32_t words[S];
+    hand_round(words, w, std::make_integer_sequence<int, S>());
+    const TD *Dh = Dict + ((int64_t)(h % dict_count) * sn + ch) * N * dc + (col - ch * dc);
+    float acc[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) acc[k] = 0.0f;
+#pragma unroll
+    for (int j0 = 0; j0 < S; j0 += 8) {   // the rows of eight pairs in flight together
+        float row[8][8];
+#pragma unroll
+        for (int j = 0; j < 8 && j0 + j < S; ++j) {
+            const uint32_t n2 = words[(j0 + j) >> 1];
+            load8f<TD>(Dh + (int64_t)(j & 1 ? n2 >> 16 : n2 & 0xffffu) * dc, row[j]);
+        }
+#pragma unroll
+        for (int j = 0; j < 8 && j0 + j < S; ++j) {
+            const float2 cf = __half22float2(*reinterpret_cast<const __half2 *>(&words[kHalf + ((j0 + j) >> 1)]));
+            const float c = j & 1 ? cf.y : cf.x;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) acc[k] = fmaf(c, row[j][k], acc[k]);
+        }
+    }
+    store8f(out + (int64_t)h * out_stride_h + (int64_t)t * out_stride_t + col, acc);
+}
+
 template <typename TD, typename TI, typename TC, typename TO>
 hipError_t launch_t(const ReconstructArgs &a)
 {
@@ -208,6 +267,29 @@ hipError_t launch_t(const ReconstructArgs &a)
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     if constexpr (sizeof(TI) == 2 && sizeof(TC) == 2) {
+        // even s: every code starts at a 32-bit word
+        const bool words = a.code_stride_h % 2 == 0 && (reinterpret_cast<uintptr_t>(a.idx) % 4) == 0 &&
+                           (reinterpret_cast<uintptr_t>(a.coef) % 4) == 0;
+        if (words && a.s % 2 == 0 && (a.d / a.sn) % 128 == 0 && total / 16 < 0x7fffffffLL) {
+#define CSR_REC_ROW(S)                                                                                              \
+    case S:                                                                                                         \
+        hipLaunchKernelGGL((reconstruct_row_kernel<TD, TO, S>), grid, dim3(256), 0, a.stream, (const TD *)a.D,      \
+                           (const uint32_t *)a.idx, (const uint32_t *)a.coef, (TO *)a.out, (uint32_t)a.T, a.d, a.N, \
+                           (uint32_t)a.sn, (uint32_t)a.dict_count, a.code_stride_h, a.out_stride_h, a.out_stride_t, \
+                           (uint32_t)(total / 16));                                                                 \
+        return hipGetLastError()
+            switch (a.s) {
+                CSR_REC_ROW(2);
+                CSR_REC_ROW(4);
+                CSR_REC_ROW(6);
+                CSR_REC_ROW(8);
+                CSR_REC_ROW(16);
+                CSR_REC_ROW(24);
+                CSR_REC_ROW(32);
+                default: break;
+            }
+#undef CSR_REC_ROW
+        }
         const bool vec = a.s % 8 == 0 && a.code_stride_h % 8 == 0 && (reinterpret_cast<uintptr_t>(a.idx) % 16) == 0 &&
                          (reinterpret_cast<uintptr_t>(a.coef) % 16) == 0;
         if (vec) {
@@ -224,9 +306,6 @@ hipError_t launch_t(const ReconstructArgs &a)
 #undef CSR_REC_VEC
             return hipGetLastError();
         }
-        // even s: every code starts at a 32-bit word
-        const bool words = a.code_stride_h % 2 == 0 && (reinterpret_cast<uintptr_t>(a.idx) % 4) == 0 &&
-                           (reinterpret_cast<uintptr_t>(a.coef) % 4) == 0;
         if (a.s < 8 && (a.s % 2 == 1 || words)) {
 #define CSR_REC_FEW(NP)                                                                                             \
     hipLaunchKernelGGL((reconstruct_few_kernel<TD, TO, NP>), grid, dim3(256), 0, a.stream, (const TD *)a.D,         \

@@ -99,3 +99,33 @@ def test_short_codes_at_any_alignment(s, out_dtype):
     # s fp32 multiply-adds, then one rounding to the output type
     bound = size * s * 2.0 ** -23 + (ref.abs() * 2.0 ** -11 + 2.0 ** -25 if out_dtype == torch.float16 else 0.0)
     assert ((one.cpu().double() - ref).abs() <= bound).all()
+
+
+@pytest.mark.parametrize("dict_dtype,out_dtype", [(torch.float16, torch.float16), (torch.float16, torch.float32), (torch.float32, torch.float16)])
+@pytest.mark.parametrize("s", [2, 4, 6, 8, 10, 16, 24, 32])
+def test_whole_vectors_share_their_code_over_a_row_of_lanes(s, dict_dtype, out_dtype):
+    # codes that start at a 32-bit word are handed round in a row of 16 lanes; off a word every lane reads its pairs one by one:
+    # the sums have one order, so the bits are equal.  131 tokens: the last workgroup is partly filled.
+    N, gen = 320, torch.Generator().manual_seed(90 + s)
+    for H, T, d, sn, dicts in [(1, 1, 128, 1, 1), (4, 131, 128, 1, 2), (2, 131, 256, 1, 2), (2, 35, 384, 1, 1), (2, 35, 256, 2, 2)]:
+        D = torch.randn(dicts, sn, N, d // sn, generator=gen).to(dict_dtype)
+        idx = torch.randint(0, N, (H, T + 3, sn, s), generator=gen).short()
+        coef = torch.randn(H, T + 3, sn, s, generator=gen).half()
+        idx[0, 0], idx[-1, T - 1] = 0, N - 1
+        if sn == 1:
+            D, idx, coef = D[:, 0], idx[:, :, 0], coef[:, :, 0]
+        D, idx, coef = D.cuda(), idx.cuda(), coef.cuda()
+
+        def off_a_word(t):
+            buf = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+            return buf[1:].view(t.shape).copy_(t)
+        one = csr.csr_reconstruct(D, idx[:, :T], coef[:, :T], out_dtype=out_dtype)   # a window of a longer cache
+        two = csr.csr_reconstruct(D, off_a_word(idx)[:, :T], off_a_word(coef)[:, :T], out_dtype=out_dtype)
+        assert torch.equal(one, two), (H, T, d, sn)
+        Dc, ic, cc = (x if sn > 1 else x.unsqueeze(-3 if x is D else -2) for x in (D, idx, coef))
+        blocks = Dc.cpu().double()[torch.arange(H) % dicts]                               # [H, sn, N, dc]
+        rows = torch.stack([torch.stack([blocks[h, c][ic[h, :T, c].cpu().long()] for c in range(sn)], 1) for h in range(H)])
+        terms = rows * cc[:, :T].cpu().double().unsqueeze(-1)                             # [H, T, sn, s, dc]
+        ref, size = terms.sum(3).view(H, T, d), terms.abs().sum(3).view(H, T, d)
+        bound = size * s * 2.0 ** -23 + (ref.abs() * 2.0 ** -11 + 2.0 ** -25 if out_dtype == torch.float16 else 0.0)
+        assert ((one.cpu().double() - ref).abs() <= bound).all(), (H, T, d, sn)
