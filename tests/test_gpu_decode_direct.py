@@ -34,6 +34,17 @@ def test_short_contexts(B, Hq, Hkv, T, N, sK, sV, dtype):
     _check(out[lens > 0], ref[lens > 0], TOL_F16_OUT if dtype == "f16" else TOL_F32_OUT, f"direct {B} {Hq} {Hkv} {T}")
 
 
+@pytest.mark.parametrize("chunks", [2, 16, 17, 64, 65, 128, 129, 256, 257, 520])
+def test_the_combine_of_any_number_of_chunks(chunks):
+    # one head: chunks of 16 tokens; the shorter sequence leaves its last chunks without tokens, never written
+    T = 16 * chunks - 5
+    args = _case(65, 2, 2, 1, T, 256, 2, 2) if chunks <= 256 else _case(65, 1, 2, 1, T, 256, 2, 2)
+    lens = np.full(args[0].shape[0], T, dtype=np.int32)
+    lens[-1] = T if len(lens) == 1 else 16 * (chunks // 2) + 1
+    ref = oracle.decode_attn(*args[:2], *(a if i % 3 else _u16(a) for i, a in enumerate(args[2:])), seq_lens=lens)
+    _check(_run(*args, seq_lens=lens), ref, TOL_F16_OUT, f"combine of {chunks} chunks")
+
+
 @pytest.mark.parametrize("snK,sK,snV,sV", [(1, 8, 2, 4), (2, 4, 4, 2), (8, 2, 8, 3)])
 def test_short_contexts_in_chunks(snK, sK, snV, sV):
     q, DK, iK, cK, DV, iV, cV = _chunked_case(62, 2, 4, 2, 150, 256, snK, sK, snV, sV)
