@@ -319,9 +319,10 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 const int kk = (int)(pick & 15u);
                 const int tile0 = ntiles - 1 - (int)(best_u & code_mask);
                 best_n = tile0 * 32 + 4 * best_half + 8 * (kk >> 2) + (kk & 3);
-                const bool unsure = !zero && (ncand > 1 || overflow || (pick & 16u) != 0u);
+                const bool unsure = valid && !zero && (ncand > 1 || overflow || (pick & 16u) != 0u);
 
-                // the undecided vectors, one at a time, by the whole wave (both lanes of a pair agree on `unsure`)
+                // the undecided vectors, one at a time, by the whole wave (both lanes of a pair agree on `unsure`); not the
+                // copies of the last vector past the end, whose picks nobody reads
                 uint32_t todo = (uint32_t)__ballot(unsure);
                 while (todo) {
                     const int t = __ffs((int)todo) - 1;

@@ -647,8 +647,8 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
             ends = row_reduce<L>(ends, OpPkMax());
             count = row_reduce<L>(count, OpAdd());
             int n_lo = min(65535 - (int)(ends & 0xffffu), p.N - 1), n_hi = min((int)(ends >> 16), p.N - 1);
-            // vectors with more candidates, one at a time, by the whole wave
-            unsigned long long todo = __ballot(!zero && count != 1u && count != 2u && sub == 0);
+            // vectors with more candidates, one at a time, by the whole wave (what stands past the end is not worth it)
+            unsigned long long todo = __ballot(st.code_at >= 0 && !zero && count != 1u && count != 2u && sub == 0);
             while (todo) {
                 const int lead = __ffsll((long long)todo) - 1;   // first lane of the vector's team
                 todo &= todo - 1;

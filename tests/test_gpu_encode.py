@@ -767,3 +767,36 @@ def test_closed_loop_with_fp32_coefficients_is_the_open_loop():
         assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
     with pytest.raises(csr.CsrError, match="CLOSED_LOOP"):
         csr.csr_encode(Xg[:, :4], Dg[:, :256], s, algo=csr.CSR_ENCODE_GRAM, closed_loop=True)
+
+
+def _least_us(call, runs=12, calls=4):
+    best = np.inf
+    for _ in range(runs):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        call()
+        start.record()
+        for _ in range(calls):
+            call()
+        end.record()
+        end.synchronize()
+        best = min(best, start.elapsed_time(end) * 1000 / calls)
+    return best
+
+
+@pytest.mark.parametrize("algo,T,N,d", [("resident", 257, 512, 128), ("resident", 513, 512, 64), ("mfma", 257, 1024, 128), ("mfma", 65, 1024, 64),
+                                        ("wide", 33, 1024, 128)])
+def test_copies_of_the_last_vector_past_the_end_are_not_resolved(algo, T, N, d):
+    # lanes past the last vector work on copies of it.  A last vector that no bound decides (four sums of atoms that are there
+    # three times) costs what any undecided vector costs, not a resolve for each of its copies, one after the other
+    D = synth.dictionary(110, "dict_k", 1, N, d, "f16")
+    D[0, N // 2:N // 2 + 4] = D[0, :4]
+    D[0, N - 4:] = D[0, :4]
+    X = synth.vectors(110, "values", 1, T, d, "f16")
+    tied = X.copy()
+    tied[0, -1] = (np.array([8, 4, 2, 1], dtype=np.float32) @ D[0, :4].astype(np.float32)).astype(np.float16)
+    Dg, run = torch.from_numpy(D).cuda(), {"wide": csr.CSR_ENCODE_WIDE, **ALGOS}[algo]
+    calls = [lambda x=torch.from_numpy(x).cuda(): csr.csr_encode(x, Dg, 4, algo=run) for x in (X, tied)]
+    idx = calls[1]()[0].cpu().numpy()
+    assert idx[0, -1, 0] == 0
+    plain, undecided = (_least_us(c) for c in calls)
+    assert undecided < 1.4 * plain, (plain, undecided)   # with the copies 2 to 7 times as long
