@@ -53,12 +53,11 @@ int64_t auto_head(const csr::EncodeArgs &a, int algo)
         case CSR_ENCODE_RESIDENT: return csr::encode_wide_cost(a, M) < csr::encode_resident_cost(a) ? 0 : M;
         case CSR_ENCODE_MFMA: {
             if (a.d == 32) return M;
-            const float gen = csr::encode_mfma_generation_cost(a);
             const int64_t per = csr::kMfmaWorkgroupVectors, groups = (M + per - 1) / per * dicts, full = groups / csr::kCus;
-            // a last, partial generation: 0.83 to 0.9 of a full one
-            const float own = gen * ((float)full + (groups % csr::kCus ? 0.87f : 0.0f)), wide = csr::encode_wide_cost(a, M);
+            const int64_t halves = (M + per / 2 - 1) / (per / 2) * dicts;
+            const float own = csr::encode_mfma_cost(a, full, groups % csr::kCus != 0, full == 0 && halves <= csr::kCus), wide = csr::encode_wide_cost(a, M);
             const int64_t head = full * csr::kCus / dicts * per;   // what fills whole generations
-            const float both = head > 0 && head < M ? gen * (float)full + csr::encode_wide_cost(a, M - head) : own;
+            const float both = head > 0 && head < M ? csr::encode_mfma_cost(a, full, false, false) + csr::encode_wide_cost(a, M - head) : own;
             if (wide <= own && wide <= both) return 0;
             return both < own ? head : M;
         }

@@ -55,8 +55,9 @@ hipError_t launch_encode_wide(const EncodeArgs &a);
 
 // fp16 matrix-core encoder: chunks of 64 or 128 dimensions, fp16 inputs.
 bool encode_mfma_supported(const EncodeArgs &a);
-// What one full generation of its 512-vector workgroups (one per CU) costs, in the unit of encode_wide_cost.
-float encode_mfma_generation_cost(const EncodeArgs &a);
+// What `full` generations of its 512-vector workgroups (one per CU) cost, in the unit of encode_wide_cost, and where there is `more`, a
+// partial one besides (`half`: of at most one 256-vector workgroup per CU).
+float encode_mfma_cost(const EncodeArgs &a, int64_t full, bool more, bool half);
 constexpr int64_t kMfmaWorkgroupVectors = 512, kCus = 256;
 size_t encode_mfma_workspace_bytes(int32_t n_dicts, int64_t T, int32_t N, int32_t s);
 hipError_t launch_encode_mfma(const EncodeArgs &a);

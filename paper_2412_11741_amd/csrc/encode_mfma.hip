@@ -600,11 +600,15 @@ bool encode_mfma_supported(const EncodeArgs &a)
     return a.f16 && (a.d == 128 || a.d == 64 || a.d == 32) && a.N >= 32 && a.N % 32 == 0 && a.N <= 65536;
 }
 
-// Measured on 16 dictionaries, s = 8 (us; the wide encoder's pass: 25 at N = 1024, 68 at 4096, 64-dimensional 35 at 1536 and
-// 66 at 4096): a generation takes 320 at N = 1024 and 945 at 4096, of 64-dimensional chunks 260 at 1536 and 585 at 4096.
-float encode_mfma_generation_cost(const EncodeArgs &a)
+// Measured on 8 dictionaries, s = 8, in passes of the wide encoder (us at N = 640, 1024, 2048, 4096: 21, 25, 36, 62; of 64-dimensional chunks at
+// 1280, 2048, 4096: 26, 34, 57): a full generation takes 269, 345, 564, 999 and 221, 318, 545.  A partial one that is more than one
+// workgroup of 256 vectors per CU: 252, 315, 483, 890 with 0.6 of the vectors, and 216, 297, 513; one that is not: 208, 260, 409, 691 with
+// half of them, 203, 253, 392, 703 with a fifth, and 184, 254, 466.
+float encode_mfma_cost(const EncodeArgs &a, int64_t full, bool more, bool half)
 {
-    return a.d == 128 ? 14.5f - 2000.0f / (float)a.N : 9.5f - 3200.0f / (float)a.N;
+    const bool whole = a.d == 128;
+    const float gen = whole ? 16.8f - 2700.0f / (float)a.N : 10.0f - 2000.0f / (float)a.N;
+    return gen * ((float)full + (!more ? 0.0f : half ? (whole ? 0.75f : 0.83f) : (whole ? 0.9f : 0.95f)));
 }
 
 size_t encode_mfma_workspace_bytes(int32_t H, int64_t T, int32_t N, int32_t s)

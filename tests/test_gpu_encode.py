@@ -800,3 +800,17 @@ def test_copies_of_the_last_vector_past_the_end_are_not_resolved(algo, T, N, d):
     assert idx[0, -1, 0] == 0
     plain, undecided = (_least_us(c) for c in calls)
     assert undecided < 1.4 * plain, (plain, undecided)   # with the copies 2 to 7 times as long
+
+
+@pytest.mark.parametrize("heads,T,N,s_n", [(32, 1289, 2048, 2), (3, 31799, 2048, 1), (12, 5666, 640, 1), (8, 4812, 2560, 2), (4, 22694, 4096, 1)])
+def test_auto_takes_neither_the_slower_encoder(heads, T, N, s_n):
+    # partial generations of the prefill encoder cost nearly a full one: at these sizes it took up to 1.5 times the wide encoder's time
+    s, d = 4, 128 // s_n
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(111)
+    D = torch.randn((heads, s_n, N, d) if s_n > 1 else (heads, N, d), device="cuda", generator=gen)
+    D = (D / D.norm(dim=-1, keepdim=True)).half()
+    X = torch.randn(heads, T, 128, device="cuda", generator=gen).half()
+    auto, mfma, wide = (_least_us(lambda a=a: csr.csr_encode(X, D, s, algo=a), runs=6, calls=2)
+                        for a in (csr.CSR_ENCODE_AUTO, csr.CSR_ENCODE_MFMA, csr.CSR_ENCODE_WIDE))
+    assert auto < 1.08 * min(mfma, wide), (auto, mfma, wide)
