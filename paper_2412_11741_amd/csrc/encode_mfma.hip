@@ -670,8 +670,9 @@ hipError_t launch_encode_mfma_t(const EncodeArgs &a)
         n_cus[dev].store(v > 0 ? v : 1, std::memory_order_release);
     }
     const int cus = n_cus[dev].load(std::memory_order_relaxed);
-    // 512-vector workgroups (one per CU) once there is one for every CU
-    const int64_t M = a.m_end;
+    // 512-vector workgroups (one per CU) once there is one for every CU.  All vectors of the call count, also where the wide encoder takes
+    // the last of them: what is left here are whole generations of these, up to a workgroup per dictionary
+    const int64_t M = (int64_t)(a.H / a.dict_count) * a.T;
     const int64_t groups8 = (M + 8 * kTokPerWave - 1) / (8 * kTokPerWave) * a.dict_count * a.sn;
     if (groups8 >= (int64_t)cus) return launch_encode_mfma_w<DC, 8>(a);
     return launch_encode_mfma_w<DC, 4>(a);
