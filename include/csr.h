@@ -161,7 +161,9 @@ csr_status csr_encode(const csr_encode_desc *desc, const void *X, const void *D,
  * V-side histogram, which is summed exactly in fixed point with integer atomics (per chunk of at most 16384 tokens: 32-bit
  * bins whose unit is fitted to the data, checked after the scatter for overflow and for resolution, and repeated in 64-bit
  * bins where the check fails), so the result does not depend on the order in which the hardware serves the scatter: the
- * same inputs give the same bits on every run.
+ * same inputs give the same bits on every run.  How the tokens of a sequence are cut into chunks follows from the descriptor
+ * and, where contexts are long and lengths are given, from the lengths of ALL sequences of the batch: the low bits of one
+ * sequence's output (about 1e-5 of it) may depend on the others' lengths.
  */
 typedef struct {
     int32_t B;          /* sequences; >= 0                                                  */

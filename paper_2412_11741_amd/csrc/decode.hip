@@ -262,7 +262,8 @@ __global__ __launch_bounds__(256) void qd_rows_kernel(const __half *__restrict__
 // NP > 0: a token's key code and its value code have NP pairs each, in all chunks together: the whole codes are
 // requested ahead of their use - the first rounds' before the score table is loaded - so that several round trips to
 // memory overlap.  NP = 0: any number of pairs, PV of a chunk at a time, loaded where they are used.
-template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int NP, int THREADS = kStreamThreads>
+// CUT_FROM: see chunk_of.
+template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int NP, int THREADS, int CUT_FROM>
 __global__ __launch_bounds__(THREADS) void stream_kernel(
     const float *__restrict__ qd, const TI *__restrict__ idxK, const TC *__restrict__ coefK,
     const TI *__restrict__ idxV, const TC *__restrict__ coefV, const int32_t *__restrict__ seq_lens,
@@ -284,7 +285,7 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
     // (KV head, group slice) is the fastest grid dimension: workgroups are dealt to the 8 XCDs round-robin in that
     // order, so the chunks of one (sequence, KV head) - which load the same score table - tend to share an L2
     const int h = blockIdx.x / ngs, gs = blockIdx.x % ngs;
-    const Chunk part = chunk_of<THREADS, 12288>(seq_lens, T, nchunks, chunk_tokens);
+    const Chunk part = chunk_of<THREADS, CUT_FROM>(seq_lens, T, nchunks, chunk_tokens);
     const int c = part.c, b = part.b;
     const int64_t t0 = part.t0, t_end = part.t_end;
     const int64_t slot = (((int64_t)b * Hkv + h) * ngs + gs) * nchunks + c;
@@ -905,10 +906,17 @@ __global__ __launch_bounds__(256) void finalize_kernel(const float *__restrict__
     }
 }
 
-template <int GB, typename TI, typename TC, int PV, bool CH, int TPT = max_rounds(GB), int NP = 0, int THREADS = kStreamThreads>
+// Codes requested as a whole: a variant of its own for calls that are cut by lengths (long contexts without lengths lost 0.4 % by carrying
+// its code); other codes have one for all calls.
+template <int GB, typename TI, typename TC, int PV, bool CH, int TPT = max_rounds(GB), int NP = 0, int THREADS = kStreamThreads, bool LONG = (TPT * THREADS >= kCutFromStream),
+          int CUT_FROM = (NP == 0 && LONG ? kCutFromStream : 0)>
 hipError_t launch_stream_t(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
 {
-    auto kern = stream_kernel<GB, TI, TC, PV, CH, TPT, NP, THREADS>;
+    if constexpr (LONG && CUT_FROM == 0) {
+        if (cut_by_lengths(a.seq_lens, p.nchunks, a.B, p.chunk_tokens, kCutFromStream))
+            return launch_stream_t<GB, TI, TC, PV, CH, TPT, NP, THREADS, LONG, kCutFromStream>(a, p, qd, hist, ml);
+    }
+    auto kern = stream_kernel<GB, TI, TC, PV, CH, TPT, NP, THREADS, CUT_FROM>;
     // raising the dynamic-LDS limit is needed once per kernel and device
     static std::atomic<bool> attr_set[kMaxDevices];
     int dev = 0;

@@ -368,6 +368,25 @@ template <bool CH, int NP> struct ChunkBase {
 // their side of it, so that only the explicitly requested vectors (fetch_codes) are in flight.
 __device__ __forceinline__ void round_fence() { asm volatile("" ::: "memory"); }
 
+// Long chunks (this many tokens or more), several per sequence, are cut anew where lengths are given: see chunk_of.
+constexpr int kCutFromStream = 12288, kCutFromRope = 4096;
+inline bool cut_by_lengths(const int32_t *seq_lens, int nchunks, int B, int64_t chunk_tokens, int from)
+{
+    return seq_lens && nchunks > 1 && B <= 64 && chunk_tokens >= from;
+}
+
+template <int CTRL, int ROWS> __device__ __forceinline__ int scan_step(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+// sum of v over the lanes up to this one
+__device__ __forceinline__ int wave_scan(int v)
+{
+    v = scan_step<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8: sums within the rows of 16 lanes
+    v = scan_step<0x112, 0xf>(v);
+    v = scan_step<0x114, 0xf>(v);
+    v = scan_step<0x118, 0xf>(v);
+    v = scan_step<0x142, 0xa>(v);   // row_bcast 15: rows 0 and 2 to rows 1 and 3
+    return scan_step<0x143, 0xc>(v);   // row_bcast 31: the first half to the second
+}
+
 // A workgroup's part of the work: tokens [t0, t_end) of sequence b, its chunk c (of slots 0 .. nchunks - 1; one without tokens has
 // t_end <= t0).  The grid is (heads, nchunks, B): KV heads x group slices first.
 struct Chunk {
@@ -379,15 +398,21 @@ struct Chunk {
 // so that those without tokens come last: one that ends at once in the middle of the numbers gives one shader engine a
 // workgroup more than it has CUs, and another one less.  A workgroup costs about kFixedRounds rounds besides its own, so a
 // sequence gets as few chunks as the plan's size allows, or more (at most the plan's number) where the whole launch then
-// makes cheaper generations of 256 workgroups, one per CU.  All of it follows from the lengths alone, and every wave works it out
-// for itself, in about 2 us: shorter chunks, one chunk per sequence and more than 64 sequences keep the plan's.  8 sequences of
-// 73728 to 131072 tokens, 8 KV heads x 4 query heads 147 us before, 136 now; 20 sequences of 15000 to 30000, 4 x 8 heads 134 and 113.
+// makes cheaper generations of 256 workgroups, one per CU.  All of it follows from the lengths alone - of all sequences: the low bits
+// of one's output depend on the others' - and every wave works it out for itself, in about a microsecond: shorter chunks, one chunk per
+// sequence and more than 64 sequences keep the plan's.  CUT_FROM = 0: all calls do, and the kernel does not carry the code.
+// 8 sequences of 73728 to 131072 tokens, 8 KV heads x 4 query heads 146 us with the plan's chunks, 134 longest first, 136 to 143 in other
+// orders; 20 sequences of 15000 to 30000, 4 x 8 heads 134 and 113; 50 random batches of 2 to 64 sequences 0.83 of the time, the worst 1.03.
+// The lines, by the time with the cut over the time without (9 random batches each): chunks of up to 4096 tokens 0.99, 8192 0.92, 12288
+// 0.97, 16384 0.82; rotary keys of up to 1024 0.95, 2048 0.92, 3072 0.90.  So a lower line would pay, too, with more variants of
+// the kernels.  0.92: with 1.0 the same (stream), 5 % either way (rotary keys).  Tried: longest first in every batch, and prices by
+// the chunks as they come out; what every workgroup pays for that is more than it brings (64 sequences 91 -> 112 us).
 template <int THREADS, int CUT_FROM>
 __device__ __forceinline__ Chunk chunk_of(const int32_t *__restrict__ seq_lens, int64_t T, int nchunks, int64_t chunk_tokens)
 {
     constexpr float kFixedRounds = 7.0f;
     const int B = gridDim.z, heads = gridDim.x, lane = threadIdx.x & 63;
-    if (__builtin_expect(!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM, 1)) {
+    if (CUT_FROM == 0 || __builtin_expect(!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM, 1)) {
         int64_t len = T;
         if (seq_lens) {
             const int32_t l = seq_lens[blockIdx.z];
@@ -415,10 +440,14 @@ __device__ __forceinline__ Chunk chunk_of(const int32_t *__restrict__ seq_lens, 
     // workgroup j of a head: the j-th of all sequences' chunks, or, behind the last, the (j - all)-th empty slot
     const int n = lane < B ? chunks(r) : 0;
     int upto = n;
+    if constexpr (CUT_FROM == kCutFromRope) {   // with the shorter form the rotary kernel's loop comes out 1 - 3 % slower (one head, 8 pairs)
 #pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-        const int o = __shfl_up(upto, m, 64);
-        if (lane >= m) upto += o;
+        for (int m = 1; m < 64; m <<= 1) {
+            const int o = __shfl_up(upto, m, 64);
+            if (lane >= m) upto += o;
+        }
+    } else {
+        upto = wave_scan(n);
     }
     const int j = (int)(blockIdx.y + nchunks * blockIdx.z), all = __builtin_amdgcn_readlane(upto, 63);
     const bool empty = j >= all;

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(rope_threads(GB)) void stream_rope_kernel(
     const int lane = tid & 63, wave = tid >> 6;
     const int sub = lane & 7, eighth = lane >> 3;
     const int h = blockIdx.x / ngs, gs = blockIdx.x % ngs;
-    const Chunk part = chunk_of<THREADS, 4096>(seq_lens, T, nchunks, chunk_tokens);
+    const Chunk part = chunk_of<THREADS, kCutFromRope>(seq_lens, T, nchunks, chunk_tokens);
     const int c = part.c, b = part.b;
     const int64_t t0 = part.t0, t_end = part.t_end;
     const int64_t slot = (((int64_t)b * Hkv + h) * ngs + gs) * nchunks + c;

@@ -52,3 +52,16 @@ def test_rotary_kernels_spill_no_more_for_value_codes_requested_ahead(kernels):
     assert len(by_shape) > 8
     for shape, sizes in by_shape.items():
         assert max(map(max, sizes.values())) <= max(sizes[0]), shape
+
+
+def test_only_long_chunks_carry_the_cut_by_lengths(kernels):
+    # whole codes: a variant with the cut and one without where a chunk may be long enough for it, else one without
+    found = {}
+    for n in kernels:
+        m = re.search(r"stream_kernelILi(\d+)E(t|i)(.*?)Li(\d+)ELb(\d)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E", n)
+        if m:
+            heads, index, coef, piece, chunked, rounds, pairs, threads, cut_from = m.groups()
+            if int(pairs) > 0:
+                found.setdefault((heads, chunked, pairs, int(rounds) * int(threads)), set()).add(int(cut_from))
+    assert len(found) > 30
+    assert {k: v for k, v in found.items() if v != ({0, 12288} if k[3] >= 12288 else {0})} == {}

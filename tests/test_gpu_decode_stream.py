@@ -69,16 +69,20 @@ def test_both_halves_of_a_code_are_sampled():
     assert np.array_equal(one, np.concatenate([two[..., 64:], two[..., :64]], axis=-1))
 
 
-@pytest.mark.parametrize("B,Hkv,G,T,N,rope_base", [
-    (13, 8, 4, 60000, 256, 0.0),       # 8-wave shape, four chunks of the plan
-    (6, 32, 1, 40000, 128, 0.0),       # 16-wave shape, one query head
-    (64, 1, 4, 50000, 128, 0.0),       # as many sequences as a wave has lanes
-    (9, 8, 4, 16000, 128, 10000.0),    # rotary keys, a group
-    (5, 32, 1, 12000, 64, 10000.0),    # rotary keys, one query head
+@pytest.mark.parametrize("B,Hkv,G,T,N,s,rope_base", [
+    (13, 8, 4, 60000, 256, 4, 0.0),       # 8-wave shape, four chunks of the plan
+    (6, 32, 1, 40000, 128, 4, 0.0),       # 16-wave shape, one query head
+    (13, 8, 2, 40000, 128, 4, 0.0),       # two query heads
+    (7, 16, 1, 40000, 128, 5, 0.0),       # codes that are not requested as a whole: one kernel, with and without the cut
+    (64, 1, 4, 50000, 128, 4, 0.0),       # as many sequences as a wave has lanes
+    (65, 1, 4, 50000, 128, 4, 0.0),       # one more: the plan's chunks
+    (9, 8, 4, 16000, 128, 4, 10000.0),    # rotary keys, a group
+    (13, 8, 2, 18000, 128, 4, 10000.0),   # rotary keys, two query heads
+    (5, 32, 1, 12000, 64, 4, 10000.0),    # rotary keys, one query head
 ])
-def test_long_sequences_are_cut_by_their_own_lengths(B, Hkv, G, T, N, rope_base):
+def test_long_sequences_are_cut_by_their_own_lengths(B, Hkv, G, T, N, s, rope_base):
     # lengths of 0, 1, the edges of the plan's chunks and rounds, out of range on both sides; sampled pairs against the oracle
-    s, d = 4, 128
+    d = 128
     gen = torch.Generator(device="cuda")
     gen.manual_seed(75)
     unit = lambda *sh: (lambda a: (a / a.norm(dim=-1, keepdim=True)).half())(torch.randn(*sh, device="cuda", generator=gen))
