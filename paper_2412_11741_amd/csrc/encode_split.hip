@@ -194,7 +194,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
     // The best candidate of vectors m0 .. m0 + 31 over the tiles first, first + step .. below last, as a packed word with
     // `tag` (lanes col of either half); `own`: this wave's tiles of the workgroup's slice, the first ones in registers.
     // kNarrow (at most 16 vectors): hi takes columns 0 - 15 and lo columns 16 - 31: one pass of matrix instructions instead of two, and
-    // half the values per lane behind it.
+    // half the values per lane behind it.  hi . d and lo . d are then sums of their own instead of one chain: the low bits of a
+    // coefficient, and at a tie the atom, are not those of a launch with more vectors.  Error of a coefficient against 64 bits, over |R| (128
+    // dimensions, 4096 atoms, s = 8): 2.4e-8 on average and 1.1e-7 at most, with more vectors 3.0e-8 and 1.5e-7.
     auto sweep = [&](int m0, int first, int last, int step, bool own, int tag) {
         half8 hi[kFrags], lo[kNarrow ? 1 : kFrags];
         // columns past the last vector repeat it: one LDS address for them all

@@ -66,3 +66,29 @@ def test_codes_do_not_depend_on_who_computed_them(dicts, M, N, d, s, sn, closed)
         torch.cuda.synchronize()
         got.append((idx, coef, err))
     assert all(torch.equal(a, b) for a, b in zip(*got))
+
+
+@pytest.mark.parametrize("d,N,s", [(128, 4096, 8), (64, 2048, 8), (128, 320, 3)])
+def test_sixteen_vectors_are_coded_as_in_a_launch_of_seventeen(d, N, s):
+    # with at most 16 vectors hi . d and lo . d are sums of their own, with more one chain: 2 d products either way, whose rounding
+    # errors have a standard deviation of sqrt(2 d) 2^-25 |R| |d| = 4.8e-7 |R| at most.  Four of them for a coefficient, and atoms agree
+    # wherever the two largest correlations are further apart than both launches' errors
+    dicts, bound = 6, 4 * (2 * d) ** 0.5 * 2.0 ** -25
+    D = torch.from_numpy(synth.dictionary(95, "dict_k", dicts, N, d, "f16")).cuda()
+    X = torch.from_numpy(synth.vectors(95, "keys", dicts, 17, d, "f16", outliers=4)).cuda()
+    (i16, c16), (i17, c17) = ([t[:, :16] for t in csr.csr_encode(X[:, :M].contiguous(), D, s, algo=csr.CSR_ENCODE_SPLIT, coef_dtype=torch.float32)]
+                              for M in (16, 17))
+    i16, i17 = i16.long() & 0xffff, i17.long() & 0xffff
+    D64, R = D.double(), X[:, :16].double()
+    sure = torch.ones(dicts, 16, dtype=torch.bool, device="cuda")
+    for g in range(s):
+        first, second = (R @ D64.transpose(1, 2).contiguous()).abs().topk(2, dim=-1).values.unbind(-1)
+        error = bound * R.norm(dim=-1)
+        sure &= first - second > 2 * error
+        atom = D64.gather(1, i16[:, :, g, None].expand(-1, -1, d))
+        exact = (R * atom).sum(-1)
+        assert torch.equal(i16[:, :, g][sure], i17[:, :, g][sure])
+        for c in (c16, c17):
+            assert ((c[:, :, g].double() - exact).abs() <= error)[sure].all()
+        R = R - exact[..., None] * atom
+    assert sure.float().mean() > 0.9
