@@ -65,3 +65,10 @@ def test_only_long_chunks_carry_the_cut_by_lengths(kernels):
                 found.setdefault((heads, chunked, pairs, int(rounds) * int(threads)), set()).add(int(cut_from))
     assert len(found) > 30
     assert {k: v for k, v in found.items() if v != ({0, 12288} if k[3] >= 12288 else {0})} == {}
+
+
+def test_the_wide_encoder_spills_little(kernels):
+    # vectors of 128 dimensions in passes of 32: with four and five of them a few registers more than there are
+    wide = {n: k["vgpr_spill_count"] for n, k in kernels.items() if "encode_wide_kernel" in n}
+    assert len(wide) > 20
+    assert {n: v for n, v in wide.items() if v > (20 if re.search(r"Li128ELi[01]ELi8ELi[45]E", n) else 0)} == {}

@@ -34,13 +34,18 @@ def test_short_contexts(B, Hq, Hkv, T, N, sK, sV, dtype):
     _check(out[lens > 0], ref[lens > 0], TOL_F16_OUT if dtype == "f16" else TOL_F32_OUT, f"direct {B} {Hq} {Hkv} {T}")
 
 
-@pytest.mark.parametrize("chunks", [2, 16, 17, 64, 65, 128, 129, 256, 257, 520])
+@pytest.mark.parametrize("chunks", [2, 16, 17, 64, 65, 128, 129, 256, 257, 513, 1024])
 def test_the_combine_of_any_number_of_chunks(chunks):
     # one head: chunks of 16 tokens; the shorter sequence leaves its last chunks without tokens, never written
     T = 16 * chunks - 5
-    args = _case(65, 2, 2, 1, T, 256, 2, 2) if chunks <= 256 else _case(65, 1, 2, 1, T, 256, 2, 2)
-    lens = np.full(args[0].shape[0], T, dtype=np.int32)
-    lens[-1] = T if len(lens) == 1 else 16 * (chunks // 2) + 1
+    B, Hq = (2, 2) if chunks <= 256 else (1, 1)   # two query heads: at most 256 chunks for each of two sequences; one: 1024
+    args = _case(65, B, Hq, 1, T, 256, 2, 2)
+    lens = np.full(B, T, dtype=np.int32)
+    lens[-1] = 16 * (chunks // 2) + 1
+    if chunks >= 16:   # the scratch is what so many partial outputs and their weights take
+        t = [torch.from_numpy(a) for a in args]
+        up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+        assert csr.csr_decode_workspace_bytes(csr.decode_desc(t[0], t[1], t[2], t[3], t[5])) == up(B * Hq * chunks * 512) + up(B * Hq * chunks * 8)
     ref = oracle.decode_attn(*args[:2], *(a if i % 3 else _u16(a) for i, a in enumerate(args[2:])), seq_lens=lens)
     _check(_run(*args, seq_lens=lens), ref, TOL_F16_OUT, f"combine of {chunks} chunks")
 

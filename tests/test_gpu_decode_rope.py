@@ -83,10 +83,11 @@ def test_rotary_keys_shapes(B, Hq, Hkv, T, N, sK, sV, snV, layout, pos0):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,T,N,sK,sV,snV,layout,pos0,lens", [
-    (1, 4, 4, 8193, 256, 8, 8, 1, 0, 0, [8193]),         # one token past eight full rounds: steps of one token in a last chunk
+    # (chunks of one round each: several rounds are the next test's)
+    (1, 4, 4, 8193, 256, 8, 8, 1, 0, 0, [8193]),         # one token past eight full chunks: steps of one token in a last one
     (2, 4, 4, 9000, 256, 4, 4, 1, 0, 7, [9000, 65]),     # whole codes of 4 key pairs; a wave of one token
     (1, 8, 2, 32800, 512, 4, 4, 1, 1, 0, [32767]),       # the same for a group of 4; a length below the buffer's
-    (1, 4, 2, 16500, 384, 16, 4, 1, 0, 0, [16421]),      # a group of 2, two blocks of 8 key pairs, last round ragged inside a step
+    (1, 4, 2, 16500, 384, 16, 4, 1, 0, 0, [16421]),      # a group of 2, two blocks of 8 key pairs, a last chunk ragged inside a step
     (2, 8, 8, 2100, 256, 12, 8, 1, 1, 100, [2100, 1]),   # three blocks of 4 key pairs, a single token
 ])
 def test_rotary_keys_streamed_at_the_edges_of_rounds_and_steps(B, Hq, Hkv, T, N, sK, sV, snV, layout, pos0, lens):
@@ -95,6 +96,46 @@ def test_rotary_keys_streamed_at_the_edges_of_rounds_and_steps(B, Hq, Hkv, T, N,
     out = _run(args, 10000.0, layout, pos0, seq_lens=lens)
     ref = oracle.decode_attn_rope(*args, 10000.0, layout, pos0, seq_lens=np.asarray(lens, dtype=np.int32))
     _check(out, ref, f"streamed: B{B} Hq{Hq} Hkv{Hkv} T{T} N{N} s{sK}/{sV} layout{layout} pos0 {pos0} lens {lens}")
+
+
+@pytest.mark.parametrize("G,T,N,sK,sV,snV,layout", [
+    (1, 3000, 256, 8, 8, 1, 0),     # whole codes, three rounds of 1024 tokens; one key pair block
+    (2, 3000, 256, 8, 4, 2, 1),     # groups of 2: six rounds of 512
+    (4, 2100, 256, 8, 8, 1, 0),     # groups of 4
+    (1, 2100, 256, 16, 8, 1, 1),    # codes in two blocks of 8, looped over in every step
+    (2, 1600, 384, 16, 16, 1, 0),
+    (4, 1600, 256, 16, 4, 1, 1),
+    (1, 2049, 256, 12, 3, 1, 0),    # three blocks of 4, a last round of one token
+    (2, 1500, 128, 12, 8, 1, 0),
+    (4, 1025, 256, 12, 4, 1, 1),    # a last round of one token
+    (1, 2100, 768, 8, 8, 1, 0),     # rows gathered from device memory
+    (2, 1600, 1024, 8, 4, 1, 1),
+    (4, 1300, 640, 4, 8, 1, 0),
+])
+def test_rotary_keys_over_several_rounds_of_a_chunk(G, T, N, sK, sV, snV, layout):
+    # as many heads as the chip has CUs: one chunk per sequence, whose rounds carry the rotating state and the requests on
+    B, Hkv, base, pos0, d = 8, 32, 10000.0, 77, 128
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(76)
+    unit = lambda *sh: (lambda a: (a / a.norm(dim=-1, keepdim=True)).half())(torch.randn(*sh, device="cuda", generator=gen))  # noqa: E731
+    chunks = (snV,) if snV > 1 else ()
+    codes = lambda *sh: (torch.randint(0, N, sh, device="cuda", generator=gen, dtype=torch.int32).to(torch.int16),  # noqa: E731
+                         (torch.randn(*sh, device="cuda", generator=gen) * 3).half())
+    q, DK = torch.randn(B, Hkv * G, d, device="cuda", generator=gen).half(), unit(Hkv, N, d)
+    DV = unit(Hkv, *chunks, N, d // snV)
+    (ik, ck), (iv, cv) = codes(B, Hkv, T, sK), codes(B, Hkv, T, *chunks, sV)
+    need = lambda t: csr.csr_decode_workspace_bytes(csr.decode_desc(q, DK, ik[:, :, :t], ck, iv[:, :, :t], rope_base=base))  # noqa: E731
+    assert need(T) == need(512) and T > 1024   # one chunk
+    lens = np.array([T, T - 1, T - 63, 513, T, 1024, 1, T - 500], dtype=np.int32)
+    out = csr.csr_decode_attn(q, DK, ik, ck, DV, iv, cv, seq_lens=torch.from_numpy(lens).cuda(), rope_base=base, rope_layout=layout, rope_pos0=pos0)
+    torch.cuda.synchronize()
+    n = lambda t: t.cpu().numpy()  # noqa: E731
+    for b in range(B):
+        h = (5 * b + 3) % Hkv
+        one = [n(a) for a in (q[b:b + 1, h * G:(h + 1) * G], DK[h:h + 1], ik[b:b + 1, h:h + 1], ck[b:b + 1, h:h + 1], DV[h:h + 1],
+                              iv[b:b + 1, h:h + 1], cv[b:b + 1, h:h + 1])]
+        ref = oracle.decode_attn_rope(*one, base, layout, pos0, seq_lens=lens[b:b + 1])
+        _check(n(out[b:b + 1, h * G:(h + 1) * G]), ref, f"rounds: G{G} T{T} N{N} s{sK}/{sV} snV{snV} layout{layout}: sequence {b}, {lens[b]} tokens")
 
 
 def test_rotary_keys_sequence_lengths_base_and_scale():
