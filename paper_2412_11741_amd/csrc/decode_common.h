@@ -400,7 +400,7 @@ struct Chunk {
 // sequence gets as few chunks as the plan's size allows, or more (at most the plan's number) where the whole launch then
 // makes cheaper generations of 256 workgroups, one per CU.  All of it follows from the lengths alone - of all sequences: the low bits
 // of one's output depend on the others' - and every wave works it out for itself, in about a microsecond: shorter chunks, one chunk per
-// sequence and more than 64 sequences keep the plan's.  CUT_FROM = 0: all calls do, and the kernel does not carry the code.
+// sequence and more than 64 sequences keep the plan's.  CUT_FROM = 0: all calls do, and the kernel is the one without any of this.
 // 8 sequences of 73728 to 131072 tokens, 8 KV heads x 4 query heads 146 us with the plan's chunks, 134 longest first, 136 to 143 in other
 // orders; 20 sequences of 15000 to 30000, 4 x 8 heads 134 and 113; 50 random batches of 2 to 64 sequences 0.83 of the time, the worst 1.03.
 // The lines, by the time with the cut over the time without (9 random batches each): chunks of up to 4096 tokens 0.99, 8192 0.92, 12288
@@ -410,9 +410,19 @@ struct Chunk {
 template <int THREADS, int CUT_FROM>
 __device__ __forceinline__ Chunk chunk_of(const int32_t *__restrict__ seq_lens, int64_t T, int nchunks, int64_t chunk_tokens)
 {
+    if constexpr (CUT_FROM == 0) {
+        const int c = blockIdx.y, b = blockIdx.z;
+        int64_t len = T;
+        if (seq_lens) {
+            const int32_t l = seq_lens[b];
+            len = l < 0 ? 0 : (l > T ? T : l);
+        }
+        const int64_t t0 = (int64_t)c * chunk_tokens;
+        return {b, c, t0, min(t0 + chunk_tokens, len)};
+    }
     constexpr float kFixedRounds = 7.0f;
     const int B = gridDim.z, heads = gridDim.x, lane = threadIdx.x & 63;
-    if (CUT_FROM == 0 || __builtin_expect(!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM, 1)) {
+    if (__builtin_expect(!seq_lens || nchunks == 1 || B > 64 || chunk_tokens < CUT_FROM, 1)) {
         int64_t len = T;
         if (seq_lens) {
             const int32_t l = seq_lens[blockIdx.z];
