@@ -34,8 +34,8 @@
 //   kRes    encode_resident.hip: fp32 residual; comparisons as kMfma on its hi and lo, coefficients in four chains per half
 // The chains of a sum are spread over lanes (each chain keeps its order; the tree that joins them is the same).
 //
-// Bound by the sweep at the clock the chip allows the matrix cores under full load, and behind it by the select phase, in which
-// they stand still: three prompts of 1571 tokens on 8 KV heads, 4096 atoms, spend 250 of a call's 337 us in the sweeps (160
+// Bound by the sweep, which runs at the rate of a large library product (1.38 against 1.32 PFLOP/s), and behind it by the select phase, in
+// which the matrix cores stand still: three prompts of 1571 tokens on 8 KV heads, 4096 atoms, spend 250 of a call's 337 us in the sweeps (160
 // vectors a workgroup; 8 iterations of 31 us, 1.38 PFLOP/s) and 10 us an iteration in lists, select and update.  With 64
 // vectors a workgroup the same call made three generations and took 420 us.  Two vectors of a team selected together, so that
 // their chains overlap, is slower (356): the select phase is bound by its instructions.  The rules in csr_api.hip say what
@@ -370,7 +370,8 @@ template <int DC, int W, int P> struct WideLds {
 };
 
 // Blocks whose fp16 operand a wave holds in registers for the whole sweep (the others are read from LDS for every tile): with
-// five or six of them 256 registers take three or two.
+// five or six of them 256 registers take three or two.  (Four blocks of 128 dimensions spill 19 registers, five of which three are
+// held 11.)
 template <int DC, int P> constexpr int blocks_held() { return P <= 4 ? P * 128 / DC : P == 5 ? 3 : 2; }
 
 // W waves; P * 128 / DC blocks of 32 vectors.  HELD: the dictionary's tiles - at most 16 / (DC / 16) a wave, 128 KB of
@@ -480,11 +481,13 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
         const int tok = q * kTeams + team;
         const int64_t m = p.m_first + (int64_t)tile_wg * kTok + tok;
         const bool valid = m < p.M;
-        const int64_t mc = valid ? m : p.M - 1;   // past the end the last vector is recomputed, and never stored
+        const int64_t mc = valid ? m : p.M - 1;   // past the end: a zero vector, for which nothing is resolved, and never stored
         const int rep = (int)(mc / p.T);
         const int64_t t = mc - rep * p.T, h = (int64_t)rep * p.dict_count + dict;
         float R[8];
         load8e<TE>(reinterpret_cast<const TE *>(p.X) + h * p.x_stride_h + t * p.x_stride_t + ch * DC + sub * 8, R);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) R[e] = valid ? R[e] : 0.0f;
         float amax = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(R[e]));
@@ -647,8 +650,8 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
             ends = row_reduce<L>(ends, OpPkMax());
             count = row_reduce<L>(count, OpAdd());
             int n_lo = min(65535 - (int)(ends & 0xffffu), p.N - 1), n_hi = min((int)(ends >> 16), p.N - 1);
-            // vectors with more candidates, one at a time, by the whole wave (what stands past the end is not worth it)
-            unsigned long long todo = __ballot(st.code_at >= 0 && !zero && count != 1u && count != 2u && sub == 0);
+            // vectors with more candidates, one at a time, by the whole wave
+            unsigned long long todo = __ballot(!zero && count != 1u && count != 2u && sub == 0);
             while (todo) {
                 const int lead = __ffsll((long long)todo) - 1;   // first lane of the vector's team
                 todo &= todo - 1;
