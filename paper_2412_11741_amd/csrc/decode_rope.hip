@@ -277,8 +277,8 @@ __global__ __launch_bounds__(rope_threads(GB)) void stream_rope_kernel(
     }
     // PVK pairs of a token, read by all 8 lanes of the eighth (one 16-byte piece, and the 8 eighths' tokens are neighbours:
     // a wave reads 128 contiguous bytes per stream and step); indices and coefficients as packed 16-bit words, at a 32-bit
-    // byte offset from the chunk's first token.  Whole codes are requested three steps ahead of their use (a step takes
-    // about a microsecond, a request up to two), blocks of longer ones one block ahead.
+    // byte offset from the chunk's first token.  Whole codes are requested three steps ahead of their use, blocks of
+    // longer ones one block ahead.
     constexpr int AHEAD = ONEB ? 3 : 1, SLOTS = ONEB ? 4 : 1;
     uint32_t ni[SLOTS][PVK / 2], nc[SLOTS][PVK / 2];
     const unsigned char *ibase = reinterpret_cast<const unsigned char *>(idxK + (code_row + t0) * sK);

@@ -37,7 +37,6 @@ constexpr int kWaves = 8;                    // two per SIMD; one workgroup per 
 constexpr int kThreads = 64 * kWaves;
 constexpr int kBlockVectors = kWaves * 32;   // a workgroup takes whole multiples of this: its waves work through as many
                                              // 32-vector blocks each, one after the other
-constexpr int kMostBlocks = 4;
 constexpr int kMaxDictBytes = 128 * 1024;
 constexpr int kScratchPerWave = 1024;        // LDS a wave uses to share one vector's state
 constexpr int kTrack = 4;                    // group maxima tracked per lane and sweep

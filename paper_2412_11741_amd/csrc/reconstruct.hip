@@ -3,7 +3,9 @@
 // paper puts in front of ordinary attention; the code-domain decode kernel never needs it, but callers that must
 // touch the dense vectors (a position embedding applied to rebuilt keys, inspection, a loss on X - X~) do.
 //
-// Bound: HBM writes (2 d bytes per vector in fp16 against 4 s bytes of code read); the atom rows come from L2.
+// Bound: the texture path, 64 bytes a cycle and CU, and behind it the L1 misses of the atom rows, which come from L2 (32 x 4096 vectors, 8
+// pairs: 19.5 thousand cycles of accesses per CU; its data unit is busy 22.9 of the 26.1 thousand cycles in which waves run with 256
+// atoms, 30.7 of 33.8 with 4096, where 1.6 times the lines miss).  HBM sees 2 d bytes per vector written and 4 s read.
 // Lane (vector, chunk, 8-dimension piece): all lanes of a vector's chunk read the same s pairs (one broadcast
 // load each) and gather 16 bytes of each of the s atom rows, so a chunk's rows are fetched as whole lines.
 #include <utility>
@@ -207,7 +209,8 @@ __global__ __launch_bounds__(256) void reconstruct_few_kernel(const TD *__restri
 // round; with every lane requesting the whole code, pairs were a fifth of the bytes that the texture path delivered.
 // Divisions are in 32 bits.  Same sum order.  32 x 4096 vectors (us): 4096 atoms, 8
 // pairs 19.2 -> 18.4, 6 pairs 17.8 -> 17.1, 8192 atoms, 16 pairs 40.5 -> 39.2; 256 atoms, 8 pairs 16.1 -> 14.9, twice the vectors with 4 pairs
-// 22.5 -> 18.7; 4096 atoms, 4 pairs level (14.5).  Workgroups that stay and request the next tile's words ahead are slower (8 pairs 18.9).
+// 22.5 -> 18.7; 4 pairs of 256 to 2048 atoms 13.2 -> 10.9 and 12.5 -> 11.5, of 3072 and 8192
+// level, of 4096 13.7 -> 14.2.  Workgroups that stay and request the next tile's words ahead are slower (8 pairs 18.9).
 template <int S, int W, int... K>
 __device__ __forceinline__ void hand_round(uint32_t (&code)[S], const uint32_t (&w)[W], std::integer_sequence<int, K...>)
 {
