@@ -804,13 +804,14 @@ def test_copies_of_the_last_vector_past_the_end_are_not_resolved(algo, T, N, d):
 
 @pytest.mark.parametrize("heads,T,N,s_n", [(32, 1289, 2048, 2), (3, 31799, 2048, 1), (12, 5666, 640, 1), (8, 4812, 2560, 2), (4, 22694, 4096, 1)])
 def test_auto_takes_neither_the_slower_encoder(heads, T, N, s_n):
-    # partial generations of the prefill encoder cost nearly a full one: at these sizes it took up to 1.5 times the wide encoder's time
+    # partial generations of the prefill encoder cost nearly a full one: priced below that, it was taken here and 12 to 28 % slower than
+    # the wide encoder.  The least of ten times each is repeatable to 2 %
     s, d = 4, 128 // s_n
     gen = torch.Generator(device="cuda")
     gen.manual_seed(111)
     D = torch.randn((heads, s_n, N, d) if s_n > 1 else (heads, N, d), device="cuda", generator=gen)
     D = (D / D.norm(dim=-1, keepdim=True)).half()
     X = torch.randn(heads, T, 128, device="cuda", generator=gen).half()
-    auto, mfma, wide = (_least_us(lambda a=a: csr.csr_encode(X, D, s, algo=a), runs=6, calls=2)
+    auto, mfma, wide = (_least_us(lambda a=a: csr.csr_encode(X, D, s, algo=a), runs=10, calls=2)
                         for a in (csr.CSR_ENCODE_AUTO, csr.CSR_ENCODE_MFMA, csr.CSR_ENCODE_WIDE))
-    assert auto < 1.08 * min(mfma, wide), (auto, mfma, wide)
+    assert auto < 1.1 * min(mfma, wide), (auto, mfma, wide)
