@@ -11,7 +11,8 @@
 //   prepare   the dictionary as fp16 in the order the matrix instructions take it - [tile][fragment][lane][8 halves],
 //             rows past N zero - so that every request of the sweep is one contiguous KiB; per slice of atoms the
 //             largest norm and the largest |d_n - fp16(d_n)| (0 for fp16 dictionaries): the screening bound needs both.
-//             A dictionary of at most 128 KB needs none of this: its tiles stay in the waves' registers (HELD).
+//             A dictionary of at most 128 KB needs none of this: its tiles stay in the waves' registers (HELD).  One of at most
+//             256 KB is prepared, and with one pass of vectors read once, three quarters into registers and a quarter into LDS.
 //   sweep     hi . d^_n on the matrix cores, hi = fp16(R), d^ = fp16(d); atoms straight from L2 into registers, the next
 //             tile requested while the present one is multiplied; no barrier.  Per lane (a vector's column, half of the
 //             tile's rows) the three largest 16-atom groups with their tile in the low mantissa bits, and the 16
@@ -362,10 +363,11 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
 }
 
 // What a workgroup of P * 128 / DC blocks keeps in LDS: residuals | lists | state | HELD's bounds of the waves
-template <int DC, int W, int P> struct WideLds {
+template <int DC, int W, int P, int LDS_TILES> struct WideLds {
     static constexpr int kTok = 32 * (P * 128 / DC);
     static constexpr int kList = kTok * DC * 4, kState = kList + kTok * 2 * W * 16, kHeld = kState + kTok * (int)sizeof(VectorState);
-    static constexpr int kBytes = kHeld + W * 8;
+    static constexpr int kTiles = kHeld + W * 8;
+    static constexpr int kBytes = kTiles + W * LDS_TILES * DC * 64;
     static_assert(kBytes <= 160 * 1024, "a CU's LDS");
 };
 
@@ -374,10 +376,14 @@ template <int DC, int W, int P> struct WideLds {
 // held 11.)
 template <int DC, int P> constexpr int blocks_held() { return P <= 4 ? P * 128 / DC : P == 5 ? 3 : 2; }
 
-// W waves; P * 128 / DC blocks of 32 vectors.  HELD: the dictionary's tiles - at most 16 / (DC / 16) a wave, 128 KB of
-// fp16 in all - are read once, from the dictionary itself, and stay in registers for all iterations: no prepared copy,
-// no scratch, no dictionary traffic in the sweeps.
-template <typename TE, int DC, int MODE, int W, int P, bool HELD>
+// W waves; P * 128 / DC blocks of 32 vectors.  HELD: the dictionary's first HELD tiles of every wave are read once and stay in
+// registers for all iterations, the next LDS_TILES in the wave's part of the LDS: no dictionary traffic in the sweeps.
+//   128 KB of fp16, 16 / (DC / 16) tiles in registers: read from the dictionary itself, no prepared copy, no scratch.
+//   256 KB, 24 / (DC / 16) in registers and 8 / (DC / 16) in LDS, one pass of vectors: read from the prepared copy (every workgroup
+//   would spend 10 us on the conversion of 512 KB of fp32).  With L1 and L2 in the way a sweep of 1024 atoms took 3.6 us, 2.7 now
+//   (all four tiles of 128 dimensions in registers spill 59 of them): 2 x 4096 fp32 vectors, 1024 atoms, s = 8, with the attention that
+//   follows 63.5 -> 58.7 us, 8 x 1024, s = 16 106 -> 91.5, fp16 8 x 1024, s = 8 45.9 -> 39.7, with 640 atoms 37.8 -> 34.0.
+template <typename TE, int DC, int MODE, int W, int P, int HELD, int LDS_TILES>
 __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
 {
     constexpr int L = DC / 8;                    // lanes per team = 8-dimension pieces of a vector
@@ -393,7 +399,7 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
     static_assert(P <= 4 || (MODE == kMfma && DC == 128), "operands from LDS: the residual's fp16 plane, whole vectors");
     constexpr int kInRegs = blocks_held<DC, P>();
     using RES = Residuals<DC, MODE, kTok>;
-    using LDS = WideLds<DC, W, P>;
+    using LDS = WideLds<DC, W, P, LDS_TILES>;
     static_assert(RES::kBytes == LDS::kList, "layout");
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_s[];
     uint4(*list_s)[kLists] = reinterpret_cast<uint4(*)[kLists]>(lds_s + LDS::kList);   // (tracked groups, best group: atom << 16 | place of the second << 2 | flags)
@@ -423,10 +429,13 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
 #pragma unroll
         for (int j = 0; j < kFrags; ++j) a[j] = src[j * 64];
     };
-    constexpr int kHeld = HELD ? 16 / kFrags : 1;
+    constexpr int kHeld = HELD ? HELD : 1;
+    // this lane's first fragment of the wave's tiles in LDS; not known from one iteration to the next, or they would be read once, into
+    // registers that are not there
+    uint32_t lds_at = (uint32_t)(LDS::kTiles + wave * (LDS_TILES * kFrags * 1024) + lane * 16);
     uint4 a0[kHeld][kFrags];   // HELD: the wave's tiles; else the first of the two buffers of the sweep
     float dmax = 0.0f, derr = 0.0f;
-    if constexpr (HELD) {
+    if constexpr (HELD > 0 && LDS_TILES == 0) {
 #pragma unroll
         for (int i = 0; i < kHeld; ++i) {
             const int n = (wave + W * i) * 32 + col;
@@ -464,7 +473,17 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
         dmax = sqrtf(dmax);
         derr = sqrtf(derr) * 1.001f;
     } else {
-        if (my_tiles > 0) load_tile(0, a0[0]);
+#pragma unroll
+        for (int i = 0; i < kHeld; ++i)
+            if (i < my_tiles) load_tile(i, a0[i]);
+#pragma unroll
+        for (int i = 0; i < LDS_TILES; ++i)
+            if (kHeld + i < my_tiles) {
+                uint4 a1[kFrags];
+                load_tile(kHeld + i, a1);
+#pragma unroll
+                for (int j = 0; j < kFrags; ++j) *reinterpret_cast<uint4 *>(lds_s + lds_at + (i * kFrags + j) * 1024) = a1[j];   // only this lane reads it
+            }
         if (lane < p.slices) {
             const float2 b = p.bound[dct * kMaxSlices + lane];
             dmax = b.x;
@@ -569,10 +588,21 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
                 }
             };
             auto none = [](int) {};
-            if constexpr (HELD) {
+            if constexpr (HELD > 0) {
 #pragma unroll
-                for (int i = 0; i < kHeld; ++i)
+                for (int i = 0; i < kHeld; ++i) {
                     if (i < my_tiles) sweep(i, a0[i], none);
+                    if constexpr (LDS_TILES > 0) __builtin_amdgcn_sched_barrier(0);   // accumulators of one tile at a time
+                }
+                asm volatile("" : "+v"(lds_at));
+#pragma unroll
+                for (int i = 0; i < LDS_TILES; ++i)
+                    if (kHeld + i < my_tiles) {
+                        uint4 a1[kFrags];
+#pragma unroll
+                        for (int j = 0; j < kFrags; ++j) a1[j] = *reinterpret_cast<const uint4 *>(lds_s + lds_at + (i * kFrags + j) * 1024);
+                        sweep(kHeld + i, a1, none);
+                    }
             } else if constexpr (P > 2) {
                 // a tile's fragments make room for the next tile's one by one (behind the last tile the next sweep's first):
                 // a wave waits for them a little, while the other one of its SIMD multiplies
@@ -800,6 +830,9 @@ WidePasses wide_passes(const EncodeArgs &a, int64_t vectors)
     return best;
 }
 
+// Whether a workgroup can hold the dictionary (see HELD); with more than one pass of vectors there are no registers for it.
+bool held_on_the_cu(const EncodeArgs &a) { return (int64_t)((a.N + 31) / 32) * (a.d * 64) <= 256 * 1024; }
+
 WidePlan plan_wide(const EncodeArgs &a)
 {
     WidePlan pl{};
@@ -813,7 +846,7 @@ WidePlan plan_wide(const EncodeArgs &a)
     return pl;
 }
 
-template <typename TE, int DC, int MODE, int P, bool HELD>
+template <typename TE, int DC, int MODE, int P, int HELD = 0, int LDS_TILES = 0>
 hipError_t launch_p(const EncodeArgs &a, WideParams &p)
 {
     constexpr int W = 8, kTok = 32 * (P * 128 / DC);
@@ -824,7 +857,7 @@ hipError_t launch_p(const EncodeArgs &a, WideParams &p)
     int bits = 0;
     while ((1 << bits) < (p.ntiles + W - 1) / W) ++bits;
     p.code_mask = (1u << bits) - 1u;
-    constexpr int kLds = WideLds<DC, W, P>::kBytes;
+    constexpr int kLds = WideLds<DC, W, P, LDS_TILES>::kBytes;
     if constexpr (kLds > 64 * 1024) {   // above the default limit: per device, once
         static std::atomic<bool> attr_set[64];
         int dev = 0;
@@ -832,20 +865,20 @@ hipError_t launch_p(const EncodeArgs &a, WideParams &p)
         if (e != hipSuccess) return e;
         if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
         if (!attr_set[dev].load(std::memory_order_acquire)) {
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_wide_kernel<TE, DC, MODE, W, P, HELD>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(encode_wide_kernel<TE, DC, MODE, W, P, HELD, LDS_TILES>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
             if (e != hipSuccess) return e;
             attr_set[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((encode_wide_kernel<TE, DC, MODE, W, P, HELD>), dim3((unsigned)groups), dim3(64 * W), kLds, a.stream, p);
+    hipLaunchKernelGGL((encode_wide_kernel<TE, DC, MODE, W, P, HELD, LDS_TILES>), dim3((unsigned)groups), dim3(64 * W), kLds, a.stream, p);
     return hipGetLastError();
 }
 
 template <typename TE, int DC, int MODE>
 hipError_t launch_m(const EncodeArgs &a)
 {
-    constexpr bool HELD = MODE == kRes;
+    constexpr int kTileRegs = DC / 16;   // 16-byte registers of a tile
     const WidePlan pl = plan_wide(a);
     char *ws = static_cast<char *>(a.workspace);
     __half *frag = reinterpret_cast<__half *>(ws);
@@ -857,27 +890,28 @@ hipError_t launch_m(const EncodeArgs &a)
     p.x_stride_h = a.x_stride_h; p.x_stride_t = a.x_stride_t; p.code_stride_h = a.code_stride_h;
     p.N = a.N; p.s = a.s; p.sn = a.sn; p.dict_count = a.dict_count; p.ntiles = pl.ntiles; p.slices = pl.slices;
     p.idx16 = a.idx16; p.coef_mode = (a.coef16 ? kCoefF16 : 0) | (a.closed_loop ? kCoefClosed : 0);
-    if constexpr (!HELD) {
+    const int P = wide_passes(a, a.m_end - a.m_first).P;
+    if constexpr (MODE == kRes) {
+        return P == 2 ? launch_p<TE, DC, MODE, 2, 16 / kTileRegs>(a, p) : launch_p<TE, DC, MODE, 1, 16 / kTileRegs>(a, p);
+    } else {
         hipLaunchKernelGGL((wide_prepare_kernel<TE, DC>), dim3((unsigned)dicts, (unsigned)pl.slices), dim3(256), 0, a.stream,
                            (const TE *)a.D, frag, bound, a.N, pl.ntiles, pl.slices);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+        if constexpr (MODE == kMfma && DC == 128) {
+            if (P == 6) return launch_p<TE, DC, MODE, 6>(a, p);
+            if (P == 5) return launch_p<TE, DC, MODE, 5>(a, p);
+        }
+        if constexpr (DC == 128) {
+            if (P == 4) return launch_p<TE, DC, MODE, 4>(a, p);
+        }
+        if constexpr (DC > 32) {
+            if (P == 3) return launch_p<TE, DC, MODE, 3>(a, p);
+            if (P == 2) return launch_p<TE, DC, MODE, 2>(a, p);
+        }
+        if (held_on_the_cu(a)) return launch_p<TE, DC, MODE, 1, 24 / kTileRegs, 8 / kTileRegs>(a, p);
+        return launch_p<TE, DC, MODE, 1>(a, p);
     }
-    const int P = wide_passes(a, a.m_end - a.m_first).P;
-    if constexpr (MODE == kMfma && DC == 128) {
-        if (P == 6) return launch_p<TE, DC, MODE, 6, HELD>(a, p);
-        if (P == 5) return launch_p<TE, DC, MODE, 5, HELD>(a, p);
-    }
-    if constexpr (!HELD && DC == 128) {
-        if (P == 4) return launch_p<TE, DC, MODE, 4, HELD>(a, p);
-    }
-    if constexpr (!HELD && DC > 32) {
-        if (P == 3) return launch_p<TE, DC, MODE, 3, HELD>(a, p);
-    }
-    if constexpr (DC > 32) {
-        if (P == 2) return launch_p<TE, DC, MODE, 2, HELD>(a, p);
-    }
-    return launch_p<TE, DC, MODE, 1, HELD>(a, p);
 }
 
 template <typename TE>
