@@ -22,16 +22,25 @@
 // Every vector is first multiplied by a power of two that brings its largest element into [2^11, 2^12)
 // (Matching Pursuit commutes with it; lo stays clear of the fp16 subnormals).  The largest atom norm, which scales
 // delta, is computed while the dictionary is loaded.
+//
+// Bound: with 128 dimensions and two waves per SIMD, a tile's matrix instructions and its 8 KB a wave out of LDS (512 cycles of either
+// for the two waves of a SIMD and the eight of a CU; 0.39 us measured), then the instructions of select and update (about 900 a block
+// and iteration).  64 x 4096 vectors, s = 8 (us; before the sweep requested its fragments a tile ahead, the resolve left the LDS out
+// of its reductions and the update lost a fifth of its instructions): 128 atoms 217 -> 160, 256 265 -> 222, 512 367 -> 322; keys of 256
+// atoms and values in two chunks 222 -> 188.  A tile's bookkeeping laid between the next tile's matrix instructions is slower (240 with
+// 256 atoms): the other wave fills that time anyway.
 #include <atomic>
 #include <cmath>
 
 #include "csr_internal.h"
 #include "encode_common.h"
+#include "lane_ops.h"
 
 namespace csr {
 namespace {
 
 using namespace enc;
+using namespace lane;
 
 constexpr int kWaves = 8;                    // two per SIMD; one workgroup per CU (the dictionary fills the LDS)
 constexpr int kThreads = 64 * kWaves;
@@ -41,14 +50,32 @@ constexpr int kMaxDictBytes = 128 * 1024;
 constexpr int kScratchPerWave = 1024;        // LDS a wave uses to share one vector's state
 constexpr int kTrack = 4;                    // group maxima tracked per lane and sweep
 
-
-
-
-
-
 // XOR term of a row's 16-byte piece positions, so that 16 consecutive rows read at one logical piece cover all
 // banks: a 256-byte row spans the 64 banks (16 different terms), two 128-byte rows span them (8, one per pair).
 template <int DC> __device__ __forceinline__ int swz(int row) { return DC == 128 ? (row & 15) : ((row >> 1) & 7); }
+
+// r - h in one instruction that takes h as fp16: a product with a one that the compiler does not know to be one (it would convert h
+// first).  Exact, like the product, where h is the rounding of r.
+__device__ __forceinline__ float minus_half(float r, _Float16 h, float one) { return fmaf(-(float)h, one, r); }
+
+// screen_delta with the hardware's square roots (1 ulp) and |R|^2 as known to 2^-9
+__device__ __forceinline__ float fast_delta(float dmax, float lo2, float r2)
+{
+    return 2.0f * dmax * (1.000001f * __builtin_amdgcn_sqrtf(lo2) + 1.01f * kGammaAcc * __builtin_amdgcn_sqrtf(r2));
+}
+
+__device__ __forceinline__ half8 to_half8(const float (&f)[8])   // v_cvt_pk_f16_f32, two at a time
+{
+    typedef float float2v __attribute__((ext_vector_type(2)));
+    half8 h;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        const half2v p = __builtin_convertvector((float2v{f[e], f[e + 1]}), half2v);
+        h[e] = p[0];
+        h[e + 1] = p[1];
+    }
+    return h;
+}
 
 // byte offset in the LDS copy of the dictionary of piece `piece` (8 dimensions) of atom `row`
 template <int DC> __device__ __forceinline__ uint32_t piece_at(int row, int piece)
@@ -57,64 +84,68 @@ template <int DC> __device__ __forceinline__ uint32_t piece_at(int row, int piec
 }
 
 // The whole wave resolves ONE vector whose pick the kept values could not decide.  `scr` holds that vector's
-// state, written by its two owner lanes:
+// residual, written by its two owner lanes:
 //   [0, 256)    hi, dimensions in order        [256, 512)  lo
-//   [512, 544)  tracked group values, lane half 0 then half 1
-//   [544, 552)  threshold bits, overflow flag
+// `own`: the tracked group values of this lane's vector and half; the vector's are those of lanes v and v + 32.
 // Lane (a = lane / 4, q = lane % 4) evaluates atom a of a 16-atom group over a quarter of the dimensions.
-// Returns the arg-max of |hi . d + lo . d| (lowest index on ties) over the candidate groups, or over all atoms
-// when the overflow flag is set.
+// Returns the arg-max of |hi . d + lo . d| (lowest index on ties) over the groups that reach thr_bits, or over all atoms
+// when a lane's last tracked group does.
+// (The group values through LDS, one at a time, and the reductions by ds_bpermute were a chain of two dozen LDS trips, 10 of the
+// 33 us of an iteration of 64 x 4096 vectors, 256 atoms.)
 template <int DC>
 __device__ __forceinline__ int resolve_vector(const unsigned char *dict, int32_t N, int ntiles, uint32_t code_mask,
-                                              const unsigned char *scr, int lane)
+                                              const unsigned char *scr, const uint32_t (&own)[kTrack], uint32_t thr_own, int v, int lane)
 {
     constexpr int kQ = DC / 32;  // 8-element pieces of a quarter vector
     const int a = lane >> 2, q = lane & 3;
+    const uint32_t thr_bits = lane_read(thr_own, v);
+    uint32_t group[2 * kTrack];   // tracked group values, lane half 0 then half 1 (scalars)
+    uint32_t todo = 0u;
+#pragma unroll
+    for (int e = 0; e < 2 * kTrack; ++e) {
+        group[e] = lane_read(own[e % kTrack], v + 32 * (e / kTrack));
+        todo |= group[e] >= thr_bits ? 1u << e : 0u;
+    }
     half8 th[kQ], tl[kQ];
 #pragma unroll
     for (int j = 0; j < kQ; ++j) {
         th[j] = *reinterpret_cast<const half8 *>(scr + q * (DC / 2) + j * 16);
         tl[j] = *reinterpret_cast<const half8 *>(scr + 256 + q * (DC / 2) + j * 16);
     }
-    const uint2 tf = *reinterpret_cast<const uint2 *>(scr + 544);
-    const uint32_t thr_bits = __builtin_amdgcn_readfirstlane(tf.x);
-    const bool ovf = __builtin_amdgcn_readfirstlane(tf.y) != 0;
-
-    float ba = -1.0f;
-    int bn = 0;
+    unsigned long long best = 0xffffffffull;   // |correlation|, then the lower atom: bits << 32 | ~atom
     auto eval = [&](int n) {
         float s0 = 0.0f, s1 = 0.0f, l0 = 0.0f, l1 = 0.0f;
+        half8 dv[kQ];
+#pragma unroll
+        for (int j = 0; j < kQ; ++j) dv[j] = *reinterpret_cast<const half8 *>(dict + piece_at<DC>(n, q * kQ + j));
 #pragma unroll
         for (int j = 0; j < kQ; ++j) {
-            const half8 dv = *reinterpret_cast<const half8 *>(dict + piece_at<DC>(n, q * kQ + j));
-            dot8(th[j], dv, s0, s1);
-            dot8(tl[j], dv, l0, l1);
+            dot8(th[j], dv[j], s0, s1);
+            dot8(tl[j], dv[j], l0, l1);
         }
-        float c = (s0 + s1) + (l0 + l1);
-        c += __shfl_xor(c, 1, 64);
-        c += __shfl_xor(c, 2, 64);
-        const float ab = fabsf(c);
-        if (ab > ba || (ab == ba && n < bn)) { ba = ab; bn = n; }
+        const float ab = fabsf(row_reduce<4>((s0 + s1) + (l0 + l1), OpAdd()));
+        const unsigned long long key = ((unsigned long long)__float_as_uint(ab) << 32) | (uint32_t)~n;
+        if (ab >= 0.0f && key > best) best = key;   // (not a number: never the best)
     };
-    if (!ovf) {
-#pragma unroll 1
-        for (int e = 0; e < 2 * kTrack; ++e) {
-            const uint32_t u = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t *>(scr + 512 + 4 * e));
-            if (u < thr_bits) continue;
-            const int tile = ntiles - 1 - (int)(u & code_mask);
-            eval(tile * 32 + 4 * (e / kTrack) + 8 * (a >> 2) + (a & 3));
-        }
+    if (!(todo & ((1u << (kTrack - 1)) | (1u << (2 * kTrack - 1))))) {
+        const int at = 8 * (a >> 2) + (a & 3);
+#pragma unroll
+        for (int e = 0; e < 2 * kTrack; ++e)
+            if ((todo >> e) & 1u) eval((ntiles - 1 - (int)(group[e] & code_mask)) * 32 + 4 * (e / kTrack) + at);
     } else {
 #pragma unroll 1
         for (int n0 = 0; n0 < N; n0 += 16) eval(n0 + a);
     }
-#pragma unroll
-    for (int m = 4; m <= 32; m <<= 1) {
-        const float oa = __shfl_xor(ba, m, 64);
-        const int on = __shfl_xor(bn, m, 64);
-        if (oa > ba || (oa == ba && on < bn)) { ba = oa; bn = on; }
-    }
-    return __builtin_amdgcn_readfirstlane(bn);
+    // the 16 atoms: the four quads of a row, then the rows
+    auto take = [&](unsigned long long o) { best = o > best ? o : best; };
+    take(dpp_mov<0x141>(best));   // row_half_mirror
+    take(dpp_mov<0x140>(best));   // row_mirror
+    const unsigned long long lower = lane_read(best, 0), upper = lane_read(best, 32);
+    take(lane_read(best, 16));
+    take(lane_read(best, 48));
+    take(lower);
+    take(upper);
+    return ~__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
 }
 
 // OCC: waves per SIMD the register budget is set for.  64-dimensional vectors need few enough registers for 4, so
@@ -188,6 +219,8 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
     // ~code_mask in a vector register: packing value and tile code is then one instruction
     uint32_t keep_mask;
     asm volatile("v_mov_b32 %0, %1" : "=v"(keep_mask) : "s"(~code_mask));
+    float one;   // see minus_half
+    asm volatile("v_mov_b32 %0, 1.0" : "=v"(one));
     // relative slack of a packed value: its low mantissa bits were replaced by the tile code
     const float pack_q = (float)(code_mask + 1) * 1.1920929e-7f;
 
@@ -238,7 +271,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
             }
             rn2 = r2 + xchg32f(r2, hf);
             lo2 += xchg32f(lo2, hf);
-            delta = screen_delta(dmax, lo2, rn2);
+            delta = fast_delta(dmax, lo2, rn2);
         }
 
         for (int g = 0; g < s; ++g) {
@@ -249,16 +282,26 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
             for (int k = 0; k < kTrack; ++k) u[k] = 0u;
 #pragma unroll
             for (int r = 0; r < 8; ++r) keep[r] = 0u;
-            for (int t = 0; t < ntiles; ++t) {
-                half8 a[kFrags];
+            // A tile's fragments make room for the next tile's one by one, so that a request has a tile's eight instructions of
+            // time: requested in pairs just ahead of their use, they were what a wave waited for.  Two tiles a round: the second
+            // one's addresses are the first one's plus a constant.
+            half8 a[kFrags];
+            using LdsBytes = const __attribute__((address_space(3))) unsigned char *;   // (the array's base added once, not in every tile)
+            LdsBytes at[kFrags];
 #pragma unroll
-                for (int j = 0; j < kFrags; ++j)
-                    a[j] = *reinterpret_cast<const half8 *>(lds + t * 32 * kRowBytes + frag_off[j]);
+            for (int j = 0; j < kFrags; ++j) {
+                at[j] = (LdsBytes)lds + frag_off[j];
+                a[j] = *(const __attribute__((address_space(3))) half8 *)at[j];
+            }
+            auto tile = [&](int t, int ahead) {   // `ahead`: bytes from at[] to the tile that is requested
                 floatx16 acc;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-                for (int j = 0; j < kFrags; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[j], hi[j], acc, 0, 0, 0);
+                for (int j = 0; j < kFrags; ++j) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[j], hi[j], acc, 0, 0, 0);
+                    a[j] = *(const __attribute__((address_space(3))) half8 *)(at[j] + ahead);
+                }
                 const uint32_t code = (uint32_t)(ntiles - 1 - t);  // earlier tile = larger code
                 float mx = 0.0f;  // eight v_max3_f32 with |.| operand modifiers
 #pragma unroll
@@ -279,7 +322,16 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 u[1] = n1;
                 u[2] = n2;
                 u[3] = n3;
+            };
+            int t = 0;
+            for (; t + 1 < ntiles; t += 2) {
+                tile(t, 32 * kRowBytes);
+                const uint32_t step = t + 2 < ntiles ? 64 * kRowBytes : 0;   // behind the last pair: a tile that nobody multiplies
+#pragma unroll
+                for (int j = 0; j < kFrags; ++j) at[j] += step;
+                tile(t + 1, 0);
             }
+            if (t < ntiles) tile(t, 0);
 
             // ---- select: the iteration's atom for every vector of the block -------------------------
             int best_n;
@@ -300,15 +352,18 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 for (int k = 0; k < kTrack; ++k) ncand += (int)(u[k] >= thr_bits) + (int)(pu[k] >= thr_bits);
                 const bool overflow = u[kTrack - 1] >= thr_bits || pu[kTrack - 1] >= thr_bits;
 
-                // this lane's best group as kept during the sweep: largest value, its position, runner-up
-                float ba = -1.0f, sa = -1.0f;
-                int bk = 0;
+                // this lane's best group as kept during the sweep: its two largest values, the place of each in the low bits
+                uint32_t k1 = 0u, k2 = 0u;
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&keep[r]));
-                    if (f.x > ba) { sa = ba; ba = f.x; bk = 2 * r; } else sa = fmaxf(sa, f.x);
-                    if (f.y > ba) { sa = ba; ba = f.y; bk = 2 * r + 1; } else sa = fmaxf(sa, f.y);
+                for (int r = 0; r < 16; ++r) {
+                    const uint32_t w = keep[r >> 1];
+                    const uint32_t v = ((r & 1) ? (w & 0xffff0000u) : (w << 16)) | (uint32_t)r;
+                    k2 = umed3(k1, k2, v);
+                    k1 = max(k1, v);
                 }
+                auto kept = [](uint32_t k) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(k >> 16)); };
+                const float ba = kept(k1), sa = kept(k2);
+                const int bk = (int)(k1 & 15u);
                 // kept values were rounded toward zero to 11 bits: two of them are told apart only beyond
                 // delta + 2^-10 of the larger
                 const bool close_own = !(sa < ba - delta - ba * 9.765625e-4f);
@@ -324,24 +379,22 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 // copies of the last vector past the end, whose picks nobody reads
                 uint32_t todo = (uint32_t)__ballot(unsure);
                 while (todo) {
-                    const int t = __ffs((int)todo) - 1;
+                    const int v = __ffs((int)todo) - 1;
                     todo &= todo - 1;
-                    if (col == t) {
+                    if (col == v) {
 #pragma unroll
                         for (int j = 0; j < kFrags; ++j) {
                             half8 lo;
 #pragma unroll
-                            for (int e = 0; e < 8; ++e) lo[e] = (_Float16)(R[j][e] - (float)hi[j][e]);
+                            for (int e = 0; e < 8; ++e) lo[e] = (_Float16)minus_half(R[j][e], hi[j][e], one);
                             *reinterpret_cast<half8 *>(scr + hf * DC + j * 16) = hi[j];
                             *reinterpret_cast<half8 *>(scr + 256 + hf * DC + j * 16) = lo;
                         }
-                        *reinterpret_cast<uint4 *>(scr + 512 + hf * 16) = make_uint4(u[0], u[1], u[2], u[3]);
-                        if (hf == 0) *reinterpret_cast<uint2 *>(scr + 544) = make_uint2(thr_bits, overflow ? 1u : 0u);
                     }
                     wave_lds_fence();
-                    const int n_res = resolve_vector<DC>(lds, N, ntiles, code_mask, scr, lane);
+                    const int n_res = resolve_vector<DC>(lds, N, ntiles, code_mask, scr, u, thr_bits, v, lane);
                     wave_lds_fence();
-                    if (col == t) best_n = n_res;
+                    if (col == v) best_n = n_res;
                 }
                 if (zero) best_n = 0;
             }
@@ -363,46 +416,67 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
             if (!(rn2 > 0.0f)) best_c = 0.0f;
             // closed loop: what Eq.4 subtracts is the coefficient as it will be stored (rounded in the input's scale)
             if (coef_rounds_in_loop(coef_mode)) best_c = ldexpf(__half2float(__float2half_rn(ldexpf(best_c, -sexp))), sexp);
-            float r2 = 0.0f;
 #pragma unroll
             for (int j = 0; j < kFrags; ++j) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    R[j][e] = fmaf(-best_c, (float)dv[j][e], R[j][e]);
-                    r2 = fmaf(R[j][e], R[j][e], r2);
-                }
+                for (int e = 0; e < 8; ++e) R[j][e] = fmaf(-best_c, (float)dv[j][e], R[j][e]);
             }
-            r2 += xchg32f(r2, hf);
+            auto norm2 = [&]() {
+                float r2 = 0.0f;
+#pragma unroll
+                for (int j = 0; j < kFrags; ++j) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) r2 = fmaf(R[j][e], R[j][e], r2);
+                }
+                return r2 + xchg32f(r2, hf);
+            };
+            // hi, and |hi|^2 for |R|^2, which it equals to 2^-9: half the instructions.  What |R| decides below is asked again with the
+            // sum itself where |hi| is near a line, and the last iteration has it for res_norm2.
+            auto split = [&]() {
+                float h0 = 0.0f, h1 = 0.0f;
+#pragma unroll
+                for (int j = 0; j < kFrags; ++j) {
+                    hi[j] = to_half8(R[j]);
+                    dot8(hi[j], hi[j], h0, h1);
+                }
+                const float h2 = h0 + h1;
+                return h2 + xchg32f(h2, hf);
+            };
+            rn2 = split();
             const int sexp_used = sexp;
-            // A residual that has shrunk a lot (a vector that is nearly a multiple of an atom) is scaled up again
-            // before the split, or lo would sink into the fp16 subnormals; one that has grown (atoms of norm above
-            // sqrt(2) make Eq.4 expand it) is scaled down before hi could leave the fp16 range.
-            if ((r2 < 65536.0f && r2 > 0.0f) || (r2 >= 1073741824.0f && r2 < INFINITY)) {
-                int e2 = 0;
-                (void)frexpf(r2, &e2);             // |R| in [2^((e2-1)/2), 2^(e2/2))
-                const int k = 14 - (e2 + 1) / 2;   // brings |R| into [2^12.5, 2^14.5)
-                const float sc = ldexpf(1.0f, k);
+            if (!(rn2 >= 66000.0f && rn2 <= 1.07e9f)) {
+                rn2 = norm2();
+                // A residual that has shrunk a lot (a vector that is nearly a multiple of an atom) is scaled up again
+                // before the split, or lo would sink into the fp16 subnormals; one that has grown (atoms of norm above
+                // sqrt(2) make Eq.4 expand it) is scaled down before hi could leave the fp16 range.
+                if ((rn2 < 65536.0f && rn2 > 0.0f) || (rn2 >= 1073741824.0f && rn2 < INFINITY)) {
+                    int e2 = 0;
+                    (void)frexpf(rn2, &e2);            // |R| in [2^((e2-1)/2), 2^(e2/2))
+                    const int k = 14 - (e2 + 1) / 2;   // brings |R| into [2^12.5, 2^14.5)
+                    const float sc = ldexpf(1.0f, k);
 #pragma unroll
-                for (int j = 0; j < kFrags; ++j)
+                    for (int j = 0; j < kFrags; ++j) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) R[j][e] *= sc;
-                r2 *= sc * sc;
-                sexp += k;
+                        for (int e = 0; e < 8; ++e) R[j][e] *= sc;
+                        hi[j] = to_half8(R[j]);
+                    }
+                    rn2 *= sc * sc;
+                    sexp += k;
+                }
+            } else if (g + 1 == s && res_norm2) {
+                rn2 = norm2();
             }
             float lo2 = 0.0f;
 #pragma unroll
             for (int j = 0; j < kFrags; ++j) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const _Float16 hh = (_Float16)R[j][e];
-                    const float l = R[j][e] - (float)hh;
-                    hi[j][e] = hh;
+                    const float l = minus_half(R[j][e], hi[j][e], one);
                     lo2 = fmaf(l, l, lo2);
                 }
             }
             lo2 += xchg32f(lo2, hf);
-            rn2 = r2;
-            delta = screen_delta(dmax, lo2, r2);
+            delta = fast_delta(dmax, lo2, rn2);
             if (valid) {
                 const int64_t o = (int64_t)h * code_stride_h + (tok * sn + ch) * s + g;
                 if (hf == 0) {
@@ -435,7 +509,7 @@ static bool two_per_cu(const EncodeArgs &a)
 
 // Blocks of 32 vectors per wave.  What counts is how many generations of workgroups the launch makes; a workgroup costs as
 // many block times, and the load of the dictionary besides, about a tenth of one.  Always two: 16 dictionaries of 256 atoms,
-// s = 8 (us) 4096 vectors each 134, 9000 247; as many as the rule takes 77 and 205.
+// s = 8 (us, with the sweep of before) 4096 vectors each 134, 9000 247; as many as the rule takes 77 and 205.
 struct ResidentBlocks {
     int blocks;
     float cost;   // block times
@@ -452,10 +526,11 @@ static ResidentBlocks resident_blocks(const EncodeArgs &a)
     return best;
 }
 
-// A block time is 66 us with 256 atoms and 87 with 512 (s = 8), where a pass of the wide encoder is 24 and 27.
+// One generation of one block a wave takes 45 us with 128 atoms, 55 with 256 and 74 with 512 (s = 8); of the wide encoder's passes, of which
+// 2.4 make a generation of two, one is 15, 20 and 22 us.
 float encode_resident_cost(const EncodeArgs &a)
 {
-    return resident_blocks(a).cost * (2.35f + (float)(a.N * a.d) / (128.0f * 550.0f));
+    return resident_blocks(a).cost * (2.35f + (float)(a.N * a.d) / (128.0f * 700.0f));
 }
 
 template <int DC, int OCC>

@@ -127,6 +127,32 @@ def test_resident_encoder_with_one_to_four_blocks_per_wave(N, d, T, H):
     assert torch.equal(ir, iw) and torch.equal(cr, cw)
 
 
+@pytest.mark.parametrize("N,d", [(32, 128), (96, 128), (256, 128), (512, 128), (32, 64), (160, 64), (1024, 64)])   # one tile, odd and even numbers of them
+@pytest.mark.parametrize("gain", [1.0, 1.6])   # 1.6: Eq.4 lengthens the residual
+def test_resident_encoder_where_the_residual_collapses_or_grows(N, d, gain):
+    # |hi|^2 stands for |R|^2 but near the lines where the residual is scaled again: vectors on either side of them
+    T, s = 600, 7
+    rng = np.random.default_rng(13)
+    D = (synth.dictionary(13, "dict_k", 1, N, d, "f16").astype(np.float32) * gain)
+    D[0, :min(N, d) // 2] = gain * np.eye(d, dtype=np.float32)[:min(N, d) // 2]       # unit vectors: residuals of exactly zero, and of one subnormal
+    D = D.astype(np.float16)
+    X = rng.standard_normal((1, T, d)).astype(np.float32)
+    X[0, 0] = 0.0
+    near = D[0, rng.integers(0, N, T // 2)].astype(np.float32)
+    X[0, 1:1 + T // 2] = near * 3.0 + rng.standard_normal((T // 2, d)) * 10.0 ** rng.uniform(-6, 0, (T // 2, 1))
+    X[0, -2] = 0.0
+    X[0, -2, 0], X[0, -2, 1] = 65504.0, 6e-8
+    X = X.astype(np.float16)
+    Xg, Dg = torch.from_numpy(X).cuda(), torch.from_numpy(D).cuda()
+    er, ew = torch.empty(1, T, device="cuda"), torch.empty(1, T, device="cuda")
+    ir, cr = csr.csr_encode(Xg, Dg, s, algo=csr.CSR_ENCODE_RESIDENT, res_norm2=er)
+    iw, cw = csr.csr_encode(Xg, Dg, s, algo=csr.CSR_ENCODE_WIDE, res_norm2=ew)
+    assert torch.equal(ir, iw) and torch.equal(cr, cw)
+    assert torch.allclose(er, ew, rtol=2e-5, atol=0.0)   # the same terms in another order: 128 roundings of 2^-24
+    if gain == 1.0:
+        _assert_ok(_compare(X, D, s, ir.cpu().numpy(), cr.cpu().numpy()))
+
+
 @pytest.mark.parametrize("B,Hkv,T,N,sn", [
     (1, 2, 70000, 544, 1),     # one generation of the prefill encoder's workgroups, 4464 vectors of each dictionary left over
     (5, 3, 9001, 544, 1),      # sequences that share three dictionaries: the line lies inside one of them
