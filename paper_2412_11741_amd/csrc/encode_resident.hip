@@ -526,11 +526,12 @@ static ResidentBlocks resident_blocks(const EncodeArgs &a)
     return best;
 }
 
-// One generation of one block a wave takes 45 us with 128 atoms, 55 with 256 and 74 with 512 (s = 8); of the wide encoder's passes, of which
-// 2.4 make a generation of two, one is 15, 20 and 22 us.
+// In passes of the wide encoder, of which 2.4 make a generation of two.  One generation of one block a wave, s = 8 (us): 128 dimensions 36 with
+// 32 atoms, 44 with 128, 55 with 256, 74 with 512, where such a pass is 18 to 22; 64 dimensions 28 with 64 atoms, 31 with 128, 37 with 256, 48 with
+// 512, 74 with 1024, where it is 21 to 29 (with the line of 128 dimensions 16 x 1386 vectors of 64, 256 atoms, went the other way: 51).
 float encode_resident_cost(const EncodeArgs &a)
 {
-    return resident_blocks(a).cost * (2.35f + (float)(a.N * a.d) / (128.0f * 700.0f));
+    return resident_blocks(a).cost * (a.d == 64 ? 1.05f + (float)a.N / 480.0f : 1.7f + (float)a.N / 350.0f);
 }
 
 template <int DC, int OCC>
