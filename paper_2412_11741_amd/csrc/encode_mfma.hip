@@ -33,6 +33,11 @@
 //            lowest index on ties.  Should even the fourth tracked group of a lane be a candidate
 //            (about 1e-5 of the steps), untracked groups could matter too, and the wave evaluates
 //            all N atoms that way.
+//            The eight waves of a workgroup wait for the one with the most such tokens, so a token's chain counts: with the
+//            candidates' numbers in scalar registers, both candidate groups' rows requested at once and no LDS trips in
+//            the reductions (resolve_vector), and fp16 operands taken as they are in the update, 64 x 4096 vectors take
+//            1.968 ms instead of 2.036 (4096 atoms, s = 8), 64 x 16384 on 1024 atoms 2.36 instead of 2.62, two chunks of 64 dimensions
+//            on 2048 atoms 1.63 instead of 1.73, 64 x 8192 on 8192 atoms, s = 16 14.6 instead of 14.8.
 //   update   c = (hi + lo) . d exactly, R -= c d in fp32 (Eq.4), new hi / lo split, new delta.
 //
 // Orientation: atoms are the M rows of the MFMA (A operand = dictionary tile from LDS), tokens the
@@ -88,7 +93,7 @@ template <int DC> struct Shape {
 constexpr int kScratchPerWave = 1024;                 // LDS a wave uses to share one token's state
 constexpr int kScratchOff = kRing * kStageBytes;
 template <int W> constexpr int lds_bytes() { return kScratchOff + W * kScratchPerWave; }  // 52 KiB (W = 4) | 56 KiB
-constexpr int kTrack = 4;                             // group maxima tracked per lane and sweep
+constexpr int kTrack = kResolveTrack;                 // group maxima tracked per lane and sweep
 constexpr int kNormSlices = 8;                        // workgroups per dictionary in the norm pre-pass
 
 
@@ -156,86 +161,17 @@ __global__ __launch_bounds__(256) void dict_norm_kernel(const __half *__restrict
     if (tid == 0) dnorm[h * kNormSlices + sl] = sqrtf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
 }
 
-// The whole wave resolves ONE token whose pick the fast path could not decide.  `scr` holds that
-// token's state, written by its two owner lanes:
-//   [0, 256)    hi, dimensions in order        [256, 512)  lo
-//   [512, 544)  tracked group values, lane half 0 then half 1
-//   [544, 552)  threshold bits, overflow flag
-// Lane (a = lane / 4, q = lane % 4) evaluates atom a of a 16-atom group over a quarter of the dimensions.
-// Returns the arg-max of |hi . d + lo . d| (lowest index on ties) over the candidate groups, or over
-// all atoms when the overflow flag is set.
-template <int DC>
-__device__ __forceinline__ int resolve_token(const __half *__restrict__ Dh, int32_t N, int ntiles, uint32_t code_mask,
-                                             const unsigned char *scr, int lane)
-{
-    constexpr int kQ = DC / 32;  // 8-element pieces of a quarter vector
-    const int a = lane >> 2, q = lane & 3;
-    half8 th[kQ], tl[kQ];
+// (resolve_vector) atom rows from L2
+template <int DC> struct GlobalRows {
+    static constexpr bool kFar = true;
+    const __half *Dh;
+    __device__ __forceinline__ void operator()(int n, int q, half8 (&d)[DC / 32]) const
+    {
+        const __half *row = Dh + (int64_t)n * DC + q * (DC / 4);
 #pragma unroll
-    for (int j = 0; j < kQ; ++j) {
-        th[j] = *reinterpret_cast<const half8 *>(scr + q * (DC / 2) + j * 16);
-        tl[j] = *reinterpret_cast<const half8 *>(scr + 256 + q * (DC / 2) + j * 16);
+        for (int j = 0; j < DC / 32; ++j) d[j] = *reinterpret_cast<const half8 *>(row + 8 * j);
     }
-    const uint2 tf = *reinterpret_cast<const uint2 *>(scr + 544);
-    const uint32_t thr_bits = __builtin_amdgcn_readfirstlane(tf.x);
-    const bool ovf = __builtin_amdgcn_readfirstlane(tf.y) != 0;
-
-    float ba = -1.0f;
-    int bn = 0;
-    // `batch` atoms at a time: all their rows are requested before the first product waits
-    auto eval = [&](const int (&n)[2], int batch) {
-        uint4 raw[2][kQ];
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            if (b < batch) {
-                const __half *row = Dh + (int64_t)n[b] * DC + q * (DC / 4);
-#pragma unroll
-                for (int j = 0; j < kQ; ++j) raw[b][j] = *reinterpret_cast<const uint4 *>(row + 8 * j);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            if (b < batch) {
-                float s0 = 0.0f, s1 = 0.0f, l0 = 0.0f, l1 = 0.0f;
-#pragma unroll
-                for (int j = 0; j < kQ; ++j) {
-                    const half8 dv = *reinterpret_cast<const half8 *>(&raw[b][j]);
-                    dot8(th[j], dv, s0, s1);
-                    dot8(tl[j], dv, l0, l1);
-                }
-                float c = (s0 + s1) + (l0 + l1);
-                c += __shfl_xor(c, 1, 64);
-                c += __shfl_xor(c, 2, 64);
-                const float ab = fabsf(c);
-                if (ab > ba || (ab == ba && n[b] < bn)) { ba = ab; bn = n[b]; }
-            }
-        }
-    };
-    if (!ovf) {
-#pragma unroll 1
-        for (int e = 0; e < 2 * kTrack; ++e) {
-            const uint32_t u = __builtin_amdgcn_readfirstlane(*reinterpret_cast<const uint32_t *>(scr + 512 + 4 * e));
-            if (u < thr_bits) continue;
-            const int tile = ntiles - 1 - (int)(u & code_mask);
-            const int n[2] = {tile * 32 + 4 * (e / kTrack) + 8 * (a >> 2) + (a & 3), 0};
-            eval(n, 1);
-        }
-    } else {
-        int n0 = 0;
-#pragma unroll 1
-        for (; n0 < N; n0 += 32) {
-            const int n[2] = {n0 + a, n0 + 16 + a};
-            eval(n, 2);
-        }
-    }
-#pragma unroll
-    for (int m = 4; m <= 32; m <<= 1) {
-        const float oa = __shfl_xor(ba, m, 64);
-        const int on = __shfl_xor(bn, m, 64);
-        if (oa > ba || (oa == ba && on < bn)) { ba = oa; bn = on; }
-    }
-    return __builtin_amdgcn_readfirstlane(bn);
-}
+};
 
 template <int DC, int W>
 __global__ __launch_bounds__(64 * W, 8 / W) void encode_mfma_kernel(
@@ -288,6 +224,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void encode_mfma_kernel(
     // the code as its only scalar operand
     uint32_t keep_mask;
     asm volatile("v_mov_b32 %0, %1" : "=v"(keep_mask) : "s"(~code_mask));
+    const float one = opaque_one();
     // relative slack of a packed value: its low mantissa bits were replaced by the tile code
     const float pack_q = (float)(code_mask + 1) * 1.1920929e-7f;
 
@@ -451,18 +388,18 @@ __global__ __launch_bounds__(64 * W, 8 / W) void encode_mfma_kernel(
             for (int k = 0; k < kTrack; ++k) ncand += (int)(u[bi][k] >= thr_bits) + (int)(pu[k] >= thr_bits);
             const bool overflow = u[bi][kTrack - 1] >= thr_bits || pu[kTrack - 1] >= thr_bits;
 
-            // this lane's best group as kept during the sweep: largest value, its position, runner-up
-            float ba = -1.0f, sa = -1.0f;
-            int bk = 0;
-            {
-                const uint32_t(&w)[8] = keep[bi];
+            // this lane's best group as kept during the sweep: its two largest values, the place of each in the low bits
+            uint32_t k1 = 0u, k2 = 0u;
 #pragma unroll
-                for (int r = 0; r < 8; ++r) {
-                    const float2 f = __half22float2(*reinterpret_cast<const __half2 *>(&w[r]));
-                    if (f.x > ba) { sa = ba; ba = f.x; bk = 2 * r; } else sa = fmaxf(sa, f.x);
-                    if (f.y > ba) { sa = ba; ba = f.y; bk = 2 * r + 1; } else sa = fmaxf(sa, f.y);
-                }
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t w = keep[bi][r >> 1];
+                const uint32_t v = ((r & 1) ? (w & 0xffff0000u) : (w << 16)) | (uint32_t)r;
+                k2 = umed3(k1, k2, v);
+                k1 = max(k1, v);
             }
+            auto kept = [](uint32_t k) { return (float)__builtin_bit_cast(_Float16, (uint16_t)(k >> 16)); };
+            const float ba = kept(k1), sa = kept(k2);
+            const int bk = (int)(k1 & 15u);
             // kept values were rounded toward zero to 11 bits: two of them are told apart only
             // beyond delta + 2^-10 of the larger
             const bool close_own = !(sa < ba - delta[bi] - ba * 9.765625e-4f);
@@ -486,11 +423,9 @@ __global__ __launch_bounds__(64 * W, 8 / W) void encode_mfma_kernel(
                         *reinterpret_cast<half8 *>(scr + hf * DC + j * 16) = hi[bi][j];
                         *reinterpret_cast<half8 *>(scr + 256 + hf * DC + j * 16) = lo[bi][j];
                     }
-                    *reinterpret_cast<uint4 *>(scr + 512 + hf * 16) = make_uint4(u[bi][0], u[bi][1], u[bi][2], u[bi][3]);
-                    if (hf == 0) *reinterpret_cast<uint2 *>(scr + 544) = make_uint2(thr_bits, overflow ? 1u : 0u);
                 }
                 wave_lds_fence();
-                const int n_res = resolve_token<DC>(Dh, N, ntiles, code_mask, scr, lane);
+                const int n_res = resolve_vector<DC>(GlobalRows<DC>{Dh}, N, ntiles, code_mask, scr, u[bi], thr_bits, t, lane);
                 wave_lds_fence();
                 if (col == t) best_n[bi] = n_res;
             }
@@ -528,7 +463,7 @@ __global__ __launch_bounds__(64 * W, 8 / W) void encode_mfma_kernel(
                 const half8 ho = hi[bi][j], lo_o = lo[bi][j];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float r = (float)ho[e] + (float)lo_o[e];  // exact: 22 significant bits
+                    const float r = plus_halves(ho[e], lo_o[e], one);  // exact: 22 significant bits
                     v[j][e] = fmaf(-best_c, f[e], r);
                     r2 = fmaf(v[j][e], v[j][e], r2);
                 }
@@ -555,17 +490,14 @@ __global__ __launch_bounds__(64 * W, 8 / W) void encode_mfma_kernel(
             float lo2 = 0.0f;
 #pragma unroll
             for (int j = 0; j < kFrags; ++j) {
-                half8 hv, lv;
+                hi[bi][j] = to_half8(v[j]);
+                float l[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const _Float16 hh = (_Float16)v[j][e];
-                    const float l = v[j][e] - (float)hh;
-                    hv[e] = hh;
-                    lv[e] = (_Float16)l;
-                    lo2 = fmaf(l, l, lo2);
+                    l[e] = minus_half(v[j][e], hi[bi][j][e], one);
+                    lo2 = fmaf(l[e], l[e], lo2);
                 }
-                hi[bi][j] = hv;
-                lo[bi][j] = lv;
+                lo[bi][j] = to_half8(l);
             }
             lo2 += xchg32f(lo2, hf);
             rn2[bi] = r2;

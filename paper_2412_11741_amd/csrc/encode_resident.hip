@@ -26,8 +26,8 @@
 // Bound: with 128 dimensions and two waves per SIMD, a tile's matrix instructions and its 8 KB a wave out of LDS (512 cycles of either
 // for the two waves of a SIMD and the eight of a CU; 0.39 us measured), then the instructions of select and update (about 900 a block
 // and iteration).  64 x 4096 vectors, s = 8 (us; before the sweep requested its fragments a tile ahead, the resolve left the LDS out
-// of its reductions and the update lost a fifth of its instructions): 128 atoms 217 -> 160, 256 265 -> 222, 512 367 -> 322; keys of 256
-// atoms and values in two chunks 222 -> 188.  A tile's bookkeeping laid between the next tile's matrix instructions is slower (240 with
+// of its reductions and the update lost a fifth of its instructions): 128 atoms 217 -> 160, 256 265 -> 220, 512 367 -> 322; keys of 256
+// atoms and values in two chunks 212 -> 176.  A tile's bookkeeping laid between the next tile's matrix instructions is slower (240 with
 // 256 atoms): the other wave fills that time anyway.
 #include <atomic>
 #include <cmath>
@@ -48,34 +48,11 @@ constexpr int kBlockVectors = kWaves * 32;   // a workgroup takes whole multiple
                                              // 32-vector blocks each, one after the other
 constexpr int kMaxDictBytes = 128 * 1024;
 constexpr int kScratchPerWave = 1024;        // LDS a wave uses to share one vector's state
-constexpr int kTrack = 4;                    // group maxima tracked per lane and sweep
+constexpr int kTrack = kResolveTrack;        // group maxima tracked per lane and sweep
 
 // XOR term of a row's 16-byte piece positions, so that 16 consecutive rows read at one logical piece cover all
 // banks: a 256-byte row spans the 64 banks (16 different terms), two 128-byte rows span them (8, one per pair).
 template <int DC> __device__ __forceinline__ int swz(int row) { return DC == 128 ? (row & 15) : ((row >> 1) & 7); }
-
-// r - h in one instruction that takes h as fp16: a product with a one that the compiler does not know to be one (it would convert h
-// first).  Exact, like the product, where h is the rounding of r.
-__device__ __forceinline__ float minus_half(float r, _Float16 h, float one) { return fmaf(-(float)h, one, r); }
-
-// screen_delta with the hardware's square roots (1 ulp) and |R|^2 as known to 2^-9
-__device__ __forceinline__ float fast_delta(float dmax, float lo2, float r2)
-{
-    return 2.0f * dmax * (1.000001f * __builtin_amdgcn_sqrtf(lo2) + 1.01f * kGammaAcc * __builtin_amdgcn_sqrtf(r2));
-}
-
-__device__ __forceinline__ half8 to_half8(const float (&f)[8])   // v_cvt_pk_f16_f32, two at a time
-{
-    typedef float float2v __attribute__((ext_vector_type(2)));
-    half8 h;
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        const half2v p = __builtin_convertvector((float2v{f[e], f[e + 1]}), half2v);
-        h[e] = p[0];
-        h[e + 1] = p[1];
-    }
-    return h;
-}
 
 // byte offset in the LDS copy of the dictionary of piece `piece` (8 dimensions) of atom `row`
 template <int DC> __device__ __forceinline__ uint32_t piece_at(int row, int piece)
@@ -83,70 +60,16 @@ template <int DC> __device__ __forceinline__ uint32_t piece_at(int row, int piec
     return (uint32_t)(row * (DC * 2) + ((piece ^ swz<DC>(row)) << 4));
 }
 
-// The whole wave resolves ONE vector whose pick the kept values could not decide.  `scr` holds that vector's
-// residual, written by its two owner lanes:
-//   [0, 256)    hi, dimensions in order        [256, 512)  lo
-// `own`: the tracked group values of this lane's vector and half; the vector's are those of lanes v and v + 32.
-// Lane (a = lane / 4, q = lane % 4) evaluates atom a of a 16-atom group over a quarter of the dimensions.
-// Returns the arg-max of |hi . d + lo . d| (lowest index on ties) over the groups that reach thr_bits, or over all atoms
-// when a lane's last tracked group does.
-// (The group values through LDS, one at a time, and the reductions by ds_bpermute were a chain of two dozen LDS trips, 10 of the
-// 33 us of an iteration of 64 x 4096 vectors, 256 atoms.)
-template <int DC>
-__device__ __forceinline__ int resolve_vector(const unsigned char *dict, int32_t N, int ntiles, uint32_t code_mask,
-                                              const unsigned char *scr, const uint32_t (&own)[kTrack], uint32_t thr_own, int v, int lane)
-{
-    constexpr int kQ = DC / 32;  // 8-element pieces of a quarter vector
-    const int a = lane >> 2, q = lane & 3;
-    const uint32_t thr_bits = lane_read(thr_own, v);
-    uint32_t group[2 * kTrack];   // tracked group values, lane half 0 then half 1 (scalars)
-    uint32_t todo = 0u;
+// (resolve_vector) atom rows out of LDS
+template <int DC> struct LdsRows {
+    static constexpr bool kFar = false;
+    const unsigned char *dict;
+    __device__ __forceinline__ void operator()(int n, int q, half8 (&d)[DC / 32]) const
+    {
 #pragma unroll
-    for (int e = 0; e < 2 * kTrack; ++e) {
-        group[e] = lane_read(own[e % kTrack], v + 32 * (e / kTrack));
-        todo |= group[e] >= thr_bits ? 1u << e : 0u;
+        for (int j = 0; j < DC / 32; ++j) d[j] = *reinterpret_cast<const half8 *>(dict + piece_at<DC>(n, q * (DC / 32) + j));
     }
-    half8 th[kQ], tl[kQ];
-#pragma unroll
-    for (int j = 0; j < kQ; ++j) {
-        th[j] = *reinterpret_cast<const half8 *>(scr + q * (DC / 2) + j * 16);
-        tl[j] = *reinterpret_cast<const half8 *>(scr + 256 + q * (DC / 2) + j * 16);
-    }
-    unsigned long long best = 0xffffffffull;   // |correlation|, then the lower atom: bits << 32 | ~atom
-    auto eval = [&](int n) {
-        float s0 = 0.0f, s1 = 0.0f, l0 = 0.0f, l1 = 0.0f;
-        half8 dv[kQ];
-#pragma unroll
-        for (int j = 0; j < kQ; ++j) dv[j] = *reinterpret_cast<const half8 *>(dict + piece_at<DC>(n, q * kQ + j));
-#pragma unroll
-        for (int j = 0; j < kQ; ++j) {
-            dot8(th[j], dv[j], s0, s1);
-            dot8(tl[j], dv[j], l0, l1);
-        }
-        const float ab = fabsf(row_reduce<4>((s0 + s1) + (l0 + l1), OpAdd()));
-        const unsigned long long key = ((unsigned long long)__float_as_uint(ab) << 32) | (uint32_t)~n;
-        if (ab >= 0.0f && key > best) best = key;   // (not a number: never the best)
-    };
-    if (!(todo & ((1u << (kTrack - 1)) | (1u << (2 * kTrack - 1))))) {
-        const int at = 8 * (a >> 2) + (a & 3);
-#pragma unroll
-        for (int e = 0; e < 2 * kTrack; ++e)
-            if ((todo >> e) & 1u) eval((ntiles - 1 - (int)(group[e] & code_mask)) * 32 + 4 * (e / kTrack) + at);
-    } else {
-#pragma unroll 1
-        for (int n0 = 0; n0 < N; n0 += 16) eval(n0 + a);
-    }
-    // the 16 atoms: the four quads of a row, then the rows
-    auto take = [&](unsigned long long o) { best = o > best ? o : best; };
-    take(dpp_mov<0x141>(best));   // row_half_mirror
-    take(dpp_mov<0x140>(best));   // row_mirror
-    const unsigned long long lower = lane_read(best, 0), upper = lane_read(best, 32);
-    take(lane_read(best, 16));
-    take(lane_read(best, 48));
-    take(lower);
-    take(upper);
-    return ~__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
-}
+};
 
 // OCC: waves per SIMD the register budget is set for.  64-dimensional vectors need few enough registers for 4, so
 // that two workgroups share a CU when their dictionaries both fit its LDS (measured 12 - 14 % faster; with one
@@ -219,8 +142,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
     // ~code_mask in a vector register: packing value and tile code is then one instruction
     uint32_t keep_mask;
     asm volatile("v_mov_b32 %0, %1" : "=v"(keep_mask) : "s"(~code_mask));
-    float one;   // see minus_half
-    asm volatile("v_mov_b32 %0, 1.0" : "=v"(one));
+    const float one = opaque_one();
     // relative slack of a packed value: its low mantissa bits were replaced by the tile code
     const float pack_q = (float)(code_mask + 1) * 1.1920929e-7f;
 
@@ -271,7 +193,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
             }
             rn2 = r2 + xchg32f(r2, hf);
             lo2 += xchg32f(lo2, hf);
-            delta = fast_delta(dmax, lo2, rn2);
+            delta = screen_delta(dmax, lo2, rn2);
         }
 
         for (int g = 0; g < s; ++g) {
@@ -392,7 +314,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                         }
                     }
                     wave_lds_fence();
-                    const int n_res = resolve_vector<DC>(lds, N, ntiles, code_mask, scr, u, thr_bits, v, lane);
+                    const int n_res = resolve_vector<DC>(LdsRows<DC>{lds}, N, ntiles, code_mask, scr, u, thr_bits, v, lane);
                     wave_lds_fence();
                     if (col == v) best_n = n_res;
                 }
@@ -476,7 +398,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 }
             }
             lo2 += xchg32f(lo2, hf);
-            delta = fast_delta(dmax, lo2, rn2);
+            delta = screen_delta(dmax, lo2, rn2);
             if (valid) {
                 const int64_t o = (int64_t)h * code_stride_h + (tok * sn + ch) * s + g;
                 if (hf == 0) {
