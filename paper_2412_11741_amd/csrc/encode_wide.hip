@@ -36,8 +36,10 @@
 // The chains of a sum are spread over lanes (each chain keeps its order; the tree that joins them is the same).
 //
 // Bound by the sweep, which runs at the rate of a large library product (1.38 against 1.32 PFLOP/s), and behind it by the select phase, in
-// which the matrix cores stand still: three prompts of 1571 tokens on 8 KV heads, 4096 atoms, spend 250 of a call's 337 us in the sweeps (160
-// vectors a workgroup; 8 iterations of 31 us, 1.38 PFLOP/s) and 10 us an iteration in lists, select and update.  With 64
+// which the matrix cores stand still: three prompts of 1571 tokens on 8 KV heads, 4096 atoms, spend 250 of a call's 329 us in the sweeps (160
+// vectors a workgroup; 8 iterations of 31 us, 1.38 PFLOP/s) and 9 us an iteration in lists, select and update (10 with IEEE square roots for the
+// bound, fp16 operands converted first and an undecided vector's reductions through the LDS; 2 x 4096 fp32 vectors, 1024 atoms 58.7 us a call, 56.0
+// without).  With 64
 // vectors a workgroup the same call made three generations and took 420 us.  Two vectors of a team selected together, so that
 // their chains overlap, is slower (356): the select phase is bound by its instructions.  The rules in csr_api.hip say what
 // this encoder replaces, with figures.
@@ -143,6 +145,7 @@ struct OpPkMax { __device__ __forceinline__ uint32_t operator()(uint32_t a, uint
 // XOR-swizzled by the vector: the 32 columns of a fragment read have to spread over the banks.
 template <int DC, int MODE, int TOK> struct Residuals {
     unsigned char *s;
+    float unit;   // see opaque_one
     static constexpr int kBytes = TOK * DC * 4;
     static __device__ __forceinline__ int half_at(int tok, int p)    // piece of 8 halves
     {
@@ -162,10 +165,7 @@ template <int DC, int MODE, int TOK> struct Residuals {
         } else {
             float v[8];
             full8(tok, p, v);
-            half8 h;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) h[e] = (_Float16)v[e];
-            return h;
+            return to_half8(v);
         }
     }
     // hi (part 0) or lo (part 1) as fp16
@@ -174,15 +174,13 @@ template <int DC, int MODE, int TOK> struct Residuals {
         if constexpr (MODE == kMfma) {
             return *reinterpret_cast<const half8 *>(s + part * (TOK * DC * 2) + half_at(tok, p));
         } else {
-            float v[8];
+            float v[8], l[8];
             full8(tok, p, v);
-            half8 h;
+            const half8 h = to_half8(v);
+            if (!part) return h;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const _Float16 hh = (_Float16)v[e];
-                h[e] = part ? (_Float16)(v[e] - (float)hh) : hh;
-            }
-            return h;
+            for (int e = 0; e < 8; ++e) l[e] = minus_half(v[e], h[e], unit);
+            return to_half8(l);
         }
     }
     __device__ __forceinline__ void full8(int tok, int p, float (&v)[8]) const
@@ -190,7 +188,7 @@ template <int DC, int MODE, int TOK> struct Residuals {
         if constexpr (MODE == kMfma) {
             const half8 h = part8(tok, p, 0), l = part8(tok, p, 1);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (float)h[e] + (float)l[e];   // exact: 22 significant bits
+            for (int e = 0; e < 8; ++e) v[e] = plus_halves(h[e], l[e], unit);   // exact: 22 significant bits
         } else {
             const float4 x = *reinterpret_cast<const float4 *>(s + word_at(tok, 2 * p));
             const float4 y = *reinterpret_cast<const float4 *>(s + word_at(tok, 2 * p + 1));
@@ -204,18 +202,16 @@ template <int DC, int MODE, int TOK> struct Residuals {
     // stores 8 dimensions; returns their share of |R - hi|^2
     __device__ __forceinline__ float put8(int tok, int p, const float (&v)[8]) const
     {
-        half8 h, l;
-        float l2 = 0.0f;
+        const half8 h = to_half8(v);
+        float d[8], l2 = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            h[e] = (_Float16)v[e];
-            const float d = v[e] - (float)h[e];
-            l[e] = (_Float16)d;
-            l2 = fmaf(d, d, l2);
+            d[e] = minus_half(v[e], h[e], unit);
+            l2 = fmaf(d[e], d[e], l2);
         }
         if constexpr (MODE == kMfma) {
             *reinterpret_cast<half8 *>(s + half_at(tok, p)) = h;
-            *reinterpret_cast<half8 *>(s + TOK * DC * 2 + half_at(tok, p)) = l;
+            *reinterpret_cast<half8 *>(s + TOK * DC * 2 + half_at(tok, p)) = to_half8(d);
         } else {
             *reinterpret_cast<float4 *>(s + word_at(tok, 2 * p)) = make_float4(v[0], v[1], v[2], v[3]);
             *reinterpret_cast<float4 *>(s + word_at(tok, 2 * p + 1)) = make_float4(v[4], v[5], v[6], v[7]);
@@ -302,8 +298,8 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
             tl[j] = res.part8(tok, q * kQ + j, 1);
         }
     }
-    float ba = -1.0f;
-    int bn = 0;
+    unsigned long long best = 0xffffffffull;   // |correlation|, then the lower atom: bits << 32 | ~atom
+    auto take = [&](unsigned long long o) { best = o > best ? o : best; };
     auto eval_group = [&](int list, int code) {
         const int na = ((list >> 1) + W * code) * 32 + 4 * (list & 1) + 8 * (a >> 2) + (a & 3);
         const TE *row = Dh + (int64_t)min(na, N - 1) * DC;
@@ -323,7 +319,7 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
             c = row_reduce<4>((s0 + s1) + (l0 + l1), OpAdd());
         }
         const float ab = fabsf(c);
-        if (na < N && (ab > ba || (ab == ba && na < bn))) { ba = ab; bn = na; }
+        if (na < N && ab >= 0.0f) take(((unsigned long long)__float_as_uint(ab) << 32) | (uint32_t)~na);   // (not a number: never)
     };
     const uint32_t team_mask = (uint32_t)((1ull << L) - 1);
 #pragma unroll
@@ -352,14 +348,15 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
             }
         }
     }
-    // the 16 atoms: rows of four quads, then the four rows
-#pragma unroll
-    for (int m = 4; m <= 32; m <<= 1) {
-        const float oa = __shfl_xor(ba, m, 64);
-        const int on = __shfl_xor(bn, m, 64);
-        if (oa > ba || (oa == ba && on < bn)) { ba = oa; bn = on; }
-    }
-    return __builtin_amdgcn_readfirstlane(bn);
+    // the 16 atoms: the four quads of a row, then the rows
+    take(dpp_mov<0x141>(best));   // row_half_mirror
+    take(dpp_mov<0x140>(best));   // row_mirror
+    const unsigned long long r0 = lane_read(best, 0), r1 = lane_read(best, 16), r2 = lane_read(best, 32), r3 = lane_read(best, 48);
+    take(r0);
+    take(r1);
+    take(r2);
+    take(r3);
+    return ~__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
 }
 
 // What a workgroup of P * 128 / DC blocks keeps in LDS: residuals | lists | state | HELD's bounds of the waves
@@ -405,7 +402,7 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
     uint4(*list_s)[kLists] = reinterpret_cast<uint4(*)[kLists]>(lds_s + LDS::kList);   // (tracked groups, best group: atom << 16 | place of the second << 2 | flags)
     VectorState *state_s = reinterpret_cast<VectorState *>(lds_s + LDS::kState);
     float2 *held_s = reinterpret_cast<float2 *>(lds_s + LDS::kHeld);
-    const RES res{lds_s};
+    const RES res{lds_s, opaque_one()};
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -494,7 +491,7 @@ __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
     }
 
     // ---- the vectors: scaled by a power of two that brings max |x_k| into [2^11, 2^12) ----------------------------------
-    auto bound_of = [&](float lo2, float n2) { return 2.0f * (dmax * (sqrtf(lo2) + kGammaAcc * sqrtf(n2)) + derr * sqrtf(n2)); };
+    auto bound_of = [&](float lo2, float n2) { return screen_delta(dmax, lo2, n2) + 2.000002f * derr * __builtin_amdgcn_sqrtf(n2); };
 #pragma unroll 1
     for (int q = 0; q < kPass; ++q) {
         const int tok = q * kTeams + team;
