@@ -262,8 +262,8 @@ __global__ __launch_bounds__(256) void qd_rows_kernel(const __half *__restrict__
 // NP > 0: a token's key code and its value code have NP pairs each, in all chunks together: the whole codes are
 // requested ahead of their use - the first rounds' before the score table is loaded - so that several round trips to
 // memory overlap.  NP = 0: any number of pairs, PV of a chunk at a time, loaded where they are used.
-// CUT_FROM: see chunk_of.
-template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int NP, int THREADS, int CUT_FROM>
+// CUT_FROM: see chunk_of; PAST: see launch_stream_t.
+template <int GB, typename TI, typename TC, int PV, bool CH, int TPT, int NP, int THREADS, int CUT_FROM, bool PAST>
 __global__ __launch_bounds__(THREADS) void stream_kernel(
     const float *__restrict__ qd, const TI *__restrict__ idxK, const TC *__restrict__ coefK,
     const TI *__restrict__ idxV, const TC *__restrict__ coefV, const int32_t *__restrict__ seq_lens,
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
     if constexpr (NP > 0) {
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
-            fetch_codes(ring[k], walk, k / STEPS < n_mine && tok0 + (int64_t)(k / STEPS) * THREADS < t_end);
+            fetch_codes<PAST>(ring[k], walk, k / STEPS < n_mine && tok0 + (int64_t)(k / STEPS) * THREADS < t_end);
             walk.next(k);
         }
     }
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
                     await_codes(cur);
                     const int nx = st + PF;
                     if (nx < TPT * STEPS) {
-                        fetch_codes(ring[nx % (PF + 1)], walk, nx / STEPS < n_mine && tok0 + (int64_t)(nx / STEPS) * THREADS < t_end);
+                        fetch_codes<PAST>(ring[nx % (PF + 1)], walk, nx / STEPS < n_mine && tok0 + (int64_t)(nx / STEPS) * THREADS < t_end);
                         walk.next(nx);
                     }
                     if (t < t_end) {
@@ -415,7 +415,7 @@ __global__ __launch_bounds__(THREADS) void stream_kernel(
             }
         }
     }
-    finish_chunk<GB, TI, TC, PV, CH, TPT, THREADS, NP>(smem_raw, red, sc, mx, n_mine, t0, t_end, code_row, tid, idxV,
+    finish_chunk<GB, TI, TC, PV, CH, TPT, THREADS, NP, PAST>(smem_raw, red, sc, mx, n_mine, t0, t_end, code_row, tid, idxV,
                                                              coefV, N, sV, snV_arg, ml, part_hist, slot);
 }
 
@@ -909,14 +909,21 @@ __global__ __launch_bounds__(256) void finalize_kernel(const float *__restrict__
 // Codes requested as a whole: a variant of its own for calls that are cut by lengths (long contexts without lengths lost 0.4 % by carrying
 // its code); other codes have one for all calls.
 template <int GB, typename TI, typename TC, int PV, bool CH, int TPT = max_rounds(GB), int NP = 0, int THREADS = kStreamThreads, bool LONG = (TPT * THREADS >= kCutFromStream),
-          int CUT_FROM = (NP == 0 && LONG ? kCutFromStream : 0)>
+          int CUT_FROM = (NP == 0 && LONG ? kCutFromStream : 0), bool PAST = false>
 hipError_t launch_stream_t(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
 {
+    // Long chunks of four query heads request their codes non-temporally: they are read once, and what they push out of the L2s is the
+    // score tables that the sequence's other chunks load (8 sequences of 73728 to 131072 tokens, 8 KV heads x 4 query heads 130.8 -> 126.8 us).
+    // Not where a second workgroup reads the same codes (8 query heads per KV head, 20 sequences of 20000 tokens 95 -> 104) or a code is
+    // requested in halves (16 pairs 76.4 -> 77.1); with one query head, and in short chunks, it changes nothing or costs 0.5 %.
+    if constexpr (GB == 4 && LONG && NP > 0 && NP <= 8 && !CH && !PAST) {
+        if (p.ngs == 1) return launch_stream_t<GB, TI, TC, PV, CH, TPT, NP, THREADS, LONG, CUT_FROM, true>(a, p, qd, hist, ml);
+    }
     if constexpr (LONG && CUT_FROM == 0) {
         if (cut_by_lengths(a.seq_lens, p.nchunks, a.B, p.chunk_tokens, kCutFromStream))
-            return launch_stream_t<GB, TI, TC, PV, CH, TPT, NP, THREADS, LONG, kCutFromStream>(a, p, qd, hist, ml);
+            return launch_stream_t<GB, TI, TC, PV, CH, TPT, NP, THREADS, LONG, kCutFromStream, PAST>(a, p, qd, hist, ml);
     }
-    auto kern = stream_kernel<GB, TI, TC, PV, CH, TPT, NP, THREADS, CUT_FROM>;
+    auto kern = stream_kernel<GB, TI, TC, PV, CH, TPT, NP, THREADS, CUT_FROM, PAST>;
     // raising the dynamic-LDS limit is needed once per kernel and device
     static std::atomic<bool> attr_set[kMaxDevices];
     int dev = 0;
