@@ -720,19 +720,20 @@ __global__ __launch_bounds__(256) void out_kernel(const TD *__restrict__ DV, con
     }
 }
 
-// The same for fp16 dictionaries, whole-vector values and ONE (sequence, query head) pair per KV head (a single
-// sequence without query groups; with more pairs out_kernel's LDS-staged slice is the faster form), with the slice read the way qd_rows_kernel reads D_K: 16 lanes
+// The same for fp16 dictionaries, whole-vector values and few (sequence, query head) pairs per KV head (below 16, where the matrix cores
+// take over), with the slice read the way qd_rows_kernel reads D_K: 16 lanes
 // share an atom row (16 bytes each), all eight row requests of a thread are issued ahead of everything else, and the
 // slice never passes through LDS.  Thread (arow, sub) owns dimensions 8 sub .. 8 sub + 7 of atoms arow + 16 i; it takes
-// the combined histogram values of its atoms from LDS (one value per atom and pair, shared by the 16 lanes of the
-// row), and the 16 atom groups meet through lane exchanges inside a wave and LDS across the four waves.
+// the combined histogram values of its atoms from LDS (all pairs of an atom side by side, shared by the 16 lanes of the
+// row), and the 16 atom groups meet in lane swaps inside a wave, each of which halves what a lane holds, and in LDS across the four
+// waves.  Bound: the read of D_V.  out_kernel takes two bytes of the slice per LDS read: 4 sequences x 32 heads, 8192 atoms 22.3 us.
 template <int NQ>
 __global__ __launch_bounds__(256) void out_rows_kernel(const __half *__restrict__ DV, const float *__restrict__ part_hist,
                                                        const float *__restrict__ part_ml, float *__restrict__ part_out,
                                                        int32_t B, int32_t Hkv, int32_t G, int32_t GB, int32_t N, int32_t nchunks)
 {
     constexpr int ATOMS = kOutAtomsF16, kRows = ATOMS / 16;
-    __shared__ __attribute__((aligned(16))) float hist_s[NQ][ATOMS];
+    __shared__ __attribute__((aligned(16))) float hist_s[ATOMS][NQ];
     __shared__ float w_s[NQ][kMaxChunks];
     __shared__ __attribute__((aligned(16))) float red_s[4][NQ][128];
     const int tid = threadIdx.x;
@@ -818,44 +819,52 @@ __global__ __launch_bounds__(256) void out_rows_kernel(const __half *__restrict_
 #pragma unroll
     for (int i = 0; i < kElems; ++i) {
         const int e = i * 256 + tid;
-        if (e < NQ * ATOMS) hist_s[e / ATOMS][e % ATOMS] = hacc[i];
+        if (e < NQ * ATOMS) hist_s[e % ATOMS][e / ATOMS] = hacc[i];
     }
     __syncthreads();
-    float acc[NQ][8];
+    float acc[NQ * 8];
 #pragma unroll
-    for (int r = 0; r < NQ; ++r)
-#pragma unroll
-        for (int k = 0; k < 8; ++k) acc[r][k] = 0.0f;
+    for (int v = 0; v < NQ * 8; ++v) acc[v] = 0.0f;
 #pragma unroll
     for (int i = 0; i < kRows; ++i) {
-        float d[8];
+        float d[8], hv[NQ];
         load8_raw(raw[i], d);
+        const float *hp = hist_s[arow + 16 * i];
+        if constexpr (NQ == 1) {
+            hv[0] = hp[0];
+        } else if constexpr (NQ == 2) {
+            const float2 w = *reinterpret_cast<const float2 *>(hp);
+            hv[0] = w.x; hv[1] = w.y;
+        } else {
+#pragma unroll
+            for (int r = 0; r < NQ; r += 4) {
+                const float4 w = *reinterpret_cast<const float4 *>(hp + r);
+                hv[r] = w.x; hv[r + 1] = w.y; hv[r + 2] = w.z; hv[r + 3] = w.w;
+            }
+        }
 #pragma unroll
         for (int r = 0; r < NQ; ++r) {
-            const float hv = hist_s[r][arow + 16 * i];
 #pragma unroll
-            for (int k = 0; k < 8; ++k) acc[r][k] = fmaf(hv, d[k], acc[r][k]);
+            for (int k = 0; k < 8; ++k) acc[r * 8 + k] = fmaf(hv[r], d[k], acc[r * 8 + k]);
         }
     }
-    // the four atom groups of a wave (rows of 16 lanes) meet through two lane exchanges, the waves through LDS
-    const int wave = tid >> 6, lane = tid & 63;
+    // The four atom groups of a wave (rows of 16 lanes): a swap lays the halves of two values side by side, so that one add serves both.
+    // Behind the second, row 0, 1, 2, 3 has values 4 j, 4 j + 2, 4 j + 1, 4 j + 3.
+    const int wave = tid >> 6, row = (tid >> 4) & 3;
+    float w[NQ * 4], x[NQ * 2];
 #pragma unroll
-    for (int r = 0; r < NQ; ++r) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            float v = acc[r][k];
-            v += __shfl_xor(v, 16, 64);
-            v += __shfl_xor(v, 32, 64);
-            acc[r][k] = v;
-        }
+    for (int v = 0; v < NQ * 4; ++v) {
+        const auto o = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[2 * v]), __float_as_uint(acc[2 * v + 1]), false, false);
+        w[v] = __uint_as_float(o[0]) + __uint_as_float(o[1]);
     }
-    if (lane < 16) {
 #pragma unroll
-        for (int r = 0; r < NQ; ++r) {
-            *reinterpret_cast<float4 *>(&red_s[wave][r][8 * sub]) = make_float4(acc[r][0], acc[r][1], acc[r][2], acc[r][3]);
-            *reinterpret_cast<float4 *>(&red_s[wave][r][8 * sub + 4]) = make_float4(acc[r][4], acc[r][5], acc[r][6], acc[r][7]);
-        }
+    for (int v = 0; v < NQ * 2; ++v) {
+        const auto o = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[2 * v]), __float_as_uint(w[2 * v + 1]), false, false);
+        x[v] = __uint_as_float(o[0]) + __uint_as_float(o[1]);
     }
+    const int mine = 8 * sub + ((row & 1) << 1 | row >> 1);
+#pragma unroll
+    for (int v = 0; v < NQ * 2; ++v) red_s[wave][v >> 1][mine + 4 * (v & 1)] = x[v];
     __syncthreads();
     float *dst = part_out + (((int64_t)h * nslices + blockIdx.x) * BG + bg0) * 128;
     for (int e = tid; e < nbg * 128; e += 256) {
@@ -1136,8 +1145,13 @@ hipError_t launch_decode(const DecodeArgs &a, const DecodePlan &p)
             else
                 hipLaunchKernelGGL(out_mfma_kernel<8>, mgrid, dim3(256), 0, a.stream, (const __half *)a.DV, hist, ml, acc,
                                    a.B, a.Hkv, a.G, p.GB, a.N, p.nchunks);
-        } else if (a.dict16 && a.snV == 1 && nq == 1) {   // measured faster for one pair per KV head only
-            CSR_OUTR(1);
+        } else if (a.dict16 && a.snV == 1) {
+            switch (nq) {
+                case 8: CSR_OUTR(8); break;
+                case 4: CSR_OUTR(4); break;
+                case 2: CSR_OUTR(2); break;
+                default: CSR_OUTR(1); break;
+            }
         } else if (a.dict16) { CSR_OUT_NQ(__half, kOutAtomsF16) } else { CSR_OUT_NQ(float, kOutAtomsF32) }
 #undef CSR_OUTR
 #undef CSR_OUT_NQ
