@@ -237,6 +237,22 @@ def test_many_pairs_per_kv_head_take_the_matrix_core_product(B, Hq, Hkv, T, N):
     _check(out, oracle.decode_attn(*args, seq_lens=lens), TOL_F32_OUT, f"matrix-core D_V product, {B * Hq // Hkv} pairs per KV head")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,T,N", [
+    (2, 1, 1, 17000, 130),     # 2 pairs per KV head, 17 chunks; two atoms in the last slice
+    (1, 3, 1, 33000, 100),     # 3: more than eight chunks a lane's turn, a slice that is not full
+    (5, 1, 1, 8000, 1000),     # 5: two launches' worth of four
+    (8, 8, 8, 1100, 4096),     # 8
+    (3, 20, 4, 3000, 257),     # 15, five query heads per KV head
+    (1, 4, 1, 130000, 64),     # 127 chunks: two a lane in the last sum
+])
+def test_few_pairs_per_kv_head_take_the_product_from_registers(B, Hq, Hkv, T, N):
+    args = _case(33, B, Hq, Hkv, T, N, 8, 8)
+    lens = None if B == 1 else np.array([T, 0, T // 2, 1, T - 1, 1025, 64, T // 3][:B], dtype=np.int32)
+    out = _run(*args, seq_lens=lens)
+    _check(out, oracle.decode_attn(*args, seq_lens=lens), TOL_F16_OUT, f"{B * Hq // Hkv} pairs per KV head")
+    assert lens is None or not out[1].any()
+
+
 def test_decode_is_bit_reproducible():
     # Histogram sums are integer, partial outputs are added in a fixed order: same inputs, same bits.
     args = _case(22, 2, 8, 2, 5000, 4096, 8, 8)
