@@ -25,10 +25,11 @@
 // iteration, costs every call 1.5 %.)  The slots
 // are cleared by a launch of their own before (a workspace's contents are undefined); a slot is written once per call.
 //
-// Bound: reading the dictionaries once, then a dependent chain per iteration - hi and lo from LDS, 16 dependent matrix
-// instructions per tile (8 with at most 16 vectors), the tournament over the waves, publish and poll (one trip each to where
-// the chip's L2s meet, 0.5 us together), the row of the chosen atom, the update.  32 dictionaries of 4096 atoms, s = 8, one vector
-// each: 34 us a call (36 with 16 instructions per tile; with 8192 atoms 48 and 53), 64 vectors each 62.
+// Bound: reading the dictionaries once (11 us of a call with one iteration), then a dependent chain per iteration, 2.4 us: hi and lo from LDS, 16
+// dependent matrix instructions per tile (8 with at most 16 vectors; 0.24 us), the tournament over the accumulators and the waves, publish and
+// poll (one trip each to where the chip's L2s meet, 0.8 us together), the row of the chosen atom (hidden), the update.  32 dictionaries of 4096
+// atoms, s = 8, one vector each: 28 us a call; 33 before the tournament's winner was numbered bit by bit and the state stayed in registers; a
+// whole decoding step with them 94.8 -> 84.9, with 8192 atoms and s = 16 183 -> 150, 60 vectors for each of 8 dictionaries 131 -> 122.
 #include <atomic>
 #include <cmath>
 
@@ -155,12 +156,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             h[e] = hh;
             l[e] = (_Float16)(R[e] - (float)hh);
         }
-        *reinterpret_cast<float4 *>(res + res_at<DC>(v, 2 * sub)) = make_float4(R[0], R[1], R[2], R[3]);
-        *reinterpret_cast<float4 *>(res + res_at<DC>(v, 2 * sub + 1)) = make_float4(R[4], R[5], R[6], R[7]);
+        if constexpr (!kNarrow) {
+            *reinterpret_cast<float4 *>(res + res_at<DC>(v, 2 * sub)) = make_float4(R[0], R[1], R[2], R[3]);
+            *reinterpret_cast<float4 *>(res + res_at<DC>(v, 2 * sub + 1)) = make_float4(R[4], R[5], R[6], R[7]);
+        }
         *reinterpret_cast<half8 *>(hi_s + half_at<DC>(v, sub)) = h;
         *reinterpret_cast<half8 *>(lo_s + half_at<DC>(v, sub)) = l;
     };
 
+    // kNarrow: a team has one vector at most, and what it needs of it from one iteration to the next is in its registers (out of LDS it
+    // is a chain of trips in every one: 0.1 of an iteration's 3.1 us)
+    static_assert(!kNarrow || kTeams >= 32, "a team for every column");
+    float own_R[8];
+    SplitState own{};
     // ---- the vectors, scaled by a power of two that brings max |x_k| into [2^11, 2^12): hi and lo stay normal ----------
     for (int v = team; v < m_pad; v += kTeams) {
         // vector m of this dictionary: block h = (m / T) dict_count + dict, its token m % T
@@ -181,11 +189,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
 #pragma unroll
         for (int e = 0; e < 8; ++e) R[e] = ldexpf(R[e], ex);
         put(v, R);
-        if (sub == 0 && v < p.M) {
-            SplitState st;
-            st.sexp = ex; st.pad = 0;
-            st.vid = (h * p.T + t) * p.sn + ch;
-            st.code_at = h * p.code_stride_h + (t * p.sn + ch) * p.s;
+        SplitState st;
+        st.sexp = ex; st.pad = 0;
+        st.vid = (h * p.T + t) * p.sn + ch;
+        st.code_at = h * p.code_stride_h + (t * p.sn + ch) * p.s;
+        if constexpr (kNarrow) {
+            own = st;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) own_R[e] = R[e];
+        } else if (sub == 0 && v < p.M) {
             state[v] = st;
         }
     }
@@ -231,11 +243,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
                 if constexpr (kNarrow) {   // lanes 0 - 15 of a half get the sum of accumulator 2 r, lanes 16 - 31 of 2 r + 1
                     const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(acc[2 * r]), __float_as_uint(acc[2 * r + 1]), false, false);
                     c[r] = __uint_as_float(x[0]) + __uint_as_float(x[1]);
-                    at[r] = 2 * r;
+                    at[r] = 0;
                 } else {
                     const bool right = fabsf(acc[2 * r + 1]) > fabsf(acc[2 * r]);
                     c[r] = right ? acc[2 * r + 1] : acc[2 * r];
-                    at[r] = right ? 2 * r + 1 : 2 * r;
+                    at[r] = right ? 1 : 0;
                 }
             }
 #pragma unroll
@@ -244,7 +256,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
                 for (int r = 0; r < m; ++r) {
                     const bool right = fabsf(c[2 * r + 1]) > fabsf(c[2 * r]);
                     c[r] = right ? c[2 * r + 1] : c[2 * r];
-                    at[r] = right ? at[2 * r + 1] : at[2 * r];
+                    // the winner's number, a bit a round (chosen from ready numbers, the compiler turns the choice into a search
+                    // through a table, a hundred instructions a tile)
+                    at[r] = right ? (at[2 * r + 1] | (8 / m)) : at[2 * r];
                 }
             }
             if constexpr (kNarrow) at[0] += col >> 4;
@@ -284,23 +298,32 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
         __syncthreads();
         // From here to the next barrier a vector is its team's affair.  The slice's best of every vector, published:
         unsigned long long *slot = p.slots + (int64_t)g * p.V * p.k;
-        for (int v = team; v < p.M; v += kTeams) {
-            unsigned long long w = red[(sub & (kWaves - 1)) * m_pad + v];
-            w = row_reduce<kWaves>(w, OpMaxU64());
-            if (sub == 0) {
-                red[v] = w;
-                if (p.k > 1) __hip_atomic_store(slot + state[v].vid * p.k + sl, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long own_w = 0ull;
+        if constexpr (kNarrow) {
+            if (team < p.M) {
+                own_w = row_reduce<kWaves>(red[(sub & (kWaves - 1)) * m_pad + team], OpMaxU64());
+                if (sub == 0 && p.k > 1) __hip_atomic_store(slot + own.vid * p.k + sl, own_w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+        } else {
+            for (int v = team; v < p.M; v += kTeams) {
+                unsigned long long w = red[(sub & (kWaves - 1)) * m_pad + v];
+                w = row_reduce<kWaves>(w, OpMaxU64());
+                if (sub == 0) {
+                    red[v] = w;
+                    if (p.k > 1) __hip_atomic_store(slot + state[v].vid * p.k + sl, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            wave_lds_fence();
         }
-        wave_lds_fence();
         // ---- the other slices' candidates, the pick, Eq.4 -----------------------------------------------------------------
         for (int v0 = wave * (64 / L); v0 < p.M; v0 += kTeams) {   // (uniform over the wave)
             const int v = v0 + lane / L;
             const int vc = min(v, p.M - 1);   // a team past the last vector idles along: it waits for nobody
             const int slices = v < p.M ? p.k : 0;
-            unsigned long long w = vc == v ? red[v] : 0ull;
+            const SplitState st = kNarrow ? own : state[vc];
+            unsigned long long w = kNarrow ? own_w : vc == v ? red[v] : 0ull;
             if (p.k > 1) {
-                unsigned long long *mine = slot + state[vc].vid * p.k;
+                unsigned long long *mine = slot + st.vid * p.k;
                 unsigned long long got[kSlots];
                 bool ok = true;
 #pragma unroll
@@ -345,11 +368,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             float c = candidate_coef(w);
             float d[8];
             unpack8(*reinterpret_cast<const uint4 *>(Dh + (int64_t)n * DC + sub * 8), d);
-            const int sexp = state[vc].sexp;
+            const int sexp = st.sexp;
             // closed loop: what Eq.4 subtracts is the coefficient as it will be stored (rounded in the input's scale)
             if (coef_rounds_in_loop(p.coef_mode)) c = ldexpf(__half2float(__float2half_rn(ldexpf(c, -sexp))), sexp);
             if (sl == 0 && v < p.M) {
-                const int64_t o = state[vc].code_at + g;
+                const int64_t o = st.code_at + g;
                 if (sub == 0) {
                     if (p.idx16) reinterpret_cast<uint16_t *>(p.idx_out)[o] = (uint16_t)n;
                     else reinterpret_cast<int32_t *>(p.idx_out)[o] = n;
@@ -359,9 +382,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
                     else reinterpret_cast<float *>(p.coef_out)[o] = c_out;
                 }
             }
-            const float4 x = *reinterpret_cast<const float4 *>(res + res_at<DC>(v, 2 * sub));
-            const float4 y = *reinterpret_cast<const float4 *>(res + res_at<DC>(v, 2 * sub + 1));
-            float R[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+            float R[8];
+            if constexpr (kNarrow) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) R[e] = own_R[e];
+            } else {
+                const float4 x = *reinterpret_cast<const float4 *>(res + res_at<DC>(v, 2 * sub));
+                const float4 y = *reinterpret_cast<const float4 *>(res + res_at<DC>(v, 2 * sub + 1));
+                R[0] = x.x; R[1] = x.y; R[2] = x.z; R[3] = x.w; R[4] = y.x; R[5] = y.y; R[6] = y.z; R[7] = y.w;
+            }
             float r2 = 0.0f;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
@@ -370,7 +399,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             }
             r2 = row_reduce<L>(r2, OpAdd());
             if (g + 1 == p.s) {
-                if (p.res_norm2 && sl == 0 && sub == 0 && v < p.M) p.res_norm2[state[vc].vid] = ldexpf(r2, -2 * sexp);
+                if (p.res_norm2 && sl == 0 && sub == 0 && v < p.M) p.res_norm2[st.vid] = ldexpf(r2, -2 * sexp);
                 continue;
             }
             // A residual that has shrunk a lot (a vector that is nearly a multiple of an atom) is scaled up again
@@ -383,10 +412,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
                 const float sc = ldexpf(1.0f, k2);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) R[e] *= sc;
-                wave_lds_fence();                     // the team has read the old exponent
-                if (sub == 0 && v < p.M) state[v].sexp = sexp + k2;
+                if constexpr (kNarrow) {
+                    own.sexp = sexp + k2;
+                } else {
+                    wave_lds_fence();                 // the team has read the old exponent
+                    if (sub == 0 && v < p.M) state[v].sexp = sexp + k2;
+                }
             }
             if (v < p.M) put(v, R);
+            if constexpr (kNarrow) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) own_R[e] = R[e];
+            }
         }
         __syncthreads();
     }
