@@ -270,7 +270,7 @@ __global__ __launch_bounds__(THREADS) void iterate_kernel(const __half *__restri
     float dmax2 = 0.0f;
     for (int sl = lane; sl < nslices; sl += 64) dmax2 = fmaxf(dmax2, dmax2_part[(int64_t)dct * nslices + sl]);
     dmax2 = lane::wave_max(dmax2);
-    const float dmax = sqrtf(dmax2);
+    const float dmax = 1.000001f * __builtin_amdgcn_sqrtf(dmax2);   // (bounds: the hardware's root is within 1 ulp)
     const float g_eps = dmax2 * (2.44140625e-4f + kGammaAcc) + 2.98023224e-8f;  // |G16 - G| <= g_eps
 
     // the residual: every group of LPR lanes holds all of it, 8 dimensions per lane, the same in all waves
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(THREADS) void iterate_kernel(const __half *__restri
 #pragma unroll
     for (int e = 0; e < 8; ++e) r2 = fmaf(R[e], R[e], r2);
     r2 = row_sum<LPR>(r2);
-    const float xnorm = sqrtf(r2);
+    const float xnorm = 1.000001f * __builtin_amdgcn_sqrtf(r2);
 
     // this thread's correlations: atoms 8 (tid + THREADS j) + e
     float C[NR][8];
@@ -346,6 +346,7 @@ __global__ __launch_bounds__(THREADS) void iterate_kernel(const __half *__restri
             n1 = k.x > A1 ? __float_as_int(k.z) : n1;
             A1 = fmaxf(A1, k.x);
         }
+        n1 = __builtin_amdgcn_readfirstlane(n1);   // (the same in all lanes: the rows' addresses are scalars)
         const bool zero = !(r2 > 0.0f);
 
         // requested now, used after the decision (which is n1 almost always)
@@ -446,7 +447,7 @@ __global__ __launch_bounds__(THREADS) void iterate_kernel(const __half *__restri
                 for (int e = 0; e < 8; ++e) C[j][e] = fmaf(-best_c, gv[e], C[j][e]);
             }
         }
-        rmax = fmaxf(rmax, sqrtf(r2));  // (atoms longer than sqrt 2 can make a residual grow)
+        rmax = fmaxf(rmax, 1.000001f * __builtin_amdgcn_sqrtf(r2));  // (atoms longer than sqrt 2 can make a residual grow)
         delta += fabsf(best_c) * g_eps + 2.4e-7f * rmax * dmax;
 
         if (tid == 0) {
