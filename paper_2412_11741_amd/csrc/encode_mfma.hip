@@ -532,14 +532,14 @@ bool encode_mfma_supported(const EncodeArgs &a)
     return a.f16 && (a.d == 128 || a.d == 64 || a.d == 32) && a.N >= 32 && a.N % 32 == 0 && a.N <= 65536;
 }
 
-// Measured on 8 dictionaries, s = 8, in passes of the wide encoder (us at N = 640, 1024, 2048, 4096: 21, 25, 36, 62; of 64-dimensional chunks at
-// 1280, 2048, 4096: 26, 34, 57): a full generation takes 269, 345, 564, 999 and 221, 318, 545.  A partial one that is more than one
-// workgroup of 256 vectors per CU: 252, 315, 483, 890 with 0.6 of the vectors, and 216, 297, 513; one that is not: 208, 260, 409, 691 with
-// half of them, 203, 253, 392, 703 with a fifth, and 184, 254, 466.
+// Measured with s = 8, in passes of the wide encoder (us at N = 640, 1024, 2048, 4096: 21, 25, 35, 61; of 64-dimensional chunks at
+// 1280, 2048, 4096: 26, 34, 57): a full generation takes 232, 305, 520, 962 and 190, 280, 500.  A partial one that is more than one
+// workgroup of 256 vectors per CU: 0.9 to 0.97 of that; one that is not: 233 at 1024 and 370 at 2048, 161 at 1280 and 255 at 2048.  36 random launches of
+// 20000 to 400000 vectors with the prices of before undecided vectors were resolved faster (269, 345, 564, 999): up to 8 % slower than the better encoder.
 float encode_mfma_cost(const EncodeArgs &a, int64_t full, bool more, bool half)
 {
     const bool whole = a.d == 128;
-    const float gen = whole ? 16.8f - 2700.0f / (float)a.N : 10.0f - 2000.0f / (float)a.N;
+    const float gen = whole ? 16.1f - 3400.0f / (float)a.N : 9.5f - 2700.0f / (float)a.N;
     return gen * ((float)full + (!more ? 0.0f : half ? (whole ? 0.75f : 0.83f) : (whole ? 0.9f : 0.95f)));
 }
 
