@@ -100,9 +100,11 @@ template <int DC> __device__ __forceinline__ int half_at(int v, int p) { return 
 struct SplitState { int32_t sexp, pad; int64_t vid, code_at; };   // scale of a vector's residual, its number, its code's first pair
 
 // HELD: tiles of 32 atoms a wave keeps in registers.  A workgroup is two waves per SIMD, and with 128 dimensions there is no
-// room for a second one: the compiler is told so, or it spends instructions on registers that nobody can use.
+// room for a second one: the compiler is told so, or it spends instructions on registers that nobody can use.  With 64 dimensions and up to two
+// tiles it has to stay within 128 registers, so that two workgroups share a CU where a launch has more of them than there are CUs (512
+// dictionaries of 512 atoms, s = 8, one vector each: 31.3 us with 132 registers, 23.2 with 128; 40 vectors each 55.5 and 42.2; one workgroup per CU level).
 template <int DC, int HELD, bool kNarrow>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC == 128 ? 2 : 4))) void encode_split_kernel(const SplitParams p)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DC == 64 && HELD <= 2 ? 4 : 2, DC == 128 ? 2 : 4))) void encode_split_kernel(const SplitParams p)
 {
     constexpr int kFrags = DC / 16;
     constexpr int L = DC / 8;                  // lanes of a vector's team in the update, 8 dimensions each
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, DC 
             const int v = v0 + lane / L;
             const int vc = min(v, p.M - 1);   // a team past the last vector idles along: it waits for nobody
             const int slices = v < p.M ? p.k : 0;
-            const SplitState st = kNarrow ? own : state[vc];
+            const SplitState &st = kNarrow ? own : state[vc];   // (in LDS: what is used late is read late)
             unsigned long long w = kNarrow ? own_w : vc == v ? red[v] : 0ull;
             if (p.k > 1) {
                 unsigned long long *mine = slot + st.vid * p.k;

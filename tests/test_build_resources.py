@@ -72,3 +72,17 @@ def test_the_wide_encoder_spills_little(kernels):
     wide = {n: k["vgpr_spill_count"] for n, k in kernels.items() if "encode_wide_kernel" in n}
     assert len(wide) > 20
     assert {n: v for n, v in wide.items() if v > (20 if re.search(r"Li128ELi[01]ELi8ELi[45]E", n) else 0)} == {}
+
+
+def test_split_encoder_workgroups_of_64_dimensions_share_a_cu(kernels):
+    # eight waves a workgroup: two of them on a CU take at most 128 registers a lane.  With four tiles a lane there is one, as with 128 dimensions
+    split = {}
+    for n, k in kernels.items():
+        m = re.search(r"encode_split_kernelILi(\d+)ELi(\d)ELb(\d)E", n)
+        if m:
+            split[tuple(map(int, m.groups()))] = k
+    assert len(split) == 12
+    for (dims, held, _), k in split.items():
+        if dims == 64 and held <= 2:
+            assert k["vgpr_count"] <= 128 and k["vgpr_spill_count"] == 0, (dims, held)
+        assert k["vgpr_spill_count"] <= (4 if (dims, held) == (128, 4) else 0), (dims, held)
