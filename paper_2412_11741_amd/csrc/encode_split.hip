@@ -46,6 +46,7 @@ using namespace lane;
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxVectors = 128;   // per dictionary; beyond that the prefill encoders' shapes are the better ones
+constexpr int kNarrowVectors = 16; // ... and up to here half a block is enough (kNarrow)
 constexpr int kMaxSlices = 16;
 constexpr int kTargetGroups = 256; // one workgroup per CU
 constexpr int kPatience = 4000;    // ticks of the 100 MHz counter a wave waits for the partners, 40 us: a whole call's time
@@ -112,8 +113,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(DC == 
     constexpr int kSlots = kMaxSlices / L;     // slices a lane of a team waits for, at most: 1 or 2
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int m_pad = (p.M + 31) & ~31;        // vectors, whole blocks of 32
-    unsigned char *res = lds;                        // [m_pad][DC] fp32: the residuals
-    unsigned char *hi_s = res + m_pad * DC * 4;      // [m_pad][DC] fp16: hi, and behind it lo
+    unsigned char *res = lds;                        // [m_pad][DC] fp32: the residuals (kNarrow: none, nor states)
+    unsigned char *hi_s = res + (kNarrow ? 0 : m_pad * DC * 4);                                   // [m_pad][DC] fp16: hi, and behind it lo
     unsigned char *lo_s = hi_s + m_pad * DC * 2;
     unsigned long long *red = reinterpret_cast<unsigned long long *>(lo_s + m_pad * DC * 2);      // [kWaves][m_pad]
     SplitState *state = reinterpret_cast<SplitState *>(red + kWaves * m_pad);                     // [M]
@@ -454,7 +455,8 @@ SplitPlan plan_split(const EncodeArgs &a)
     const int per_wave = ((tiles + k - 1) / k + kWaves - 1) / kWaves;
     pl.held = per_wave <= 1 ? 1 : per_wave <= 2 ? 2 : 4;   // of 128 dimensions: 32, 64 or 128 registers
     const int m_pad = (pl.M + 31) & ~31;
-    pl.lds = (size_t)m_pad * a.d * 8 + (size_t)kWaves * m_pad * 8 + (size_t)pl.M * sizeof(SplitState);
+    pl.lds = (size_t)m_pad * a.d * 4 + (size_t)kWaves * m_pad * 8;
+    if (pl.M > kNarrowVectors) pl.lds += (size_t)m_pad * a.d * 4 + (size_t)pl.M * sizeof(SplitState);
     pl.total = r256((size_t)a.s * pl.V * k * sizeof(unsigned long long));
     return pl;
 }
@@ -480,7 +482,7 @@ hipError_t launch_split_t(const EncodeArgs &a, const SplitPlan &pl, const SplitP
 template <int DC>
 hipError_t launch_split_held(const EncodeArgs &a, const SplitPlan &pl, const SplitParams &p)
 {
-    if (pl.M <= 16)
+    if (pl.M <= kNarrowVectors)
         return pl.held == 1 ? launch_split_t<DC, 1, true>(a, pl, p) : pl.held == 2 ? launch_split_t<DC, 2, true>(a, pl, p) : launch_split_t<DC, 4, true>(a, pl, p);
     return pl.held == 1 ? launch_split_t<DC, 1, false>(a, pl, p) : pl.held == 2 ? launch_split_t<DC, 2, false>(a, pl, p) : launch_split_t<DC, 4, false>(a, pl, p);
 }
