@@ -922,11 +922,12 @@ template <int GB, typename TI, typename TC, int PV, bool CH, int TPT = max_round
           int CUT_FROM = (NP == 0 && LONG ? kCutFromStream : 0), bool PAST = false>
 hipError_t launch_stream_t(const DecodeArgs &a, const DecodePlan &p, float *qd, float *hist, float *ml)
 {
-    // Long chunks of four query heads request their codes non-temporally: they are read once, and what they push out of the L2s is the
+    // Long chunks of four query heads request codes of 8 pairs non-temporally: they are read once, and what they push out of the L2s is the
     // score tables that the sequence's other chunks load (8 sequences of 73728 to 131072 tokens, 8 KV heads x 4 query heads 130.8 -> 126.8 us).
     // Not where a second workgroup reads the same codes (8 query heads per KV head, 20 sequences of 20000 tokens 95 -> 104) or a code is
-    // requested in halves (16 pairs 76.4 -> 77.1); with one query head, and in short chunks, it changes nothing or costs 0.5 %.
-    if constexpr (GB == 4 && LONG && NP > 0 && NP <= 8 && !CH && !PAST) {
+    // requested in halves (16 pairs 76.4 -> 77.1); with one query head, and in short chunks, it changes nothing or costs 0.5 %.  Codes that are no
+    // whole 16-byte vectors (4 and 6 pairs) are requested word by word, without it.
+    if constexpr (GB == 4 && LONG && NP > 0 && NP <= 8 && CodeVec<TI, TC, pair_piece<GB, NP>()>::kQuads && !CH && !PAST) {
         if (p.ngs == 1) return launch_stream_t<GB, TI, TC, PV, CH, TPT, NP, THREADS, LONG, CUT_FROM, true>(a, p, qd, hist, ml);
     }
     if constexpr (LONG && CUT_FROM == 0) {

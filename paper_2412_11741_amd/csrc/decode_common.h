@@ -288,6 +288,7 @@ template <int W> __device__ __forceinline__ void load_words(const unsigned char 
 template <bool PAST, typename TI, typename TC, int NP, int PIECE, int THREADS>
 __device__ __forceinline__ void fetch_codes(CodeVec<TI, TC, PIECE> &r, const CodeWalk<TI, TC, NP, PIECE, THREADS> &w, bool have)
 {
+    static_assert(!PAST || CodeVec<TI, TC, PIECE>::kQuads, "only 16-byte vectors are requested non-temporally");
     const uint32_t o = have ? w.off : 0u;
     if constexpr (CodeVec<TI, TC, PIECE>::kQuads) {
 #pragma unroll

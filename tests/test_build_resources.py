@@ -86,3 +86,13 @@ def test_split_encoder_workgroups_of_64_dimensions_share_a_cu(kernels):
         if dims == 64 and held <= 2:
             assert k["vgpr_count"] <= 128 and k["vgpr_spill_count"] == 0, (dims, held)
         assert k["vgpr_spill_count"] <= (4 if (dims, held) == (128, 4) else 0), (dims, held)
+
+
+def test_only_codes_of_whole_vectors_are_requested_past_the_l2s(kernels):
+    # a variant with non-temporal requests where they are made: codes of 8 pairs, four query heads, long chunks, with the cut by lengths and without
+    past = {}
+    for n in kernels:
+        m = re.search(r"13stream_kernelILi(\d+)E\w+?Lb(\d)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb1EE", n)
+        if m:
+            past[n] = tuple(map(int, m.groups()))
+    assert sorted(past.values()) == [(4, 0, 32, 8, 512, 0), (4, 0, 32, 8, 512, 12288)]
