@@ -72,8 +72,11 @@ template <int DC> struct LdsRows {
 };
 
 // OCC: waves per SIMD the register budget is set for.  64-dimensional vectors need few enough registers for 4, so
-// that two workgroups share a CU when their dictionaries both fit its LDS (measured 12 - 14 % faster; with one
-// workgroup per CU the tighter budget only costs spills).
+// that two workgroups share a CU when their dictionaries both fit its LDS (32 heads x 4096 vectors in two chunks, s = 4, 256 atoms
+// 72 us against 77 with one workgroup per CU, 16 x 1386 vectors, s = 8 36 against 35; where only one fits the tighter budget just costs spills).
+// With 4 what follows from the lane's number, a fragment's address and a vector's place are worked out again instead of kept: 8 spilled
+// registers, none used in the loop over the tiles, where there were 19 (32 x 4096 vectors, 256 atoms, s = 8 68 -> 64 us).  With the
+// larger budgets keeping them is 1 to 2 % faster.
 // BLOCKS: blocks per wave where known at compile time (two: the loop over them unrolled is worth 2 - 6 %), else 0.
 template <int DC, int OCC, int BLOCKS>
 __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
@@ -86,6 +89,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
     constexpr int kFrags = DC / 16;       // 8-element operand fragments per lane
     constexpr int kRowBytes = DC * 2;
     constexpr int kPieces = kRowBytes / 16;
+    constexpr bool kTight = OCC == 4;     // registers are short: what can be worked out again is not kept
     const int blocks = BLOCKS ? BLOCKS : blocks_arg;
 
     const int tid = threadIdx.x;
@@ -135,10 +139,6 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
         dmax = sqrtf(v);
     }
 
-    // LDS byte offset, inside a 32-row tile, of this lane's operand fragment j (row = col, piece kFrags hf + j)
-    uint32_t frag_off[kFrags];
-#pragma unroll
-    for (int j = 0; j < kFrags; ++j) frag_off[j] = piece_at<DC>(col, hf * kFrags + j);
     // ~code_mask in a vector register: packing value and tile code is then one instruction
     uint32_t keep_mask;
     asm volatile("v_mov_b32 %0, %1" : "=v"(keep_mask) : "s"(~code_mask));
@@ -150,10 +150,16 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
         const int64_t m0 = ((int64_t)tile_wg * blocks + bi) * kBlockVectors + wave * 32, m = m0 + col;
         if (m0 >= M) break;  // wave-uniform
         const bool valid = m < M;
-        const int64_t mc = valid ? m : M - 1;  // tail lanes recompute the last vector, never store
-        const int rep = (int)(mc / T);
-        const int64_t tok = mc - rep * T;     // position in its block
-        const int h = rep * dict_count + dict;
+        // vector m of the dictionary: block h, its token tok; tail lanes recompute the last vector, never store
+        auto place = [&](int64_t m, int64_t &tok) {
+            const int64_t mc = min(m, M - 1);
+            const int rep = (int)(mc / T);
+            tok = mc - rep * T;
+            return rep * dict_count + dict;
+        };
+        int64_t tok;
+        const int h = place(m, tok);
+        const int64_t code_at = (int64_t)h * code_stride_h + (tok * sn + ch) * s;
 
         // ---- load the vector, scale by a power of two, split into hi + lo -------------------------
         half8 hi[kFrags];          // fp16 rounding of the residual: the MFMA operand
@@ -197,6 +203,11 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
         }
 
         for (int g = 0; g < s; ++g) {
+            // everything that follows from the lane's number is worked out where it is used: kept from one iteration to the next it
+            // would be spilled
+            int me = lane;
+            if constexpr (kTight) asm volatile("" : "+v"(me));
+            const int col = me & 31, hf = me >> 5;
             // ---- screen: one MFMA sweep over the dictionary in LDS ---------------------------------
             uint32_t u[kTrack];
             uint32_t keep[8];
@@ -209,12 +220,18 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
             // one's addresses are the first one's plus a constant.
             half8 a[kFrags];
             using LdsBytes = const __attribute__((address_space(3))) unsigned char *;   // (the array's base added once, not in every tile)
-            LdsBytes at[kFrags];
+            // Fragment j is piece kFrags hf + j of row col: fragment 0's address ^ (j << 4).  Where registers are short one address is kept
+            // and the others come from it in every tile.
+            constexpr int kAt = kTight ? 1 : kFrags;
+            uint32_t at[kAt];
 #pragma unroll
-            for (int j = 0; j < kFrags; ++j) {
-                at[j] = (LdsBytes)lds + frag_off[j];
-                a[j] = *(const __attribute__((address_space(3))) half8 *)at[j];
-            }
+            for (int j = 0; j < kAt; ++j) at[j] = (uint32_t)(uintptr_t)(LdsBytes)lds + piece_at<DC>(col, hf * kFrags + j);
+            auto fragment = [&](int j, int ahead) {
+                const uint32_t p = kAt == 1 ? at[0] ^ (uint32_t)(j << 4) : at[j % kAt];
+                return *(const __attribute__((address_space(3))) half8 *)((LdsBytes)(uintptr_t)p + ahead);
+            };
+#pragma unroll
+            for (int j = 0; j < kFrags; ++j) a[j] = fragment(j, 0);
             auto tile = [&](int t, int ahead) {   // `ahead`: bytes from at[] to the tile that is requested
                 floatx16 acc;
 #pragma unroll
@@ -222,7 +239,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
 #pragma unroll
                 for (int j = 0; j < kFrags; ++j) {
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[j], hi[j], acc, 0, 0, 0);
-                    a[j] = *(const __attribute__((address_space(3))) half8 *)(at[j] + ahead);
+                    a[j] = fragment(j, ahead);
                 }
                 const uint32_t code = (uint32_t)(ntiles - 1 - t);  // earlier tile = larger code
                 float mx = 0.0f;  // eight v_max3_f32 with |.| operand modifiers
@@ -250,7 +267,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 tile(t, 32 * kRowBytes);
                 const uint32_t step = t + 2 < ntiles ? 64 * kRowBytes : 0;   // behind the last pair: a tile that nobody multiplies
 #pragma unroll
-                for (int j = 0; j < kFrags; ++j) at[j] += step;
+                for (int j = 0; j < kAt; ++j) at[j] += step;
                 tile(t + 1, 0);
             }
             if (t < ntiles) tile(t, 0);
@@ -314,7 +331,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                         }
                     }
                     wave_lds_fence();
-                    const int n_res = resolve_vector<DC>(LdsRows<DC>{lds}, N, ntiles, code_mask, scr, u, thr_bits, v, lane);
+                    const int n_res = resolve_vector<DC>(LdsRows<DC>{lds}, N, ntiles, code_mask, scr, u, thr_bits, v, me);
                     wave_lds_fence();
                     if (col == v) best_n = n_res;
                 }
@@ -400,7 +417,7 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
             lo2 += xchg32f(lo2, hf);
             delta = screen_delta(dmax, lo2, rn2);
             if (valid) {
-                const int64_t o = (int64_t)h * code_stride_h + (tok * sn + ch) * s + g;
+                const int64_t o = code_at + g;
                 if (hf == 0) {
                     if (idx16) reinterpret_cast<uint16_t *>(idx_out)[o] = (uint16_t)best_n;
                     else reinterpret_cast<int32_t *>(idx_out)[o] = best_n;
@@ -411,7 +428,14 @@ __global__ __launch_bounds__(kThreads, OCC) void encode_resident_kernel(
                 }
             }
         }
-        if (res_norm2 && valid && hf == 0) res_norm2[((int64_t)h * T + tok) * sn + ch] = ldexpf(rn2, -2 * sexp);
+        if (res_norm2) {   // (its place worked out again rather than kept all the time)
+            int me = lane;
+            if constexpr (kTight) asm volatile("" : "+v"(me));
+            const int64_t m = m0 + (me & 31);
+            int64_t tok;
+            const int h = place(m, tok);
+            if (m < M && me < 32) res_norm2[((int64_t)h * T + tok) * sn + ch] = ldexpf(rn2, -2 * sexp);
+        }
     }
 }
 

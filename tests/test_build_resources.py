@@ -96,3 +96,14 @@ def test_only_codes_of_whole_vectors_are_requested_past_the_l2s(kernels):
         if m:
             past[n] = tuple(map(int, m.groups()))
     assert sorted(past.values()) == [(4, 0, 32, 8, 512, 0), (4, 0, 32, 8, 512, 12288)]
+
+
+def test_the_resident_encoder_spills_little(kernels):
+    # 64 dimensions with two workgroups per CU have 128 registers: what is spilled is one vector's place, outside of the loop over the tiles
+    resident = {}
+    for n, k in kernels.items():
+        m = re.search(r"encode_resident_kernelILi(\d+)ELi(\d)ELi(\d)E", n)
+        if m:
+            resident[tuple(map(int, m.groups()))] = k["vgpr_spill_count"]
+    assert len(resident) == 6
+    assert {n: v for n, v in resident.items() if v > (8 if n[:2] == (64, 4) else 0)} == {}
