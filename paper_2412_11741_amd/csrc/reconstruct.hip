@@ -32,27 +32,40 @@ template <> __device__ __forceinline__ void load8f<float>(const float *p, float 
     const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + 4);
     f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
 }
-// Non-temporal: the vectors of a layer are larger than the L2s, which should keep atom rows instead, and what of them is still dirty when
-// the kernel ends is written back before the next one starts.  32 x 4096 vectors twice, new codes every time (us): 4096 atoms, 8 pairs
-// 47.2 -> 31.8; on the same codes again 39.5 -> 36.2, 256 atoms 31.1 -> 28.8, 8 times the vectors on 2048 atoms 296 -> 199, 32 x 500 vectors level.
-// (The code words as non-temporal loads, too: 36.2 -> 43; a line of them serves eight vectors.)
+// From 4 MB of output on the stores are non-temporal: the vectors do not push atom rows out of the L2s and the cache behind them, and nothing
+// is dirty when the kernel ends.  That is for the call itself and for what runs between it and the vectors' use; a kernel right behind it that
+// reads them all finds fewer of them cached, and between 16 and 270 MB the two together are up to 9 % slower for it.  us, plain -> non-temporal: the
+// call alone; with such a kernel behind it, x + 1; with another, the maximum over d.
+//   32 x 4096 vectors, 4096 atoms, 8 pairs (33.5 MB), keys and values in turn (two calls)
+//     three layers, all of whose dictionaries and codes stay in the 256 MB behind the L2s: 50.4 -> 32.9; 68.0 -> 73.8; 91.3 -> 92.3
+//     eight layers: 47.0 -> 49.3; 67.9 -> 74.4; 87.9 -> 94.5
+//   one call, dictionaries, codes and outputs in turn through 1.5 GB
+//     4.1 MB, 4096 atoms 7.8 -> 7.0; 10.3 -> 9.9; 12.4 -> 12.0         16 MB 16.1 -> 15.4; 21.4 -> 22.6; 27.0 -> 28.0
+//     34 MB, 256 atoms 20.6 -> 14.3; 30.7 -> 32.2; 40.0 -> 42.0        131 MB, 1024 atoms 73 -> 51; 113 -> 110; 141 -> 149
+//     268 MB, 4096 atoms 157 -> 148; 243 -> 244; 300 -> 309            537 MB, 2048 atoms 290 -> 274; 463 -> 456; 599 -> 596
+//   one call, everything cached
+//     8.2 MB 6.4 -> 5.8; 11.4 -> 11.4; 14.5 -> 14.7                    4.1 MB 4.7 -> 4.4; 7.5 -> 7.7; 9.4 -> 9.5
+//     1.0 MB 2.5 -> 2.5; 4.7 -> 4.9; 5.8 -> 6.1                        0.5 MB 2.4 -> 2.4; 4.6 -> 4.7; 5.7 -> 5.9
+// Below 4 MB they stay plain.  (The code words as non-temporal loads, too, on codes already seen: 36.2 -> 43; a line of them serves eight vectors.)
+constexpr uint64_t kPastBytes = 4u << 20;
 typedef uint32_t uint4v __attribute__((ext_vector_type(4)));
-template <typename V> __device__ __forceinline__ void store16(void *p, const V &v)
+template <bool PAST, typename V> __device__ __forceinline__ void store16(void *p, const V &v)
 {
-    __builtin_nontemporal_store(__builtin_bit_cast(uint4v, v), reinterpret_cast<uint4v *>(p));
+    if constexpr (PAST) __builtin_nontemporal_store(__builtin_bit_cast(uint4v, v), reinterpret_cast<uint4v *>(p));
+    else *reinterpret_cast<uint4v *>(p) = __builtin_bit_cast(uint4v, v);
 }
-__device__ __forceinline__ void store8f(__half *p, const float (&f)[8])
+template <bool PAST> __device__ __forceinline__ void store8f(__half *p, const float (&f)[8])
 {
     uint4 raw;
     __half2 *h2 = reinterpret_cast<__half2 *>(&raw);
 #pragma unroll
     for (int j = 0; j < 4; ++j) h2[j] = __floats2half2_rn(f[2 * j], f[2 * j + 1]);
-    store16(p, raw);
+    store16<PAST>(p, raw);
 }
-__device__ __forceinline__ void store8f(float *p, const float (&f)[8])
+template <bool PAST> __device__ __forceinline__ void store8f(float *p, const float (&f)[8])
 {
-    store16(p, make_float4(f[0], f[1], f[2], f[3]));
-    store16(p + 4, make_float4(f[4], f[5], f[6], f[7]));
+    store16<PAST>(p, make_float4(f[0], f[1], f[2], f[3]));
+    store16<PAST>(p + 4, make_float4(f[4], f[5], f[6], f[7]));
 }
 __device__ __forceinline__ int load_idx(const uint16_t *p) { return *p; }
 __device__ __forceinline__ int load_idx(const int32_t *p) { return *p; }
@@ -87,7 +100,7 @@ __device__ __forceinline__ Where locate(int64_t e, int pieces, int ppc, int64_t 
 }
 
 // Any types, any s, any alignment: one pair at a time.
-template <typename TD, typename TI, typename TC, typename TO>
+template <bool PAST, typename TD, typename TI, typename TC, typename TO>
 __global__ __launch_bounds__(256) void reconstruct_kernel(const TD *__restrict__ Dict, const TI *__restrict__ idx,
                                                           const TC *__restrict__ coef, TO *__restrict__ out, int64_t T,
                                                           int32_t d, int32_t N, int32_t s, int32_t sn, int32_t dict_count,
@@ -111,12 +124,12 @@ __global__ __launch_bounds__(256) void reconstruct_kernel(const TD *__restrict__
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc[k] = fmaf(c, row[k], acc[k]);
     }
-    store8f(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
+    store8f<PAST>(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
 }
 
 // The paper's storage (16-bit indices, fp16 coefficients) with s = 8 G pairs: a lane reads eight pairs with one
 // 16-byte load per stream and has the eight atom-row pieces of a group in flight together; same sum order.
-template <typename TD, typename TO, int G>
+template <bool PAST, typename TD, typename TO, int G>
 __global__ __launch_bounds__(256) void reconstruct_vec_kernel(const TD *__restrict__ Dict, const uint16_t *__restrict__ idx,
                                                               const __half *__restrict__ coef, TO *__restrict__ out,
                                                               int64_t T, int32_t d, int32_t N, int32_t sn,
@@ -156,13 +169,13 @@ __global__ __launch_bounds__(256) void reconstruct_vec_kernel(const TD *__restri
             for (int k = 0; k < 8; ++k) acc[k] = fmaf(c, row[j][k], acc[k]);
         }
     }
-    store8f(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
+    store8f<PAST>(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
 }
 
 // The paper's storage with 1 to 7 pairs: the code is requested as a whole (in 32-bit words, or for odd NP pair by pair),
 // then all its rows; same sum order.  One pair at a time every row waits for its own index: 32 x 4096 vectors, 4096 atoms
 // (us) 4 pairs 20.3 -> 15.2, 6 pairs 22.7 -> 17.9, 2 x 2 15.9 -> 12.9, 2 x 3 16.7 -> 13.8, 2 x 4 18.5 -> 14.2.
-template <typename TD, typename TO, int NP>
+template <bool PAST, typename TD, typename TO, int NP>
 __global__ __launch_bounds__(256) void reconstruct_few_kernel(const TD *__restrict__ Dict, const uint16_t *__restrict__ idx,
                                                               const __half *__restrict__ coef, TO *__restrict__ out,
                                                               int64_t T, int32_t d, int32_t N, int32_t sn,
@@ -210,7 +223,7 @@ __global__ __launch_bounds__(256) void reconstruct_few_kernel(const TD *__restri
 #pragma unroll
         for (int k = 0; k < 8; ++k) acc[k] = fmaf(c[j], row[j][k], acc[k]);
     }
-    store8f(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
+    store8f<PAST>(out + w.h * out_stride_h + w.t * out_stride_t + (w.ch * ppc + w.pc) * 8, acc);
 }
 
 // The paper's storage, whole vectors of 128 dimensions or a multiple: the 16 lanes of a row share one code.  A lane requests ONE
@@ -226,7 +239,7 @@ __device__ __forceinline__ void hand_round(uint32_t (&code)[S], const uint32_t (
     ((code[K] = (uint32_t)__builtin_amdgcn_mov_dpp((int)w[K / 16], 0x150 + K % 16, 0xf, 0xf, true)), ...);   // row_newbcast
 }
 
-template <typename TD, typename TO, int S>
+template <bool PAST, typename TD, typename TO, int S>
 __global__ __launch_bounds__(256) void reconstruct_row_kernel(const TD *__restrict__ Dict, const uint32_t *__restrict__ idx,
                                                               const uint32_t *__restrict__ coef, TO *__restrict__ out,
                                                               uint32_t T, int32_t d, int32_t N, uint32_t sn, uint32_t dict_count,
@@ -268,10 +281,10 @@ __global__ __launch_bounds__(256) void reconstruct_row_kernel(const TD *__restri
             for (int k = 0; k < 8; ++k) acc[k] = fmaf(c, row[j][k], acc[k]);
         }
     }
-    store8f(out + (int64_t)h * out_stride_h + (int64_t)t * out_stride_t + col, acc);
+    store8f<PAST>(out + (int64_t)h * out_stride_h + (int64_t)t * out_stride_t + col, acc);
 }
 
-template <typename TD, typename TI, typename TC, typename TO>
+template <bool PAST, typename TD, typename TI, typename TC, typename TO>
 hipError_t launch_t(const ReconstructArgs &a)
 {
     const int64_t total = (int64_t)a.H * a.T * (a.d / 8);
@@ -285,7 +298,7 @@ hipError_t launch_t(const ReconstructArgs &a)
         if (words && a.s % 2 == 0 && (a.d / a.sn) % 128 == 0 && total / 16 < 0x7fffffffLL) {
 #define CSR_REC_ROW(S)                                                                                              \
     case S:                                                                                                         \
-        hipLaunchKernelGGL((reconstruct_row_kernel<TD, TO, S>), grid, dim3(256), 0, a.stream, (const TD *)a.D,      \
+        hipLaunchKernelGGL((reconstruct_row_kernel<PAST, TD, TO, S>), grid, dim3(256), 0, a.stream, (const TD *)a.D,      \
                            (const uint32_t *)a.idx, (const uint32_t *)a.coef, (TO *)a.out, (uint32_t)a.T, a.d, a.N, \
                            (uint32_t)a.sn, (uint32_t)a.dict_count, a.code_stride_h, a.out_stride_h, a.out_stride_t, \
                            (uint32_t)(total / 16));                                                                 \
@@ -306,7 +319,7 @@ hipError_t launch_t(const ReconstructArgs &a)
                          (reinterpret_cast<uintptr_t>(a.coef) % 16) == 0;
         if (vec) {
 #define CSR_REC_VEC(G)                                                                                              \
-    hipLaunchKernelGGL((reconstruct_vec_kernel<TD, TO, G>), grid, dim3(256), 0, a.stream, (const TD *)a.D,          \
+    hipLaunchKernelGGL((reconstruct_vec_kernel<PAST, TD, TO, G>), grid, dim3(256), 0, a.stream, (const TD *)a.D,          \
                        (const uint16_t *)a.idx, (const __half *)a.coef, (TO *)a.out, a.T, a.d, a.N, a.sn,           \
                        a.dict_count, a.code_stride_h, a.out_stride_h, a.out_stride_t, total)
             switch (a.s / 8) {
@@ -320,7 +333,7 @@ hipError_t launch_t(const ReconstructArgs &a)
         }
         if (a.s < 8 && (a.s % 2 == 1 || words)) {
 #define CSR_REC_FEW(NP)                                                                                             \
-    hipLaunchKernelGGL((reconstruct_few_kernel<TD, TO, NP>), grid, dim3(256), 0, a.stream, (const TD *)a.D,         \
+    hipLaunchKernelGGL((reconstruct_few_kernel<PAST, TD, TO, NP>), grid, dim3(256), 0, a.stream, (const TD *)a.D,         \
                        (const uint16_t *)a.idx, (const __half *)a.coef, (TO *)a.out, a.T, a.d, a.N, a.sn,           \
                        a.dict_count, a.code_stride_h, a.out_stride_h, a.out_stride_t, total)
             switch (a.s) {
@@ -336,7 +349,7 @@ hipError_t launch_t(const ReconstructArgs &a)
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((reconstruct_kernel<TD, TI, TC, TO>), grid, dim3(256), 0, a.stream, (const TD *)a.D,
+    hipLaunchKernelGGL((reconstruct_kernel<PAST, TD, TI, TC, TO>), grid, dim3(256), 0, a.stream, (const TD *)a.D,
                        (const TI *)a.idx, (const TC *)a.coef, (TO *)a.out, a.T, a.d, a.N, a.s, a.sn, a.dict_count,
                        a.code_stride_h, a.out_stride_h, a.out_stride_t, total);
     return hipGetLastError();
@@ -345,7 +358,9 @@ hipError_t launch_t(const ReconstructArgs &a)
 template <typename TD, typename TI, typename TC>
 hipError_t launch_o(const ReconstructArgs &a)
 {
-    return a.out16 ? launch_t<TD, TI, TC, __half>(a) : launch_t<TD, TI, TC, float>(a);
+    const bool past = (uint64_t)a.H * (uint64_t)a.T * (uint64_t)a.d * (a.out16 ? 2 : 4) >= kPastBytes;
+    if (past) return a.out16 ? launch_t<true, TD, TI, TC, __half>(a) : launch_t<true, TD, TI, TC, float>(a);
+    return a.out16 ? launch_t<false, TD, TI, TC, __half>(a) : launch_t<false, TD, TI, TC, float>(a);
 }
 template <typename TD, typename TI>
 hipError_t launch_c(const ReconstructArgs &a)

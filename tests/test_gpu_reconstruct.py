@@ -129,3 +129,17 @@ def test_whole_vectors_share_their_code_over_a_row_of_lanes(s, dict_dtype, out_d
         ref, size = terms.sum(3).view(H, T, d), terms.abs().sum(3).view(H, T, d)
         bound = size * s * 2.0 ** -23 + (ref.abs() * 2.0 ** -11 + 2.0 ** -25 if out_dtype == torch.float16 else 0.0)
         assert ((one.cpu().double() - ref).abs() <= bound).all(), (H, T, d, sn)
+
+
+@pytest.mark.parametrize("dtype,s,per_block", [(torch.float16, 8, 4096), (torch.float16, 5, 4096), (torch.float16, 16, 4096), (torch.float32, 6, 2048)])
+@pytest.mark.parametrize("more", [-1, 0, 1])   # tokens of the last block: one less than 4 MB of output, as many, one more
+def test_outputs_around_the_line_of_the_non_temporal_stores(dtype, s, per_block, more):
+    H, N, gen = 4, 200, torch.Generator(device="cuda").manual_seed(17)
+    T = per_block + more
+    D = torch.randn(H, N, 128, device="cuda", generator=gen).to(dtype)
+    idx = torch.randint(0, N, (H, T, s), device="cuda", generator=gen).short()
+    coef = torch.randn(H, T, s, device="cuda", generator=gen).half()
+    whole = torch.full((H, T + 1, 128), 7.0, device="cuda", dtype=dtype)   # a row of each block that is not written
+    csr.csr_reconstruct(D, idx, coef, out=whole[:, :T])
+    parts = torch.cat([csr.csr_reconstruct(D[h:h + 1], idx[h:h + 1], coef[h:h + 1]) for h in range(H)])   # below the line
+    assert torch.equal(whole[:, :T], parts.to(dtype)) and (whole[:, T] == 7.0).all()
