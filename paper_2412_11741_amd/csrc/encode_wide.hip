@@ -827,8 +827,16 @@ WidePasses wide_passes(const EncodeArgs &a, int64_t vectors)
     return best;
 }
 
-// Whether a workgroup can hold the dictionary (see HELD); with more than one pass of vectors there are no registers for it.
-bool held_on_the_cu(const EncodeArgs &a) { return (int64_t)((a.N + 31) / 32) * (a.d * 64) <= 256 * 1024; }
+// Whether a workgroup holds the dictionary (see HELD); with more than one pass of vectors there are no registers for it.  What is held is read
+// ahead of the first sweep instead of during it, so that it takes a few iterations to pay, more of them with tiles in LDS (above 192 KB).
+// us, not held -> held: one pair, 1024 atoms, 2 x 200 vectors fp16 11.1 -> 13.0, fp32 11.9 -> 13.6; 300 x 33 fp16 56 -> 63; 544 atoms 10.0 -> 9.8
+// and 36.5 -> 37.0.  Two, 1024 atoms 16.2 -> 16.8, 16.8 -> 17.8, 71.0 -> 73.4; 544 atoms 13.6 -> 12.6, 14.6 -> 13.5, 47.9 -> 46.1.  Three, 1024
+// atoms 20.9 -> 20.2, 21.6 -> 21.3, 85.3 -> 84.6; 544 atoms 17.4 -> 15.4, 16.4 -> 15.2, 58.0 -> 54.6.
+bool held_on_the_cu(const EncodeArgs &a)
+{
+    const int64_t bytes = (int64_t)((a.N + 31) / 32) * (a.d * 64);
+    return bytes <= (a.s >= 3 ? 256 : a.s == 2 ? 192 : 0) * 1024;
+}
 
 WidePlan plan_wide(const EncodeArgs &a)
 {

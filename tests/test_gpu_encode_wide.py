@@ -101,18 +101,19 @@ def test_same_bits_with_several_passes_per_workgroup(algo, dtype, d, N, T, H):
     assert torch.equal(iw, ie) and torch.equal(cw, ce)
 
 
+@pytest.mark.parametrize("s", [1, 2, 3, 6])   # one pair: no dictionary is held, two: those without tiles in LDS
 @pytest.mark.parametrize("algo,dtype,d,N,T,H", [   # the dictionary on the CU: its last tiles in LDS, waves without one there, one atom too many
     ("valu", "f32", 128, 513, 40, 2), ("valu", "f32", 128, 769, 33, 3), ("valu", "f32", 128, 1023, 1000, 2), ("valu", "f32", 128, 1025, 100, 2),
     ("valu", "f32", 64, 1537, 100, 2), ("valu", "f32", 64, 2047, 700, 2), ("valu", "f32", 32, 3073, 150, 2), ("valu", "f32", 32, 4096, 300, 1),
     ("valu", "f16", 128, 1000, 100, 2), ("mfma", "f16", 128, 800, 300, 2), ("mfma", "f16", 128, 1024, 1001, 4), ("mfma", "f16", 128, 1056, 300, 2),
     ("mfma", "f16", 64, 1568, 300, 2), ("mfma", "f16", 64, 2048, 1001, 2),
 ])
-def test_same_bits_with_the_dictionary_on_the_cu(algo, dtype, d, N, T, H):
+def test_same_bits_with_the_dictionary_on_the_cu(algo, dtype, d, N, T, H, s):
     algo = {"valu": csr.CSR_ENCODE_VALU, "mfma": csr.CSR_ENCODE_MFMA}[algo]
     X = torch.from_numpy(synth.vectors(12, "keys", H, T, d, dtype, outliers=4)).cuda()
     D = torch.from_numpy(synth.dictionary(12, "dict_k", H, N, d, dtype)).cuda()
-    iw, cw = csr.csr_encode(X, D, 6, algo=csr.CSR_ENCODE_WIDE)
-    ie, ce = csr.csr_encode(X, D, 6, algo=algo)
+    iw, cw = csr.csr_encode(X, D, s, algo=csr.CSR_ENCODE_WIDE)
+    ie, ce = csr.csr_encode(X, D, s, algo=algo)
     assert torch.equal(iw, ie) and torch.equal(cw, ce)
 
 
