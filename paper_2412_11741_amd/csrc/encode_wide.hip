@@ -863,6 +863,7 @@ hipError_t launch_p(const EncodeArgs &a, WideParams &p)
     while ((1 << bits) < (p.ntiles + W - 1) / W) ++bits;
     p.code_mask = (1u << bits) - 1u;
     constexpr int kLds = WideLds<DC, W, P, LDS_TILES>::kBytes;
+    const int lds = p.ntiles <= HELD * W ? WideLds<DC, W, P, 0>::kBytes : kLds;   // no wave has a tile there
     if constexpr (kLds > 64 * 1024) {   // above the default limit: per device, once
         static std::atomic<bool> attr_set[64];
         int dev = 0;
@@ -876,7 +877,7 @@ hipError_t launch_p(const EncodeArgs &a, WideParams &p)
             attr_set[dev].store(true, std::memory_order_release);
         }
     }
-    hipLaunchKernelGGL((encode_wide_kernel<TE, DC, MODE, W, P, HELD, LDS_TILES>), dim3((unsigned)groups), dim3(64 * W), kLds, a.stream, p);
+    hipLaunchKernelGGL((encode_wide_kernel<TE, DC, MODE, W, P, HELD, LDS_TILES>), dim3((unsigned)groups), dim3(64 * W), lds, a.stream, p);
     return hipGetLastError();
 }
 
