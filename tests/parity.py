@@ -57,6 +57,11 @@ def _as_index(a):
     return a.astype(np.int64)
 
 
+def f16_ulp(c):
+    """Spacing of fp16 at |c|; of its largest binade (32) there and beyond, where numpy's own is infinite."""
+    return np.spacing(np.minimum(np.abs(c), 2.0 ** 15).astype(np.float16)).astype(np.float64)
+
+
 def check_encode(X, D, idx_c, coef_c, idx_o, coef_o, diag, coef_tol, tie_rel=TIE_REL, max_report=10,
                  coef_storage="f32", coef_o_exact=None):
     """X [T, d], D [N, d] (the exact input bits, any float dtype); candidate and oracle codes [T, s];
@@ -79,20 +84,23 @@ def check_encode(X, D, idx_c, coef_c, idx_o, coef_o, diag, coef_tol, tie_rel=TIE
     abs_floor = FP32_ULP * xnorm                       # per vector
     ulp = np.zeros_like(coef_o)
     if coef_storage == "f16":
-        ulp = np.spacing(np.abs(coef_o).astype(np.float16)).astype(np.float64)
+        ulp = f16_ulp(coef_o)
     # error measured against the larger of |c| and (floor + storage ulp) / coef_tol: `rel <= coef_tol` then
     # reads |err| <= max(coef_tol |c|, floor + ulp)
     denom = np.maximum(np.abs(coef_o), (abs_floor[:, None] + ulp) / coef_tol)
-    rel = np.abs(coef_c - coef_o) / np.where(denom > 0, denom, 1.0)
+    beyond = np.isinf(coef_o)                          # beyond the storage type: stored as the same infinity
+    with np.errstate(invalid="ignore"):
+        rel = np.where(beyond, np.where(coef_c == coef_o, 0.0, np.inf), np.abs(coef_c - coef_o) / np.where(denom > 0, denom, 1.0))
     # the same error against |c| alone: where it exceeds coef_tol although `rel` does not, the floor decided
-    plain = np.abs(coef_c - coef_o) > coef_tol * np.abs(coef_o)
+    with np.errstate(invalid="ignore"):
+        plain = np.abs(coef_c - coef_o) > coef_tol * np.abs(coef_o)
     for t in range(T):
         L = int(lead[t])
         if L:
             e = float(rel[t, :L].max())
             rep.floor_coefs += int(np.count_nonzero(plain[t, :L] & (rel[t, :L] <= coef_tol)))
             rep.max_coef_err = max(rep.max_coef_err, e)
-            if e > coef_tol and len(rep.failures) < max_report:
+            if not e <= coef_tol and len(rep.failures) < max_report:   # (not a number: not passed)
                 g = int(np.argmax(rel[t, :L]))
                 rep.failures.append(f"vector {t} step {g}: coef {coef_c[t, g]!r} vs oracle {coef_o[t, g]!r}")
         if L == s:
@@ -118,10 +126,10 @@ def check_encode(X, D, idx_c, coef_c, idx_o, coef_o, diag, coef_tol, tie_rel=TIE
                 if len(rep.failures) < max_report:
                     rep.failures.append(f"vector {t} step {g} (after tie at {L}): index {n} is not a greedy pick")
                 break
-            u16 = float(np.spacing(np.float16(abs(C[n])))) if coef_storage == "f16" else 0.0
+            u16 = float(f16_ulp(C[n])) if coef_storage == "f16" else 0.0
             e = abs(coef_c[t, g] - C[n]) / max(abs(C[n]), (abs_floor[t] + u16) / coef_tol, 1e-300)
             rep.max_coef_err = max(rep.max_coef_err, float(e))
-            if e > coef_tol:
+            if not e <= coef_tol:
                 if len(rep.failures) < max_report:
                     rep.failures.append(f"vector {t} step {g} (after tie at {L}): coef {coef_c[t, g]!r} vs {C[n]!r}")
                 break

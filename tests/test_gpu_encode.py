@@ -38,7 +38,8 @@ def _compare(X, D, s, idx_g, coef_g, heads=None, rows=None):
         r = slice(None) if rows is None else rows
         Xh = X[h][r]
         idx_o, coef_o, diag = oracle.mp_encode(Xh, D[h], s, diagnostics=True)
-        coef_o_st = coef_o.astype(coef_g.dtype).astype(np.float64)      # storage rounding, RNE
+        with np.errstate(over="ignore"):
+            coef_o_st = coef_o.astype(coef_g.dtype).astype(np.float64)  # storage rounding, RNE; infinite beyond the largest value
         rep = parity.check_encode(Xh, D[h], idx_g[h][r], coef_g[h][r], idx_o, coef_o_st, diag, TOL,
                                   coef_storage="f16" if coef_g.dtype == np.float16 else "f32", coef_o_exact=coef_o)
         reports.append(rep)

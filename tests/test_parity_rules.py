@@ -95,3 +95,27 @@ def test_fp16_storage_allows_one_storage_ulp_and_no_more():
     three_ulp = c16 + 3 * np.spacing(np.abs(c16).astype(np.float16)).astype(np.float64)
     assert not parity.check_encode(X, D, idx, three_ulp, idx, c16, diag, 1e-3, coef_storage="f16").ok
     assert not parity.check_encode(X, D, idx, one_ulp, idx, c16, diag, 1e-3, coef_storage="f32").ok
+
+
+def test_the_largest_fp16_values_are_checked_and_what_is_no_number_fails():
+    X, D, idx, coef, diag = _setup(seed=3)
+    k = 65504.0 / np.abs(coef[:, 0]).max()              # the largest coefficient is the largest fp16 value, others lie in its binade
+    X, coef = X * k, coef * k
+    diag = dict(diag, best_abs=diag["best_abs"] * k, second_abs=diag["second_abs"] * k)
+    t = int(np.argmax(np.abs(coef[:, 0])))
+    c16 = coef.astype(np.float16).astype(np.float64)
+    assert abs(c16[t, 0]) == 65504.0
+
+    def check(cand, ref):
+        return parity.check_encode(X, D, idx, cand, idx, ref, diag, 1e-3, coef_storage="f16").ok
+    assert check(c16, c16)
+    bad = c16.copy(); bad[t, 0] *= 0.99
+    assert not check(bad, c16)
+    one_ulp = c16.copy(); one_ulp[t, 0] -= np.sign(c16[t, 0]) * 32.0
+    assert check(one_ulp, c16)
+    # beyond the largest value both are stored as the same infinity
+    over = c16.copy(); over[t, 0] = np.sign(c16[t, 0]) * np.inf
+    assert check(over, over) and not check(c16, over) and not check(-over, over) and not check(over, c16)
+    for value in (np.nan, np.inf):
+        bad = c16.copy(); bad[1, 2] = value
+        assert not check(bad, c16)
