@@ -39,10 +39,10 @@ size_t round256(size_t v) { return (v + 255) & ~size_t(255); }
 //   fp32, or an N that is no multiple of 32: the alternative is the vector ALU (2 x 4096 fp32 vectors, N = 1024: 775
 //     against 57); a handful of vectors stays there, which needs no scratch
 //   dictionaries that fit the LDS: the resident encoder needs 256 vectors per CU to fill the chip (N = 256, 16 x 1024
-//     vectors: 55 against 49, 16 x 2048: 56 against 94)
+//     vectors: 57 against 47, 16 x 2048: 57 against 86)
 //   the prefill encoder takes 512 vectors per CU and generation and a last generation costs nearly as much as a full one, however few
-//     workgroups it has (16 x 8192 vectors, N = 4096: 991, 16 x 10240: 1752; the generation alone with 16 x 2048 left to the
-//     wide encoder 1280): whole generations go to it and what remains to the wide encoder, or all to one of the two.
+//     workgroups it has (16 x 8192 vectors, N = 4096: 970, 16 x 10240: 1707; the generation alone with 16 x 2048 left to the
+//     wide encoder 1307): whole generations go to it and what remains to the wide encoder, or all to one of the two.
 int64_t auto_head(const csr::EncodeArgs &a, int algo)
 {
     const int64_t M = a.m_end;   // vectors per dictionary

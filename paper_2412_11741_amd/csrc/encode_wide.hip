@@ -369,8 +369,8 @@ template <int DC, int W, int P, int LDS_TILES> struct WideLds {
 };
 
 // Blocks whose fp16 operand a wave holds in registers for the whole sweep (the others are read from LDS for every tile): with
-// five or six of them 256 registers take three or two.  (Four blocks of 128 dimensions spill 19 registers, five of which three are
-// held 11.)
+// five or six of them 256 registers take three or two.  (Four blocks of 128 dimensions spill 17 registers, 14 in the vector
+// ALU's order, five of which three are held 11.)
 template <int DC, int P> constexpr int blocks_held() { return P <= 4 ? P * 128 / DC : P == 5 ? 3 : 2; }
 
 // W waves; P * 128 / DC blocks of 32 vectors.  HELD: the dictionary's first HELD tiles of every wave are read once and stay in
@@ -379,7 +379,7 @@ template <int DC, int P> constexpr int blocks_held() { return P <= 4 ? P * 128 /
 //   256 KB, 24 / (DC / 16) in registers and 8 / (DC / 16) in LDS, one pass of vectors: read from the prepared copy (every workgroup
 //   would spend 10 us on the conversion of 512 KB of fp32).  With L1 and L2 in the way a sweep of 1024 atoms took 3.6 us, 2.7 now
 //   (all four tiles of 128 dimensions in registers spill 59 of them): 2 x 4096 fp32 vectors, 1024 atoms, s = 8, with the attention that
-//   follows 63.5 -> 58.7 us, 8 x 1024, s = 16 106 -> 91.5, fp16 8 x 1024, s = 8 45.9 -> 39.7, with 640 atoms 37.8 -> 34.0.
+//   follows 59.7 -> 56.1 us, 8 x 1024, s = 16 106 -> 91.5, fp16 8 x 1024, s = 8 45.9 -> 39.7, with 640 atoms 37.8 -> 34.0.
 template <typename TE, int DC, int MODE, int W, int P, int HELD, int LDS_TILES>
 __global__ __launch_bounds__(64 * W) void encode_wide_kernel(const WideParams p)
 {
@@ -806,8 +806,9 @@ Mode wide_mode(const EncodeArgs &a)
 }
 
 // How many passes P of 4096 / d vectors a workgroup takes.  A generation of workgroups (one per CU) costs about P + 0.4 passes
-// (16 dictionaries, s = 8, 4096 atoms, one full generation: 102, 159, 222, 299, 365, 433 us for P = 1 .. 6; 1024 atoms 37, 62,
-// 84, 115, 139, 164; fp32 on 1024 atoms 45, 77, 106, 141 for P = 1 .. 4), so what counts is how many generations a launch
+// (16 dictionaries, s = 8, 4096 atoms, one full generation with the preparation: 107, 161, 221, 298, 360, 423 us for P = 1 .. 6; 1024 atoms,
+// which one pass holds on the CU (a pass is then 34 of them, two are 62), 44, 72, 97, 122, 142, 164; fp32 114, 170, 232, 307 and 44, 73, 98, 131 for P = 1 .. 4; 64 dimensions, 2048 atoms
+// 48, 89, 128 and 54, 98, 141), so what counts is how many generations a launch
 // makes: three prompts of 1571 tokens on 8 KV heads are 592 workgroups of 64 vectors, three generations, or 240 of 160, one.
 struct WidePasses {
     int P;
