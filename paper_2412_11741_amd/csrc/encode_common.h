@@ -103,6 +103,21 @@ __device__ __forceinline__ void take_better(float &ba, int &bi, float &bc, float
     if (oa > ba || (oa == ba && oi < bi)) { ba = oa; bi = oi; bc = oc; }
 }
 
+// Of the 16 atoms that a wave's quads have evaluated, the one with the largest key: |correlation|, then the lower atom, bits << 32 | ~atom.
+__device__ __forceinline__ int best_atom(unsigned long long best)
+{
+    using namespace lane;
+    auto take = [&](unsigned long long o) { best = o > best ? o : best; };
+    take(dpp_mov<0x141>(best));   // row_half_mirror: the four quads of a row
+    take(dpp_mov<0x140>(best));   // row_mirror
+    const unsigned long long r0 = lane_read(best, 0), r1 = lane_read(best, 16), r2 = lane_read(best, 32), r3 = lane_read(best, 48);
+    take(r0);
+    take(r1);
+    take(r2);
+    take(r3);
+    return ~__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
+}
+
 // The whole wave resolves ONE vector whose pick the kept values of a sweep could not decide (encode_mfma.hip, encode_resident.hip).
 // `scr` holds that vector's residual, written by its two owner lanes:
 //   [0, 256)    hi, dimensions in order        [256, 512)  lo
@@ -137,7 +152,7 @@ __device__ __forceinline__ int resolve_vector(const Rows &rows, int32_t N, int n
         else if (second < 0) second = n;
         else more |= 1u << e;
     }
-    unsigned long long best = 0xffffffffull;   // |correlation|, then the lower atom: bits << 32 | ~atom
+    unsigned long long best = 0xffffffffull;   // (best_atom)
     half8 th[kQ], tl[kQ];
     auto take = [&](unsigned long long o) { best = o > best ? o : best; };
     auto eval = [&](int n, const half8 (&d)[kQ]) {
@@ -196,15 +211,7 @@ __device__ __forceinline__ int resolve_vector(const Rows &rows, int32_t N, int n
             eval(n0 + 16 + a, d1);
         }
     }
-    // the 16 atoms: the four quads of a row, then the rows
-    take(dpp_mov<0x141>(best));   // row_half_mirror
-    take(dpp_mov<0x140>(best));   // row_mirror
-    const unsigned long long r0 = lane_read(best, 0), r1 = lane_read(best, 16), r2 = lane_read(best, 32), r3 = lane_read(best, 48);
-    take(r0);
-    take(r1);
-    take(r2);
-    take(r3);
-    return ~__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
+    return best_atom(best);
 }
 
 }  // namespace enc

@@ -298,7 +298,7 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
             tl[j] = res.part8(tok, q * kQ + j, 1);
         }
     }
-    unsigned long long best = 0xffffffffull;   // |correlation|, then the lower atom: bits << 32 | ~atom
+    unsigned long long best = 0xffffffffull;   // (best_atom)
     auto take = [&](unsigned long long o) { best = o > best ? o : best; };
     auto eval_group = [&](int list, int code) {
         const int na = ((list >> 1) + W * code) * 32 + 4 * (list & 1) + 8 * (a >> 2) + (a & 3);
@@ -348,15 +348,7 @@ __device__ __forceinline__ int resolve(const TE *__restrict__ Dh, int32_t N, int
             }
         }
     }
-    // the 16 atoms: the four quads of a row, then the rows
-    take(dpp_mov<0x141>(best));   // row_half_mirror
-    take(dpp_mov<0x140>(best));   // row_mirror
-    const unsigned long long r0 = lane_read(best, 0), r1 = lane_read(best, 16), r2 = lane_read(best, 32), r3 = lane_read(best, 48);
-    take(r0);
-    take(r1);
-    take(r2);
-    take(r3);
-    return ~__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
+    return best_atom(best);
 }
 
 // What a workgroup of P * 128 / DC blocks keeps in LDS: residuals | lists | state | HELD's bounds of the waves
