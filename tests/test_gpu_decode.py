@@ -244,12 +244,15 @@ def test_many_pairs_per_kv_head_take_the_matrix_core_product(B, Hq, Hkv, T, N):
     (8, 8, 8, 1100, 4096),     # 8
     (3, 20, 4, 3000, 257),     # 15, five query heads per KV head
     (1, 4, 1, 130000, 64),     # 127 chunks: two a lane in the last sum
+    (17, 1, 1, 2100, 200),     # 16 pairs and more, where the atoms are no whole slices for the matrix cores: 17, two launches' worth of eight and one
+    (11, 12, 4, 1500, 320),    # 33, three query heads per KV head
+    (16, 8, 1, 1100, 1000),    # 128
 ])
 def test_few_pairs_per_kv_head_take_the_product_from_registers(B, Hq, Hkv, T, N):
     args = _case(33, B, Hq, Hkv, T, N, 8, 8)
-    lens = None if B == 1 else np.array([T, 0, T // 2, 1, T - 1, 1025, 64, T // 3][:B], dtype=np.int32)
-    out = _run(*args, seq_lens=lens)
-    _check(out, oracle.decode_attn(*args, seq_lens=lens), TOL_F16_OUT, f"{B * Hq // Hkv} pairs per KV head")
+    lens = None if B == 1 else np.resize([T, 0, T // 2, 1, T - 1, 1025, 64, T // 3], B).clip(0, T).astype(np.int32)
+    out = _run(*args, seq_lens=lens, out_dtype=torch.float32)
+    _check(out, oracle.decode_attn(*args, seq_lens=lens), TOL_F32_OUT, f"{B * Hq // Hkv} pairs per KV head")
     assert lens is None or not out[1].any()
 
 
