@@ -107,3 +107,10 @@ def test_the_resident_encoder_spills_little(kernels):
             resident[tuple(map(int, m.groups()))] = k["vgpr_spill_count"]
     assert len(resident) == 6
     assert {n: v for n, v in resident.items() if v > (8 if n[:2] == (64, 4) else 0)} == {}
+
+
+def test_streaming_kernels_for_four_heads_spill_little_where_codes_are_not_requested_whole(kernels):
+    # the 32 scores of a thread leave few registers for the non-temporal stores' addresses: measured level with plain ones that spill none
+    four = {n: k["vgpr_spill_count"] for n, k in kernels.items() if re.search(r"13stream_kernelILi4E\w+?Lb[01]ELi8ELi0E", n)}
+    assert len(four) == 24
+    assert max(four.values()) <= 6
